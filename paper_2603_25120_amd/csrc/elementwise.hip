@@ -489,29 +489,51 @@ __global__ void zero_rows_kernel(bf16_t* __restrict__ dst, const int32_t* __rest
   const int64_t r = rows[i / vec_per_row], c = i % vec_per_row;
   reinterpret_cast<uint4*>(dst)[r * vec_per_row + c] = make_uint4(0, 0, 0, 0);
 }
-__global__ void splitk_reduce_kernel(const float4* __restrict__ partial, float4* __restrict__ out,
-                                     int splits, int64_t nvec, int accumulate) {
+// Sum of the partial products of a split K loop, in their order, four of their loads in flight at a time; then
+// the epilogue terms of the product.  A thread takes eight consecutive columns of a row.
+template <bool OUT_F32>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float4* __restrict__ partial, void* __restrict__ c, int splits,
+                                                            int64_t nvec, int64_t vec_per_row, int accumulate,
+                                                            const bf16_t* __restrict__ bias, const bf16_t* __restrict__ residual,
+                                                            int64_t ldres) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nvec) return;
-  // the parts are added in their order; four of their loads are in flight at a time
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (accumulate) o = out[i];
-  float4 t = partial[i];
-  int sp = 1;
+  const int64_t row = i / vec_per_row, col = (i % vec_per_row) * 8;
+  float t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  auto add = [&](const float4& a, const float4& b) {
+    t[0] += a.x; t[1] += a.y; t[2] += a.z; t[3] += a.w; t[4] += b.x; t[5] += b.y; t[6] += b.z; t[7] += b.w;
+  };
+  const float4* src = partial + 2 * i;
+  const int64_t step = 2 * nvec;
+  int sp = 0;
   for (; sp + 3 < splits; sp += 4) {
-    const float4 a = partial[(int64_t)sp * nvec + i], b = partial[(int64_t)(sp + 1) * nvec + i];
-    const float4 c = partial[(int64_t)(sp + 2) * nvec + i], d = partial[(int64_t)(sp + 3) * nvec + i];
-    t.x += a.x; t.y += a.y; t.z += a.z; t.w += a.w;
-    t.x += b.x; t.y += b.y; t.z += b.z; t.w += b.w;
-    t.x += c.x; t.y += c.y; t.z += c.z; t.w += c.w;
-    t.x += d.x; t.y += d.y; t.z += d.z; t.w += d.w;
+    float4 a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) { a[q] = src[(sp + q) * step]; b[q] = src[(sp + q) * step + 1]; }
+#pragma unroll
+    for (int q = 0; q < 4; q++) add(a[q], b[q]);
   }
-  for (; sp < splits; sp++) {
-    const float4 v = partial[(int64_t)sp * nvec + i];
-    t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+  for (; sp < splits; sp++) add(src[sp * step], src[sp * step + 1]);
+  if (bias) {
+    float v[8];
+    unpack8(*reinterpret_cast<const uint4*>(bias + col), v);
+#pragma unroll
+    for (int e = 0; e < 8; e++) t[e] += v[e];
   }
-  t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-  out[i] = t;
+  if constexpr (OUT_F32) {
+    float4* o = reinterpret_cast<float4*>(c) + 2 * i;
+    if (accumulate) add(o[0], o[1]);
+    o[0] = make_float4(t[0], t[1], t[2], t[3]);
+    o[1] = make_float4(t[4], t[5], t[6], t[7]);
+  } else {
+    if (residual) {
+      float v[8];
+      unpack8(*reinterpret_cast<const uint4*>(residual + row * ldres + col), v);
+#pragma unroll
+      for (int e = 0; e < 8; e++) t[e] += v[e];
+    }
+    reinterpret_cast<uint4*>(c)[i] = pack8(t);
+  }
 }
 __global__ void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t nvec) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -815,13 +837,19 @@ hipError_t launch_zero_rows(void* dst, const int32_t* rows, int64_t n_rows, int6
   return hipGetLastError();
 }
 
-hipError_t launch_splitk_reduce(const float* partial, float* out, int splits, int64_t n, int accumulate,
-                                hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  if (n % 4 != 0) return hipErrorInvalidValue;
-  ProfScope prof(PROF_ELEMENTWISE, 4.0 * (double)n * (splits + 1 + (accumulate ? 1 : 0)), s);
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks_for(n / 4, 256)), dim3(256), 0, s,
-                     (const float4*)partial, (float4*)out, splits, n / 4, accumulate);
+hipError_t launch_splitk_reduce(const float* partial, void* c, int splits, int64_t m, int64_t n, int out_fp32,
+                                int accumulate, const void* bias, const void* residual, int64_t ldres, hipStream_t s) {
+  if (m == 0 || n == 0) return hipSuccess;
+  if (n % 8 != 0 || (residual && ldres % 8 != 0)) return hipErrorInvalidValue;
+  const int64_t nvec = m * n / 8;
+  ProfScope prof(PROF_ELEMENTWISE, (double)m * (double)n * (4.0 * splits + (out_fp32 ? (accumulate ? 8.0 : 4.0) : (residual ? 4.0 : 2.0))), s);
+  const dim3 grid(blocks_for(nvec, 256)), block(256);
+  if (out_fp32)
+    hipLaunchKernelGGL(splitk_reduce_kernel<true>, grid, block, 0, s, (const float4*)partial, c, splits, nvec, n / 8, accumulate,
+                       (const bf16_t*)bias, (const bf16_t*)nullptr, (int64_t)0);
+  else
+    hipLaunchKernelGGL(splitk_reduce_kernel<false>, grid, block, 0, s, (const float4*)partial, c, splits, nvec, n / 8, 0,
+                       (const bf16_t*)bias, (const bf16_t*)residual, ldres);
   return hipGetLastError();
 }
 

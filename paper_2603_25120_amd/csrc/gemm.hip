@@ -4,24 +4,16 @@
 // (Model Profiler, "Throughput Profiling"): QKV / output / MLP projections and the connector,
 // their input gradients (dX = dY.W^T) and their weight gradients (dW = X^T.dY).
 //
-// Layout handling.  v_mfma_f32_32x32x16_bf16 wants, per lane, eight consecutive values along
-// the contraction index.  Operands whose contraction index is contiguous in memory are staged
-// in LDS as [row][k] and fetched with one 16-byte read; operands whose contraction index is the
-// strided one (W in Y = X.W, both operands of dW = X^T.dY) are staged as they lie in memory,
-// [k][row], and fetched with the LDS transposing read (two ds_read_b64_tr_b16 per fragment), so
-// no operand is ever transposed in global memory or in registers.
-//
-// Tiling.  One workgroup computes a BM x BN tile with NW = (BM/WM)*(BN/WN) wavefronts, each
-// owning a WM x WN sub-tile of 32x32 MFMA blocks.  The K loop moves BK = 64 at a time:
-// global -> registers (prefetch of the next tile, issued before the MFMAs of the current one)
-// -> LDS.  Tiles are visited in an order that keeps the workgroups resident on one XCD (they
-// share that XCD's L2) on neighbouring tiles of a GROUP_M-tall panel.
-//
-// Two kernels.  gemm4_kernel: 256x256 tiles on four wavefronts of 128x128 with a hand-placed
-// k-loop, for every problem that fills the chip with such tiles and whose K is a multiple of 64
-// (also with 192x256 tiles, when those need fewer rounds of one-per-CU workgroups).
-// gemm_kernel: the general template (128x128 tiles on four wavefronts of 64x64 for small
-// problems, 256x256 tiles on eight wavefronts of 128x64 when K has a ragged tail).
+// Two kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
+// hand-placed k-loop, for every K that is a multiple of 64 and for any K of a weight gradient; plan_gemm
+// below chooses the tile and whether the K loop is split.  gemm_kernel (here): a general template for what is
+// left, K no multiple of 64 with an operand whose contiguous dimension is k.  It wants, per lane, eight
+// consecutive values along the contraction index for v_mfma_f32_32x32x16_bf16: operands whose
+// contraction index is contiguous in memory are staged in LDS as [row][k] and fetched with one 16-byte read;
+// operands whose contraction index is the strided one are staged as they lie in memory, [k][row], and
+// fetched with the LDS transposing read, so no operand is transposed in global memory or in registers.  One
+// workgroup computes a BM x BN tile with (BM/WM)*(BN/WN) wavefronts, each owning a WM x WN sub-tile; the K
+// loop moves BK = 64 at a time: global -> registers (prefetch of the next tile) -> LDS.
 #include <algorithm>
 #include <utility>
 
@@ -245,393 +237,39 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
                               m0 + wm * WM, n0 + wn * WN, lane);
 }
 
-// ---------------------------------------------------------------------------------------------
-// 256x256x64 tiles on four wavefronts (one per SIMD), each owning 128x128 = 4x4 MFMA blocks with
-// the accumulators in AGPRs: a third fewer LDS fragment reads per MFMA than 128x64 sub-tiles.
-// With a single wavefront per SIMD nothing else hides a stall, so the k-loop is written slot by
-// slot: every MFMA slot names the LDS read, LDS store and global load that issue in front of it and
-// a scheduling barrier after every slot keeps that order.  Two sets of staging registers: a
-// global load has two whole iterations to land.  The k-advance of the global loads is a scalar
-// offset (no per-load address arithmetic), clamped to the last tile so that no address leaves the
-// operand; that needs K to be a multiple of 64, except in the ragged-K form for operands stored
-// [K, .], which sends the last tile's advance through the range-checked lane offsets.
-template <class F, int... Is>
-__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
+// The tile kernel (gemm_tile.h) takes K a positive multiple of 64, or any K when k runs along the rows of
+// both operands (the weight-gradient layout).
+bool takes_tile_kernel(const GemmArgs& g) {
+  return g.k > 0 && (g.k % BK == 0 || (g.a_layout != 0 && g.b_layout == 0));
 }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  for_each_index(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
-}
-
-template <int ROWS, int COLS, int PADC, int NT, bool K_ROWS>
-struct ScalarStepLoader {
-  static constexpr int VEC_PER_ROW = COLS / 8;
-  static constexpr int NVEC = ROWS * COLS / 8;
-  static constexpr int PER_THREAD = NVEC / NT;
-  static constexpr int STRIDE = COLS + PADC;
-  static_assert(NVEC % NT == 0 && NT % VEC_PER_ROW == 0, "tile must divide among threads");
-  u32x4 r[2][PER_THREAD];
-  uint32_t off[PER_THREAD];   // byte offset of this thread's vectors in k-tile 0, OOB if never valid
-  uint32_t kstep;             // bytes per k-tile
-
-  // pair_half > 0 (operands stored [K, N] only): the tile's 256 columns are, in blocks of 64,
-  // columns [c, c + 64) of the left half of the matrix, the same columns of the right half
-  // (+ pair_half), then [c + 64, c + 128) of the left half and of the right half, with
-  // c = fixed0 / 2: each wavefront's 128 columns then hold matching gate and up columns.
-  __device__ __forceinline__ void init(int64_t ld, int64_t fixed0, int64_t nfixed, int tid, int64_t pair_half = 0) {
-    kstep = (uint32_t)(K_ROWS ? BK * ld * 2 : BK * 2);
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; i++) {
-      const int v = tid + i * NT, rr = v / VEC_PER_ROW, cc = (v % VEC_PER_ROW) * 8;
-      int64_t fx = fixed0 + (K_ROWS ? cc : rr);
-      if (K_ROWS && pair_half > 0) {
-        const int blk = cc >> 6;
-        fx = (blk & 1) * pair_half + (fixed0 >> 1) + 64 * (blk >> 1) + (cc & 63);
-      }
-      const int64_t lin = K_ROWS ? (int64_t)rr * ld + fx : fx * ld + cc;
-      off[i] = fx < nfixed ? (uint32_t)(lin * 2) : OOB;
-    }
-  }
-  template <int S, int I>
-  __device__ __forceinline__ void load1(__amdgpu_buffer_rsrc_t rsrc, uint32_t soff) {
-    r[S][I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off[I], (int)soff, 0);
-  }
-  // The same with part of the k-advance in the lane's own offset, which the buffer's range check
-  // sees (the scalar offset it does not): rows past the operand's end then read as zeros.
-  template <int S, int I>
-  __device__ __forceinline__ void load1_checked(__amdgpu_buffer_rsrc_t rsrc, uint32_t lane_adv, uint32_t soff) {
-    uint32_t v = off[I] + lane_adv;
-    v = v < lane_adv ? OOB : v;   // an offset that is OOB already stays so instead of wrapping
-    r[S][I] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)v, (int)soff, 0);
-  }
-  template <int S, int I>
-  __device__ __forceinline__ void store1(bf16_t* lds, int tid) const {
-    const int v = tid + I * NT, rr = v / VEC_PER_ROW, cc = (v % VEC_PER_ROW) * 8;
-    *reinterpret_cast<u32x4*>(lds + rr * STRIDE + cc) = r[S][I];
-  }
-};
-
-// k-advance of the loads of k-tile t: all of it in the scalar offset, except (RAGGED_K) for the
-// last, partial k-tile, where it goes through the lanes' offsets so that the range check applies.
-struct KAdvance { uint32_t lane, scalar; };
-template <bool RAGGED_K>
-__device__ __forceinline__ KAdvance k_advance(uint32_t t, uint32_t last_tile, uint32_t kstep) {
-  if (RAGGED_K && t == last_tile) return {t * kstep, 0u};
-  return {0u, t * kstep};
-}
-
-// EPI: 0 plain epilogue; 1 SwiGLU forward fused; 2 SwiGLU gradient fused; 3 / 4 rotary positions
-// fused for heads of 128 / 64.
-template <int TM, bool A_T, bool B_T, bool OUT_F32, bool RAGGED_K, int EPI = 0>
-__device__ __forceinline__ void gemm4_tile(GemmParams p) {
-  constexpr bool SWIGLU = EPI == 1;
-  // TM = 4: 256x256 tiles, wavefronts of 128x128.  TM = 3: 192x256 tiles, wavefronts of 96x128,
-  // for problems whose 256-row tiles would leave the last round of workgroups mostly empty.
-  static_assert(TM == 4 || (TM == 3 && !A_T), "192-row tiles only for an A operand stored [M, K]");
-  // RAGGED_K: K need not be a multiple of 64.  Only when k runs along the rows of both operands:
-  // the rows of the last k-tile that lie past K are then past the end of the operand.
-  static_assert(!RAGGED_K || (A_T && B_T), "a ragged K needs both operands stored [K, .]");
-  // SWIGLU: C = [gate | up]; the epilogue also writes silu(gate) * up (forward layout only).
-  static_assert(!SWIGLU || (TM == 4 && !A_T && B_T && !OUT_F32), "fused SwiGLU: Y = X.W with W stored [K, N], bf16");
-  static_assert(EPI != 2 || (TM == 4 && !A_T && !B_T && !OUT_F32), "fused SwiGLU gradient: dA = dY.W^T with W stored [N, K], bf16");
-  static_assert((EPI != 3 && EPI != 4) || (TM == 4 && !A_T && B_T && !OUT_F32), "fused rotary positions: Y = X.W with W stored [K, N], bf16");
-  constexpr int BM = 64 * TM, BN = 256, WM = 32 * TM, WN = 128, NT = 256, TN = 4;
-  constexpr int NA = 2 * TM;          // A vectors per thread and k-tile (B: 8)
-  constexpr int NU = TM + 4;          // fragment units per k-step
-  constexpr int NS = 4 * TM;          // MFMA slots per k-step
-  constexpr int Q3 = TM == 4 ? 4 : 3; // vectors moved in the last k-step (into the tile's own stage)
-  constexpr int A_ROWS = A_T ? BK : BM, A_COLS = A_T ? BM : BK, A_PAD = A_T ? PAD_T : PAD_K;
-  constexpr int B_ROWS = B_T ? BK : BN, B_COLS = B_T ? BN : BK, B_PAD = B_T ? PAD_T : PAD_K;
-  constexpr int A_STRIDE = A_COLS + A_PAD, B_STRIDE = B_COLS + B_PAD;
-  constexpr int A_SIZE = A_ROWS * A_STRIDE, B_SIZE = B_ROWS * B_STRIDE;
-  __shared__ __attribute__((aligned(16))) bf16_t As[2 * A_SIZE];
-  __shared__ __attribute__((aligned(16))) bf16_t Bs[2 * B_SIZE];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  int tm, tn;
-  tile_of_block(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-
-  using LA = ScalarStepLoader<A_ROWS, A_COLS, A_PAD, NT, A_T>;
-  using LB = ScalarStepLoader<B_ROWS, B_COLS, B_PAD, NT, B_T>;
-  static_assert(LA::PER_THREAD == NA && LB::PER_THREAD == 8, "vectors per thread and operand");
-  LA la;
-  LB lb;
-  la.init(p.lda, m0, p.M, tid);
-  lb.init(p.ldb, n0, p.N, tid, SWIGLU ? p.N >> 1 : 0);
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.a, p.a_bytes), rb = make_rsrc(p.b, p.b_bytes);
-
-  // The accumulators are not cleared: the first k-step of the first k-tile multiplies into a
-  // constant zero (256 register writes per lane saved on every output tile).
-  f32x16 acc[TM][TN];
-
-  const int kt0 = blockIdx.y * p.kt_per_split;
-  const int last_tile = (int)((p.K + BK - 1) / BK) - 1;
-  // a split past the end of K (the last ones, when K does not divide evenly) has no k-tiles: zeros
-  const int nk = max(0, min(p.kt_per_split, last_tile + 1 - kt0));
-  auto load_a = [&](auto s_c, auto i_c, uint32_t t) __attribute__((always_inline)) {
-    constexpr int S = decltype(s_c)::value, I = decltype(i_c)::value;
-    if constexpr (RAGGED_K) {
-      const KAdvance k = k_advance<true>(t, (uint32_t)last_tile, la.kstep);
-      la.template load1_checked<S, I>(ra, k.lane, k.scalar);
-    } else {
-      la.template load1<S, I>(ra, t * la.kstep);
-    }
-  };
-  auto load_b = [&](auto s_c, auto i_c, uint32_t t) __attribute__((always_inline)) {
-    constexpr int S = decltype(s_c)::value, I = decltype(i_c)::value;
-    if constexpr (RAGGED_K) {
-      const KAdvance k = k_advance<true>(t, (uint32_t)last_tile, lb.kstep);
-      lb.template load1_checked<S, I>(rb, k.lane, k.scalar);
-    } else {
-      lb.template load1<S, I>(rb, t * lb.kstep);
-    }
-  };
-  auto load_all = [&](auto s_c, int kt) {
-    const uint32_t t = (uint32_t)min(kt, last_tile);
-    static_for<NA>([&](auto i) { load_a(s_c, i, t); });
-    static_for<8>([&](auto i) { load_b(s_c, i, t); });
-  };
-  using C0 = std::integral_constant<int, 0>;
-  using C1 = std::integral_constant<int, 1>;
-  // Prologue.  Tiles 0 and 1 are requested together (one exposed latency for both); tile 0 goes
-  // to stage 0 and its registers take tile 2.  From here on, at k-tile kt of parity P, set P^1
-  // holds tile kt+1 and set P tile kt+2.  The first Q3 of tile 1's A vectors are moved here: the
-  // k-loop moves those in the last k-step of the tile before.
-  load_all(C0{}, kt0);
-  load_all(C1{}, kt0 + 1);
-  static_for<NA>([&](auto i) { la.template store1<0, decltype(i)::value>(As, tid); });
-  static_for<8>([&](auto i) { lb.template store1<0, decltype(i)::value>(Bs, tid); });
-  load_all(C0{}, kt0 + 2);
-  {
-    const uint32_t t = (uint32_t)min(kt0 + 3, last_tile);
-    static_for<Q3>([&](auto i) { la.template store1<1, decltype(i)::value>(As + A_SIZE, tid); });
-    static_for<Q3>([&](auto i) { load_a(C1{}, i, t); });
-  }
-  __syncthreads();
-
-  // Fragments, double-buffered: unit u of a k-step, in the order of first use: A0, B0..B3, A1...
-  bf16x8 af[2][TM], bfr[2][TN];
-  auto fetch_unit = [&](auto u_c, auto buf_c, const bf16_t* at, const bf16_t* bt, auto kk_c) {
-    constexpr int u = decltype(u_c)::value, buf = decltype(buf_c)::value, kk = decltype(kk_c)::value;
-    if constexpr (u == 0) af[buf][0] = fetch_frag<A_T, A_STRIDE>(at, wm * WM, kk, lane);
-    else if constexpr (u <= 4) bfr[buf][u - 1] = fetch_frag<B_T, B_STRIDE>(bt, wn * WN + 32 * (u - 1), kk, lane);
-    else af[buf][u - 4] = fetch_frag<A_T, A_STRIDE>(at, wm * WM + 32 * (u - 4), kk, lane);
-  };
-  static_for<NU>([&](auto u) { fetch_unit(u, C0{}, As, Bs, C0{}); });
-
-  // One k-tile.  P = parity of the tile = its LDS stage = the staging set that holds tile kt+2
-  // (the other set holds tile kt+1).
-  auto iteration = [&](auto p_c, auto first_c, int kt) __attribute__((always_inline)) {
-    constexpr int P = decltype(p_c)::value;
-    constexpr bool FIRST = decltype(first_c)::value;
-    bf16_t* an = As + (P ^ 1) * A_SIZE;
-    bf16_t* bn = Bs + (P ^ 1) * B_SIZE;
-    const bf16_t* at = As + P * A_SIZE;
-    const bf16_t* bt = Bs + P * B_SIZE;
-    const uint32_t t3 = (uint32_t)min(kt0 + kt + 3, last_tile), t4 = (uint32_t)min(kt0 + kt + 4, last_tile);
-    // The tile move, vector q of NA + 8 (A vectors, then B vectors).  k-steps 0..2 move vectors
-    // Q3.. of tile kt+1 (set P^1 -> the other stage, refilled with tile kt+3); k-step 3, once the
-    // barrier has freed this tile's own stage, vectors 0..Q3-1 of tile kt+2 (set P -> this stage,
-    // refilled with tile kt+4).
-    auto move_store = [&](auto kk_c, auto q_c) __attribute__((always_inline)) {
-      constexpr int kk = decltype(kk_c)::value, q = decltype(q_c)::value, S = kk == 3 ? P : (P ^ 1);
-      if constexpr (q < NA) la.template store1<S, q>(kk == 3 ? const_cast<bf16_t*>(at) : an, tid);
-      else lb.template store1<S, q - NA>(kk == 3 ? const_cast<bf16_t*>(bt) : bn, tid);
-    };
-    auto move_load = [&](auto kk_c, auto q_c) __attribute__((always_inline)) {
-      constexpr int kk = decltype(kk_c)::value, q = decltype(q_c)::value, S = kk == 3 ? P : (P ^ 1);
-      using SC = std::integral_constant<int, S>;
-      if constexpr (q < NA) load_a(SC{}, q_c, kk == 3 ? t4 : t3);
-      else load_b(SC{}, std::integral_constant<int, q - NA>{}, kk == 3 ? t4 : t3);
-    };
-    // slot m of k-step kk: MFMA block (m / 4, m % 4), preceded by one memory operation.
-    //   TM = 4 (16 slots): even m reads fragment unit m/2 of the next k-step (in the last k-step,
-    //     after the barrier, of the next tile's first k-step); odd m does half a vector move,
-    //     alternately the store to LDS and the refill of the register.
-    //   TM = 3 (12 slots): m = 0, 2, .., 10 and 11 read the seven fragment units; m = 1, 3, .., 9
-    //     each move one whole vector (store, then refill) while vectors remain.
-    auto slot = [&](auto kk_c, auto m_c) __attribute__((always_inline)) {
-      constexpr int kk = decltype(kk_c)::value, m = decltype(m_c)::value;
-      if constexpr (kk == 3 && m == 0) __syncthreads();
-      constexpr int unit = (m % 2 == 0) ? m / 2 : ((TM == 3 && m == 11) ? 6 : -1);
-      if constexpr (unit >= 0) {
-        using U = std::integral_constant<int, unit>;
-        if constexpr (kk < 3)
-          fetch_unit(U{}, std::integral_constant<int, (kk + 1) & 1>{}, at, bt, std::integral_constant<int, kk + 1>{});
-        else
-          fetch_unit(U{}, C0{}, an, bn, C0{});
-      } else if constexpr (TM == 4) {
-        constexpr int o = (m - 1) / 2;                          // 0..7 within the k-step
-        using Q = std::integral_constant<int, (kk == 3 ? 0 : 4 + 4 * kk) + o / 2>;
-        if constexpr (o % 2 == 0) move_store(kk_c, Q{});
-        else move_load(kk_c, Q{});
-      } else {
-        constexpr int o = (m - 1) / 2;                          // 0..4 within the k-step
-        constexpr int q = kk == 3 ? o : Q3 + 5 * kk + o;
-        if constexpr (kk == 3 ? (o < Q3) : (q < NA + 8)) {
-          move_store(kk_c, std::integral_constant<int, q>{});
-          move_load(kk_c, std::integral_constant<int, q>{});
-        }
-      }
-      constexpr int i = m / 4, j = m % 4;
-      if constexpr (FIRST && kk == 0) {
-        constexpr f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[0][j], af[0][i], zero, 0, 0, 0);
-      } else {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[kk & 1][j], af[kk & 1][i], acc[i][j], 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto step = [&](auto kk_c) __attribute__((always_inline)) {
-      static_for<NS>([&](auto m) __attribute__((always_inline)) { slot(kk_c, m); });
-    };
-    step(std::integral_constant<int, 0>{});
-    step(std::integral_constant<int, 1>{});
-    step(std::integral_constant<int, 2>{});
-    step(std::integral_constant<int, 3>{});
-  };
-  if (nk >= 1) {
-    iteration(C0{}, std::true_type{}, 0);
-  } else {   // a split without k-tiles writes zeros
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-  }
-  for (int kt = 1; kt + 1 < nk; kt += 2) {
-    iteration(C1{}, std::false_type{}, kt);
-    iteration(C0{}, std::false_type{}, kt + 1);
-  }
-  if (nk >= 2 && !(nk & 1)) iteration(C1{}, std::false_type{}, nk - 1);
-
-  // the epilogue stages through the B stages (large enough for either tile height)
-  constexpr int ST_STRIDE = WN + 4;  // floats
-  static_assert(4 * 32 * ST_STRIDE * 4 <= 2 * B_SIZE * 2, "staging must fit in the B stages");
-  if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + blockIdx.y * p.c_split_stride;
-  if constexpr (SWIGLU)
-    store_tile_swiglu<TM>(p, acc, reinterpret_cast<float*>(Bs) + wave * 32 * ST_STRIDE, m0 + wm * WM,
-                          (n0 >> 1) + 64 * wn, lane);
-  else if constexpr (EPI == 2)
-    store_tile_swiglu_bwd<TM>(p, acc, reinterpret_cast<float*>(Bs) + wave * 32 * ST_STRIDE, m0 + wm * WM,
-                              n0 + wn * WN, lane);
-  else {
-    if constexpr (EPI == 3 || EPI == 4) {
-      if (rope_rotate_tile<TM, EPI == 3 ? 128 : 64>(p, acc, m0 + wm * WM, n0 + wn * WN, lane)) p.bias = nullptr;
-    }
-    store_tile<TM, TN, OUT_F32, true>(p, acc, reinterpret_cast<float*>(Bs) + wave * 32 * ST_STRIDE,
-                                      m0 + wm * WM, n0 + wn * WN, lane);
-  }
-}
-
-template <int TM, bool A_T, bool B_T, bool OUT_F32>
-__global__ __launch_bounds__(256) void gemm4_kernel(GemmParams p) {
-  gemm4_tile<TM, A_T, B_T, OUT_F32, false>(p);
-}
-// Weight gradients over a token count that is no multiple of 64.
-template <bool OUT_F32>
-__global__ __launch_bounds__(256) void gemm4_ragged_k_kernel(GemmParams p) {
-  gemm4_tile<4, true, true, OUT_F32, true>(p);
-}
-
-// Y = [gate | up] = X.W and silu(gate) * up in one pass (the decoder's MLP up-projection).
-__global__ __launch_bounds__(256) void gemm4_swiglu_kernel(GemmParams p) {
-  gemm4_tile<4, false, true, false, false, 1>(p);
-}
-// dA = dY.W_d^T kept in registers; [d gate | d up] written (the decoder's MLP down-projection, backward).
-__global__ __launch_bounds__(256) void gemm4_swiglu_bwd_kernel(GemmParams p) {
-  gemm4_tile<4, false, false, false, false, 2>(p);
-}
-
-// Y = X.W (+ b) with the rotary positions applied to the q and k heads in the epilogue.
-template <int HD>
-__global__ __launch_bounds__(256) void gemm4_rope_kernel(GemmParams p) {
-  gemm4_tile<4, false, true, false, false, HD == 128 ? 3 : 4>(p);
-}
-
-// The four-wavefront kernel takes a problem tiled 256 x 256 when K is a positive multiple of 64,
-// or any K >= 64 when k runs along the rows of both operands (the weight-gradient layout).
-bool takes_gemm4(const GemmArgs& g) {
-  return g.k >= BK && (g.k % BK == 0 || (g.a_layout != 0 && g.b_layout == 0));
-}
-// Its 192-row form when that saves rounds of one-per-CU workgroups.  A round of 192-row tiles
-// has three quarters of the MFMA work but the same prologue and epilogue: measured at 0.9 of a
-// round of 256-row tiles for K = 1024..4096.  Only for A stored [M, K] and unsplit problems.
-bool takes_rows192(const GemmArgs& g, int splits) {
-  if (!takes_gemm4(g) || g.a_layout != 0 || splits != 1) return false;
-  const int64_t tn = (g.n + 255) / 256, t192 = ((g.m + 191) / 192) * tn, t256 = ((g.m + 255) / 256) * tn;
-  return 9 * ((t192 + 255) / 256) < 10 * ((t256 + 255) / 256);
-}
-
-template <int BM, int BN, int WM, int WN, int BKT = 64>
-hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int splits = 1) {
-  GemmParams p = make_gemm_params(g, BM, BN);
-  p.kt_per_split = (int)((g.k + BKT - 1) / BKT);
-  if (splits > 1) {
+hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
+  const int bm = tile == GemmTile::T256 ? 256 : tile == GemmTile::T192 ? 192 : 128, bn = tile == GemmTile::T128 ? 128 : 256;
+  GemmParams p = make_gemm_params(g, bm, bn);
+  if (splits > 1) {   // the plan has made sure that no split is empty
     p.kt_per_split = (p.kt_per_split + splits - 1) / splits;
     p.c_split_stride = g.m * g.n;
   }
-  dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits), block(64 * (BM / WM) * (BN / WN));
-  const bool at = g.a_layout != 0, bt = g.b_layout == 0;  // b_layout 0 = [K,N] = transposing reads
-  if (BM == 256 && BN == 256 && takes_gemm4(g)) {
-    const dim3 block4(256);
-    if (g.swiglu_act) {   // launch_gemm has checked gemm_swiglu_fusable()
-      hipLaunchKernelGGL(gemm4_swiglu_kernel, grid, block4, 0, s, p);
-      return hipGetLastError();
-    }
-    if (g.swiglu_dpre) {
-      hipLaunchKernelGGL(gemm4_swiglu_bwd_kernel, grid, block4, 0, s, p);
-      return hipGetLastError();
-    }
-    if (g.rope_table) {   // launch_gemm has checked gemm_rope_fusable()
-      if (g.rope_head_dim == 128) hipLaunchKernelGGL(gemm4_rope_kernel<128>, grid, block4, 0, s, p);
-      else hipLaunchKernelGGL(gemm4_rope_kernel<64>, grid, block4, 0, s, p);
-      return hipGetLastError();
-    }
-    const bool rows192 = takes_rows192(g, splits);
-    if (rows192) {
-      p.tiles_m = (int)((g.m + 191) / 192);
-      grid.x = (unsigned)(p.tiles_m * p.tiles_n);
-    }
-#define MLLM_GEMM4_CASE(AT, BT, F32)                                                     \
-  if (at == AT && bt == BT && (g.out_fp32 != 0) == F32) {                                \
-    if constexpr (!AT) {                                                                 \
-      if (rows192) {                                                                     \
-        hipLaunchKernelGGL((gemm4_kernel<3, AT, BT, F32>), grid, block4, 0, s, p);       \
-        return hipGetLastError();                                                        \
-      }                                                                                  \
-    }                                                                                    \
-    if constexpr (AT && BT) {                                                            \
-      if (g.k % BK != 0) {                                                               \
-        hipLaunchKernelGGL((gemm4_ragged_k_kernel<F32>), grid, block4, 0, s, p);         \
-        return hipGetLastError();                                                        \
-      }                                                                                  \
-    }                                                                                    \
-    hipLaunchKernelGGL((gemm4_kernel<4, AT, BT, F32>), grid, block4, 0, s, p);           \
-    return hipGetLastError();                                                            \
-  }
-    MLLM_GEMM4_CASE(false, true, false)
-    MLLM_GEMM4_CASE(false, false, false)
-    MLLM_GEMM4_CASE(true, true, true)
-    MLLM_GEMM4_CASE(false, true, true)
-    MLLM_GEMM4_CASE(false, false, true)
-    MLLM_GEMM4_CASE(true, true, false)
-    MLLM_GEMM4_CASE(true, false, false)
-    MLLM_GEMM4_CASE(true, false, true)
-#undef MLLM_GEMM4_CASE
-  }
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
+  const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
+  const bool at = g.a_layout != 0, bt = g.b_layout == 0, f32 = g.out_fp32 != 0;   // b_layout 0: stored [K, N], transposing reads
+  if (at) return bt ? launch_gemm_tile<true, true>(p, tile, f32, epi, grid, s) : launch_gemm_tile<true, false>(p, tile, f32, epi, grid, s);
+  return bt ? launch_gemm_tile<false, true>(p, tile, f32, epi, grid, s) : launch_gemm_tile<false, false>(p, tile, f32, epi, grid, s);
+}
+
+// K no multiple of 64 with an operand whose contiguous dimension is k, or K = 0.
+template <int BM, int BN, int WM, int WN, int BKT = 64>
+hipError_t launch_general(const GemmArgs& g, hipStream_t s) {
+  const GemmParams p = make_gemm_params(g, BM, BN);
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(64 * (BM / WM) * (BN / WN));
+  const bool at = g.a_layout != 0, bt = g.b_layout == 0;
 #define MLLM_GEMM_CASE(AT, BT, F32)                                                      \
   if (at == AT && bt == BT && (g.out_fp32 != 0) == F32) {                                \
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AT, BT, F32, BKT>), grid, block, 0, s, p); \
     return hipGetLastError();                                                            \
   }
-  MLLM_GEMM_CASE(false, true, false)   // Y = X.W
-  MLLM_GEMM_CASE(false, false, false)  // dX = dY.W^T (W stored [K_out.., ] as [N,K])
-  MLLM_GEMM_CASE(true, true, true)     // dW = X^T.dY, fp32
+  MLLM_GEMM_CASE(false, true, false)
+  MLLM_GEMM_CASE(false, false, false)
+  MLLM_GEMM_CASE(true, true, true)
   MLLM_GEMM_CASE(false, true, true)
   MLLM_GEMM_CASE(false, false, true)
   MLLM_GEMM_CASE(true, true, false)
@@ -643,49 +281,57 @@ hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int splits = 1) {
 
 }  // namespace
 
-// Weight-gradient GEMMs of narrow layers (M x N small, K = tokens large) have too few output tiles
-// to fill 256 CUs.  They are cut along K into `splits` partial products (fp32, in a scratch
-// buffer), summed afterwards in a fixed order.  Returns 1 when the plain launch is used.
+// Tile and number of parts of the K loop.  A problem with few output tiles leaves CUs idle, one with a bit more
+// than a multiple of 256 tiles an almost empty last round; cutting the K loop in `splits` parts (partial
+// products in fp32 in a scratch buffer, summed in a fixed order afterwards) makes as many times more
+// workgroups.  The plan is the cheapest of all choices by an estimate in microseconds whose constants were
+// fitted to every tile and split of 44 shapes (m 128..32768, n 192..12800, k 128..37888): rounds of
+// workgroups times (k-tiles of a part times the time of a k-tile, which grows with the number of
+// workgroups that share power and memory, plus a workgroup's start and end), plus the parts' trip
+// through memory.  Measured against the best choice of a shape it loses 3 % on average; examples (us):
+// 777 x 4096 x 14336 128x128 tiles 104, 256x256 in 4 parts 99; 777 x 4096 x 4096 33 and 47;
+// 2999 x 3584 x 37888 192x256 tiles 731, 256x256 in 3 parts 640; 1024 x 1024 x 26496 256x256 in 12 parts 68, in
+// 16 parts 83.
 namespace {
-struct SplitPlan { int splits; bool big_tile; };
-SplitPlan plan_split(int64_t m, int64_t n, int64_t k) {
-  const int64_t t256 = ((m + 255) / 256) * ((n + 255) / 256), t128 = ((m + 127) / 128) * ((n + 127) / 128);
+struct GemmPlan { GemmTile tile; int splits; };
+struct TileCost {
+  GemmTile tile; int bm, bn;
+  int slots;              // workgroups of a round
+  int few;                // up to this many, a k-tile costs k_few; from there on k_more, rising to k_full for a full round
+  double k_few, k_more, k_full, fixed;
+};
+GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool split_ok) {
+  static const TileCost costs[] = {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
+                                   {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
+                                   {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}};   // two on a CU from 257 on
   const int64_t nk = (k + BK - 1) / BK;
-  if (t256 >= 200) {
-    // Enough tiles to fill the chip, but a last partial round of workgroups can leave most CUs
-    // idle (1.5 rounds cost 2).  Cutting K in S parts makes S times as many, S times shorter
-    // workgroups: pick the S <= 4 with the fewest rounds per unit of work, charging the
-    // reduction pass about a twentieth of a round.
-    int best = 1;
-    double best_cost = (double)((t256 + 255) / 256);
-    for (int sp = 2; sp <= 4 && nk / sp >= 64; sp++) {
-      const double cost = (double)((t256 * sp + 255) / 256) / sp + 0.05 * sp;
-      if (cost < best_cost - 1e-9) { best_cost = cost; best = sp; }
+  GemmPlan best{GemmTile::T256, 1};
+  if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
+  double best_cost = 1e300;
+  for (const TileCost& c : costs) {
+    if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
+    const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
+    const int64_t cap = split_ok ? std::max<int64_t>(1, std::min<int64_t>(16, nk / 8)) : 1;   // at least 8 k-tiles a part
+    for (int64_t sp = 1; sp <= cap; sp++) {
+      const int64_t per = (nk + sp - 1) / sp;
+      if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
+      const int64_t wgs = tiles * sp, rounds = wgs / c.slots, rest = wgs % c.slots;
+      double cost = (double)rounds * ((double)per * c.k_full + c.fixed);
+      if (rest > 0) {
+        const double kt = rest <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(rest - c.few) / (c.slots - c.few);
+        cost += (double)per * kt + c.fixed;
+      }
+      if (sp > 1) cost += 3.0 + (double)m * n * (8.0 * sp + 4.0) * 1e-7;
+      if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp}; }
     }
-    return {best, true};
   }
-  const bool big = t256 >= 24;
-  const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(16, nk / 8));   // at least 8 k-tiles per split
-  if (big) {
-    // One 256x256 workgroup per CU: S splits make t256 * S workgroups that run in
-    // ceil(t256 * S / 256) rounds of 1/S of the K loop each; a split also costs its partial
-    // product's trip through memory, about a hundredth of a full K loop.
-    int best = 1;
-    double best_cost = 1e30;
-    for (int sp = 1; sp <= cap; sp++) {
-      const double cost = (double)((t256 * sp + 255) / 256) / sp + 0.01 * sp;
-      if (cost < best_cost - 1e-9) { best_cost = cost; best = sp; }
-    }
-    return {best, true};
-  }
-  const int64_t want = std::min<int64_t>((512 + t128 - 1) / t128, cap);
-  return {(int)std::max<int64_t>(want, 1), false};
+  return best;
 }
 }  // namespace
 
-size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k) {
-  const SplitPlan sp = plan_split(m, n, k);
-  return sp.splits > 1 ? (size_t)sp.splits * (size_t)m * (size_t)n * 4 : 0;
+size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t) {
+  const GemmPlan pl = plan_gemm(m, n, k, a_t, true);
+  return pl.splits > 1 ? (size_t)pl.splits * (size_t)m * (size_t)n * 4 : 0;
 }
 
 bool gemm_swiglu_fusable(int64_t m, int64_t n, int64_t k) {
@@ -723,31 +369,38 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.ldc * (g.out_fp32 ? 4 : 2) * 128 > 0xFFFFFFFFll || (g.residual && g.ldres * 2 * 128 > 0xFFFFFFFFll))
     return hipErrorInvalidValue;
   const int64_t big_tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
-  const SplitPlan sp = plan_split(g.m, g.n, g.k);
-  const bool split = sp.splits > 1 && g.out_fp32 && !g.bias && g.ldc == g.n && g.splitk_ws &&
-                     g.splitk_ws_bytes >= (size_t)sp.splits * g.m * g.n * 4;
-  const bool large = big_tiles >= 200 || (split && sp.big_tile);
-  // timing classes: the three layouts of the 256x256 kernel, its 192-row form, and the 128x128 kernel
-  const int cls = !large ? PROF_GEMM_SMALL : (!split && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && takes_rows192(g, 1)) ? PROF_GEMM_ROWS192
+  const bool tiled = takes_tile_kernel(g), fused = g.swiglu_act || g.swiglu_dpre || g.rope_table;
+  GemmPlan pl{GemmTile::T256, 1};   // the fused epilogues exist for this tile
+  if (tiled && !fused) {
+    const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
+    pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok);
+    if (pl.splits > 1 && g.splitk_ws_bytes < (size_t)pl.splits * g.m * g.n * 4) pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, false);
+  }
+  // timing classes: the three layouts of the large tiles, the 192-row form, and the small tiles
+  const bool small = tiled ? pl.tile == GemmTile::T128 : big_tiles < 200;
+  const int cls = small ? PROF_GEMM_SMALL : pl.tile == GemmTile::T192 ? PROF_GEMM_ROWS192
                   : g.a_layout ? PROF_GEMM_DW : (g.b_layout ? PROF_GEMM_DX : PROF_GEMM_FWD);
   const double flops = 2.0 * (double)g.m * (double)g.n * (double)g.k;
-  // 256x256 tiles (8 wavefronts of 128x64) once they fill the chip; smaller problems keep
-  // 128x128 tiles so that more workgroups exist.
-  if (!split) {
+  if (pl.splits == 1) {
     ProfScope prof(cls, flops, s);
-    return big_tiles >= 200 ? launch_tile<256, 256, 128, 64>(g, s) : launch_tile<128, 128, 64, 64>(g, s);
+    if (tiled) return launch_tiles(g, pl.tile, 1, s);
+    // 256x256 tiles (8 wavefronts of 128x64) once they fill the chip; smaller problems keep
+    // 128x128 tiles so that more workgroups exist
+    return small ? launch_general<128, 128, 64, 64>(g, s) : launch_general<256, 256, 128, 64>(g, s);
   }
   GemmArgs part = g;
   part.c = g.splitk_ws;
+  part.out_fp32 = 1;
   part.accumulate = 0;
+  part.bias = nullptr;
+  part.residual = nullptr;
   hipError_t e;
   {
     ProfScope prof(cls, flops, s);
-    e = sp.big_tile ? launch_tile<256, 256, 128, 64>(part, s, sp.splits)
-                    : launch_tile<128, 128, 64, 64>(part, s, sp.splits);
+    e = launch_tiles(part, pl.tile, pl.splits, s);
   }
   if (e != hipSuccess) return e;
-  return launch_splitk_reduce((const float*)g.splitk_ws, (float*)g.c, sp.splits, g.m * g.n, g.accumulate, s);
+  return launch_splitk_reduce((const float*)g.splitk_ws, g.c, pl.splits, g.m, g.n, g.out_fp32, g.accumulate, g.bias, g.residual, g.ldres, s);
 }
 
 }  // namespace mllm

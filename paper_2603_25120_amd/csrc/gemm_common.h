@@ -58,6 +58,12 @@ inline GemmParams make_gemm_params(const GemmArgs& g, int bm, int bn) {
   return p;
 }
 
+// Output tiles of the MFMA kernel (gemm_tile.h) and its epilogues.
+enum class GemmTile { T256, T192, T128 };   // 256 x 256, 192 x 256 (A stored [M, K]), 128 x 128
+enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_ROPE64 = 4 };
+template <bool A_T, bool B_T>
+hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
+
 constexpr int GROUP_M = 8;
 
 // Workgroups are dealt round-robin to the 8 XCDs.  Renumber so that each XCD gets a contiguous
@@ -192,180 +198,249 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM
   else emit(std::false_type{});
 }
 
-// Rotary positions on a wavefront's 32*TM x 128 sub-tile while it is still in the accumulators
-// (rows from row0, columns from col0, a multiple of 128, so the sub-tile holds whole heads of HD =
-// 128 or 64).  A lane owns row lane%32 of every band, so the row's position and its angles are the
-// lane's own, and the half-split partner of column c, c + HD/2, lies HD/64 accumulator blocks
-// further in the same lane: the rotation needs no exchange.  With a bias the rotation applies to
-// x.W + b, so the bias is added here (the caller then stores without it).  Sub-tiles past
-// rope_cols (the v columns) are left alone; the branch is wavefront-uniform.
-template <int TM, int HD>
-__device__ __forceinline__ bool rope_rotate_tile(const GemmParams& p, f32x16 (&acc)[TM][4], int64_t row0,
-                                                 int64_t col0, int lane) {
-  static_assert(HD == 128 || HD == 64, "heads of 64 or 128");
-  if (col0 >= p.rope_cols) return false;
-  constexpr int HALF = HD / 2, STEP = HD / 64;      // partner block = block + STEP
-  const int h = lane >> 5, cl = lane & 31;
-  if (p.bias) {
+// ---------------------------------------------------------------------------------------------
+// Epilogues of the large-tile kernels, straight from the accumulators.  The MFMAs (16x16x32) are
+// issued with the operands swapped, so an accumulator block holds C transposed: lane l owns row
+// l%16 of the block and columns 4*(l/16) .. +3.  In bf16 that is 8 bytes a lane and block; one
+// v_permlane16_swap per 32-bit word of a pair of neighbouring blocks exchanges the odd 16-lane rows
+// of the left block with the even ones of the right block, after which every lane holds eight
+// consecutive columns (block of the pair: (l/16)%2, columns 8*(l/32) .. +7) and the pair leaves in one
+// 16-byte store, 64 contiguous bytes a row.  The swap is its own inverse: bf16 operands of the
+// epilogue (residual, gate, up) come in as 16-byte chunks and are swapped into the accumulators'
+// layout.  Nothing passes through LDS and no barrier is needed.
+// Addresses: a buffer over the wavefront's rows of the matrix that starts at the sub-tile's first
+// element (rows past the matrix are past its end and dropped by the range check; the host keeps 128
+// row pitches below 4 GiB); chunks past the last column get an offset that is never in range.
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ void swap_rows16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+// Four bf16 columns of two neighbouring blocks (x: left, y: right) <-> the lane's 16-byte chunk.
+struct PairChunk { uint32_t x0, x1, y0, y1; };
+__device__ __forceinline__ u32x4 to_chunk(PairChunk c) {
+  swap_rows16(c.x0, c.y0);
+  swap_rows16(c.x1, c.y1);
+  return u32x4{c.x0, c.x1, c.y0, c.y1};
+}
+__device__ __forceinline__ PairChunk from_chunk(u32x4 v) {
+  PairChunk c{v[0], v[1], v[2], v[3]};
+  swap_rows16(c.x0, c.y0);
+  swap_rows16(c.x1, c.y1);
+  return c;
+}
+__device__ __forceinline__ PairChunk pack_pair(const f32x4& l, const f32x4& r) {
+  return {pack_bf16x2(l[0], l[1]), pack_bf16x2(l[2], l[3]), pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
+}
+__device__ __forceinline__ void unpack_pair(const PairChunk& c, f32x4& l, f32x4& r) {
+  l = f32x4{bf16lo(c.x0), bf16hi(c.x0), bf16lo(c.x1), bf16hi(c.x1)};
+  r = f32x4{bf16lo(c.y0), bf16hi(c.y0), bf16lo(c.y1), bf16hi(c.y1)};
+}
+// Rows [0, rows_left) of a matrix from `first` on (row pitch in bytes); rows_left <= 0: empty.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_buffer(const void* first, int rows_left, uint32_t pitch) {
+  return make_rsrc(first, rows_left > 0 ? (uint32_t)rows_left * pitch : 0u);
+}
+
+// Rotary positions on a row of blocks while it is still in registers (columns from a multiple of HD, so
+// the blocks hold whole heads of HD = 128 or 64).  A lane owns one row, so the row's position and its angles
+// are the lane's own, and the half-split partner of column c, c + HD/2, lies HD/32 blocks further in the
+// same lane: the rotation needs no exchange.  trow: the row's factors, cos then sin.
+template <int WN, int HD>
+__device__ __forceinline__ void rope_rotate_row(f32x4 (&v)[WN], const float* trow, int g) {
+  static_assert((HD == 128 || HD == 64) && 16 * WN % HD == 0, "whole heads of 64 or 128");
+  constexpr int HALF = HD / 2, STEP = HD / 32;      // partner block = block + STEP
 #pragma unroll
-    for (int j = 0; j < 4; j++)
+  for (int f = 0; f < HALF / 16; f++) {   // frequencies 16 f + 4 g .. +3
+    const f32x4 c = *reinterpret_cast<const f32x4*>(trow + 16 * f + 4 * g);
+    const f32x4 s = *reinterpret_cast<const f32x4*>(trow + HALF + 16 * f + 4 * g);
 #pragma unroll
-      for (int g4 = 0; g4 < 4; g4++) {
-        const uint2 bb = *reinterpret_cast<const uint2*>(p.bias + col0 + 32 * j + 8 * g4 + 4 * h);
-        const float b0 = bf16lo(bb.x), b1 = bf16hi(bb.x), b2 = bf16lo(bb.y), b3 = bf16hi(bb.y);
+    for (int head = 0; head < 16 * WN / HD; head++) {
+      f32x4& a = v[head * 2 * STEP + f];
+      f32x4& b = v[head * 2 * STEP + f + STEP];
 #pragma unroll
-        for (int i = 0; i < TM; i++) {
-          acc[i][j][4 * g4] += b0; acc[i][j][4 * g4 + 1] += b1; acc[i][j][4 * g4 + 2] += b2; acc[i][j][4 * g4 + 3] += b3;
+      for (int e = 0; e < 4; e++) {
+        const float x1 = a[e], x2 = b[e];
+        a[e] = x1 * c[e] - x2 * s[e];
+        b[e] = x2 * c[e] + x1 * s[e];
+      }
+    }
+  }
+}
+
+// C (+)= acc (+ bias, then rotated) (+ residual): WM x WN blocks of 16 x 16 from (row0, col0).  ROPE_HD:
+// head width of the rotary positions, 0 for none; sub-tiles past rope_cols (the v columns) are not rotated.
+// One row of blocks at a time; what a call does not have is decided once, in front of the rows.
+template <int WM, int WN, bool OUT_F32, int ROPE_HD = 0>
+__device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane) {
+  constexpr int ESIZE = OUT_F32 ? 4 : 2;
+  const int g = lane >> 4, r = lane & 15;
+  const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
+  const int cols_left = (int)max((int64_t)0, min((int64_t)(16 * WN), p.N - col0));
+  const uint32_t pitch = (uint32_t)(p.ldc * ESIZE);
+  const __amdgpu_buffer_rsrc_t rc = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + col0) * ESIZE, rows_left, pitch);
+  const int lc = OUT_F32 ? 4 * g : 16 * (g & 1) + 8 * (g >> 1);   // the lane's columns inside a block / a pair of blocks
+  const uint32_t lane_off = (uint32_t)r * pitch + (uint32_t)(ESIZE * lc);
+  const uint32_t rpitch = (uint32_t)(p.ldres * 2), rlane_off = (uint32_t)r * rpitch + (uint32_t)(2 * lc);
+  const __amdgpu_buffer_rsrc_t rr = rows_buffer(p.res + row0 * p.ldres + col0, !OUT_F32 && p.res ? rows_left : 0, rpitch);
+  auto rows = [&](auto bias_c, auto add_c, auto rope_c) __attribute__((always_inline)) {
+    constexpr bool BIAS = decltype(bias_c)::value, ADD = decltype(add_c)::value, ROPE = decltype(rope_c)::value;
+    f32x4 bias[BIAS ? WN : 1];
+    if constexpr (BIAS) {
+#pragma unroll
+      for (int j = 0; j < WN; j++) {
+        uint2 bb = make_uint2(0, 0);
+        if (16 * j + 4 * g < cols_left) bb = *reinterpret_cast<const uint2*>(p.bias + col0 + 16 * j + 4 * g);
+        bias[j] = f32x4{bf16lo(bb.x), bf16hi(bb.x), bf16lo(bb.y), bf16hi(bb.y)};
+      }
+    }
+    // what is added to C's chunks (the residual, or C itself when accumulating), a row of blocks ahead
+    constexpr int NCH = OUT_F32 ? WN : WN / 2, CHUNK = OUT_F32 ? 16 : 32;   // chunks per row of blocks, their columns
+    u32x4 add[2][ADD ? NCH : 1];
+    auto offset = [&](int i, int q, uint32_t lo, uint32_t pt) {
+      return (int)(CHUNK * q + lc < cols_left ? lo + (uint32_t)(16 * i) * pt + 64 * q : OOB);
+    };
+    auto fetch = [&](int i) {
+#pragma unroll
+      for (int q = 0; q < NCH; q++)
+        add[i & 1][q] = OUT_F32 ? __builtin_amdgcn_raw_buffer_load_b128(rc, offset(i, q, lane_off, pitch), 0, 0)
+                                : __builtin_amdgcn_raw_buffer_load_b128(rr, offset(i, q, rlane_off, rpitch), 0, 0);
+    };
+    if constexpr (ADD) fetch(0);
+#pragma unroll
+    for (int i = 0; i < WM; i++) {
+      if constexpr (ADD) {
+        if (i + 1 < WM) fetch(i + 1);
+      }
+      f32x4 v[WN];
+#pragma unroll
+      for (int j = 0; j < WN; j++) {
+        v[j] = acc[i][j];
+        if constexpr (OUT_F32) asm volatile("" : "+v"(v[j]));
+        if constexpr (BIAS) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) v[j][e] += bias[j][e];
         }
       }
+      if constexpr (ROPE) {
+        const int64_t row = row0 + 16 * i + r;
+        const int pos = row < p.M ? p.rope_pos[row] : 0;
+        rope_rotate_row<WN, ROPE_HD>(v, p.rope_table + (int64_t)pos * ROPE_HD, g);
+      }
+#pragma unroll
+      for (int q = 0; q < NCH; q++) {
+        if constexpr (OUT_F32) {
+          if constexpr (ADD) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[q][e] += __uint_as_float(add[i & 1][q][e]);
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[q]), rc, offset(i, q, lane_off, pitch), 0, 0);
+        } else {
+          f32x4 l = v[2 * q], h = v[2 * q + 1];
+          if constexpr (ADD) {
+            f32x4 a, b;
+            unpack_pair(from_chunk(add[i & 1][q]), a, b);
+#pragma unroll
+            for (int e = 0; e < 4; e++) { l[e] += a[e]; h[e] += b[e]; }
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(l, h)), rc, offset(i, q, lane_off, pitch), 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  const bool add = OUT_F32 ? p.accumulate != 0 : p.res != nullptr;
+  if constexpr (ROPE_HD != 0) {   // a forward product without residual
+    if (col0 < p.rope_cols) { if (p.bias) rows(T{}, F{}, T{}); else rows(F{}, F{}, T{}); return; }
+    if (p.bias) rows(T{}, F{}, F{}); else rows(F{}, F{}, F{});
+  } else if (p.bias) {
+    if (add) rows(T{}, T{}, F{}); else rows(T{}, F{}, F{});
+  } else {
+    if (add) rows(F{}, T{}, F{}); else rows(F{}, F{}, F{});
   }
+}
+
+// Epilogue of the fused SwiGLU product.  The left half of the sub-tile's blocks are gate columns
+// gcol0 .., the right half the up columns of the same indices.  Writes gate and up into C = [gate | up]
+// ([M, N], up at column N / 2 + gcol) and silu(gate) * up, from the fp32 accumulators, into act
+// ([M, N / 2]).  The sub-tile's columns all exist (N / 2 is a multiple of the tile's gate columns).
+template <int WM, int WN>
+__device__ __forceinline__ void store_blocks_swiglu(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t gcol0, int lane) {
+  const int g = lane >> 4, r = lane & 15, lc = 16 * (g & 1) + 8 * (g >> 1);
+  const int64_t half = p.N >> 1;
+  const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
+  const uint32_t c_pitch = (uint32_t)(p.ldc * 2), a_pitch = (uint32_t)(half * 2);
+  const __amdgpu_buffer_rsrc_t rg = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + gcol0) * 2, rows_left, c_pitch);
+  const __amdgpu_buffer_rsrc_t ru = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + half + gcol0) * 2, rows_left, c_pitch);
+  const __amdgpu_buffer_rsrc_t ra = rows_buffer(p.act + row0 * half + gcol0, rows_left, a_pitch);
+  const uint32_t c_lane = (uint32_t)r * c_pitch + (uint32_t)(2 * lc), a_lane = (uint32_t)r * a_pitch + (uint32_t)(2 * lc);
 #pragma unroll
-  for (int i = 0; i < TM; i++) {
-    const int64_t row = row0 + 32 * i + cl;
-    const int pos = row < p.M ? p.rope_pos[row] : 0;
-    const float* trow = p.rope_table + (int64_t)pos * HD;
+  for (int i = 0; i < WM; i++) {
+    const uint32_t co = c_lane + (uint32_t)(16 * i) * c_pitch, ao = a_lane + (uint32_t)(16 * i) * a_pitch;
 #pragma unroll
-    for (int jj = 0; jj < 2; jj++) {
-      // HD = 128: blocks (0, 2) and (1, 3), frequencies 32 jj + ...; HD = 64: blocks (0, 1) and (2, 3), two heads
-      const int j1 = HD == 128 ? jj : 2 * jj, j2 = j1 + STEP;
+    for (int jp = 0; jp < WN / 4; jp++) {
+      f32x4 a[2];
 #pragma unroll
-      for (int g4 = 0; g4 < 4; g4++) {
-        const int f0 = (HD == 128 ? 32 * jj : 0) + 8 * g4 + 4 * h;
-        const float4 c = *reinterpret_cast<const float4*>(trow + f0);
-        const float4 sn = *reinterpret_cast<const float4*>(trow + HALF + f0);
-        const float cs[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
+      for (int q = 0; q < 2; q++) {
+        const f32x4 gt = acc[i][2 * jp + q], up = acc[i][WN / 2 + 2 * jp + q];
+#pragma unroll
+        for (int e = 0; e < 4; e++)   // silu through the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
+          a[q][e] = gt[e] * up[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[e] * -1.44269504088896340736f));
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(acc[i][2 * jp], acc[i][2 * jp + 1])), rg, (int)(co + 64 * jp), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(acc[i][WN / 2 + 2 * jp], acc[i][WN / 2 + 2 * jp + 1])), ru, (int)(co + 64 * jp), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(a[0], a[1])), ra, (int)(ao + 64 * jp), 0, 0);
+    }
+  }
+}
+
+// Epilogue of dA = dY.W_d^T with SwiGLU's gradient: dA never reaches memory.  A lane takes the gate and
+// up chunks of its rows and columns from pre = [gate | up] ([M, 2N], requested a row of blocks ahead) and
+// writes
+//   d gate = dA * up * s * (1 + gate * (1 - s)),  d up = dA * gate * s,  s = sigmoid(gate)
+// to dpre = [d gate | d up] ([M, 2N]).
+template <int WM, int WN>
+__device__ __forceinline__ void store_blocks_swiglu_bwd(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane) {
+  const int g = lane >> 4, r = lane & 15, lc = 16 * (g & 1) + 8 * (g >> 1);
+  const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
+  const int cols_left = (int)max((int64_t)0, min((int64_t)(16 * WN), p.N - col0));
+  const uint32_t pitch = (uint32_t)(p.N * 4);   // bytes: a row of [M, 2N] bf16
+  const int64_t at = row0 * 2 * p.N + col0;
+  const __amdgpu_buffer_rsrc_t rg = rows_buffer(p.pre + at, rows_left, pitch), ru = rows_buffer(p.pre + at + p.N, rows_left, pitch);
+  const __amdgpu_buffer_rsrc_t wg = rows_buffer(p.dpre + at, rows_left, pitch), wu = rows_buffer(p.dpre + at + p.N, rows_left, pitch);
+  const uint32_t lane_off = (uint32_t)r * pitch + (uint32_t)(2 * lc);
+  auto offset = [&](int i, int jp) { return (int)(32 * jp + lc < cols_left ? lane_off + (uint32_t)(16 * i) * pitch + 64 * jp : OOB); };
+  u32x4 gq[2][WN / 2], uq[2][WN / 2];
+  auto fetch = [&](int i) {
+#pragma unroll
+    for (int jp = 0; jp < WN / 2; jp++) {
+      gq[i & 1][jp] = __builtin_amdgcn_raw_buffer_load_b128(rg, offset(i, jp), 0, 0);
+      uq[i & 1][jp] = __builtin_amdgcn_raw_buffer_load_b128(ru, offset(i, jp), 0, 0);
+    }
+  };
+  fetch(0);
+#pragma unroll
+  for (int i = 0; i < WM; i++) {
+    if (i + 1 < WM) fetch(i + 1);
+#pragma unroll
+    for (int jp = 0; jp < WN / 2; jp++) {
+      f32x4 gt[2], up[2], og[2], ou[2];
+      unpack_pair(from_chunk(gq[i & 1][jp]), gt[0], gt[1]);
+      unpack_pair(from_chunk(uq[i & 1][jp]), up[0], up[1]);
+#pragma unroll
+      for (int q = 0; q < 2; q++)
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          const float x1 = acc[i][j1][4 * g4 + e], x2 = acc[i][j2][4 * g4 + e];
-          acc[i][j1][4 * g4 + e] = x1 * cs[e] - x2 * ss[e];
-          acc[i][j2][4 * g4 + e] = x2 * cs[e] + x1 * ss[e];
+          const float d = acc[i][2 * jp + q][e];
+          const float s = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[q][e] * -1.44269504088896340736f));
+          const float gs = gt[q][e] * s;
+          og[q][e] = d * up[q][e] * (s + gs * (1.f - s));
+          ou[q][e] = d * gs;
         }
-      }
-    }
-  }
-  return true;
-}
-
-// Epilogue of the fused SwiGLU product.  The wavefront's 32*TM x 128 sub-tile holds 64 gate
-// columns (accumulator blocks 0, 1) and the 64 up columns of the same indices (blocks 2, 3):
-// columns gcol0 .. gcol0 + 63 of gate and of up.  Each band of 32 rows is staged through LDS
-// like in store_tile; a lane then takes a gate chunk of 8 columns and its up chunk of the same
-// row and writes three 16-byte pieces: gate and up into C = [gate | up] ([M, N], up at column
-// N / 2 + gcol) and silu(gate) * up into act ([M, N / 2]).  The sub-tile's columns all exist
-// (N / 2 is a multiple of 128); rows past M are skipped.
-template <int TM>
-__device__ __forceinline__ void store_tile_swiglu(const GemmParams& p, f32x16 (&acc)[TM][4], float* stage,
-                                                  int64_t row0, int64_t gcol0, int lane) {
-  constexpr int ST_STRIDE = 128 + 4;
-  const int h = lane >> 5, cl = lane & 31;
-  const int rr0 = lane >> 3, cc = (lane & 7) * 8;          // 8 rows per pass, 8 gate chunks per row
-  const int64_t half = p.N >> 1;
-  const int rows_left = (int)min((int64_t)(32 * TM), p.M - row0);
-  char* const c_base = reinterpret_cast<char*>(p.c) + (row0 * p.ldc + gcol0) * 2;
-  char* const a_base = reinterpret_cast<char*>(p.act) + (row0 * half + gcol0) * 2;
-  const uint32_t c_pitch = (uint32_t)(p.ldc * 2), a_pitch = (uint32_t)(half * 2);
-  const uint32_t up_off = (uint32_t)(half * 2);
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-    if (i == 0) __syncthreads();
-    else __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; g4++)
-        *reinterpret_cast<float4*>(stage + cl * ST_STRIDE + 32 * j + 8 * g4 + 4 * h) =
-            make_float4(acc[i][j][4 * g4], acc[i][j][4 * g4 + 1], acc[i][j][4 * g4 + 2], acc[i][j][4 * g4 + 3]);
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-      const int rr = rr0 + 8 * t, r = 32 * i + rr;
-      if (r >= rows_left) continue;
-      float g[8], u[8], a[8];
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const float4 vg = *reinterpret_cast<const float4*>(stage + rr * ST_STRIDE + cc + 4 * q);
-        const float4 vu = *reinterpret_cast<const float4*>(stage + rr * ST_STRIDE + 64 + cc + 4 * q);
-        g[4 * q] = vg.x; g[4 * q + 1] = vg.y; g[4 * q + 2] = vg.z; g[4 * q + 3] = vg.w;
-        u[4 * q] = vu.x; u[4 * q + 1] = vu.y; u[4 * q + 2] = vu.z; u[4 * q + 3] = vu.w;
-      }
-#pragma unroll
-      for (int e = 0; e < 8; e++)   // silu through the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
-        a[e] = g[e] * u[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(g[e] * -1.44269504088896340736f));
-      char* const dst = c_base + ((uint32_t)r * c_pitch + (uint32_t)(cc * 2));
-      *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3]),
-                                                  pack_bf16x2(g[4], g[5]), pack_bf16x2(g[6], g[7]));
-      *reinterpret_cast<uint4*>(dst + up_off) = make_uint4(pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3]),
-                                                           pack_bf16x2(u[4], u[5]), pack_bf16x2(u[6], u[7]));
-      *reinterpret_cast<uint4*>(a_base + ((uint32_t)r * a_pitch + (uint32_t)(cc * 2))) =
-          make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
-    }
-  }
-}
-
-// Epilogue of dA = dY.W_d^T with SwiGLU's gradient: the sub-tile of dA (32*TM x 128, columns from
-// col0) never reaches memory.  Band by band it is staged through LDS like in store_tile; a lane
-// takes a chunk of 8 columns of dA, the gate and up chunks of the same row and columns from
-// pre = [gate | up] ([M, 2N], requested for the whole band before the staging), and writes
-//   d gate = dA * up * s * (1 + gate * (1 - s)),  d up = dA * gate * s,  s = sigmoid(gate)
-// to dpre = [d gate | d up] ([M, 2N]).  Rows past M and columns past N are skipped.
-template <int TM>
-__device__ __forceinline__ void store_tile_swiglu_bwd(const GemmParams& p, f32x16 (&acc)[TM][4], float* stage,
-                                                      int64_t row0, int64_t col0, int lane) {
-  constexpr int ST_STRIDE = 128 + 4, PER_BAND = 8, ROWS_PER_PASS = 4;
-  const int h = lane >> 5, cl = lane & 31;
-  const int rr0 = lane >> 4, cc = (lane & 15) * 8;
-  const bool col_ok = col0 + cc < p.N;
-  const int rows_left = (int)min((int64_t)(32 * TM), p.M - row0);
-  const uint32_t pitch = (uint32_t)(p.N * 4), up_off = (uint32_t)(p.N * 2);   // bytes: a row of [M, 2N] bf16; the up half
-  const char* const pre_base = reinterpret_cast<const char*>(p.pre) + (row0 * 2 * p.N + col0) * 2;
-  char* const dpre_base = reinterpret_cast<char*>(p.dpre) + (row0 * 2 * p.N + col0) * 2;
-  const uint32_t lane_off = (uint32_t)rr0 * pitch + (uint32_t)(cc * 2);
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-    uint4 gq[PER_BAND], uq[PER_BAND];
-#pragma unroll
-    for (int t = 0; t < PER_BAND; t++) {
-      const int r = 32 * i + t * ROWS_PER_PASS;
-      const bool ok = r + rr0 < rows_left && col_ok;
-      const char* src = pre_base + (lane_off + (uint32_t)r * pitch);
-      gq[t] = ok ? *reinterpret_cast<const uint4*>(src) : make_uint4(0, 0, 0, 0);
-      uq[t] = ok ? *reinterpret_cast<const uint4*>(src + up_off) : make_uint4(0, 0, 0, 0);
-    }
-    if (i == 0) __syncthreads();
-    else __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; g4++)
-        *reinterpret_cast<float4*>(stage + cl * ST_STRIDE + 32 * j + 8 * g4 + 4 * h) =
-            make_float4(acc[i][j][4 * g4], acc[i][j][4 * g4 + 1], acc[i][j][4 * g4 + 2], acc[i][j][4 * g4 + 3]);
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int t = 0; t < PER_BAND; t++) {
-      const int rr = rr0 + t * ROWS_PER_PASS, r = 32 * i + t * ROWS_PER_PASS;
-      if (!(r + rr0 < rows_left && col_ok)) continue;
-      float d[8], g[8], u[8], og[8], ou[8];
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const float4 v = *reinterpret_cast<const float4*>(stage + rr * ST_STRIDE + cc + 4 * q);
-        d[4 * q] = v.x; d[4 * q + 1] = v.y; d[4 * q + 2] = v.z; d[4 * q + 3] = v.w;
-      }
-      g[0] = bf16lo(gq[t].x); g[1] = bf16hi(gq[t].x); g[2] = bf16lo(gq[t].y); g[3] = bf16hi(gq[t].y);
-      g[4] = bf16lo(gq[t].z); g[5] = bf16hi(gq[t].z); g[6] = bf16lo(gq[t].w); g[7] = bf16hi(gq[t].w);
-      u[0] = bf16lo(uq[t].x); u[1] = bf16hi(uq[t].x); u[2] = bf16lo(uq[t].y); u[3] = bf16hi(uq[t].y);
-      u[4] = bf16lo(uq[t].z); u[5] = bf16hi(uq[t].z); u[6] = bf16lo(uq[t].w); u[7] = bf16hi(uq[t].w);
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const float s = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(g[e] * -1.44269504088896340736f));
-        const float gs = g[e] * s;
-        og[e] = d[e] * u[e] * (s + gs * (1.f - s));
-        ou[e] = d[e] * gs;
-      }
-      char* const dst = dpre_base + (lane_off + (uint32_t)r * pitch);
-      *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bf16x2(og[0], og[1]), pack_bf16x2(og[2], og[3]),
-                                                  pack_bf16x2(og[4], og[5]), pack_bf16x2(og[6], og[7]));
-      *reinterpret_cast<uint4*>(dst + up_off) = make_uint4(pack_bf16x2(ou[0], ou[1]), pack_bf16x2(ou[2], ou[3]),
-                                                           pack_bf16x2(ou[4], ou[5]), pack_bf16x2(ou[6], ou[7]));
+      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(og[0], og[1])), wg, offset(i, jp), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(ou[0], ou[1])), wu, offset(i, jp), 0, 0);
     }
   }
 }

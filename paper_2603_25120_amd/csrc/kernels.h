@@ -48,11 +48,12 @@ bool gemm_swiglu_fusable(int64_t m, int64_t n, int64_t k);
 // A and B are addressed through 32-bit byte offsets: each operand must stay below this size.
 constexpr int64_t GEMM_MAX_OPERAND_BYTES = 0xFFFFFFF0ll - 16;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// Scratch bytes launch_gemm wants for an fp32-output product of this shape (0: it will not split).
-size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k);
-// out[i] (+)= sum over s of partial[s][i], s ascending.
-hipError_t launch_splitk_reduce(const float* partial, float* out, int splits, int64_t n, int accumulate,
-                                hipStream_t s);
+// Scratch bytes launch_gemm wants for a product of this shape (0: it will not split the K loop); a_t: A stored
+// [K, M].
+size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t);
+// C [M, N] (+)= sum over p of partial[p], p ascending, (+ bias) (+ residual); fp32 or bf16, N a multiple of 8.
+hipError_t launch_splitk_reduce(const float* partial, void* c, int splits, int64_t m, int64_t n, int out_fp32,
+                                int accumulate, const void* bias, const void* residual, int64_t ldres, hipStream_t s);
 
 // One workgroup of an attention kernel: a tile of a segment and a head (query head for the forward
 // and dQ passes, kv head for the dK/dV pass).  The lists are built on the host (attn_items.h).

@@ -235,6 +235,11 @@ double visible_pairs(const mllm_pack_t& p) {
   return n;
 }
 
+// Scratch of the three products of a linear map [T, k] -> [T, n]: Y, dX and dW.
+size_t linear_split_bytes(int64_t T, int64_t k, int64_t n) {
+  return std::max(gemm_splitk_ws_bytes(k, n, T, true), std::max(gemm_splitk_ws_bytes(T, n, k, false), gemm_splitk_ws_bytes(T, k, n, false)));
+}
+
 Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   Plan P;
   const bool need_img = st->n_vit > 0 || st->proj >= 0;
@@ -322,11 +327,11 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
       proj = (size_t)P.T_con * L.d_out * 2;
       P.largest_operand_bytes = std::max<int64_t>(P.largest_operand_bytes, (int64_t)P.T_img * std::max(std::max(L.d_model, L.d_out), L.d_ff) * 2);
       if (L.d_ff) {
-        split = std::max(split, gemm_splitk_ws_bytes(d_in, L.d_ff, P.T_con));
-        split = std::max(split, gemm_splitk_ws_bytes(L.d_ff, L.d_out, P.T_con));
+        split = std::max(split, linear_split_bytes(P.T_con, d_in, L.d_ff));
+        split = std::max(split, linear_split_bytes(P.T_con, L.d_ff, L.d_out));
         a = std::max(a, (size_t)P.T_con * L.d_ff * 2);
       } else {
-        split = std::max(split, gemm_splitk_ws_bytes(d_in, L.d_out, P.T_con));
+        split = std::max(split, linear_split_bytes(P.T_con, d_in, L.d_out));
       }
       if (P.pool > 1) c = std::max(c, (size_t)P.T_con * L.d_model * 2);   // gradient of the pooled rows
       part = std::max(part, (size_t)colsum_partial_rows(P.T_con) * std::max(L.d_out, L.d_ff) * 4);
@@ -350,10 +355,10 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
     delta = std::max(delta, T * L.n_q_heads * 4);
     g = std::max(g, T * d * 2);
     const int64_t fup = L.kind == MLLM_LAYER_VIT ? f : 2 * f;
-    split = std::max(split, gemm_splitk_ws_bytes(f, d, T));
-    split = std::max(split, gemm_splitk_ws_bytes(d, fup, T));
-    split = std::max(split, gemm_splitk_ws_bytes(d, d, T));
-    split = std::max(split, gemm_splitk_ws_bytes(d, nq, T));
+    split = std::max(split, linear_split_bytes(T, f, d));
+    split = std::max(split, linear_split_bytes(T, d, fup));
+    split = std::max(split, linear_split_bytes(T, d, d));
+    split = std::max(split, linear_split_bytes(T, d, nq));
   }
   P.rope_of.assign(st->layers.size(), -1);
   if (st->n_dec > 0) {
@@ -453,9 +458,10 @@ hipError_t gemm(const void* a, int64_t lda, int a_layout, const void* b, int64_t
   return launch_gemm(g, s);
 }
 // Y[T,n] = X[T,k].W[k,n] (+bias) (+res)
+struct SplitWs { void* p; size_t bytes; };   // scratch of products whose K loop is split
 hipError_t linear_fwd(const void* x, const void* w, void* y, int64_t T, int64_t k, int64_t n,
-                      const void* bias, const void* res, hipStream_t s) {
-  return gemm(x, k, 0, w, n, 0, y, n, T, n, k, 0, 0, bias, res, n, s);
+                      const void* bias, const void* res, hipStream_t s, SplitWs ws) {
+  return gemm(x, k, 0, w, n, 0, y, n, T, n, k, 0, 0, bias, res, n, s, ws.p, ws.bytes);
 }
 // Y[T,n] = X[T,k].W[k,n] (+bias) with the leading rope_cols columns (heads of head_dim) rotated by the
 // rotary angle of each row's position
@@ -481,8 +487,8 @@ hipError_t linear_fwd_swiglu(const void* x, const void* w, void* pre, void* act,
   return launch_gemm(g, s);
 }
 // dX[T,k] = dY[T,n].W[k,n]^T
-hipError_t linear_dx(const void* dy, const void* w, void* dx, int64_t T, int64_t k, int64_t n, hipStream_t s) {
-  return gemm(dy, n, 0, w, n, 1, dx, k, T, k, n, 0, 0, nullptr, nullptr, 0, s);
+hipError_t linear_dx(const void* dy, const void* w, void* dx, int64_t T, int64_t k, int64_t n, hipStream_t s, SplitWs ws) {
+  return gemm(dy, n, 0, w, n, 1, dx, k, T, k, n, 0, 0, nullptr, nullptr, 0, s, ws.p, ws.bytes);
 }
 // [d gate | d up][T,2f] from dY[T,d], W_d[f,d] and pre = [gate | up][T,2f]: dA = dY.W_d^T stays in registers
 hipError_t linear_dx_swiglu(const void* dy, const void* w, const void* pre, void* dpre, int64_t T, int64_t f,
@@ -496,7 +502,6 @@ hipError_t linear_dx_swiglu(const void* dy, const void* w, const void* pre, void
   return launch_gemm(g, s);
 }
 // dW[k,n] (+)= X[T,k]^T.dY[T,n]
-struct SplitWs { void* p; size_t bytes; };
 hipError_t linear_dw(const void* x, const void* dy, void* dw, int64_t T, int64_t k, int64_t n, int accumulate,
                      hipStream_t s, SplitWs ws) {
   return gemm(x, k, 1, dy, n, 0, dw, n, k, n, T, 1, accumulate, nullptr, nullptr, 0, s, ws.p, ws.bytes);
@@ -540,6 +545,7 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
                         int attn_list, hipStream_t s) {
   const bool vit = L.kind == MLLM_LAYER_VIT;
   const int64_t d = L.d_model, f = L.d_ff, nq = nqkv_of(L);
+  const SplitWs split{ws + P.w_split, P.split_bytes};
   char* x = saved + S.x;
   char* n1 = saved + S.n1;
   char* qkv = saved + S.qkv;
@@ -566,7 +572,7 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
     K_TRY(linear_fwd_rope(n1, wqkv, qkv, T, d, nq, bqkv, rope_table, (const int32_t*)(ws + P.meta.pos), q_cols + k_cols,
                           L.head_dim, s));
   else
-    K_TRY(linear_fwd(n1, wqkv, qkv, T, d, nq, bqkv, nullptr, s));
+    K_TRY(linear_fwd(n1, wqkv, qkv, T, d, nq, bqkv, nullptr, s, split));
   char* qk = qkv;
   if (L.qk_norm) {
     qk = saved + S.qkn;
@@ -581,15 +587,15 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
   a.o = o;
   a.lse = (float*)(saved + S.lse);
   K_TRY(launch_attn_fwd(a, s));
-  K_TRY(linear_fwd(o, wo, x1, T, d, d, bo, x, s));
+  K_TRY(linear_fwd(o, wo, x1, T, d, d, bo, x, s, split));
   K_TRY(launch_norm_fwd(vit ? 0 : 1, x1, g2, b2n, n2, (float*)(saved + S.stats2), T, d, d, L.norm_eps, s));
   if (!vit && gemm_swiglu_fusable(T, 2 * f, d)) {
     K_TRY(linear_fwd_swiglu(n2, wup, pre, act, T, d, 2 * f, s));
   } else {
-    K_TRY(linear_fwd(n2, wup, pre, T, d, vit ? f : 2 * f, bup, nullptr, s));
+    K_TRY(linear_fwd(n2, wup, pre, T, d, vit ? f : 2 * f, bup, nullptr, s, split));
     K_TRY(launch_act_fwd(L.act, pre, act, T, f, s));
   }
-  K_TRY(linear_fwd(act, wdn, y, T, f, d, bdn, x1, s));
+  K_TRY(linear_fwd(act, wdn, y, T, f, d, bdn, x1, s, split));
   return MLLM_OK;
 }
 
@@ -630,14 +636,14 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   if (!vit && gemm_swiglu_bwd_fusable(T, f, d)) {
     K_TRY(linear_dx_swiglu(dy, prm[iwdn], pre, dpre, T, f, d, s));
   } else {
-    K_TRY(linear_dx(dy, prm[iwdn], wa, T, f, d, s));
+    K_TRY(linear_dx(dy, prm[iwdn], wa, T, f, d, s, split));
     if (vit)   // the bias gradient (column sums of dpre) comes out of the same pass
       K_TRY(launch_gelu_bwd_colsum(L.act, wa, pre, dpre, (float*)dprm[ibup], accumulate, partial, T, f, s));
     else
       K_TRY(launch_act_bwd(L.act, wa, pre, dpre, T, f, s));
   }
   K_TRY(linear_dw(n2, dpre, dprm[iwup], T, d, fup, accumulate, s, split));
-  K_TRY(linear_dx(dpre, prm[iwup], wc, T, d, fup, s));
+  K_TRY(linear_dx(dpre, prm[iwup], wc, T, d, fup, s, split));
   // the gradient that leaves this norm is that of the output projection's output: its column sums are
   // the projection's bias gradient, formed in the same pass where the row width allows
   const bool bo_fused = vit && norm_bwd_colsum_fusable(d);
@@ -647,7 +653,7 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   // attention block
   K_TRY(linear_dw(o, wd, dprm[iwo], T, d, d, accumulate, s, split));
   if (vit && !bo_fused) K_TRY(launch_colsum(wd, d, (float*)dprm[ibo], accumulate, partial, T, d, s));
-  K_TRY(linear_dx(wd, prm[iwo], wc, T, d, d, s));
+  K_TRY(linear_dx(wd, prm[iwo], wc, T, d, d, s, split));
   // With QK normalisation the gradient of the normalised q, k goes to a matrix of its own (same
   // columns as in d qkv); the norm's backward then writes the gradient of the projection's q, k
   // beside dV in d qkv.
@@ -674,7 +680,7 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   }
   K_TRY(linear_dw(n1, we, dprm[iwqkv], T, d, nq, accumulate, s, split));
   if (ibqkv >= 0) K_TRY(launch_colsum(we, nq, (float*)dprm[ibqkv], accumulate, partial, T, nq, s));
-  K_TRY(linear_dx(we, prm[iwqkv], wc, T, d, nq, s));
+  K_TRY(linear_dx(we, prm[iwqkv], wc, T, d, nq, s, split));
   K_TRY(launch_norm_bwd(vit ? 0 : 1, wc, x, prm[ig1], (const float*)(saved + S.stats1), wd, dx,
                         (float*)dprm[ig1], vit ? (float*)dprm[ib1n] : nullptr, accumulate, partial, T, d, d, s, dx_colsum));
   return MLLM_OK;
@@ -835,6 +841,7 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
       if (i == 0) K_TRY(launch_copy(x_img, saved + P.saved[i].x, (size_t)P.T_img * L.d_model * 2, s));
       void* dst = last ? y : (void*)(saved + P.saved[i + 1].x);
       K_TRY(launch_copy(x_seq, dst, (size_t)P.T_seq * L.d_out * 2, s));
+      const SplitWs split{ws + P.w_split, P.split_bytes};
       const char* xin = saved + P.saved[i].x;
       // token merging: the [T_img, d] rows read as [T_img / r, r d] rows (no data movement)
       const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
@@ -846,11 +853,11 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
       if (L.d_ff) {   // p = act(x.W1 + b1).W2 + b2
         char* pre = saved + P.saved[i].pre;
         char* act = saved + P.saved[i].act;
-        K_TRY(linear_fwd(xin, prm[0], pre, P.T_con, d_in, L.d_ff, prm[1], nullptr, s));
+        K_TRY(linear_fwd(xin, prm[0], pre, P.T_con, d_in, L.d_ff, prm[1], nullptr, s, split));
         K_TRY(launch_act_fwd(L.act, pre, act, P.T_con, L.d_ff, s));
-        K_TRY(linear_fwd(act, prm[2], ws + P.w_proj, P.T_con, L.d_ff, L.d_out, prm[3], nullptr, s));
+        K_TRY(linear_fwd(act, prm[2], ws + P.w_proj, P.T_con, L.d_ff, L.d_out, prm[3], nullptr, s, split));
       } else {
-        K_TRY(linear_fwd(xin, prm[0], ws + P.w_proj, P.T_con, d_in, L.d_out, prm[1], nullptr, s));
+        K_TRY(linear_fwd(xin, prm[0], ws + P.w_proj, P.T_con, d_in, L.d_out, prm[1], nullptr, s, split));
       }
       K_TRY(launch_scatter_rows(ws + P.w_proj, dst, (const int32_t*)(ws + P.meta.i2s), P.T_con, L.d_out, 0, s));
       continue;
@@ -914,14 +921,14 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
         char* dh = ws + P.w_a;     // d act, then d pre in place   [T_con, d_ff]
         K_TRY(linear_dw(act, dproj, dprm[2], P.T_con, L.d_ff, L.d_out, accumulate, s, split));
         K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[3], accumulate, partial, P.T_con, L.d_out, s));
-        K_TRY(linear_dx(dproj, prm[2], dh, P.T_con, L.d_ff, L.d_out, s));
+        K_TRY(linear_dx(dproj, prm[2], dh, P.T_con, L.d_ff, L.d_out, s, split));
         K_TRY(launch_gelu_bwd_colsum(L.act, dh, pre, dh, (float*)dprm[1], accumulate, partial, P.T_con, L.d_ff, s));
         K_TRY(linear_dw(xin, dh, dprm[0], P.T_con, d_in, L.d_ff, accumulate, s, split));
-        K_TRY(linear_dx(dh, prm[0], dxin, P.T_con, d_in, L.d_ff, s));
+        K_TRY(linear_dx(dh, prm[0], dxin, P.T_con, d_in, L.d_ff, s, split));
       } else {
         K_TRY(linear_dw(xin, dproj, dprm[0], P.T_con, d_in, L.d_out, accumulate, s, split));
         K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[1], accumulate, partial, P.T_con, L.d_out, s));
-        K_TRY(linear_dx(dproj, prm[0], dxin, P.T_con, d_in, L.d_out, s));
+        K_TRY(linear_dx(dproj, prm[0], dxin, P.T_con, d_in, L.d_out, s, split));
       }
       if (P.pool > 1)
         K_TRY(launch_unpool_rows(dxin, out, (const int32_t*)(ws + P.meta.row_window),

@@ -1,0 +1,78 @@
+"""The GEMM tile kernel where its tiles and its split K loop can go wrong, against the fp64 oracle.
+
+Single products: bf16 results carry one rounding (2^-9 relative; 1e-2 of the maximum), fp32 results of bf16
+products accumulated in fp32 2e-3.  Layers: the stage tolerances (2e-2 outputs, 3e-2 gradients)."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from tests.gpu_util import GpuStage, compare, dev_bf16, empty_bf16, host_f64, nmax_err, oracle_run  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_25120_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("k", [1, 7, 63, 64, 65, 130, 193])
+@pytest.mark.parametrize("m,n", [(8, 8), (136, 264), (640, 120)])
+def test_weight_gradient_small_tiles_any_token_count(B, m, n, k):
+    """128x128 tiles, both operands stored [K, .]: a last k-tile of any length, tile edges inside the matrix.  The
+    rows behind the operands hold large values, so a row read past K would show."""
+    a, b = W.draw_tensor(301, k + 64, m), W.draw_tensor(302, k + 64, n)
+    a[k:], b[k:] = 1000.0, 1000.0
+    ref = a[:k].T.astype(np.float64) @ b[:k].astype(np.float64)
+    a_dev, b_dev = dev_bf16(a), dev_bf16(b)
+    init = np.random.default_rng(303).standard_normal((m, n)).astype(np.float32)
+    c = torch.from_numpy(init.copy()).cuda()
+    B.mllm_op_gemm(a_dev, b_dev, c, m, n, k, 1, 0, out_fp32=1, accumulate=1)
+    assert nmax_err(host_f64(c), ref + init) < 2e-3
+    c = empty_bf16(m, n)
+    B.mllm_op_gemm(a_dev, b_dev, c, m, n, k, 1, 0)
+    assert nmax_err(host_f64(c), ref) < 1e-2
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 8, 64), (127, 136, 128), (129, 120, 192), (513, 264, 320)])
+@pytest.mark.parametrize("b_layout,f32", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_small_tiles_edges_and_epilogue_terms(B, m, n, k, b_layout, f32):
+    a = W.draw_tensor(311, m, k)
+    b = W.bf16_round(W.draw_tensor(312, k, n) * np.float32(0.125))
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    bias = W.draw_tensor(313, 1, n)
+    b_dev = dev_bf16(np.ascontiguousarray(b.T) if b_layout else b)
+    # guard rows behind C: nothing past the last row may be written
+    c = torch.full((m + 3, n), 7.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    if f32:
+        B.mllm_op_gemm(dev_bf16(a), b_dev, c, m, n, k, 0, b_layout, out_fp32=1, bias=dev_bf16(bias))
+        want = ref + bias
+    else:
+        res = W.draw_tensor(314, m, n)
+        B.mllm_op_gemm(dev_bf16(a), b_dev, c, m, n, k, 0, b_layout, bias=dev_bf16(bias), residual=dev_bf16(res))
+        want = ref + bias + res
+    got = host_f64(c)
+    assert nmax_err(got[:m], want) < (2e-3 if f32 else 1e-2)
+    assert np.all(got[m:] == 7.0)
+
+
+@pytest.mark.parametrize("lengths", [[5], [77, 130], [300, 1, 64]])
+def test_layers_whose_products_split_the_k_loop(B, lengths):
+    """A few tokens against wide matrices: every product has too few tiles to fill the chip, so forward and input
+    gradients (bias, residual) and weight gradients go through partial products."""
+    for layer, pack in ((W.vit_layer(1024, 16, 64, 4096), "img"), (W.decoder_layer(1024, 8, 2, 128, 4096, 10000.0, qkv_bias=1), "seq")):
+        p = W.make_pack(lengths, W.MASK_BIDIR if pack == "img" else W.MASK_CAUSAL)
+        batch = W.Batch(p, None, None, []) if pack == "img" else W.Batch(None, p, None, [])
+        wl = W.make_workload("split", [layer], batch, 321)
+        st = GpuStage(B, [layer])
+        try:
+            got, ref = st.run(wl), oracle_run(wl)
+            compare(st, wl, got, ref)
+            again = st.run(wl)
+            assert all(torch.equal(x, y) for x, y in zip(got[3], again[3])) and torch.equal(got[0], again[0])
+        finally:
+            st.close()
