@@ -85,7 +85,8 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
 // kind 0 LayerNorm, 1 RMSNorm.  stats: [2][T] fp32 (rstd, mean).  ld = elements between rows of
 // every [t, d] operand (d for dense matrices; more when they are column slices of a wider one).
 hipError_t launch_norm_fwd(int kind, const void* x, const void* gamma, const void* beta, void* y,
-                           float* stats, int64_t t, int64_t d, int64_t ld, float eps, hipStream_t s);
+                           float* stats, int64_t t, int64_t d, int64_t ld, float eps, hipStream_t s,
+                           void* x_copy = nullptr);   // x_copy: also receives x (same layout)
 int64_t norm_bwd_partial_rows(int64_t t);
 hipError_t launch_norm_bwd(int kind, const void* dy, const void* x, const void* gamma,
                            const float* stats, const void* dres, void* dx, float* dgamma,

@@ -81,20 +81,24 @@ PinnedRing& op_staging() {
   return *ring;
 }
 
-mllm_status_t upload_tiles(const mllm_pack_t* pack, void* ws, AttnArgs& a, hipStream_t stream) {
+// The work lists a call needs (forward: query tiles; backward: key tiles too), one behind the other in one copy.
+mllm_status_t upload_tiles(const mllm_pack_t* pack, void* ws, AttnArgs& a, bool backward, hipStream_t stream) {
   char* w = (char*)ws;
-  const size_t qbytes = attn_list_bytes(*pack, ATTN_FWD_Q_TILE, a.n_q_heads);
-  const size_t koff = align_up(qbytes);
-  const size_t bytes = koff + attn_list_bytes(*pack, ATTN_BWD_KV_TILE, a.n_kv_heads);
+  const size_t bytes = align_up(attn_list_bytes(*pack, ATTN_FWD_Q_TILE, a.n_q_heads)) +
+                       (backward ? attn_list_bytes(*pack, ATTN_BWD_KV_TILE, a.n_kv_heads) : 0);
   PinnedRing& ring = op_staging();
   PinnedRing::Slot* slot = nullptr;
   OP_TRY(ring.acquire(bytes, &slot));
   char* h = (char*)slot->p;
   a.q_grid = build_attn_list(*pack, ATTN_FWD_Q_TILE, false, a.n_kv_heads, a.n_q_heads / a.n_kv_heads, 64, h);
-  a.kv_grid = build_attn_list(*pack, ATTN_BWD_KV_TILE, true, a.n_kv_heads, a.n_q_heads / a.n_kv_heads,
-                              a.head_dim == 64 ? 64 : 32, h + koff);
-  if (a.q_grid) OP_TRY(hipMemcpyAsync(w, h, (size_t)a.q_grid * sizeof(AttnItem), hipMemcpyHostToDevice, stream));
-  if (a.kv_grid) OP_TRY(hipMemcpyAsync(w + koff, h + koff, (size_t)a.kv_grid * sizeof(AttnItem), hipMemcpyHostToDevice, stream));
+  size_t used = (size_t)a.q_grid * sizeof(AttnItem);
+  const size_t koff = align_up(used);
+  if (backward) {
+    a.kv_grid = build_attn_list(*pack, ATTN_BWD_KV_TILE, true, a.n_kv_heads, a.n_q_heads / a.n_kv_heads,
+                                a.head_dim == 64 ? 64 : 32, h + koff);
+    used = koff + (size_t)a.kv_grid * sizeof(AttnItem);
+  }
+  if (used) OP_TRY(hipMemcpyAsync(w, h, used, hipMemcpyHostToDevice, stream));
   OP_TRY(ring.commit(slot, stream));
   a.q_list = w;
   a.kv_list = w + koff;
@@ -252,7 +256,7 @@ mllm_status_t mllm_op_attn_fwd(const void* q, const void* k, const void* v, void
   a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse;
   a.q_stride = q_stride; a.kv_stride = kv_stride; a.o_stride = o_stride;
   a.total_tokens = pack->total_tokens; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
-  if ((r = upload_tiles(pack, workspace, a, (hipStream_t)hip_stream)) != MLLM_OK) return r;
+  if ((r = upload_tiles(pack, workspace, a, false, (hipStream_t)hip_stream)) != MLLM_OK) return r;
   OP_TRY(launch_attn_fwd(a, (hipStream_t)hip_stream));
   return MLLM_OK;
 }
@@ -282,7 +286,7 @@ mllm_status_t mllm_op_attn_bwd_rope(const void* q, const void* k, const void* v,
   a.rope_table = rope_table;
   a.q_stride = q_stride; a.kv_stride = kv_stride; a.o_stride = o_stride;
   a.total_tokens = pack->total_tokens; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = head_dim;
-  if ((r = upload_tiles(pack, workspace, a, (hipStream_t)hip_stream)) != MLLM_OK) return r;
+  if ((r = upload_tiles(pack, workspace, a, true, (hipStream_t)hip_stream)) != MLLM_OK) return r;
   OP_TRY(launch_attn_bwd(a, (hipStream_t)hip_stream));
   return MLLM_OK;
 }

@@ -190,16 +190,17 @@ struct LayerSaved {  // byte offsets into `saved`
 struct AttnLists {
   bool img;
   int hq, hkv, head_dim;
-  size_t q_off = 0, kv_off = 0;     // byte offsets into the metadata blob
-  int q_grid = 0, kv_grid = 0;      // grid sizes, known once the lists are built (upload_meta)
+  // byte offsets into the metadata blob and grid sizes, known once the lists are built (upload_meta)
+  size_t q_off = 0, kv_off = 0;
+  int q_grid = 0, kv_grid = 0;
 };
 
 struct Meta {  // byte offsets into the metadata blob at the head of the workspace
-  std::vector<AttnLists> attn;
-  size_t tables = 0;                // where the tables below begin (the attention lists come first)
   size_t pos = 0, i2s = 0;
   size_t pool_first = 0, pool_count = 0, row_window = 0;   // pooling connector: window tables
-  size_t bytes = 0;
+  size_t lists = 0;                 // where the attention lists begin, one behind the other
+  std::vector<AttnLists> attn;
+  size_t bytes = 0;                 // upper bound; a call uploads what its lists really take
 };
 
 struct Plan {
@@ -290,6 +291,14 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
 
   Bump ws;
   Meta& M = P.meta;
+  if (st->n_dec > 0) M.pos = ws.take(sizeof(int32_t) * P.T_seq);
+  if (st->proj >= 0) M.i2s = ws.take(sizeof(int32_t) * P.T_con);
+  if (st->proj >= 0 && P.pool > 1) {
+    M.pool_first = ws.take(sizeof(int32_t) * P.T_con);
+    M.pool_count = ws.take(sizeof(int32_t) * P.T_con);
+    M.row_window = ws.take(sizeof(int32_t) * P.T_img);
+  }
+  M.lists = ws.off;
   P.attn_of.assign(st->layers.size(), -1);
   for (size_t i = 0; i < st->layers.size(); i++) {
     const mllm_layer_desc_t& L = st->layers[i];
@@ -303,20 +312,12 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
       AttnLists A;
       A.img = img; A.hq = L.n_q_heads; A.hkv = L.n_kv_heads; A.head_dim = L.head_dim;
       const mllm_pack_t& pk = img ? b->img : b->seq;
-      A.q_off = ws.take(attn_list_bytes(pk, ATTN_FWD_Q_TILE, L.n_q_heads));
-      A.kv_off = ws.take(attn_list_bytes(pk, ATTN_BWD_KV_TILE, L.n_kv_heads));
+      ws.take(attn_list_bytes(pk, ATTN_FWD_Q_TILE, L.n_q_heads));
+      ws.take(attn_list_bytes(pk, ATTN_BWD_KV_TILE, L.n_kv_heads));
       found = (int)M.attn.size();
       M.attn.push_back(A);
     }
     P.attn_of[i] = found;
-  }
-  M.tables = ws.off;
-  if (st->n_dec > 0) M.pos = ws.take(sizeof(int32_t) * P.T_seq);
-  if (st->proj >= 0) M.i2s = ws.take(sizeof(int32_t) * P.T_con);
-  if (st->proj >= 0 && P.pool > 1) {
-    M.pool_first = ws.take(sizeof(int32_t) * P.T_con);
-    M.pool_count = ws.take(sizeof(int32_t) * P.T_con);
-    M.row_window = ws.take(sizeof(int32_t) * P.T_img);
   }
   M.bytes = ws.off;
 
@@ -408,11 +409,15 @@ mllm_status_t upload_meta(mllm_stage* st, const mllm_batch_t* b, Plan& P, void* 
   PinnedRing::Slot* slot = nullptr;
   HIP_TRY(st->staging.acquire(M.bytes, &slot));
   char* h = (char*)slot->p;
-  memset(h + M.tables, 0, M.bytes - M.tables);
+  memset(h, 0, M.lists);
+  size_t used = M.lists;
   for (AttnLists& A : M.attn) {
     const mllm_pack_t& pk = A.img ? b->img : b->seq;
+    A.q_off = used;
     A.q_grid = build_attn_list(pk, ATTN_FWD_Q_TILE, false, A.hkv, A.hq / A.hkv, 64, h + A.q_off);
+    A.kv_off = A.q_off + align_up((size_t)A.q_grid * sizeof(AttnItem));
     A.kv_grid = build_attn_list(pk, ATTN_BWD_KV_TILE, true, A.hkv, A.hq / A.hkv, kv_residents(A.head_dim), h + A.kv_off);
+    used = A.kv_off + align_up((size_t)A.kv_grid * sizeof(AttnItem));
   }
   if (st->n_dec > 0) {
     int32_t* pos = (int32_t*)(h + M.pos);
@@ -435,13 +440,9 @@ mllm_status_t upload_meta(mllm_stage* st, const mllm_batch_t* b, Plan& P, void* 
       }
     }
   }
-  // the lists are reserved at their upper bound; only the entries of the launch grids are copied
-  char* w = (char*)workspace;
-  for (const AttnLists& A : M.attn) {
-    if (A.q_grid) HIP_TRY(hipMemcpyAsync(w + A.q_off, h + A.q_off, (size_t)A.q_grid * sizeof(AttnItem), hipMemcpyHostToDevice, s));
-    if (A.kv_grid) HIP_TRY(hipMemcpyAsync(w + A.kv_off, h + A.kv_off, (size_t)A.kv_grid * sizeof(AttnItem), hipMemcpyHostToDevice, s));
-  }
-  if (M.bytes > M.tables) HIP_TRY(hipMemcpyAsync(w + M.tables, h + M.tables, M.bytes - M.tables, hipMemcpyHostToDevice, s));
+  // Space is reserved for the lists' upper bounds; they are packed one behind the other, so that one copy
+  // moves everything (three to five took 2-4 us each on the stream, plus the gaps between them).
+  if (used > 0) HIP_TRY(hipMemcpyAsync(workspace, h, used, hipMemcpyHostToDevice, s));
   HIP_TRY(st->staging.commit(slot, s));
   return MLLM_OK;
 }
@@ -540,8 +541,9 @@ AttnArgs attn_args(const mllm_layer_desc_t& L, char* qk, char* v, int64_t T, con
 // -------------------------------------------------------------------------------------------
 // one transformer layer, forward.  x -> y; everything backward needs goes to `saved`.
 // -------------------------------------------------------------------------------------------
+// x_in: the stage's input when this is its first layer (null otherwise: the layer below has left x in `saved`).
 mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, const LayerSaved& S,
-                        char* saved, char* ws, const Plan& P, int64_t T, void* y, const float* rope_table,
+                        char* saved, char* ws, const Plan& P, int64_t T, const void* x_in, void* y, const float* rope_table,
                         int attn_list, hipStream_t s) {
   const bool vit = L.kind == MLLM_LAYER_VIT;
   const int64_t d = L.d_model, f = L.d_ff, nq = nqkv_of(L);
@@ -564,7 +566,8 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
   const int n_base = vit ? 12 : (L.has_bias ? 7 : 6);   // the QK-norm gains follow the layer's other tensors
   const int64_t q_cols = (int64_t)L.n_q_heads * L.head_dim, k_cols = (int64_t)L.n_kv_heads * L.head_dim;
 
-  K_TRY(launch_norm_fwd(vit ? 0 : 1, x, g1, b1n, n1, (float*)(saved + S.stats1), T, d, d, L.norm_eps, s));
+  // the first layer's input is copied into `saved` by the kernel that reads it anyway
+  K_TRY(launch_norm_fwd(vit ? 0 : 1, x_in ? x_in : x, g1, b1n, n1, (float*)(saved + S.stats1), T, d, d, L.norm_eps, s, x_in ? x : nullptr));
   // Rotary positions ride on the QKV projection's epilogue whenever that product takes the
   // large-tile kernel and nothing sits between the projection and the rotation.
   const bool rope_fused = !vit && !L.qk_norm && (q_cols + k_cols) % 128 == 0 && gemm_rope_fusable(T, nq, d, L.head_dim);
@@ -864,10 +867,10 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
     }
     const bool vit = L.kind == MLLM_LAYER_VIT;
     const int64_t T = vit ? P.T_img : P.T_seq;
-    if (i == 0) K_TRY(launch_copy(vit ? x_img : x_seq, saved + P.saved[i].x, (size_t)T * L.d_model * 2, s));
+    const void* x_in = i > 0 ? nullptr : vit ? x_img : x_seq;
     void* out = last ? y : (void*)(saved + P.saved[i + 1].x);
     const float* rope_table = P.rope_of[i] >= 0 ? (const float*)(ws + P.rope_tables[P.rope_of[i]].off) : nullptr;
-    if ((r = layer_fwd(L, prm, P.saved[i], saved, ws, P, T, out, rope_table, P.attn_of[i], s)) != MLLM_OK) return r;
+    if ((r = layer_fwd(L, prm, P.saved[i], saved, ws, P, T, x_in, out, rope_table, P.attn_of[i], s)) != MLLM_OK) return r;
   }
   return MLLM_OK;
 }
