@@ -2,6 +2,8 @@
 // row, wavefront reductions), rotary positions, GELU / SwiGLU forward and backward, bias-gradient
 // column sums, row scatter / gather for the connector.  All math in fp32 on bf16 storage, 16-byte
 // accesses, no atomics: every cross-row reduction is two deterministic stages.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -291,6 +293,36 @@ __global__ void rope_table_kernel(float* __restrict__ table, int64_t n_pos, int 
   sincos((double)pos * inv, &sn, &cs);
   table[pos * hd + i] = (float)cs;
   table[pos * hd + half + i] = (float)sn;
+}
+
+// The same rotation from the table (forward only): a thread takes eight pairs of one head of one token, so that a
+// small microbatch still fills the chip (777 tokens, 40 heads of 128: rope_kernel 25 us on 25 workgroups that each
+// form their angles in fp64, this one 4 us).
+__global__ __launch_bounds__(256) void rope_from_table_kernel(bf16_t* __restrict__ qk, const int32_t* __restrict__ pos,
+                                                              const float* __restrict__ table, int64_t T, int64_t row_stride,
+                                                              int n_heads, int hd) {
+  const int per_head = hd >> 4;
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int i0 = (int)(gid % per_head) * 8, h = (int)(gid / per_head % n_heads), half = hd >> 1;
+  const int64_t t = gid / ((int64_t)per_head * n_heads);
+  if (t >= T) return;
+  const float* trow = table + (int64_t)pos[t] * hd + i0;
+  bf16_t* p1 = qk + t * row_stride + (int64_t)h * hd + i0;
+  float a[8], b[8], oa[8], ob[8];
+  unpack8(*reinterpret_cast<const uint4*>(p1), a);
+  unpack8(*reinterpret_cast<const uint4*>(p1 + half), b);
+#pragma unroll
+  for (int q = 0; q < 2; q++) {
+    const float4 c = *reinterpret_cast<const float4*>(trow + 4 * q), s = *reinterpret_cast<const float4*>(trow + half + 4 * q);
+    const float cs[4] = {c.x, c.y, c.z, c.w}, sn[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      oa[4 * q + e] = a[4 * q + e] * cs[e] - b[4 * q + e] * sn[e];
+      ob[4 * q + e] = b[4 * q + e] * cs[e] + a[4 * q + e] * sn[e];
+    }
+  }
+  *reinterpret_cast<uint4*>(p1) = pack8(oa);
+  *reinterpret_cast<uint4*>(p1 + half) = pack8(ob);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -691,7 +723,12 @@ hipError_t launch_norm_bwd(int kind, const void* dy, const void* x, const void* 
   const int64_t nvec = d / 8;
   // Workgroups (= rows of partial sums).  The wavefront-per-row kernel with two vectors per lane
   // keeps three workgroups per CU resident: a grid of 768 runs in one round.
-  int64_t W = norm_bwd_partial_rows(t);
+  // For few rows the second stage (W x d floats a set) weighs more than the occupancy of the first, so a workgroup
+  // then takes several rows: two a wavefront in the wavefront-per-row kernel, three in the other one (777 x 4096: 10.8 + 10.2 us
+  // with a row a workgroup, 13.9 + 5.6 with three; 2880 x 1024, three sets: 10.4 + 8.1 and 11.8 + 4.8).
+  const int64_t rows_per_wg = nvec <= 128 ? 4 * 2 : 3;
+  int64_t W = std::min<int64_t>(norm_bwd_partial_rows(t), std::max<int64_t>(std::min<int64_t>(t, 256), t / rows_per_wg));
+  W = std::max<int64_t>(1, W);
   if (nvec > 64 && nvec <= 128) W = std::min<int64_t>(W, 768);
   ProfScope prof(PROF_ELEMENTWISE, (dres ? 8.0 : 6.0) * (double)t * (double)d, s);
   dim3 grid((unsigned)W), block(256);
@@ -727,6 +764,17 @@ hipError_t launch_rope(void* qk, const int32_t* pos, int64_t t, int64_t row_stri
   ProfScope prof(PROF_ELEMENTWISE, 4.0 * (double)t * (double)n_heads * (double)head_dim, s);
   hipLaunchKernelGGL(rope_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, (bf16_t*)qk, pos, t,
                      row_stride, col0, (int)n_heads, (int)head_dim, log2((double)rope_base), inverse);
+  return hipGetLastError();
+}
+
+hipError_t launch_rope_from_table(void* qk, const int32_t* pos, const float* table, int64_t t, int64_t row_stride,
+                                  int32_t n_heads, int32_t head_dim, hipStream_t s) {
+  if (t == 0 || n_heads == 0) return hipSuccess;
+  if (head_dim % 16 != 0 || row_stride % 8 != 0) return hipErrorInvalidValue;
+  const int64_t n = t * n_heads * (head_dim / 16);
+  ProfScope prof(PROF_ELEMENTWISE, 4.0 * (double)t * (double)n_heads * (double)head_dim, s);
+  hipLaunchKernelGGL(rope_from_table_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, (bf16_t*)qk, pos, table, t, row_stride,
+                     (int)n_heads, (int)head_dim);
   return hipGetLastError();
 }
 
@@ -781,10 +829,10 @@ hipError_t launch_gelu_bwd_colsum(int act, const void* da, const void* pre, void
   return hipGetLastError();
 }
 
-int64_t colsum_partial_rows(int64_t t) {   // row chunks of (at least) four rows, at most 512
-  if (t < 4) return 1;
-  return t < 2048 ? t / 4 : 512;
-}
+// Row chunks of the column sums: what the second stage reads is chunks x n floats, so a chunk holds at least 16 rows
+// (four a wavefront, all in flight); 512 chunks fill the chip.  2880 x 4096: second stage 7.2 us with 512 chunks,
+// 3.9 us with 180, the first stage unchanged.
+int64_t colsum_partial_rows(int64_t t) { return std::max<int64_t>(1, std::min<int64_t>(512, t / 16)); }
 
 hipError_t launch_colsum(const void* x, int64_t ldx, float* out, int accumulate, float* partial,
                          int64_t t, int64_t n, hipStream_t s) {

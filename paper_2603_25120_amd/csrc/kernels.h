@@ -98,6 +98,9 @@ bool norm_bwd_colsum_fusable(int64_t d);
 hipError_t launch_rope(void* qk, const int32_t* pos, int64_t t, int64_t row_stride, int64_t col0,
                        int32_t n_heads, int32_t head_dim, float rope_base, int inverse,
                        hipStream_t s);
+// The forward rotation of the leading n_heads heads, with the factors of launch_rope_table.
+hipError_t launch_rope_from_table(void* qk, const int32_t* pos, const float* table, int64_t t, int64_t row_stride,
+                                  int32_t n_heads, int32_t head_dim, hipStream_t s);
 // table [n_pos, head_dim] fp32: cos then sin of pos * rope_base^(-2i/head_dim), i < head_dim / 2.
 hipError_t launch_rope_table(float* table, int64_t n_pos, int32_t head_dim, float rope_base, hipStream_t s);
 hipError_t launch_act_fwd(int act, const void* pre, void* a, int64_t t, int64_t f, hipStream_t s);

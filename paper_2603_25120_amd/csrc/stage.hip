@@ -584,8 +584,8 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
                           (float*)(saved + S.statsk), T, k_cols, nq, L.norm_eps, s));
   }
   if (!vit && !rope_fused)
-    K_TRY(launch_rope(qk, (const int32_t*)(ws + P.meta.pos), T, nq, 0, L.n_q_heads + L.n_kv_heads,
-                      L.head_dim, L.rope_base, 0, s));
+    K_TRY(launch_rope_from_table(qk, (const int32_t*)(ws + P.meta.pos), rope_table, T, nq, L.n_q_heads + L.n_kv_heads,
+                                 L.head_dim, s));
   AttnArgs a = attn_args(L, qk, qkv, T, ws, P, vit, attn_list);
   a.o = o;
   a.lse = (float*)(saved + S.lse);
