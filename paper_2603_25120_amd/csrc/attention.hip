@@ -65,7 +65,32 @@ struct AttnParams {
   const AttnItem* list;      // work list, one entry per workgroup
   float scale_log2e, scale;
   const float* rope_table;   // backward: dq, dk are rotated back by the rotary angle of their row (null: not)
+  float* dkv_partial;        // dK/dV pass in gridDim.y > 1 parts: fp32 sums [part][dK, dV][T][Hkv * HD]
 };
+
+// The dK/dV pass of a key tile walks (query head of the group, query tile) pairs; with gridDim.y parts a
+// workgroup walks its share of them.
+struct KvRange { int n_it, head, q0; };   // iterations, and where they start: head of the group, first query row
+__device__ __forceinline__ KvRange kv_range(int grp, int q_begin, int seg_len, int tile_rows) {
+  const int per_head = (seg_len - q_begin + tile_rows - 1) / tile_rows, total = grp * per_head;
+  const int first = total * (int)blockIdx.y / (int)gridDim.y, last = total * ((int)blockIdx.y + 1) / (int)gridDim.y;
+  return {last - first, first / per_head, q_begin + first % per_head * tile_rows};
+}
+// A part's sums of one key row (the lane's), fp32 and unscaled.
+template <int HD>
+__device__ __forceinline__ void store_kv_partial(const AttnParams& p, const f32x16 (&dk)[HD / 32], const f32x16 (&dv)[HD / 32],
+                                                 int64_t row, int kvh, int h) {
+  const int64_t width = (int64_t)p.Hkv * HD;
+  float* k = p.dkv_partial + ((int64_t)(2 * blockIdx.y) * p.T + row) * width + kvh * HD + 4 * h;
+  float* v = k + (int64_t)p.T * width;
+#pragma unroll
+  for (int d = 0; d < HD / 32; d++)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; g4++) {
+      *reinterpret_cast<float4*>(k + 32 * d + 8 * g4) = make_float4(dk[d][4 * g4], dk[d][4 * g4 + 1], dk[d][4 * g4 + 2], dk[d][4 * g4 + 3]);
+      *reinterpret_cast<float4*>(v + 32 * d + 8 * g4) = make_float4(dv[d][4 * g4], dv[d][4 * g4 + 1], dv[d][4 * g4 + 2], dv[d][4 * g4 + 3]);
+    }
+}
 
 // Gradient of the rotary positions on an accumulator of ND = HD/32 blocks whose lane owns row `pos`
 // of its segment: the pair (c, c + HD/2) sits in blocks (d, d + ND/2) of the same lane.  Forward was
@@ -566,7 +591,8 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
 
   const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
   const int wave_first_k = t.tile0 + 32 * wave;
-  const int n_it = grp * ((t.seg_len - q_begin + BQ - 1) / BQ);
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ);
+  const int n_it = range.n_it;
 
   constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BQ / RPI / 4;
   uint32_t q_off[PER_WAVE], do_off[PER_WAVE];
@@ -581,7 +607,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
 
   // The tile to be loaded next: query head nj of the group, query rows from nq0.  Past the last
   // tile the descriptors are empty and the loads write zeros.
-  int nj = 0, nq0 = q_begin;
+  int nj = range.head, nq0 = range.q0;
   float r_lse = 0.f, r_delta = 0.f;   // statistics of the tile in flight, one row per thread (tid < BQ)
   bool r_ok = false;
   auto issue = [&](bf16_t* qs, bf16_t* dos) {
@@ -693,7 +719,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
   };
 
   issue(Qs0, dOs0);
-  int q0 = q_begin;
+  int q0 = range.q0;
   auto advance = [&]() { q0 += BQ; if (q0 >= t.seg_len) q0 = q_begin; };
   for (int it = 0; it < n_it; it += 2) {
     tile(Qs0, dOs0, lse_s0, delta_s0, Qs1, dOs1, q0, true);
@@ -705,6 +731,10 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
   // can be handed to another one
   __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
   if (!kok) return;
+  if (gridDim.y > 1) {
+    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h);
+    return;
+  }
   float out_scale = p.scale;
   if (p.rope_table) {
     rope_unrotate<HD>(dkacc, p.rope_table, krow, h, p.scale);
@@ -821,7 +851,8 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
 
   const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
   const int wave_first_k = t.tile0 + 32 * wave;
-  const int n_it = grp * ((t.seg_len - q_begin + BQ - 1) / BQ);
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ);
+  const int n_it = range.n_it;
   const float c2 = p.scale_log2e;
 
   // ---- loads ------------------------------------------------------------------------------------
@@ -836,7 +867,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
   }
   const uint32_t q_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.q_stride + HD) * 2);
   const uint32_t do_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.o_stride + HD) * 2);
-  int nj = 0, nq0 = q_begin;          // the tile to be loaded next: query head nj of the group, rows from nq0
+  int nj = range.head, nq0 = range.q0;   // the tile to be loaded next: query head nj of the group, rows from nq0
   // Past the last tile the descriptors are empty and the loads write zeros.
   const uint32_t lds_b = lds_address((MLLM_LDS const void*)lds);
   // A tile's loads are enqueued in PT parts so that they can be spread over the MFMAs of a stage.
@@ -1009,7 +1040,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
     }
   };
 
-  int q0 = q_begin;
+  int q0 = range.q0;
   // ---- prologue: tile 0 lands, its first block's scores are formed on their own ----------------
 #pragma unroll
   for (int st = 0; st < NST - 1; st++) issue(st);
@@ -1072,6 +1103,10 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
   // can be handed to another one
   wait_loads<0>();
   if (!kok) return;
+  if (gridDim.y > 1) {
+    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h);
+    return;
+  }
   float out_scale = p.scale;
   if (p.rope_table) {
     rope_unrotate<HD>(dkacc, p.rope_table, krow, h, p.scale);
@@ -1093,6 +1128,61 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
     }
 }
 
+// dK and dV from the parts' sums, added in their order; dK scaled and rotated back.  A thread takes eight
+// columns of the left and of the right half of a row of one kv head.
+__global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ dk,
+                                                              bf16_t* __restrict__ dv, int parts, int64_t T, int hkv, int hd,
+                                                              int64_t kv_stride, float scale, const float* __restrict__ rope_table,
+                                                              const int32_t* __restrict__ pos) {
+  const int per_head = hd >> 4, half = hd >> 1;
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int c0 = (int)(gid % per_head) * 8, head = (int)(gid / per_head % hkv);
+  const int64_t row = gid / ((int64_t)per_head * hkv);
+  if (row >= T) return;
+  const int64_t width = (int64_t)hkv * hd, set = T * width;
+  const float* src = partial + row * width + head * hd + c0;
+  float s[2][2][8];   // [dK, dV][half][column]
+#pragma unroll
+  for (int w = 0; w < 2; w++)
+#pragma unroll
+    for (int x = 0; x < 2; x++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) s[w][x][e] = 0.f;
+#pragma unroll 2
+  for (int p = 0; p < parts; p++)
+#pragma unroll
+    for (int w = 0; w < 2; w++)
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        const float4* f = reinterpret_cast<const float4*>(src + (2 * p + w) * set + x * half);
+        const float4 a = f[0], b = f[1];
+        s[w][x][0] += a.x; s[w][x][1] += a.y; s[w][x][2] += a.z; s[w][x][3] += a.w;
+        s[w][x][4] += b.x; s[w][x][5] += b.y; s[w][x][6] += b.z; s[w][x][7] += b.w;
+      }
+  if (rope_table) {   // dx1 = dy1 cos + dy2 sin, dx2 = dy2 cos - dy1 sin
+    const float* trow = rope_table + (int64_t)pos[row] * hd + c0;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const float c = trow[e] * scale, sn = trow[half + e] * scale, y1 = s[0][0][e], y2 = s[0][1][e];
+      s[0][0][e] = y1 * c + y2 * sn;
+      s[0][1][e] = y2 * c - y1 * sn;
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < 2; x++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) s[0][x][e] *= scale;
+  }
+#pragma unroll
+  for (int w = 0; w < 2; w++)
+#pragma unroll
+    for (int x = 0; x < 2; x++) {
+      bf16_t* dst = (w ? dv : dk) + row * kv_stride + head * hd + c0 + x * half;
+      const float* v = s[w][x];
+      *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+    }
+}
+
 AttnParams make_params(const AttnArgs& a) {
   AttnParams p;
   p.q = (const bf16_t*)a.q; p.k = (const bf16_t*)a.k; p.v = (const bf16_t*)a.v;
@@ -1104,6 +1194,7 @@ AttnParams make_params(const AttnArgs& a) {
   p.scale = 1.0f / sqrtf((float)a.head_dim);
   p.scale_log2e = p.scale * LOG2E;
   p.rope_table = a.rope_table;
+  p.dkv_partial = a.dkv_partial;
   return p;
 }
 
@@ -1130,12 +1221,28 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+int attn_kv_parts(int64_t heaviest, int64_t total, int64_t rows, int head_dim) {
+  const int64_t resident = head_dim == 64 ? 512 : 256;
+  const double per_it = head_dim == 64 ? 1.1 : 2.2;
+  int best = 1;
+  double best_cost = 1e300;
+  for (int parts = 1; parts <= 8 && (parts == 1 || heaviest / parts >= 4); parts++) {
+    const double chain = (double)((heaviest + parts - 1) / parts), fill = (double)total / (double)resident;
+    double cost = std::max(chain, fill) * per_it;
+    if (parts > 1) cost += 6.0 + (double)rows * head_dim * 16.0 * parts / 4.0e6;   // fp32 dK and dV, written and read
+    if (cost < 0.97 * best_cost) { best_cost = cost; best = parts; }
+  }
+  return best;
+}
+
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (a.q_grid == 0) return hipSuccess;
   if (!offsets_fit(a)) return hipErrorInvalidValue;
+  const bool split = a.kv_parts > 1 && a.dkv_partial;
+  if (split && a.rope_table && !a.pos) return hipErrorInvalidValue;
   ProfScope prof(PROF_ATTN_BWD, 2.0 * a.fwd_flops, s);
   AttnParams p = make_params(a);
-  const dim3 block(256), qgrid((unsigned)a.q_grid), kgrid((unsigned)a.kv_grid);
+  const dim3 block(256), qgrid((unsigned)a.q_grid), kgrid((unsigned)a.kv_grid, split ? (unsigned)a.kv_parts : 1u);
   // dQ first: it writes delta, which the dK/dV pass reads
   if (a.head_dim == 128) {
     p.list = (const AttnItem*)a.q_list;
@@ -1149,6 +1256,11 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, kgrid, block, 0, s, p);
   } else {
     return hipErrorInvalidValue;
+  }
+  if (split) {
+    const int64_t n = (int64_t)a.total_tokens * a.n_kv_heads * (a.head_dim / 16);
+    hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((unsigned)((n + 255) / 256)), block, 0, s, a.dkv_partial, (bf16_t*)a.dk, (bf16_t*)a.dv,
+                       a.kv_parts, (int64_t)a.total_tokens, a.n_kv_heads, a.head_dim, a.kv_stride, p.scale, a.rope_table, a.pos);
   }
   return hipGetLastError();
 }

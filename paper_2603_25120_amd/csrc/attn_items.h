@@ -44,6 +44,20 @@ inline size_t attn_list_bytes(const mllm_pack_t& p, int tile, int heads) {
   return (size_t)ATTN_XCDS * (size_t)attn_count_tiles(p, tile) * (size_t)heads * sizeof(AttnItem);
 }
 
+// Parts of the dK/dV pass over this token space (attn_kv_parts).
+inline int attn_kv_parts_of(const mllm_pack_t& p, int n_kv_heads, int heads_per_kv, int head_dim) {
+  int64_t heaviest = 0, total = 0;
+  for (int s = 0; s < p.n_segments; s++) {
+    const int len = p.cu_seqlens_host[s + 1] - p.cu_seqlens_host[s];
+    for (int t0 = 0; t0 < len; t0 += ATTN_BWD_KV_TILE) {
+      const int64_t its = (int64_t)heads_per_kv * (((p.mask_kind_host[s] == MLLM_MASK_CAUSAL ? len - t0 : len) + 63) / 64);
+      heaviest = std::max(heaviest, its);
+      total += its * n_kv_heads;
+    }
+  }
+  return attn_kv_parts(heaviest, total, (int64_t)p.total_tokens * n_kv_heads, head_dim);
+}
+
 // Writes the list to dst (at most attn_list_bytes(...) bytes, grid * sizeof(AttnItem) of them used) and
 // returns the grid size, 8 * the longest sub-list.
 //   kv_major: items are key tiles (dK/dV pass) and `head` is the kv head; otherwise items are query

@@ -75,10 +75,21 @@ struct AttnArgs {
   // the start of each segment), dq and dk leave rotated by the negative rotary angle of their row,
   // i.e. as gradients of the q and k that entered the rotation
   const float* rope_table;
+  // backward only: the dK/dV pass in kv_parts parts per key tile (attn_kv_parts; 0 or 1: undivided), their sums in
+  // dkv_partial, fp32 [kv_parts][2][total_tokens][n_kv_heads * head_dim]; pos: device int32, every row's
+  // position in its segment (needed with a rope_table)
+  int32_t kv_parts; float* dkv_partial; const int32_t* pos;
   double fwd_flops;                               // algorithmic forward FLOPs of this call (for timing reports)
 };
 constexpr int ATTN_FWD_Q_TILE = 128;   // query rows per workgroup, forward and dQ pass
 constexpr int ATTN_BWD_KV_TILE = 128;  // key rows per workgroup, dK/dV pass
+// In how many parts the dK/dV pass should walk its key tiles.  A workgroup owns a (key tile, kv head) and meets
+// every query tile of every query head of the group one after the other, so with few kv heads and few
+// tokens most CUs have no workgroup while the heaviest one sets the time (28 / 4 heads, 2999 tokens: 100
+// workgroups, 370 us).  heaviest, total: the largest and the summed number of 64-row query tiles that the
+// (key tile, kv head) items meet; rows: rows of the k matrix times kv heads.  Measured constants (microseconds):
+// a query tile 2.2 at head_dim 128, 1.1 at 64; the parts' sums go through memory at 4 TB/s and cost a launch.
+int attn_kv_parts(int64_t heaviest, int64_t total, int64_t rows, int head_dim);
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
 

@@ -193,6 +193,7 @@ struct AttnLists {
   // byte offsets into the metadata blob and grid sizes, known once the lists are built (upload_meta)
   size_t q_off = 0, kv_off = 0;
   int q_grid = 0, kv_grid = 0;
+  int kv_parts = 1;                 // parts of the dK/dV pass
 };
 
 struct Meta {  // byte offsets into the metadata blob at the head of the workspace
@@ -211,6 +212,7 @@ struct Plan {
   // workspace offsets (after the metadata)
   size_t w_partial = 0;           // fp32 partial sums of norm / bias gradients
   size_t w_a = 0, w_b = 0, w_c = 0, w_d = 0, w_e = 0, w_delta = 0, w_g0 = 0, w_g1 = 0, w_proj = 0, w_split = 0;
+  size_t w_dkv = 0;               // fp32 sums of the parts of a divided dK/dV pass
   size_t w_qkn = 0;               // QK normalisation: gradient of the normalised q, k  [T, nq]
   // Rotary-angle tables [longest sample, head_dim] fp32, one per distinct (rope_base, head_dim) of the
   // decoder layers; rope_of[i] = index of layer i's table (-1: the layer has none).
@@ -291,6 +293,7 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
 
   Bump ws;
   Meta& M = P.meta;
+  size_t dkv = 0;
   if (st->n_dec > 0) M.pos = ws.take(sizeof(int32_t) * P.T_seq);
   if (st->proj >= 0) M.i2s = ws.take(sizeof(int32_t) * P.T_con);
   if (st->proj >= 0 && P.pool > 1) {
@@ -312,6 +315,9 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
       AttnLists A;
       A.img = img; A.hq = L.n_q_heads; A.hkv = L.n_kv_heads; A.head_dim = L.head_dim;
       const mllm_pack_t& pk = img ? b->img : b->seq;
+      A.kv_parts = attn_kv_parts_of(pk, A.hkv, A.hq / A.hkv, A.head_dim);
+      if (A.kv_parts > 1)
+        dkv = std::max(dkv, (size_t)A.kv_parts * 2 * (size_t)pk.total_tokens * A.hkv * A.head_dim * 4);
       ws.take(attn_list_bytes(pk, ATTN_FWD_Q_TILE, L.n_q_heads));
       ws.take(attn_list_bytes(pk, ATTN_BWD_KV_TILE, L.n_kv_heads));
       found = (int)M.attn.size();
@@ -388,6 +394,7 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   P.w_e = ws.take(e);
   P.w_qkn = ws.take(qkn);
   P.w_delta = ws.take(delta);
+  P.w_dkv = ws.take(dkv);
   P.w_g0 = ws.take(g);
   P.w_g1 = ws.take(g);
   P.w_proj = ws.take(proj);
@@ -527,6 +534,9 @@ AttnArgs attn_args(const mllm_layer_desc_t& L, char* qk, char* v, int64_t T, con
   a.kv_list = ws + A.kv_off;
   a.q_grid = A.q_grid;
   a.kv_grid = A.kv_grid;
+  a.kv_parts = A.kv_parts;
+  a.dkv_partial = (float*)const_cast<char*>(ws + P.w_dkv);
+  a.pos = img ? nullptr : (const int32_t*)(ws + P.meta.pos);
   a.fwd_flops = 4.0 * (img ? P.img_pairs : P.seq_pairs) * L.n_q_heads * L.head_dim;
   return a;
 }
