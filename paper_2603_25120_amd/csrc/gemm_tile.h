@@ -20,7 +20,7 @@ namespace {
 // as 32x32x16: on normally distributed data a loop of nothing but MFMAs runs at 2020 TFLOP/s against
 // 1770 (on zeros, where power does not count, both at 2410-2430).  Whole kernel against the 32x32x16 form with
 // two staging sets that it replaced, one card, in turn: 32768 x 4096 x 28672, both operands k-contiguous,
-// 1428 -> 1475 TFLOP/s; 32768 x 4096 x 14336 with W stored [K, N] 1394 -> 1447; 4096 x 28672 x 32768, both
+// 1421 -> 1541 TFLOP/s; 32768 x 4096 x 14336 with W stored [K, N] 1394 -> 1447; 4096 x 28672 x 32768, both
 // stored [K, .], 1431 -> 1477; without its global loads and LDS stores the loop reaches 1880-1920.  128x128
 // tiles (two workgroups on a CU): 777 x 4096 x 14336 128 -> 100 us, 2999 x 3584 x 18944 464 -> 390 us.
 //
@@ -155,7 +155,8 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
   // to the registers.
   constexpr bool DIRECT = !A_T && !B_T && NS >= 48;
   constexpr int RS = DIRECT ? (NS >= 2 * NU + 8 ? 2 : 1) : (NS >= NU + 8 ? (NS - 8) / NU : 1);
-  constexpr int BAR = RS * (NU - 1) + (NS < 48 ? 4 : DIRECT ? 20 : 10);
+  constexpr int BAR = RS * (NU - 1) + (NS < 48 ? 4 : DIRECT ? 8 : 10);
+  constexpr int BAR2 = DIRECT ? NS - 1 : -1;   // second barrier of a k-tile, direct loads only
   static_assert(BAR < NS, "the first k-step's reads are issued before the barrier");
   __shared__ __attribute__((aligned(1024))) bf16_t As0[TA::SIZE];
   __shared__ __attribute__((aligned(1024))) bf16_t As1[TA::SIZE];
@@ -191,16 +192,17 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
   auto b_stage = [&](auto i_c) __attribute__((always_inline)) -> bf16_t* { return decltype(i_c)::value ? Bs1 : Bs0; };
   // The tile traffic of one k-tile's time, from the barrier of tile kt to that of tile kt + 1 ("window kt", NW
   // slots), into the LDS stage that tile kt has left.
-  //   DIRECT (both operands k-contiguous): tile kt + 2 is requested from memory straight into LDS, LOAD_STEP
-  //   slots from load to load: closer together the wavefront stands still while the memory pipeline takes
-  //   them, further apart the last ones have too little time to land.
+  //   DIRECT (both operands k-contiguous, large tiles): tile kt + 2 is requested from memory straight into LDS,
+  //   LOAD_STEP slots from load to load: closer together the wavefront stands still while the memory pipeline
+  //   takes them, further apart the last ones have too little time to land (32768 x 4096 x 28672: 4 slots 1481, 5
+  //   1532, 6 1544 TFLOP/s).
   //   Otherwise tile kt + 2 goes from the staging registers to LDS, one vector at a time over the whole
   //   window, and each register is refilled with tile kt + 3 at once, so that every load has a whole
-  //   k-tile's time to land.  Direct loads of operands stored [K, .] came too late: their 64 rows lie in other
-  //   pages with every k-tile (32768 x 4096 x 14336: 1060 TFLOP/s direct, 1382 through registers; both
-  //   k-contiguous, 32768 x 4096 x 28672: 1474 and 1412).
+  //   k-tile's time to land.  Direct loads of operands stored [K, .] are late whatever their spacing (32768 x 4096 x
+  //   14336: 1044-1067 TFLOP/s direct, 1404 through registers), and 128x128 tiles need their loads too close
+  //   together (777 x 4096 x 28672: 525 and 763).
   constexpr int NW = 2 * NS, HEAD = NS + NS - BAR;   // slots [0, HEAD) belong to iteration kt, the rest to kt + 1
-  constexpr int LOAD_STEP = NW / (2 * NU);
+  constexpr int LOAD_STEP = NS >= 64 ? 6 : 5;   // 192x256 tiles: 5 slots 1196, 6 1137 TFLOP/s (5125 x 3200 x 12800)
   u32x4 stage[DIRECT ? 1 : NU];
   auto load_vec = [&](auto q_c, const TileSource& sa, const TileSource& sb) __attribute__((always_inline)) {
     constexpr int q = decltype(q_c)::value;
@@ -294,10 +296,21 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
     auto slot = [&](auto kk_c, auto m_c) __attribute__((always_inline)) {
       constexpr int kk = decltype(kk_c)::value, m = decltype(m_c)::value;
       if constexpr (kk == 0 && m == BAR) {
-        // Every wavefront has read tile kt, and its share of tile kt + 1 is in LDS: landed (direct), or
-        // stored (then global loads stay in flight).
+        // Every wavefront has read tile kt, so its stage may take tile kt + 2; global loads stay in flight.
+        // Staged: this wavefront's share of tile kt + 1 has been stored, too.
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(DIRECT ? 0x0070 : 0xC07F);   // vmcnt(0) and lgkmcnt(0), or lgkmcnt(0) only
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (kk == 0 && m == BAR2) {
+        // Direct: this wavefront's share of tile kt + 1 has landed (of tile kt + 2's loads, those issued since the
+        // first barrier may be on their way).  A barrier of its own, as late as the tile's first reader allows, gives
+        // the loads 27 slots more than one barrier for both would.
+        constexpr int ISSUED = DIRECT ? (BAR2 - BAR - 2) / LOAD_STEP + 1 : 0, VM = ISSUED < NU ? ISSUED : NU;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (VM & 15) | ((VM >> 4) << 14));   // vmcnt(VM)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
