@@ -27,6 +27,7 @@ struct GemmParams {
   uint32_t a_bytes, b_bytes;
   int accumulate;
   int tiles_m, tiles_n;
+  int group_m;              // tile-rows of a panel in the walk over the tiles
   int kt_per_split;         // k-tiles handled by one workgroup row (gridDim.y splits of the K loop)
   int64_t c_split_stride;   // elements between the partial outputs of consecutive splits
   bf16_t* act;              // fused SwiGLU: silu(gate) * up, [M, N / 2]
@@ -47,6 +48,11 @@ inline GemmParams make_gemm_params(const GemmArgs& g, int bm, int bn) {
   p.b_bytes = (uint32_t)((g.b_layout ? g.n : g.k) * g.ldb * 2);
   p.tiles_m = (int)((g.m + bm - 1) / bm);
   p.tiles_n = (int)((g.n + bn - 1) / bn);
+  // An XCD's 32 resident tiles are a block of group_m x 32 / group_m.  8 x 4 fetches as much as 4 x 8, but reads A once
+  // for every 4 columns of tiles: once A no longer stays in the 256 MB memory-side cache, 4 x 8 halves what
+  // comes from memory (32768 x 4096 x 14336, A 0.94 GB: 1408 -> 1446 TFLOP/s; x 28672 k-contiguous 1528 -> 1559; 8192 x
+  // 4096 x 22016, A 0.36 GB: 1425 -> 1442; below, 26496 x 1024 x 4096, A 0.22 GB: 1328 -> 1304).
+  p.group_m = g.m * g.k * 2 > (int64_t)320 << 20 ? 4 : 8;
   p.kt_per_split = (int)((g.k + BK - 1) / BK);
   p.c_split_stride = 0;
   p.act = (bf16_t*)g.swiglu_act;
@@ -64,20 +70,18 @@ enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_R
 template <bool A_T, bool B_T>
 hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
 
-constexpr int GROUP_M = 8;
-
 // Workgroups are dealt round-robin to the 8 XCDs.  Renumber so that each XCD gets a contiguous
-// range of tile ids, then walk the tile grid in panels of GROUP_M tile-rows.
-__device__ __forceinline__ void tile_of_block(int pid, int nblk, int tiles_m, int tiles_n,
+// range of tile ids, then walk the tile grid in panels of group_m tile-rows.
+__device__ __forceinline__ void tile_of_block(int pid, int nblk, int tiles_m, int tiles_n, int group_m,
                                               int& tm, int& tn) {
   const int per = (nblk + 7) >> 3, r = nblk & 7;
   const int x = pid & 7, local = pid >> 3;
   int off = (r == 0 || x <= r) ? x * per : r * per + (x - r) * (per - 1);
   int t = off + local;
-  const int in_group = GROUP_M * tiles_n;
+  const int in_group = group_m * tiles_n;
   const int gid = t / in_group;
-  const int first_m = gid * GROUP_M;
-  const int gsz = min(tiles_m - first_m, GROUP_M);
+  const int first_m = gid * group_m;
+  const int gsz = min(tiles_m - first_m, group_m);
   tm = first_m + (t % in_group) % gsz;
   tn = (t % in_group) / gsz;
 }
