@@ -355,7 +355,11 @@ mllm_status_t mllm_op_act_bwd(int act, const void* da, const void* pre, void* dp
   return MLLM_OK;
 }
 
-size_t mllm_op_colsum_partial_bytes(int64_t t, int64_t n) { return (size_t)colsum_partial_rows(t) * (size_t)n * 4; }
+// What a caller provides (and what the static scratch must hold): a row of sums for every four tokens, at most
+// 512.  The kernel takes one for every 16 (colsum_partial_rows).
+size_t mllm_op_colsum_partial_bytes(int64_t t, int64_t n) {
+  return (size_t)std::max<int64_t>(1, std::min<int64_t>(512, t / 4)) * (size_t)n * 4;
+}
 
 mllm_status_t mllm_op_colsum(const void* x, float* out, int accumulate, float* partial, int64_t t, int64_t n, void* hip_stream) {
   if (!x || !out || !partial) return op_fail(MLLM_ERR_NULL, "a pointer is NULL");
