@@ -181,25 +181,28 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
   }
 }
 
-// out[c] (+)= sum_p partial[p][c].  A workgroup owns 8 columns: 128 row slices x 2 float4 column
-// groups; slice s adds rows s, s+128, ... in order (four loads in flight), then the slice sums are
-// added pairwise (s with s+64, then s with s+32, ...): a fixed association, so the result is
+// out[c] (+)= sum_p partial[p][c], for every job of a list.  A workgroup owns 8 columns of one job: 128 row
+// slices x 2 float4 column groups; slice s adds rows s, s+128, ... in order (four loads in flight), then the
+// slice sums are added pairwise (s with s+64, then s with s+32, ...): a fixed association, so the result is
 // bitwise reproducible.
 constexpr int RED_COLS = 8, RED_SLICES = 128;
-// blockIdx.y = 1, 2 (when launched with two or three rows of workgroups) reduce a second and third
-// set of partial sums, P * n and 2 P * n floats further on, into out1 and out2: a norm's gradients go
-// in one launch.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial,
-                                                              float* __restrict__ out, int P,
-                                                              int64_t n, int accumulate,
-                                                              float* __restrict__ out1 = nullptr,
-                                                              float* __restrict__ out2 = nullptr) {
+struct ReduceList {
+  const float* partial[PartialSums::MAX_JOBS];
+  float* out[PartialSums::MAX_JOBS];
+  int rows[PartialSums::MAX_JOBS], n[PartialSums::MAX_JOBS];
+  unsigned first[PartialSums::MAX_JOBS];   // first workgroup of a job; past the list: never reached
+};
+__global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceList list, int accumulate) {
   __shared__ float4 part[RED_SLICES][RED_COLS / 4];
-  if (blockIdx.y == 1) { partial += (int64_t)P * n; out = out1; }
-  if (blockIdx.y == 2) { partial += 2 * (int64_t)P * n; out = out2; }
-  if (!out) return;   // a set that this launch does not carry
+  int job = 0;
+#pragma unroll
+  for (int j = 1; j < PartialSums::MAX_JOBS; j++) job += blockIdx.x >= list.first[j] ? 1 : 0;
+  const float* __restrict__ partial = list.partial[job];
+  float* __restrict__ out = list.out[job];
+  const int P = list.rows[job];
+  const int64_t n = list.n[job];
   const int cg = threadIdx.x & 1, slice = threadIdx.x >> 1;
-  const int64_t c = ((int64_t)blockIdx.x * (RED_COLS / 4) + cg) * 4;
+  const int64_t c = ((int64_t)(blockIdx.x - list.first[job]) * (RED_COLS / 4) + cg) * 4;
   const bool valid = c < n;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (valid) {
@@ -714,22 +717,72 @@ int64_t norm_bwd_partial_rows(int64_t t) {
   return t < 1 ? 1 : (t > 1024 ? 1024 : t);
 }
 
+hipError_t PartialSums::take(int64_t rows, int64_t n, std::initializer_list<float*> outs, hipStream_t s, float** partial) {
+  const size_t need = (size_t)rows * (size_t)n * outs.size();
+  bool full = used + need > capacity || count + (int)outs.size() > MAX_JOBS;
+  for (float* out : outs)
+    for (int j = 0; out && j < count; j++) full = full || (out < jobs[j].out + jobs[j].n && jobs[j].out < out + n);
+  if (full) {
+    hipError_t e = flush(s);
+    if (e != hipSuccess) return e;
+  }
+  if (need > capacity || (int)outs.size() > MAX_JOBS) return hipErrorInvalidValue;
+  float* p = base + used;
+  *partial = p;
+  used += need;
+  for (float* out : outs) {
+    if (out) jobs[count++] = {p, out, (int)rows, n};
+    p += rows * n;
+  }
+  return hipSuccess;
+}
+
+hipError_t PartialSums::flush(hipStream_t s) {
+  ReduceList list;
+  unsigned blocks = 0;
+  for (int j = 0; j < MAX_JOBS; j++) {
+    const bool there = j < count;
+    list.partial[j] = there ? jobs[j].partial : nullptr;
+    list.out[j] = there ? jobs[j].out : nullptr;
+    list.rows[j] = there ? jobs[j].rows : 0;
+    list.n[j] = there ? (int)jobs[j].n : 0;
+    list.first[j] = there ? blocks : ~0u;
+    if (there) blocks += blocks_for(jobs[j].n, RED_COLS);
+  }
+  count = 0;
+  used = 0;
+  if (blocks == 0) return hipSuccess;
+  ProfScope prof(PROF_ELEMENTWISE, 0.0, s);   // the bytes of a sum are counted with its first stage
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks), dim3(256), 0, s, list, accumulate);
+  return hipGetLastError();
+}
+
+// Workgroups (= rows of partial sums) of the norm backward.  The wavefront-per-row kernel with two vectors per lane
+// keeps three workgroups per CU resident: a grid of 768 runs in one round.
+// For few rows the second stage (W x d floats a set) weighs more than the occupancy of the first, so a workgroup
+// then takes several rows: two a wavefront in the wavefront-per-row kernel, three in the other one (777 x 4096: 10.8 + 10.2 us
+// with a row a workgroup, 13.9 + 5.6 with three; 2880 x 1024, three sets: 10.4 + 8.1 and 11.8 + 4.8).
+int64_t norm_bwd_workgroups(int64_t t, int64_t d) {
+  const int64_t nvec = d / 8, rows_per_wg = nvec <= 128 ? 4 * 2 : 3;
+  int64_t W = std::min<int64_t>(norm_bwd_partial_rows(t), std::max<int64_t>(std::min<int64_t>(t, 256), t / rows_per_wg));
+  W = std::max<int64_t>(1, W);
+  if (nvec > 64 && nvec <= 128) W = std::min<int64_t>(W, 768);
+  return W;
+}
+
 hipError_t launch_norm_bwd(int kind, const void* dy, const void* x, const void* gamma,
                            const float* stats, const void* dres, void* dx, float* dgamma,
-                           float* dbeta, int accumulate, float* partial, int64_t t, int64_t d,
+                           float* dbeta, PartialSums& sums, int64_t t, int64_t d,
                            int64_t ld, hipStream_t s, float* dx_colsum) {
   if (d % 8 != 0 || d > 8192 || ld < d || ld % 8 != 0) return hipErrorInvalidValue;
   if (dx_colsum && !norm_bwd_colsum_fusable(d)) return hipErrorInvalidValue;
   const int64_t nvec = d / 8;
-  // Workgroups (= rows of partial sums).  The wavefront-per-row kernel with two vectors per lane
-  // keeps three workgroups per CU resident: a grid of 768 runs in one round.
-  // For few rows the second stage (W x d floats a set) weighs more than the occupancy of the first, so a workgroup
-  // then takes several rows: two a wavefront in the wavefront-per-row kernel, three in the other one (777 x 4096: 10.8 + 10.2 us
-  // with a row a workgroup, 13.9 + 5.6 with three; 2880 x 1024, three sets: 10.4 + 8.1 and 11.8 + 4.8).
-  const int64_t rows_per_wg = nvec <= 128 ? 4 * 2 : 3;
-  int64_t W = std::min<int64_t>(norm_bwd_partial_rows(t), std::max<int64_t>(std::min<int64_t>(t, 256), t / rows_per_wg));
-  W = std::max<int64_t>(1, W);
-  if (nvec > 64 && nvec <= 128) W = std::min<int64_t>(W, 768);
+  const int64_t W = norm_bwd_workgroups(t, d);
+  float* partial = nullptr;
+  float* beta_out = kind == 0 ? dbeta : nullptr;
+  hipError_t e = dx_colsum ? sums.take(W, d, {dgamma, beta_out, dx_colsum}, s, &partial)
+               : kind == 0 ? sums.take(W, d, {dgamma, beta_out}, s, &partial) : sums.take(W, d, {dgamma}, s, &partial);
+  if (e != hipSuccess) return e;
   ProfScope prof(PROF_ELEMENTWISE, (dres ? 8.0 : 6.0) * (double)t * (double)d, s);
   dim3 grid((unsigned)W), block(256);
 #define CALL(NV)                                                                                   \
@@ -748,10 +801,6 @@ hipError_t launch_norm_bwd(int kind, const void* dy, const void* x, const void* 
 #undef CALL_WAVE
 #undef CALL_WAVE_CS
 #undef CALL
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks_for(d, RED_COLS), dx_colsum ? 3 : (kind == 0 ? 2 : 1)), dim3(256), 0, s,
-                     partial, dgamma, (int)W, d, accumulate, kind == 0 ? dbeta : nullptr, dx_colsum);
   return hipGetLastError();
 }
 
@@ -818,14 +867,15 @@ hipError_t launch_act_bwd(int act, const void* da, const void* pre, void* dpre, 
 }
 
 hipError_t launch_gelu_bwd_colsum(int act, const void* da, const void* pre, void* dpre, float* colsum,
-                                  int accumulate, float* partial, int64_t t, int64_t f, hipStream_t s) {
+                                  PartialSums& sums, int64_t t, int64_t f, hipStream_t s) {
   if (f % 8 != 0 || (act != 0 && act != 1)) return hipErrorInvalidValue;
   const int64_t P = colsum_partial_rows(t);
+  float* partial = nullptr;
+  hipError_t e = sums.take(P, f, {colsum}, s, &partial);
+  if (e != hipSuccess) return e;
   ProfScope prof(PROF_ELEMENTWISE, 6.0 * (double)t * (double)f, s);
   hipLaunchKernelGGL(gelu_bwd_colsum_kernel, dim3(blocks_for(f, 512), (unsigned)P), dim3(256), 0, s, act,
                      (const bf16_t*)da, (const bf16_t*)pre, (bf16_t*)dpre, partial, t, f);
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks_for(f, RED_COLS)), dim3(256), 0, s, partial, colsum, (int)P,
-                     f, accumulate);
   return hipGetLastError();
 }
 
@@ -834,15 +884,15 @@ hipError_t launch_gelu_bwd_colsum(int act, const void* da, const void* pre, void
 // 3.9 us with 180, the first stage unchanged.
 int64_t colsum_partial_rows(int64_t t) { return std::max<int64_t>(1, std::min<int64_t>(512, t / 16)); }
 
-hipError_t launch_colsum(const void* x, int64_t ldx, float* out, int accumulate, float* partial,
-                         int64_t t, int64_t n, hipStream_t s) {
+hipError_t launch_colsum(const void* x, int64_t ldx, float* out, PartialSums& sums, int64_t t, int64_t n, hipStream_t s) {
   if (n % 8 != 0 || ldx % 8 != 0) return hipErrorInvalidValue;
   const int64_t P = colsum_partial_rows(t);
+  float* partial = nullptr;
+  hipError_t e = sums.take(P, n, {out}, s, &partial);
+  if (e != hipSuccess) return e;
   ProfScope prof(PROF_ELEMENTWISE, 2.0 * (double)t * (double)n, s);
   hipLaunchKernelGGL(colsum_partial_kernel, dim3(blocks_for(n, 512), (unsigned)P), dim3(256), 0, s,
                      (const bf16_t*)x, ldx, partial, t, n);
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks_for(n, RED_COLS)), dim3(256), 0, s, partial,
-                     out, (int)P, n, accumulate);
   return hipGetLastError();
 }
 

@@ -312,7 +312,9 @@ mllm_status_t mllm_op_norm_bwd(int kind, const void* dy, const void* x, const vo
   if (!dy || !x || !gamma || !stats || !dx || !dgamma || !partial || (kind == 0 && !dbeta)) return op_fail(MLLM_ERR_NULL, "a pointer is NULL");
   if (kind != 0 && kind != 1) return op_fail(MLLM_ERR_SHAPE, "kind must be 0 or 1");
   if (t < 0 || d <= 0 || d % 8 || d > 8192) return op_fail(MLLM_ERR_SHAPE, "d must be a multiple of 8, at most 8192");
-  OP_TRY(launch_norm_bwd(kind, dy, x, gamma, stats, dres, dx, dgamma, dbeta, accumulate, partial, t, d, d, (hipStream_t)hip_stream));
+  PartialSums sums(partial, mllm_op_norm_bwd_partial_bytes(t, d), accumulate);
+  OP_TRY(launch_norm_bwd(kind, dy, x, gamma, stats, dres, dx, dgamma, dbeta, sums, t, d, d, (hipStream_t)hip_stream));
+  OP_TRY(sums.flush((hipStream_t)hip_stream));
   return MLLM_OK;
 }
 
@@ -325,8 +327,9 @@ mllm_status_t mllm_op_norm_bwd_colsum(int kind, const void* dy, const void* x, c
   if (kind != 0 && kind != 1) return op_fail(MLLM_ERR_SHAPE, "kind must be 0 or 1");
   if (t < 0 || d <= 0 || d % 8 || !norm_bwd_colsum_fusable(d))
     return op_fail(MLLM_ERR_SHAPE, "d must be a multiple of 8, at most 1024");
-  OP_TRY(launch_norm_bwd(kind, dy, x, gamma, stats, dres, dx, dgamma, dbeta, accumulate, partial, t, d, d,
-                         (hipStream_t)hip_stream, dx_colsum));
+  PartialSums sums(partial, mllm_op_norm_bwd_partial_bytes(t, d), accumulate);
+  OP_TRY(launch_norm_bwd(kind, dy, x, gamma, stats, dres, dx, dgamma, dbeta, sums, t, d, d, (hipStream_t)hip_stream, dx_colsum));
+  OP_TRY(sums.flush((hipStream_t)hip_stream));
   return MLLM_OK;
 }
 
@@ -364,7 +367,9 @@ size_t mllm_op_colsum_partial_bytes(int64_t t, int64_t n) {
 mllm_status_t mllm_op_colsum(const void* x, float* out, int accumulate, float* partial, int64_t t, int64_t n, void* hip_stream) {
   if (!x || !out || !partial) return op_fail(MLLM_ERR_NULL, "a pointer is NULL");
   if (t < 0 || n <= 0 || n % 8) return op_fail(MLLM_ERR_SHAPE, "n must be a positive multiple of 8");
-  OP_TRY(launch_colsum(x, n, out, accumulate, partial, t, n, (hipStream_t)hip_stream));
+  PartialSums sums(partial, mllm_op_colsum_partial_bytes(t, n), accumulate);
+  OP_TRY(launch_colsum(x, n, out, sums, t, n, (hipStream_t)hip_stream));
+  OP_TRY(sums.flush((hipStream_t)hip_stream));
   return MLLM_OK;
 }
 
@@ -381,7 +386,9 @@ mllm_status_t mllm_op_colsum_static(const void* x, float* out, int accumulate, i
   mllm_status_t r = static_scratch(&partial);
   if (r != MLLM_OK) return r;
   // every partial sum the second kernel reads is written by the first: nothing to clear
-  OP_TRY(launch_colsum(x, n, out, accumulate, (float*)partial, t, n, (hipStream_t)hip_stream));
+  PartialSums sums((float*)partial, need, accumulate);
+  OP_TRY(launch_colsum(x, n, out, sums, t, n, (hipStream_t)hip_stream));
+  OP_TRY(sums.flush((hipStream_t)hip_stream));
   return MLLM_OK;
 }
 

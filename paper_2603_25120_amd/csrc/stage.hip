@@ -211,6 +211,7 @@ struct Plan {
   std::vector<int> attn_of;       // per layer: index into meta.attn (-1: no attention)
   // workspace offsets (after the metadata)
   size_t w_partial = 0;           // fp32 partial sums of norm / bias gradients
+  size_t partial_bytes = 0;
   size_t w_a = 0, w_b = 0, w_c = 0, w_d = 0, w_e = 0, w_delta = 0, w_g0 = 0, w_g1 = 0, w_proj = 0, w_split = 0;
   size_t w_dkv = 0;               // fp32 sums of the parts of a divided dK/dV pass
   size_t w_qkn = 0;               // QK normalisation: gradient of the normalised q, k  [T, nq]
@@ -236,6 +237,19 @@ double visible_pairs(const mllm_pack_t& p) {
     n += p.mask_kind_host[s] == MLLM_MASK_CAUSAL ? 0.5 * len * len : len * len;
   }
   return n;
+}
+
+// Scratch of the sums over the tokens that one layer's backward pass forms (PartialSums).
+size_t layer_partial_bytes(const mllm_layer_desc_t& L, int64_t T) {
+  const bool vit = L.kind == MLLM_LAYER_VIT;
+  const int64_t d = L.d_model;
+  const bool fused = vit && norm_bwd_colsum_fusable(d);
+  int64_t floats = 2 * norm_bwd_workgroups(T, d) * d * norm_bwd_sets(vit ? 0 : 1, fused);
+  if (vit) floats += colsum_partial_rows(T) * (d + (fused ? 0 : d) + L.d_ff);
+  if (vit || L.has_bias) floats += colsum_partial_rows(T) * nqkv_of(L);
+  if (L.qk_norm)
+    for (int64_t w : {(int64_t)L.n_q_heads * L.head_dim, (int64_t)L.n_kv_heads * L.head_dim}) floats += norm_bwd_workgroups(T, w) * w;
+  return (size_t)floats * 4;
 }
 
 // Scratch of the three products of a linear map [T, k] -> [T, n]: Y, dX and dW.
@@ -327,7 +341,7 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   }
   M.bytes = ws.off;
 
-  size_t part = 0, a = 0, bb = 0, c = 0, e = 0, delta = 0, g = 0, proj = 0, split = 0, qkn = 0;
+  size_t part = 0, part_all = 0, a = 0, bb = 0, c = 0, e = 0, delta = 0, g = 0, proj = 0, split = 0, qkn = 0;
   for (const mllm_layer_desc_t& L : st->layers) {
     if (L.kind == MLLM_LAYER_PROJECTOR) {
       const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
@@ -341,7 +355,9 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
         split = std::max(split, linear_split_bytes(P.T_con, d_in, L.d_out));
       }
       if (P.pool > 1) c = std::max(c, (size_t)P.T_con * L.d_model * 2);   // gradient of the pooled rows
-      part = std::max(part, (size_t)colsum_partial_rows(P.T_con) * std::max(L.d_out, L.d_ff) * 4);
+      const size_t sums = (size_t)colsum_partial_rows(P.T_con) * (L.d_out + L.d_ff) * 4;
+      part = std::max(part, sums);
+      part_all += sums;
       g = std::max(g, (size_t)P.T_img * L.d_model * 2);
       g = std::max(g, (size_t)P.T_seq * L.d_out * 2);
       continue;
@@ -352,8 +368,9 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
     P.largest_operand_bytes = std::max<int64_t>(P.largest_operand_bytes, (int64_t)(T * widest * 2));
     // the attention kernels' 32-bit row offsets may run 256 rows past the last token
     P.largest_operand_bytes = std::max<int64_t>(P.largest_operand_bytes, (int64_t)((T + 256) * std::max(nq, d) * 2));
-    part = std::max(part, (size_t)norm_bwd_partial_rows(T) * d * 4 * 3);
-    part = std::max(part, (size_t)colsum_partial_rows(T) * widest * 4);
+    const size_t sums = layer_partial_bytes(L, T);
+    part = std::max(part, sums);
+    part_all += sums;
     a = std::max(a, T * f * 2);
     bb = std::max(bb, L.kind == MLLM_LAYER_DECODER ? T * 2 * f * 2 : 0);
     c = std::max(c, T * d * 2);
@@ -386,7 +403,9 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   }
   P.split_bytes = split;
   P.w_split = ws.take(split);
-  P.w_partial = ws.take(part);
+  // The sums of one layer at least; several layers' together while that is small.
+  P.partial_bytes = std::min(part_all, std::max(part, (size_t)32 << 20));
+  P.w_partial = ws.take(P.partial_bytes);
   P.w_a = ws.take(a);
   P.w_b = ws.take(bb);
   P.w_c = ws.take(c);
@@ -614,7 +633,7 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
 
 // dy -> dx (both bf16 [T,d]); parameter gradients into dprm (fp32).
 mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void* const* dprm,
-                        int accumulate, const LayerSaved& S, const char* saved, char* ws,
+                        int accumulate, PartialSums& sums, const LayerSaved& S, const char* saved, char* ws,
                         const Plan& P, int64_t T, const void* dy, void* dx, const float* rope_table,
                         int attn_list, hipStream_t s, bool dy_colsum_done, float* dx_colsum) {
   // dy_colsum_done: the layer above has already formed the column sums of dy (this layer's b_2
@@ -629,7 +648,6 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   const char* n2 = saved + S.n2;
   const char* pre = saved + S.pre;
   const char* act = saved + S.act;
-  float* partial = (float*)(ws + P.w_partial);
   const SplitWs split{ws + P.w_split, P.split_bytes};
   char* wa = ws + P.w_a;      // d act            [T, f]
   char* wb = ws + P.w_b;      // d (gate|up)      [T, 2f]  (decoder)
@@ -644,14 +662,14 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
 
   // MLP
   K_TRY(linear_dw(act, dy, dprm[iwdn], T, f, d, accumulate, s, split));
-  if (vit && !dy_colsum_done) K_TRY(launch_colsum(dy, d, (float*)dprm[ibdn], accumulate, partial, T, d, s));
+  if (vit && !dy_colsum_done) K_TRY(launch_colsum(dy, d, (float*)dprm[ibdn], sums, T, d, s));
   char* dpre = vit ? wa : wb;
   if (!vit && gemm_swiglu_bwd_fusable(T, f, d)) {
     K_TRY(linear_dx_swiglu(dy, prm[iwdn], pre, dpre, T, f, d, s));
   } else {
     K_TRY(linear_dx(dy, prm[iwdn], wa, T, f, d, s, split));
     if (vit)   // the bias gradient (column sums of dpre) comes out of the same pass
-      K_TRY(launch_gelu_bwd_colsum(L.act, wa, pre, dpre, (float*)dprm[ibup], accumulate, partial, T, f, s));
+      K_TRY(launch_gelu_bwd_colsum(L.act, wa, pre, dpre, (float*)dprm[ibup], sums, T, f, s));
     else
       K_TRY(launch_act_bwd(L.act, wa, pre, dpre, T, f, s));
   }
@@ -661,11 +679,11 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   // the projection's bias gradient, formed in the same pass where the row width allows
   const bool bo_fused = vit && norm_bwd_colsum_fusable(d);
   K_TRY(launch_norm_bwd(vit ? 0 : 1, wc, x1, prm[ig2], (const float*)(saved + S.stats2), dy, wd,
-                        (float*)dprm[ig2], vit ? (float*)dprm[ib2n] : nullptr, accumulate, partial, T, d, d, s,
+                        (float*)dprm[ig2], vit ? (float*)dprm[ib2n] : nullptr, sums, T, d, d, s,
                         bo_fused ? (float*)dprm[ibo] : nullptr));
   // attention block
   K_TRY(linear_dw(o, wd, dprm[iwo], T, d, d, accumulate, s, split));
-  if (vit && !bo_fused) K_TRY(launch_colsum(wd, d, (float*)dprm[ibo], accumulate, partial, T, d, s));
+  if (vit && !bo_fused) K_TRY(launch_colsum(wd, d, (float*)dprm[ibo], sums, T, d, s));
   K_TRY(linear_dx(wd, prm[iwo], wc, T, d, d, s, split));
   // With QK normalisation the gradient of the normalised q, k goes to a matrix of its own (same
   // columns as in d qkv); the norm's backward then writes the gradient of the projection's q, k
@@ -686,16 +704,16 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   K_TRY(launch_attn_bwd(a, s));
   if (L.qk_norm) {
     K_TRY(launch_norm_bwd(1, dqk, qkv, prm[n_base], (const float*)(saved + S.statsq), nullptr, we,
-                          (float*)dprm[n_base], nullptr, accumulate, partial, T, q_cols, nq, s));
+                          (float*)dprm[n_base], nullptr, sums, T, q_cols, nq, s));
     K_TRY(launch_norm_bwd(1, dqk + q_cols * 2, qkv + q_cols * 2, prm[n_base + 1], (const float*)(saved + S.statsk),
-                          nullptr, we + q_cols * 2, (float*)dprm[n_base + 1], nullptr, accumulate, partial,
+                          nullptr, we + q_cols * 2, (float*)dprm[n_base + 1], nullptr, sums,
                           T, k_cols, nq, s));
   }
   K_TRY(linear_dw(n1, we, dprm[iwqkv], T, d, nq, accumulate, s, split));
-  if (ibqkv >= 0) K_TRY(launch_colsum(we, nq, (float*)dprm[ibqkv], accumulate, partial, T, nq, s));
+  if (ibqkv >= 0) K_TRY(launch_colsum(we, nq, (float*)dprm[ibqkv], sums, T, nq, s));
   K_TRY(linear_dx(we, prm[iwqkv], wc, T, d, nq, s, split));
   K_TRY(launch_norm_bwd(vit ? 0 : 1, wc, x, prm[ig1], (const float*)(saved + S.stats1), wd, dx,
-                        (float*)dprm[ig1], vit ? (float*)dprm[ib1n] : nullptr, accumulate, partial, T, d, d, s, dx_colsum));
+                        (float*)dprm[ig1], vit ? (float*)dprm[ib1n] : nullptr, sums, T, d, d, s, dx_colsum));
   return MLLM_OK;
 }
 
@@ -909,6 +927,7 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
   const void* cur = dy;  // gradient w.r.t. the output of layer i
   char* pp[2] = {ws + P.w_g0, ws + P.w_g1};
   int flip = 0;
+  PartialSums sums((float*)(ws + P.w_partial), P.partial_bytes, accumulate);
   bool colsum_done = false;   // the column sums of `cur` are already in the bias gradient they belong to
   for (int i = n - 1; i >= 0; i--) {
     const mllm_layer_desc_t& L = st->layers[i];
@@ -923,7 +942,6 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
         K_TRY(launch_zero_rows(dx_seq, i2s, P.T_con, L.d_out, s));
       }
       const SplitWs split{ws + P.w_split, P.split_bytes};
-      float* partial = (float*)(ws + P.w_partial);
       void* out = (i == 0 && dx_img) ? dx_img : (void*)pp[flip];
       const char* xin = P.pool > 1 ? saved + P.saved[i].n1 : saved + P.saved[i].x;
       const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
@@ -933,14 +951,14 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
         const char* act = saved + P.saved[i].act;
         char* dh = ws + P.w_a;     // d act, then d pre in place   [T_con, d_ff]
         K_TRY(linear_dw(act, dproj, dprm[2], P.T_con, L.d_ff, L.d_out, accumulate, s, split));
-        K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[3], accumulate, partial, P.T_con, L.d_out, s));
+        K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[3], sums, P.T_con, L.d_out, s));
         K_TRY(linear_dx(dproj, prm[2], dh, P.T_con, L.d_ff, L.d_out, s, split));
-        K_TRY(launch_gelu_bwd_colsum(L.act, dh, pre, dh, (float*)dprm[1], accumulate, partial, P.T_con, L.d_ff, s));
+        K_TRY(launch_gelu_bwd_colsum(L.act, dh, pre, dh, (float*)dprm[1], sums, P.T_con, L.d_ff, s));
         K_TRY(linear_dw(xin, dh, dprm[0], P.T_con, d_in, L.d_ff, accumulate, s, split));
         K_TRY(linear_dx(dh, prm[0], dxin, P.T_con, d_in, L.d_ff, s, split));
       } else {
         K_TRY(linear_dw(xin, dproj, dprm[0], P.T_con, d_in, L.d_out, accumulate, s, split));
-        K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[1], accumulate, partial, P.T_con, L.d_out, s));
+        K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[1], sums, P.T_con, L.d_out, s));
         K_TRY(linear_dx(dproj, prm[0], dxin, P.T_con, d_in, L.d_out, s, split));
       }
       if (P.pool > 1)
@@ -966,12 +984,13 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
     if (vit && i > 0 && st->layers[i - 1].kind == MLLM_LAYER_VIT && st->layers[i - 1].d_model == L.d_model &&
         norm_bwd_colsum_fusable(L.d_model))
       below = (float*)(dparams + st->param_off[i - 1])[11];
-    if ((r = layer_bwd(L, prm, dprm, accumulate, P.saved[i], saved, ws, P, T, cur, out, rope_table, P.attn_of[i], s,
+    if ((r = layer_bwd(L, prm, dprm, accumulate, sums, P.saved[i], saved, ws, P, T, cur, out, rope_table, P.attn_of[i], s,
                        colsum_done, below)) != MLLM_OK) return r;
     colsum_done = below != nullptr;
     cur = out;
     flip ^= 1;
   }
+  K_TRY(sums.flush(s));
   return MLLM_OK;
 }
 
