@@ -33,15 +33,15 @@ HBM_PEAK = 8.0e12         # B/s
 
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_full_stage_32k.md")
-TRAFFIC_KERNELS = {"gemm_fwd": "gemm4_kernel<4, false, true, false>", "gemm_dx": "gemm4_kernel<4, false, false, false>",
-                   "gemm_dw": "gemm4_kernel<4, true, true, true>"}
+TRAFFIC_KERNELS = {"gemm_fwd": "gemm4_kernel<8, 8, false, true, false, 0>", "gemm_dx": "gemm4_kernel<8, 8, false, false, false, 0>",
+                   "gemm_dw": "gemm4_kernel<8, 8, true, true, true, 0>"}
 
 
 def gemm_source_digest():
     """First 16 hex digits of the SHA-256 of the GEMM kernel sources."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gemm.hip", "gemm_common.h"):
+    for f in ("gemm.hip", "gemm_common.h", "gemm_tile.h", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip"):
         with open(os.path.join(ROOT, "paper_2603_25120_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -563,13 +563,9 @@ def main():
     gemm_all = ("gemm_fwd", "gemm_dx", "gemm_dw", "gemm_small", "gemm_rows192")
     all_gemm_ms = sum(prof[c][1] for c in gemm_all)
     all_gemm_work = sum(prof[c][2] for c in gemm_all)
-    kernel_names = {"gemm_fwd": "gemm4_kernel<4, false, true, false> and gemm4_swiglu_kernel (Y = X.W, 256x256x64 tiles)",
-                    "gemm_dx": "gemm4_kernel<4, false, false, false> and gemm4_swiglu_bwd_kernel (dX = dY.W^T, 256x256x64 tiles)",
-                    "gemm_dw": "gemm4_kernel<4, true, true, true> (dW = X^T.dY, fp32, 256x256x64 tiles)"}
-    # weight gradients contract over the tokens: a token count that is no multiple of 64 takes the ragged-K form
-    ragged = any(pk is not None and pk.total_tokens % 64 for pk in (wl.batch.img, wl.batch.seq))
-    if ragged:
-        kernel_names["gemm_dw"] = "gemm4_ragged_k_kernel<true> (dW = X^T.dY, fp32, 256x256x64 tiles, token count no multiple of 64)"
+    kernel_names = {"gemm_fwd": "gemm4_kernel<8, 8, false, true, false, *> (Y = X.W, 256x256x64 tiles; plain, SwiGLU and RoPE epilogues)",
+                    "gemm_dx": "gemm4_kernel<8, 8, false, false, false, *> (dX = dY.W^T, 256x256x64 tiles; plain and SwiGLU-gradient epilogues)",
+                    "gemm_dw": "gemm4_kernel<8, 8, true, true, true, 0> (dW = X^T.dY, fp32, 256x256x64 tiles)"}
     traffic, traffic_note = recorded_traffic(gemm_cls, args.workload)
     # the large-tile kernels stream, per XCD, the 8 A panels and 4 B panels of an 8 x 4 block of 256 x 256 tiles
     # through L2 once: 2 M N K (1 / 2048 + 1 / 1024) bytes fetched per launch (bf16 operands)
