@@ -247,8 +247,8 @@ size_t layer_partial_bytes(const mllm_layer_desc_t& L, int64_t T) {
   int64_t floats = 2 * norm_bwd_workgroups(T, d) * d * norm_bwd_sets(vit ? 0 : 1, fused);
   if (vit) floats += colsum_partial_rows(T) * (d + (fused ? 0 : d) + L.d_ff);
   if (vit || L.has_bias) floats += colsum_partial_rows(T) * nqkv_of(L);
-  if (L.qk_norm)
-    for (int64_t w : {(int64_t)L.n_q_heads * L.head_dim, (int64_t)L.n_kv_heads * L.head_dim}) floats += norm_bwd_workgroups(T, w) * w;
+  if (L.qk_norm)   // these two have no room of their own (they flush what waits when it is full), but each fits alone
+    for (int64_t w : {(int64_t)L.n_q_heads * L.head_dim, (int64_t)L.n_kv_heads * L.head_dim}) floats = std::max(floats, norm_bwd_workgroups(T, w) * w);
   return (size_t)floats * 4;
 }
 
