@@ -218,6 +218,14 @@ mllm_status_t mllm_op_gemm(const void* a, const void* b, void* c, int64_t m, int
                            int a_layout, int b_layout, int out_fp32, int accumulate,
                            const void* bias, const void* residual, void* hip_stream);
 
+/* The form a product takes (host only, no GPU work; exported so that it can be checked which kernel a size
+ * reaches): output tile tile_rows x tile_cols, or 0 x 0 for the general kernel, and into how many parts the
+ * contraction is cut when scratch_bytes of fp32 scratch are at hand (mllm_op_gemm has none: 0; the stage
+ * calls use their workspace). */
+mllm_status_t mllm_gemm_form(int64_t m, int64_t n, int64_t k, int a_layout, int b_layout,
+                             size_t scratch_bytes, int32_t* tile_rows, int32_t* tile_cols,
+                             int32_t* k_parts);
+
 /* The decoder's MLP up-projection with its activation in one pass (the linear operations of the
  * LLM run over the whole packed sequence: Model Profiler, "Throughput Profiling"):
  * pre [M, 2f] = x [M, K] . w_gu [K, 2f] with w_gu = [W_gate | W_up], and

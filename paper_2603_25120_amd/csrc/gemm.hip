@@ -238,9 +238,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
 }
 
 // The tile kernel (gemm_tile.h) takes K a positive multiple of 64, or any K when k runs along the rows of
-// both operands (the weight-gradient layout).
+// both operands (the weight-gradient layout).  There the rows of the last k-tile that lie past K are left to the
+// buffer's range check, which sees their 32-bit byte offsets: an operand so close to 4 GiB that one of them would
+// wrap round to its first rows stays with the general kernel, which compares row numbers.
 bool takes_tile_kernel(const GemmArgs& g) {
-  return g.k > 0 && (g.k % BK == 0 || (g.a_layout != 0 && g.b_layout == 0));
+  if (g.k <= 0) return false;
+  if (g.k % BK == 0) return true;
+  if (g.a_layout == 0 || g.b_layout != 0) return false;
+  const int64_t rows = (g.k + BK - 1) / BK * BK;
+  return rows * g.lda * 2 <= 0xFFFFFFFFll && rows * g.ldb * 2 <= 0xFFFFFFFFll;
 }
 hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
   const int bm = tile == GemmTile::T256 ? 256 : tile == GemmTile::T192 ? 192 : 128, bn = tile == GemmTile::T128 ? 128 : 256;
@@ -349,6 +355,24 @@ bool gemm_rope_fusable(int64_t m, int64_t n, int64_t k, int32_t head_dim) {
   return big_tiles >= 200 && (head_dim == 64 || head_dim == 128) && n % 8 == 0 && k >= BK && k % BK == 0;
 }
 
+namespace {
+// The plan of a product that takes the tile kernel.
+GemmPlan plan_of(const GemmArgs& g) {
+  GemmPlan pl{GemmTile::T256, 1};   // the fused epilogues exist for this tile
+  if (!takes_tile_kernel(g) || g.swiglu_act || g.swiglu_dpre || g.rope_table) return pl;
+  const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
+  pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok);
+  if (pl.splits > 1 && g.splitk_ws_bytes < (size_t)pl.splits * g.m * g.n * 4) pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, false);
+  return pl;
+}
+}  // namespace
+
+GemmForm gemm_form(const GemmArgs& g) {
+  if (!takes_tile_kernel(g)) return {0, 0, 1};
+  const GemmPlan pl = plan_of(g);
+  return {pl.tile == GemmTile::T256 ? 256 : pl.tile == GemmTile::T192 ? 192 : 128, pl.tile == GemmTile::T128 ? 128 : 256, pl.splits};
+}
+
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
   if (g.rope_table && (!g.rope_pos || !gemm_rope_fusable(g.m, g.n, g.k, g.rope_head_dim) || g.a_layout != 0 ||
@@ -369,13 +393,8 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.ldc * (g.out_fp32 ? 4 : 2) * 128 > 0xFFFFFFFFll || (g.residual && g.ldres * 2 * 128 > 0xFFFFFFFFll))
     return hipErrorInvalidValue;
   const int64_t big_tiles = ((g.m + 255) / 256) * ((g.n + 255) / 256);
-  const bool tiled = takes_tile_kernel(g), fused = g.swiglu_act || g.swiglu_dpre || g.rope_table;
-  GemmPlan pl{GemmTile::T256, 1};   // the fused epilogues exist for this tile
-  if (tiled && !fused) {
-    const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
-    pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok);
-    if (pl.splits > 1 && g.splitk_ws_bytes < (size_t)pl.splits * g.m * g.n * 4) pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, false);
-  }
+  const bool tiled = takes_tile_kernel(g);
+  const GemmPlan pl = plan_of(g);
   // timing classes: the three layouts of the large tiles, the 192-row form, and the small tiles
   const bool small = tiled ? pl.tile == GemmTile::T128 : big_tiles < 200;
   const int cls = small ? PROF_GEMM_SMALL : pl.tile == GemmTile::T192 ? PROF_GEMM_ROWS192

@@ -50,6 +50,9 @@ bool gemm_swiglu_fusable(int64_t m, int64_t n, int64_t k);
 // A and B are addressed through 32-bit byte offsets: each operand must stay below this size.
 constexpr int64_t GEMM_MAX_OPERAND_BYTES = 0xFFFFFFF0ll - 16;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
+// What launch_gemm takes for a product: output tile (0 x 0: the general kernel) and parts of the K loop.
+struct GemmForm { int tile_rows, tile_cols, k_parts; };
+GemmForm gemm_form(const GemmArgs& g);
 // Scratch bytes launch_gemm wants for a product of this shape (0: it will not split the K loop); a_t: A stored
 // [K, M].
 size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t);

@@ -163,6 +163,22 @@ mllm_status_t mllm_op_gemm(const void* a, const void* b, void* c, int64_t m, int
   return MLLM_OK;
 }
 
+mllm_status_t mllm_gemm_form(int64_t m, int64_t n, int64_t k, int a_layout, int b_layout, size_t scratch_bytes,
+                             int32_t* tile_rows, int32_t* tile_cols, int32_t* k_parts) {
+  if (m < 0 || n < 0 || k < 0) return op_fail(MLLM_ERR_SHAPE, "negative size");
+  if ((a_layout | b_layout) & ~1) return op_fail(MLLM_ERR_SHAPE, "layouts must be 0 or 1");
+  GemmArgs g{};
+  g.m = m; g.n = n; g.k = k; g.lda = a_layout ? m : k; g.ldb = b_layout ? k : n; g.ldc = n;
+  g.a_layout = a_layout; g.b_layout = b_layout;
+  g.splitk_ws = scratch_bytes ? &g : nullptr;   // only whether there is any
+  g.splitk_ws_bytes = scratch_bytes;
+  const GemmForm f = gemm_form(g);
+  if (tile_rows) *tile_rows = f.tile_rows;
+  if (tile_cols) *tile_cols = f.tile_cols;
+  if (k_parts) *k_parts = f.k_parts;
+  return MLLM_OK;
+}
+
 mllm_status_t mllm_op_gemm_swiglu(const void* x, const void* w_gu, void* pre, void* act, int64_t m,
                                   int64_t f, int64_t k, void* hip_stream) {
   if (!x || !w_gu || !pre || !act) return op_fail(MLLM_ERR_NULL, "a tensor pointer is NULL");

@@ -1,0 +1,42 @@
+"""Which GEMM kernel a product takes (host logic, no GPU), and that the kernel's 32-bit addresses reach it."""
+import pytest
+
+LIMIT = 0xFFFFFFF0 - 16   # bytes of an operand that a product accepts
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_25120_amd import binding
+    binding.lib()
+    return binding
+
+
+def rows_that_wrap(rows, width):
+    """Rows past the end of a [rows, width] bf16 operand that a whole last k-tile of 64 reads at a 32-bit offset
+    which falls into the operand again."""
+    pitch, end = 2 * width, -(-rows // 64) * 64
+    return [r for r in range(rows, end) if (r * pitch + 2 * (width - 8)) % 2 ** 32 < rows * pitch or (r * pitch) % 2 ** 32 < rows * pitch]
+
+
+# widths of both operands; the last ones only one of the two close to 4 GiB
+@pytest.mark.parametrize("m,n", [(3200, 3200), (5120, 5120), (32760, 32760), (28672, 64), (64, 28672)])
+def test_ragged_contraction_near_4_gib_keeps_to_the_kernel_that_compares_rows(B, m, n):
+    most = LIMIT // (2 * max(m, n))
+    seen = set()
+    for k in range(most - 200, most + 1):
+        wraps = bool(rows_that_wrap(k, m) or rows_that_wrap(k, n))
+        tiled = B.mllm_gemm_form(m, n, k, 1, 0)[0] != 0
+        assert not (tiled and wraps), k
+        assert tiled or k % 64, k          # whole k-tiles have no row past the end
+        seen.add((tiled, wraps))
+    assert (True, False) in seen           # further from the limit the tile kernel stays
+
+
+def test_ragged_contraction_examples(B):
+    assert rows_that_wrap(671050, 3200)                        # 247 KB short of 4 GiB
+    assert B.mllm_gemm_form(3200, 3200, 671050, 1, 0) == (0, 0, 1)
+    assert B.mllm_gemm_form(3200, 3200, 671040, 1, 0)[0] != 0    # a multiple of 64
+    assert B.mllm_gemm_form(5120, 5120, 419400, 1, 0) == (0, 0, 1)
+    assert B.mllm_gemm_form(4096, 4096, 777, 1, 0)[0] != 0
+    assert B.mllm_gemm_form(4096, 4096, 776, 0, 0) == (0, 0, 1)  # k along the rows of only one operand
+    assert B.mllm_gemm_form(64, 64, 0, 1, 0) == (0, 0, 1)

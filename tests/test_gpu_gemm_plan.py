@@ -76,3 +76,18 @@ def test_layers_whose_products_split_the_k_loop(B, lengths):
             assert all(torch.equal(x, y) for x, y in zip(got[3], again[3])) and torch.equal(got[0], again[0])
         finally:
             st.close()
+
+
+def test_ragged_contraction_close_to_4_gib(B):
+    """Both operands are 247 KB short of 4 GiB with a partial last k-tile: 32-bit offsets of the rows past
+    K would come round to the first rows, which are the only non-zero ones here besides the last."""
+    k, w, head, tail = 671050, 3200, 64, 10
+    a, b = (torch.zeros(k, w, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ref = 0.0
+    for t, seed in ((a, 341), (b, 342)):
+        rows = W.draw_tensor(seed, head + tail, w)
+        t[:head], t[k - tail:] = dev_bf16(rows[:head]), dev_bf16(rows[head:])
+        ref = rows.T.astype(np.float64) if t is a else ref @ rows.astype(np.float64)
+    c = torch.empty(w, w, dtype=torch.float32, device="cuda")
+    B.mllm_op_gemm(a, b, c, w, w, k, 1, 0, out_fp32=1)
+    assert nmax_err(host_f64(c), ref) < 2e-3
