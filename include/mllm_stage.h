@@ -30,7 +30,8 @@
  *     microbatch it is asked about; mllm_stage_fwd / mllm_stage_bwd allocate pinned host memory
  *     only for a microbatch whose metadata exceed every earlier reservation.
  *   - One handle must not be used from two threads at once.  Same inputs give bitwise-identical
- *     outputs (no atomics in any reduction).
+ *     outputs (no atomics in any reduction); a stage's workspace smaller than mllm_stage_sizes says
+ *     changes the order of some fp32 sums.
  */
 #ifndef MLLM_STAGE_H
 #define MLLM_STAGE_H
@@ -52,7 +53,7 @@ typedef enum {
   MLLM_ERR_CU_SEQLENS = 4,  /* cu_seqlens not starting at 0, decreasing, or wrong total    */
   MLLM_ERR_MASK_KIND = 5,   /* mask kind outside {BIDIR, CAUSAL}                           */
   MLLM_ERR_INDEX = 6,       /* img_to_seq_row out of range or not strictly increasing      */
-  MLLM_ERR_WORKSPACE = 7,   /* saved / workspace buffer smaller than mllm_stage_sizes says */
+  MLLM_ERR_WORKSPACE = 7,   /* saved / workspace buffer too small (mllm_stage_sizes)       */
   MLLM_ERR_UNSUPPORTED = 8, /* valid request that this build does not implement            */
   MLLM_ERR_HIP = 9          /* a HIP call or kernel launch reported an error               */
 } mllm_status_t;
@@ -160,7 +161,11 @@ mllm_status_t mllm_stage_param_info(const mllm_stage_t* stage, size_t i, const c
                                     int32_t* layer, int64_t* rows, int64_t* cols);
 
 /* Bytes of the `saved` buffer (activations kept from forward to backward) and of the scratch
- * `workspace` that fwd and bwd need for this microbatch. */
+ * `workspace` that fwd and bwd want for this microbatch.  Part of the workspace holds partial results of
+ * products that are cut into parts where they alone would leave the GPU idle, and that part does not
+ * grow with the microbatch.  A call runs with less of it (fewer parts, the same sums in another
+ * order), down to nothing; what it cannot do without grows with the tokens, so buffers sized for
+ * the longest microbatch serve every shorter one of the same kind. */
 mllm_status_t mllm_stage_sizes(const mllm_stage_t* stage, const mllm_batch_t* batch,
                                size_t* saved_bytes, size_t* workspace_bytes);
 

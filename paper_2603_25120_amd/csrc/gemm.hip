@@ -306,18 +306,20 @@ struct TileCost {
   int few;                // up to this many, a k-tile costs k_few; from there on k_more, rising to k_full for a full round
   double k_few, k_more, k_full, fixed;
 };
-GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool split_ok) {
+// split_bytes: scratch for the parts; the cheapest plan that fits it.
+GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes) {
   static const TileCost costs[] = {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
                                    {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
                                    {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}};   // two on a CU from 257 on
   const int64_t nk = (k + BK - 1) / BK;
   GemmPlan best{GemmTile::T256, 1};
   if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
+  const int64_t most = std::min<int64_t>(16, std::min<int64_t>(nk / 8, (int64_t)(split_bytes / 4 / ((uint64_t)m * (uint64_t)n))));
+  const int64_t cap = std::max<int64_t>(1, most);   // at least 8 k-tiles a part
   double best_cost = 1e300;
   for (const TileCost& c : costs) {
     if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
-    const int64_t cap = split_ok ? std::max<int64_t>(1, std::min<int64_t>(16, nk / 8)) : 1;   // at least 8 k-tiles a part
     for (int64_t sp = 1; sp <= cap; sp++) {
       const int64_t per = (nk + sp - 1) / sp;
       if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
@@ -336,7 +338,7 @@ GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool split_ok) {
 }  // namespace
 
 size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t) {
-  const GemmPlan pl = plan_gemm(m, n, k, a_t, true);
+  const GemmPlan pl = plan_gemm(m, n, k, a_t, SIZE_MAX);
   return pl.splits > 1 ? (size_t)pl.splits * (size_t)m * (size_t)n * 4 : 0;
 }
 
@@ -358,12 +360,9 @@ bool gemm_rope_fusable(int64_t m, int64_t n, int64_t k, int32_t head_dim) {
 namespace {
 // The plan of a product that takes the tile kernel.
 GemmPlan plan_of(const GemmArgs& g) {
-  GemmPlan pl{GemmTile::T256, 1};   // the fused epilogues exist for this tile
-  if (!takes_tile_kernel(g) || g.swiglu_act || g.swiglu_dpre || g.rope_table) return pl;
+  if (!takes_tile_kernel(g) || g.swiglu_act || g.swiglu_dpre || g.rope_table) return {GemmTile::T256, 1};   // the fused epilogues exist for this tile
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
-  pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok);
-  if (pl.splits > 1 && g.splitk_ws_bytes < (size_t)pl.splits * g.m * g.n * 4) pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, false);
-  return pl;
+  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok ? g.splitk_ws_bytes : 0);
 }
 }  // namespace
 

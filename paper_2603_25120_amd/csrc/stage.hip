@@ -212,8 +212,7 @@ struct Plan {
   // workspace offsets (after the metadata)
   size_t w_partial = 0;           // fp32 partial sums of norm / bias gradients
   size_t partial_bytes = 0;
-  size_t w_a = 0, w_b = 0, w_c = 0, w_d = 0, w_e = 0, w_delta = 0, w_g0 = 0, w_g1 = 0, w_proj = 0, w_split = 0;
-  size_t w_dkv = 0;               // fp32 sums of the parts of a divided dK/dV pass
+  size_t w_a = 0, w_b = 0, w_c = 0, w_d = 0, w_e = 0, w_delta = 0, w_g0 = 0, w_g1 = 0, w_proj = 0;
   size_t w_qkn = 0;               // QK normalisation: gradient of the normalised q, k  [T, nq]
   // Rotary-angle tables [longest sample, head_dim] fp32, one per distinct (rope_base, head_dim) of the
   // decoder layers; rope_of[i] = index of layer i's table (-1: the layer has none).
@@ -221,8 +220,11 @@ struct Plan {
   std::vector<RopeTable> rope_tables;
   std::vector<int> rope_of;
   int64_t longest_seq = 0;
-  size_t split_bytes = 0;
-  size_t workspace_bytes = 0;
+  // fp32 partial results, used by one launch at a time: the parts of a split K loop, or those of a divided
+  // dK/dV pass.  They come last and a call makes do with what the caller's buffer holds of them
+  // (fit_scratch), so that a workspace sized for a longer microbatch serves a shorter one: what the
+  // parts want does not grow with the tokens, everything before them does.
+  size_t w_scratch = 0, scratch_bytes = 0;
   int64_t T_img = 0, T_seq = 0;
   int64_t T_con = 0;              // rows of the connector (T_img, or the pooling windows)
   int pool = 1;
@@ -256,6 +258,9 @@ size_t layer_partial_bytes(const mllm_layer_desc_t& L, int64_t T) {
 size_t linear_split_bytes(int64_t T, int64_t k, int64_t n) {
   return std::max(gemm_splitk_ws_bytes(k, n, T, true), std::max(gemm_splitk_ws_bytes(T, n, k, false), gemm_splitk_ws_bytes(T, k, n, false)));
 }
+
+// Bytes of partial dK and dV that a part of the dK/dV pass takes.
+size_t kv_part_bytes(const AttnLists& A, int64_t T) { return (size_t)2 * (size_t)T * A.hkv * A.head_dim * 4; }
 
 Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   Plan P;
@@ -331,7 +336,7 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
       const mllm_pack_t& pk = img ? b->img : b->seq;
       A.kv_parts = attn_kv_parts_of(pk, A.hkv, A.hq / A.hkv, A.head_dim);
       if (A.kv_parts > 1)
-        dkv = std::max(dkv, (size_t)A.kv_parts * 2 * (size_t)pk.total_tokens * A.hkv * A.head_dim * 4);
+        dkv = std::max(dkv, A.kv_parts * kv_part_bytes(A, pk.total_tokens));
       ws.take(attn_list_bytes(pk, ATTN_FWD_Q_TILE, L.n_q_heads));
       ws.take(attn_list_bytes(pk, ATTN_BWD_KV_TILE, L.n_kv_heads));
       found = (int)M.attn.size();
@@ -401,8 +406,6 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
       P.rope_of[i] = found;
     }
   }
-  P.split_bytes = split;
-  P.w_split = ws.take(split);
   // The sums of one layer at least; several layers' together while that is small.
   P.partial_bytes = std::min(part_all, std::max(part, (size_t)32 << 20));
   P.w_partial = ws.take(P.partial_bytes);
@@ -413,12 +416,21 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   P.w_e = ws.take(e);
   P.w_qkn = ws.take(qkn);
   P.w_delta = ws.take(delta);
-  P.w_dkv = ws.take(dkv);
   P.w_g0 = ws.take(g);
   P.w_g1 = ws.take(g);
   P.w_proj = ws.take(proj);
-  P.workspace_bytes = std::max<size_t>(ws.off, ALIGN);
+  P.w_scratch = std::max<size_t>(ws.off, ALIGN);
+  P.scratch_bytes = align_up(std::max(split, dkv));
   return P;
+}
+
+// The partial results a workspace of this size has room for (check_io has seen to the rest).
+void fit_scratch(Plan& P, size_t workspace_bytes) {
+  P.scratch_bytes = std::min(P.scratch_bytes, workspace_bytes - P.w_scratch);
+  for (AttnLists& A : P.meta.attn) {
+    const size_t part = kv_part_bytes(A, A.img ? P.T_img : P.T_seq);
+    if (part) A.kv_parts = std::max(1, (int)std::min<size_t>(A.kv_parts, P.scratch_bytes / part));
+  }
 }
 
 // -------------------------------------------------------------------------------------------
@@ -554,7 +566,7 @@ AttnArgs attn_args(const mllm_layer_desc_t& L, char* qk, char* v, int64_t T, con
   a.q_grid = A.q_grid;
   a.kv_grid = A.kv_grid;
   a.kv_parts = A.kv_parts;
-  a.dkv_partial = (float*)const_cast<char*>(ws + P.w_dkv);
+  a.dkv_partial = (float*)const_cast<char*>(ws + P.w_scratch);
   a.pos = img ? nullptr : (const int32_t*)(ws + P.meta.pos);
   a.fwd_flops = 4.0 * (img ? P.img_pairs : P.seq_pairs) * L.n_q_heads * L.head_dim;
   return a;
@@ -576,7 +588,7 @@ mllm_status_t layer_fwd(const mllm_layer_desc_t& L, const void* const* prm, cons
                         int attn_list, hipStream_t s) {
   const bool vit = L.kind == MLLM_LAYER_VIT;
   const int64_t d = L.d_model, f = L.d_ff, nq = nqkv_of(L);
-  const SplitWs split{ws + P.w_split, P.split_bytes};
+  const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
   char* x = saved + S.x;
   char* n1 = saved + S.n1;
   char* qkv = saved + S.qkv;
@@ -648,7 +660,7 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   const char* n2 = saved + S.n2;
   const char* pre = saved + S.pre;
   const char* act = saved + S.act;
-  const SplitWs split{ws + P.w_split, P.split_bytes};
+  const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
   char* wa = ws + P.w_a;      // d act            [T, f]
   char* wb = ws + P.w_b;      // d (gate|up)      [T, 2f]  (decoder)
   char* wc = ws + P.w_c;      // d n2 / d o / d n1 [T, d]
@@ -733,7 +745,7 @@ mllm_status_t check_io(const mllm_stage* st, const mllm_batch_t* b, const void* 
   if (!saved || !workspace) return fail(MLLM_ERR_NULL, "saved or workspace is NULL");
   if (((uintptr_t)saved | (uintptr_t)workspace) % ALIGN) return fail(MLLM_ERR_WORKSPACE, "saved and workspace must be 256-byte aligned");
   if (saved_bytes < P.saved_bytes) return fail(MLLM_ERR_WORKSPACE, "saved buffer has %zu bytes, %zu needed", saved_bytes, P.saved_bytes);
-  if (workspace_bytes < P.workspace_bytes) return fail(MLLM_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, P.workspace_bytes);
+  if (workspace_bytes < P.w_scratch) return fail(MLLM_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, P.w_scratch);
   (void)b;
   return MLLM_OK;
 }
@@ -836,7 +848,7 @@ mllm_status_t mllm_stage_sizes(const mllm_stage_t* st, const mllm_batch_t* b, si
   // grow the slot they take if they must and report the error then.
   if (P.meta.bytes && st->staging.reserve(P.meta.bytes) != hipSuccess) (void)hipGetLastError();
   if (saved_bytes) *saved_bytes = P.saved_bytes;
-  if (workspace_bytes) *workspace_bytes = P.workspace_bytes;
+  if (workspace_bytes) *workspace_bytes = P.w_scratch + P.scratch_bytes;
   return MLLM_OK;
 }
 
@@ -849,6 +861,7 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
   Plan P = make_plan(st, b);
   if ((r = check_plan(P)) != MLLM_OK) return r;
   if ((r = check_io(st, b, params, P, saved_bytes, workspace_bytes, saved_v, workspace)) != MLLM_OK) return r;
+  fit_scratch(P, workspace_bytes);
   const bool need_img = st->n_vit > 0 || st->proj >= 0;
   const bool need_seq = st->n_dec > 0 || st->proj >= 0;
   if (need_img && P.T_img > 0 && !x_img) return fail(MLLM_ERR_NULL, "x_img is NULL");
@@ -872,7 +885,7 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
       if (i == 0) K_TRY(launch_copy(x_img, saved + P.saved[i].x, (size_t)P.T_img * L.d_model * 2, s));
       void* dst = last ? y : (void*)(saved + P.saved[i + 1].x);
       K_TRY(launch_copy(x_seq, dst, (size_t)P.T_seq * L.d_out * 2, s));
-      const SplitWs split{ws + P.w_split, P.split_bytes};
+      const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
       const char* xin = saved + P.saved[i].x;
       // token merging: the [T_img, d] rows read as [T_img / r, r d] rows (no data movement)
       const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
@@ -912,6 +925,7 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
   Plan P = make_plan(st, b);
   if ((r = check_plan(P)) != MLLM_OK) return r;
   if ((r = check_io(st, b, params, P, saved_bytes, workspace_bytes, saved_v, workspace)) != MLLM_OK) return r;
+  fit_scratch(P, workspace_bytes);
   if (!dy) return fail(MLLM_ERR_NULL, "dy is NULL");
   if (!dparams) return fail(MLLM_ERR_NULL, "dparams is NULL");
   for (size_t i = 0; i < st->params.size(); i++)
@@ -941,7 +955,7 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
         K_TRY(launch_copy(cur, dx_seq, (size_t)P.T_seq * L.d_out * 2, s));
         K_TRY(launch_zero_rows(dx_seq, i2s, P.T_con, L.d_out, s));
       }
-      const SplitWs split{ws + P.w_split, P.split_bytes};
+      const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
       void* out = (i == 0 && dx_img) ? dx_img : (void*)pp[flip];
       const char* xin = P.pool > 1 ? saved + P.saved[i].n1 : saved + P.saved[i].x;
       const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
