@@ -1,5 +1,5 @@
 // Pieces shared by the GEMM kernels: launch parameters, buffer resources, the XCD-aware tile
-// order and the LDS-staged epilogue.
+// order and the LDS-staged epilogues.
 #pragma once
 #include <type_traits>
 
@@ -11,6 +11,7 @@ namespace mllm {
 constexpr int BK = 64;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t OOB = 0xFFFFFFFFu;  // byte offset beyond any buffer these kernels accept (< 4 GiB - 16)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
@@ -203,44 +204,29 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM
 }
 
 // ---------------------------------------------------------------------------------------------
-// Epilogues of the large-tile kernels, straight from the accumulators.  The MFMAs (16x16x32) are
-// issued with the operands swapped, so an accumulator block holds C transposed: lane l owns row
-// l%16 of the block and columns 4*(l/16) .. +3.  In bf16 that is 8 bytes a lane and block; one
-// v_permlane16_swap per 32-bit word of a pair of neighbouring blocks exchanges the odd 16-lane rows
-// of the left block with the even ones of the right block, after which every lane holds eight
-// consecutive columns (block of the pair: (l/16)%2, columns 8*(l/32) .. +7) and the pair leaves in one
-// 16-byte store, 64 contiguous bytes a row.  The swap is its own inverse: bf16 operands of the
-// epilogue (residual, gate, up) come in as 16-byte chunks and are swapped into the accumulators'
-// layout.  Nothing passes through LDS and no barrier is needed.
+// Epilogues of the tile kernel.  The MFMAs (16x16x32) are issued with the operands swapped, so an accumulator
+// block holds C transposed: lane l owns row l%16 of the block and columns 4*(l/16) .. +3.  Stored like that,
+// consecutive lanes write 16 bytes to 16 different rows, and the memory pipeline takes such a store apart: fp32
+// tiles of 256 x 256, one per CU (1024 x 12800), leave in 12.0 us that way and in 9.4 when every four lanes write 64
+// contiguous bytes (permuting half rows so that a store covers 8 rows of 128 bytes, lanes still in row order: 12.0).  So
+// a row of blocks at a time passes through the wavefront's own part of the LDS that the tiles have left (`stage`,
+// two buffers, no barrier: a wavefront's LDS accesses execute in order) and leaves in row order, 16 bytes a lane, 128 to 512
+// contiguous bytes a row; bf16 operands of the epilogue (residual, gate, up) come in in the same order.  What needs
+// nothing added is staged already rounded.  The padding of 4 words puts the 16 rows on different banks.  Whole products,
+// stores from the accumulators -> staged: 5120 x 11008 x 100 weight gradient 53 -> 44 us, 1024 x 12800 x 480 24.4 -> 21.9;
+// forward 7488 x 4096 x 1024 64.8 -> 61.6, 2880 x 4096 x 1024 26.6 -> 25.3.
 // Addresses: a buffer over the wavefront's rows of the matrix that starts at the sub-tile's first
 // element (rows past the matrix are past its end and dropped by the range check; the host keeps 128
 // row pitches below 4 GiB); chunks past the last column get an offset that is never in range.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ void swap_rows16(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-// Four bf16 columns of two neighbouring blocks (x: left, y: right) <-> the lane's 16-byte chunk.
-struct PairChunk { uint32_t x0, x1, y0, y1; };
-__device__ __forceinline__ u32x4 to_chunk(PairChunk c) {
-  swap_rows16(c.x0, c.y0);
-  swap_rows16(c.x1, c.y1);
-  return u32x4{c.x0, c.x1, c.y0, c.y1};
-}
-__device__ __forceinline__ PairChunk from_chunk(u32x4 v) {
-  PairChunk c{v[0], v[1], v[2], v[3]};
-  swap_rows16(c.x0, c.y0);
-  swap_rows16(c.x1, c.y1);
+// Sixteen bytes of a staged row.  Kept out of the accumulation registers, where the allocator would put it and move
+// accumulators out of its way.
+__device__ __forceinline__ u32x4 staged_chunk(const uint32_t* src) {
+  u32x4 c = *reinterpret_cast<const u32x4*>(src);
+  asm volatile("" : "+v"(c));
   return c;
 }
-__device__ __forceinline__ PairChunk pack_pair(const f32x4& l, const f32x4& r) {
-  return {pack_bf16x2(l[0], l[1]), pack_bf16x2(l[2], l[3]), pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])};
-}
-__device__ __forceinline__ void unpack_pair(const PairChunk& c, f32x4& l, f32x4& r) {
-  l = f32x4{bf16lo(c.x0), bf16hi(c.x0), bf16lo(c.x1), bf16hi(c.x1)};
-  r = f32x4{bf16lo(c.y0), bf16hi(c.y0), bf16lo(c.y1), bf16hi(c.y1)};
-}
+__device__ __forceinline__ u32x2 pack4(const f32x4& v) { return u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}; }
 // Rows [0, rows_left) of a matrix from `first` on (row pitch in bytes); rows_left <= 0: empty.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_buffer(const void* first, int rows_left, uint32_t pitch) {
   return make_rsrc(first, rows_left > 0 ? (uint32_t)rows_left * pitch : 0u);
@@ -274,21 +260,26 @@ __device__ __forceinline__ void rope_rotate_row(f32x4 (&v)[WN], const float* tro
 
 // C (+)= acc (+ bias, then rotated) (+ residual): WM x WN blocks of 16 x 16 from (row0, col0).  ROPE_HD:
 // head width of the rotary positions, 0 for none; sub-tiles past rope_cols (the v columns) are not rotated.
-// One row of blocks at a time; what a call does not have is decided once, in front of the rows.
+// What a call does not have is decided once, in front of the rows.
 template <int WM, int WN, bool OUT_F32, int ROPE_HD = 0>
-__device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane) {
+__device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane,
+                                             uint32_t* stage) {
   constexpr int ESIZE = OUT_F32 ? 4 : 2;
+  constexpr int LPR = WN * ESIZE, RPS = 64 / LPR, NS = 16 / RPS;   // a row's lanes, rows of a store, stores of a row of blocks
   const int g = lane >> 4, r = lane & 15;
   const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
   const int cols_left = (int)max((int64_t)0, min((int64_t)(16 * WN), p.N - col0));
   const uint32_t pitch = (uint32_t)(p.ldc * ESIZE);
   const __amdgpu_buffer_rsrc_t rc = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + col0) * ESIZE, rows_left, pitch);
-  const int lc = OUT_F32 ? 4 * g : 16 * (g & 1) + 8 * (g >> 1);   // the lane's columns inside a block / a pair of blocks
-  const uint32_t lane_off = (uint32_t)r * pitch + (uint32_t)(ESIZE * lc);
-  const uint32_t rpitch = (uint32_t)(p.ldres * 2), rlane_off = (uint32_t)r * rpitch + (uint32_t)(2 * lc);
+  const int srow = lane / LPR, scol = lane % LPR * (16 / ESIZE);    // the lane's row and columns in a store
+  const uint32_t past = scol < cols_left ? 0u : OOB;                // past the last column: an offset that is never in range
+  const uint32_t lane_off = (uint32_t)srow * pitch + (uint32_t)(ESIZE * scol);
+  const uint32_t rpitch = (uint32_t)(p.ldres * 2), rlane_off = (uint32_t)srow * rpitch + (uint32_t)(2 * scol);
   const __amdgpu_buffer_rsrc_t rr = rows_buffer(p.res + row0 * p.ldres + col0, !OUT_F32 && p.res ? rows_left : 0, rpitch);
   auto rows = [&](auto bias_c, auto add_c, auto rope_c) __attribute__((always_inline)) {
     constexpr bool BIAS = decltype(bias_c)::value, ADD = decltype(add_c)::value, ROPE = decltype(rope_c)::value;
+    constexpr bool WIDE = OUT_F32 || ADD;                            // staged in fp32, otherwise already rounded
+    constexpr int PITCH = (WIDE ? 16 : 8) * WN + 4;                  // 32-bit words of a staged row
     f32x4 bias[BIAS ? WN : 1];
     if constexpr (BIAS) {
 #pragma unroll
@@ -299,14 +290,11 @@ __device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&
       }
     }
     // what is added to C's chunks (the residual, or C itself when accumulating), a row of blocks ahead
-    constexpr int NCH = OUT_F32 ? WN : WN / 2, CHUNK = OUT_F32 ? 16 : 32;   // chunks per row of blocks, their columns
-    u32x4 add[2][ADD ? NCH : 1];
-    auto offset = [&](int i, int q, uint32_t lo, uint32_t pt) {
-      return (int)(CHUNK * q + lc < cols_left ? lo + (uint32_t)(16 * i) * pt + 64 * q : OOB);
-    };
+    u32x4 add[2][ADD ? NS : 1];
+    auto offset = [&](int i, int q, uint32_t lo, uint32_t pt) { return (int)((lo + (uint32_t)(16 * i + RPS * q) * pt) | past); };
     auto fetch = [&](int i) {
 #pragma unroll
-      for (int q = 0; q < NCH; q++)
+      for (int q = 0; q < NS; q++)
         add[i & 1][q] = OUT_F32 ? __builtin_amdgcn_raw_buffer_load_b128(rc, offset(i, q, lane_off, pitch), 0, 0)
                                 : __builtin_amdgcn_raw_buffer_load_b128(rr, offset(i, q, rlane_off, rpitch), 0, 0);
     };
@@ -316,11 +304,12 @@ __device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&
       if constexpr (ADD) {
         if (i + 1 < WM) fetch(i + 1);
       }
+      uint32_t* const st = stage + (i & 1) * 16 * PITCH;
       f32x4 v[WN];
 #pragma unroll
       for (int j = 0; j < WN; j++) {
         v[j] = acc[i][j];
-        if constexpr (OUT_F32) asm volatile("" : "+v"(v[j]));
+        asm volatile("" : "+v"(v[j]));
         if constexpr (BIAS) {
 #pragma unroll
           for (int e = 0; e < 4; e++) v[j][e] += bias[j][e];
@@ -332,24 +321,30 @@ __device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&
         rope_rotate_row<WN, ROPE_HD>(v, p.rope_table + (int64_t)pos * ROPE_HD, g);
       }
 #pragma unroll
-      for (int q = 0; q < NCH; q++) {
-        if constexpr (OUT_F32) {
-          if constexpr (ADD) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[q][e] += __uint_as_float(add[i & 1][q][e]);
-          }
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[q]), rc, offset(i, q, lane_off, pitch), 0, 0);
-        } else {
-          f32x4 l = v[2 * q], h = v[2 * q + 1];
-          if constexpr (ADD) {
-            f32x4 a, b;
-            unpack_pair(from_chunk(add[i & 1][q]), a, b);
-#pragma unroll
-            for (int e = 0; e < 4; e++) { l[e] += a[e]; h[e] += b[e]; }
-          }
-          __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(l, h)), rc, offset(i, q, lane_off, pitch), 0, 0);
-        }
+      for (int j = 0; j < WN; j++) {
+        if constexpr (WIDE) *reinterpret_cast<u32x4*>(st + r * PITCH + 16 * j + 4 * g) = __builtin_bit_cast(u32x4, v[j]);
+        else *reinterpret_cast<u32x2*>(st + r * PITCH + 8 * j + 2 * g) = pack4(v[j]);
       }
+      asm volatile("" ::: "memory");   // a wavefront's own LDS accesses execute in order
+#pragma unroll
+      for (int q = 0; q < NS; q++) {
+        const uint32_t* src = st + (srow + RPS * q) * PITCH + (WIDE ? scol : scol / 2);
+        u32x4 c = staged_chunk(src);
+        if constexpr (OUT_F32 && ADD) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) c[e] = __float_as_uint(__uint_as_float(c[e]) + __uint_as_float(add[i & 1][q][e]));
+        }
+        if constexpr (!OUT_F32 && ADD) {
+          const u32x4 d = staged_chunk(src + 4), x = add[i & 1][q];
+          const uint32_t w0 = pack_bf16x2(__uint_as_float(c[0]) + bf16lo(x[0]), __uint_as_float(c[1]) + bf16hi(x[0]));
+          const uint32_t w1 = pack_bf16x2(__uint_as_float(c[2]) + bf16lo(x[1]), __uint_as_float(c[3]) + bf16hi(x[1]));
+          const uint32_t w2 = pack_bf16x2(__uint_as_float(d[0]) + bf16lo(x[2]), __uint_as_float(d[1]) + bf16hi(x[2]));
+          const uint32_t w3 = pack_bf16x2(__uint_as_float(d[2]) + bf16lo(x[3]), __uint_as_float(d[3]) + bf16hi(x[3]));
+          c = u32x4{w0, w1, w2, w3};
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(c, rc, offset(i, q, lane_off, pitch), 0, 0);
+      }
+      asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -371,32 +366,43 @@ __device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x4 (&
 // ([M, N], up at column N / 2 + gcol) and silu(gate) * up, from the fp32 accumulators, into act
 // ([M, N / 2]).  The sub-tile's columns all exist (N / 2 is a multiple of the tile's gate columns).
 template <int WM, int WN>
-__device__ __forceinline__ void store_blocks_swiglu(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t gcol0, int lane) {
-  const int g = lane >> 4, r = lane & 15, lc = 16 * (g & 1) + 8 * (g >> 1);
+__device__ __forceinline__ void store_blocks_swiglu(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t gcol0, int lane,
+                                                    uint32_t* stage) {
+  constexpr int LPR = WN, RPS = 64 / LPR, NS = 16 / RPS;   // a row's lanes (8 columns each), rows of a store, stores of a row of blocks
+  constexpr int PART = 4 * WN, PITCH = 3 * PART + 4;       // staged row: gate, up, act, rounded to bf16
+  const int g = lane >> 4, r = lane & 15, srow = lane / LPR, scol = lane % LPR * 8;
   const int64_t half = p.N >> 1;
   const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
   const uint32_t c_pitch = (uint32_t)(p.ldc * 2), a_pitch = (uint32_t)(half * 2);
   const __amdgpu_buffer_rsrc_t rg = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + gcol0) * 2, rows_left, c_pitch);
   const __amdgpu_buffer_rsrc_t ru = rows_buffer(reinterpret_cast<const char*>(p.c) + (row0 * p.ldc + half + gcol0) * 2, rows_left, c_pitch);
   const __amdgpu_buffer_rsrc_t ra = rows_buffer(p.act + row0 * half + gcol0, rows_left, a_pitch);
-  const uint32_t c_lane = (uint32_t)r * c_pitch + (uint32_t)(2 * lc), a_lane = (uint32_t)r * a_pitch + (uint32_t)(2 * lc);
+  const uint32_t c_lane = (uint32_t)srow * c_pitch + (uint32_t)(2 * scol), a_lane = (uint32_t)srow * a_pitch + (uint32_t)(2 * scol);
 #pragma unroll
   for (int i = 0; i < WM; i++) {
-    const uint32_t co = c_lane + (uint32_t)(16 * i) * c_pitch, ao = a_lane + (uint32_t)(16 * i) * a_pitch;
+    uint32_t* const st = stage + (i & 1) * 16 * PITCH;
 #pragma unroll
-    for (int jp = 0; jp < WN / 4; jp++) {
-      f32x4 a[2];
+    for (int j = 0; j < WN / 2; j++) {
+      f32x4 gt = acc[i][j], up = acc[i][WN / 2 + j], a;
 #pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const f32x4 gt = acc[i][2 * jp + q], up = acc[i][WN / 2 + 2 * jp + q];
-#pragma unroll
-        for (int e = 0; e < 4; e++)   // silu through the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
-          a[q][e] = gt[e] * up[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[e] * -1.44269504088896340736f));
-      }
-      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(acc[i][2 * jp], acc[i][2 * jp + 1])), rg, (int)(co + 64 * jp), 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(acc[i][WN / 2 + 2 * jp], acc[i][WN / 2 + 2 * jp + 1])), ru, (int)(co + 64 * jp), 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(a[0], a[1])), ra, (int)(ao + 64 * jp), 0, 0);
+      for (int e = 0; e < 4; e++)   // silu through the hardware exp2 and reciprocal (1 ulp each; the result is rounded to bf16)
+        a[e] = gt[e] * up[e] * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[e] * -1.44269504088896340736f));
+      uint32_t* const w = st + r * PITCH + 8 * j + 2 * g;
+      *reinterpret_cast<u32x2*>(w) = pack4(gt);
+      *reinterpret_cast<u32x2*>(w + PART) = pack4(up);
+      *reinterpret_cast<u32x2*>(w + 2 * PART) = pack4(a);
     }
+    asm volatile("" ::: "memory");   // a wavefront's own LDS accesses execute in order
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+      const uint32_t* src = st + (srow + RPS * q) * PITCH + scol / 2;
+      const uint32_t row = (uint32_t)(16 * i + RPS * q);
+      __builtin_amdgcn_raw_buffer_store_b128(staged_chunk(src), rg, (int)(c_lane + row * c_pitch), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(staged_chunk(src + PART), ru, (int)(c_lane + row * c_pitch), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(staged_chunk(src + 2 * PART), ra, (int)(a_lane + row * a_pitch), 0, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -406,46 +412,65 @@ __device__ __forceinline__ void store_blocks_swiglu(const GemmParams& p, f32x4 (
 //   d gate = dA * up * s * (1 + gate * (1 - s)),  d up = dA * gate * s,  s = sigmoid(gate)
 // to dpre = [d gate | d up] ([M, 2N]).
 template <int WM, int WN>
-__device__ __forceinline__ void store_blocks_swiglu_bwd(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane) {
-  const int g = lane >> 4, r = lane & 15, lc = 16 * (g & 1) + 8 * (g >> 1);
+__device__ __forceinline__ void store_blocks_swiglu_bwd(const GemmParams& p, f32x4 (&acc)[WM][WN], int64_t row0, int64_t col0, int lane,
+                                                        uint32_t* stage) {
+  constexpr int LPR = 2 * WN, RPS = 64 / LPR, NS = 16 / RPS, PITCH = 16 * WN + 4;   // staged row: dA in fp32
+  const int g = lane >> 4, r = lane & 15, srow = lane / LPR, scol = lane % LPR * 8;
   const int rows_left = (int)max((int64_t)0, min((int64_t)(16 * WM), p.M - row0));
   const int cols_left = (int)max((int64_t)0, min((int64_t)(16 * WN), p.N - col0));
+  const uint32_t past = scol < cols_left ? 0u : OOB;
   const uint32_t pitch = (uint32_t)(p.N * 4);   // bytes: a row of [M, 2N] bf16
   const int64_t at = row0 * 2 * p.N + col0;
   const __amdgpu_buffer_rsrc_t rg = rows_buffer(p.pre + at, rows_left, pitch), ru = rows_buffer(p.pre + at + p.N, rows_left, pitch);
   const __amdgpu_buffer_rsrc_t wg = rows_buffer(p.dpre + at, rows_left, pitch), wu = rows_buffer(p.dpre + at + p.N, rows_left, pitch);
-  const uint32_t lane_off = (uint32_t)r * pitch + (uint32_t)(2 * lc);
-  auto offset = [&](int i, int jp) { return (int)(32 * jp + lc < cols_left ? lane_off + (uint32_t)(16 * i) * pitch + 64 * jp : OOB); };
-  u32x4 gq[2][WN / 2], uq[2][WN / 2];
+  const uint32_t lane_off = (uint32_t)srow * pitch + (uint32_t)(2 * scol);
+  auto offset = [&](int i, int q) { return (int)((lane_off + (uint32_t)(16 * i + RPS * q) * pitch) | past); };
+  u32x4 gq[2][NS], uq[2][NS];
   auto fetch = [&](int i) {
 #pragma unroll
-    for (int jp = 0; jp < WN / 2; jp++) {
-      gq[i & 1][jp] = __builtin_amdgcn_raw_buffer_load_b128(rg, offset(i, jp), 0, 0);
-      uq[i & 1][jp] = __builtin_amdgcn_raw_buffer_load_b128(ru, offset(i, jp), 0, 0);
+    for (int q = 0; q < NS; q++) {
+      gq[i & 1][q] = __builtin_amdgcn_raw_buffer_load_b128(rg, offset(i, q), 0, 0);
+      uq[i & 1][q] = __builtin_amdgcn_raw_buffer_load_b128(ru, offset(i, q), 0, 0);
     }
   };
   fetch(0);
 #pragma unroll
   for (int i = 0; i < WM; i++) {
     if (i + 1 < WM) fetch(i + 1);
+    uint32_t* const st = stage + (i & 1) * 16 * PITCH;
 #pragma unroll
-    for (int jp = 0; jp < WN / 2; jp++) {
-      f32x4 gt[2], up[2], og[2], ou[2];
-      unpack_pair(from_chunk(gq[i & 1][jp]), gt[0], gt[1]);
-      unpack_pair(from_chunk(uq[i & 1][jp]), up[0], up[1]);
-#pragma unroll
-      for (int q = 0; q < 2; q++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const float d = acc[i][2 * jp + q][e];
-          const float s = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[q][e] * -1.44269504088896340736f));
-          const float gs = gt[q][e] * s;
-          og[q][e] = d * up[q][e] * (s + gs * (1.f - s));
-          ou[q][e] = d * gs;
-        }
-      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(og[0], og[1])), wg, offset(i, jp), 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b128(to_chunk(pack_pair(ou[0], ou[1])), wu, offset(i, jp), 0, 0);
+    for (int j = 0; j < WN; j++) {
+      f32x4 v = acc[i][j];
+      asm volatile("" : "+v"(v));
+      *reinterpret_cast<u32x4*>(st + r * PITCH + 16 * j + 4 * g) = __builtin_bit_cast(u32x4, v);
     }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+      const uint32_t* src = st + (srow + RPS * q) * PITCH + scol;
+      const u32x4 d[2] = {staged_chunk(src), staged_chunk(src + 4)};
+      u32x4 og, ou;
+#pragma unroll
+      for (int w = 0; w < 4; w++) {
+        const uint32_t gw = gq[i & 1][q][w], uw = uq[i & 1][q][w];
+        const float gt[2] = {bf16lo(gw), bf16hi(gw)}, up[2] = {bf16lo(uw), bf16hi(uw)};
+        float dg[2], du[2];
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          const float da = __uint_as_float(d[w >> 1][2 * (w & 1) + e]);
+          const float s = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(gt[e] * -1.44269504088896340736f));
+          const float gs = gt[e] * s;
+          dg[e] = da * up[e] * (s + gs * (1.f - s));
+          du[e] = da * gs;
+        }
+        og[w] = pack_bf16x2(dg[0], dg[1]);
+        ou[w] = pack_bf16x2(du[0], du[1]);
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(og, wg, offset(i, q), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(ou, wu, offset(i, q), 0, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 

@@ -334,23 +334,31 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
     iteration(C1{}, kt + 1);
   }
   if (nk & 1) iteration(C0{}, nk - 1);
-  // the loads enqueued last (tiles past the end: zeros) must have landed before this workgroup's LDS
-  // can be handed to another one
-  if constexpr (DIRECT) __builtin_amdgcn_s_waitcnt(0x0F70);
+  // The epilogue stages its rows where the tiles were: whatever is still on its way there (tiles past the end,
+  // zeros) has to land first, of every wavefront.
+  if constexpr (DIRECT) __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+  else __builtin_amdgcn_s_waitcnt(0xC07F);                    // lgkmcnt(0)
   mfma_results_ready();
+  // the epilogue's addresses depend on the lane alone; hidden from the loop, they take none of its registers
+  int lane_out = lane;
+  asm volatile("" : "+v"(lane_out));
 #pragma unroll
   for (int i = 0; i < WM; i++)
 #pragma unroll
     for (int j = 0; j < WN; j++) asm volatile("" : "+a"(acc[i][j]));   // no read above the wait
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  uint32_t* const out_stage = reinterpret_cast<uint32_t*>(wave == 0 ? As0 : wave == 1 ? As1 : wave == 2 ? Bs0 : Bs1);
+  static_assert(2 * 16 * (16 * WN + 4) * 4 <= 2 * (TA::SIZE < TB::SIZE ? TA::SIZE : TB::SIZE), "two staged rows of blocks in a tile's LDS");
 
   const int64_t row0 = m0 + wm * 16 * WM, col0 = n0 + wn * 16 * WN;
   if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + blockIdx.y * p.c_split_stride;
   if constexpr (EPI == EPI_SWIGLU) {
-    store_blocks_swiglu<WM, WN>(p, acc, row0, (n0 >> 1) + 8 * WN * wn, lane);
+    store_blocks_swiglu<WM, WN>(p, acc, row0, (n0 >> 1) + 8 * WN * wn, lane_out, out_stage);
   } else if constexpr (EPI == EPI_SWIGLU_BWD) {
-    store_blocks_swiglu_bwd<WM, WN>(p, acc, row0, col0, lane);
+    store_blocks_swiglu_bwd<WM, WN>(p, acc, row0, col0, lane_out, out_stage);
   } else {
-    store_blocks<WM, WN, OUT_F32, EPI == EPI_ROPE128 ? 128 : EPI == EPI_ROPE64 ? 64 : 0>(p, acc, row0, col0, lane);
+    store_blocks<WM, WN, OUT_F32, EPI == EPI_ROPE128 ? 128 : EPI == EPI_ROPE64 ? 64 : 0>(p, acc, row0, col0, lane_out, out_stage);
   }
 }
 
