@@ -186,17 +186,21 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
 // slice sums are added pairwise (s with s+64, then s with s+32, ...): a fixed association, so the result is
 // bitwise reproducible.
 constexpr int RED_COLS = 8, RED_SLICES = 128;
+// JOBS: room in the list, which travels as the kernel's argument.  A list of 32 costs each workgroup a walk over 32
+// entries before it knows its job, 0.7 us of a launch of 2-5; one norm or bias (at most 3 jobs) takes the short form.
+template <int JOBS>
 struct ReduceList {
-  const float* partial[PartialSums::MAX_JOBS];
-  float* out[PartialSums::MAX_JOBS];
-  int rows[PartialSums::MAX_JOBS], n[PartialSums::MAX_JOBS];
-  unsigned first[PartialSums::MAX_JOBS];   // first workgroup of a job; past the list: never reached
+  const float* partial[JOBS];
+  float* out[JOBS];
+  int rows[JOBS], n[JOBS];
+  unsigned first[JOBS];   // first workgroup of a job; past the list: never reached
 };
-__global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceList list, int accumulate) {
+template <int JOBS>
+__global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceList<JOBS> list, int accumulate) {
   __shared__ float4 part[RED_SLICES][RED_COLS / 4];
   int job = 0;
 #pragma unroll
-  for (int j = 1; j < PartialSums::MAX_JOBS; j++) job += blockIdx.x >= list.first[j] ? 1 : 0;
+  for (int j = 1; j < JOBS; j++) job += blockIdx.x >= list.first[j] ? 1 : 0;
   const float* __restrict__ partial = list.partial[job];
   float* __restrict__ out = list.out[job];
   const int P = list.rows[job];
@@ -737,10 +741,12 @@ hipError_t PartialSums::take(int64_t rows, int64_t n, std::initializer_list<floa
   return hipSuccess;
 }
 
-hipError_t PartialSums::flush(hipStream_t s) {
-  ReduceList list;
+namespace {
+template <int JOBS>
+hipError_t launch_reduce(const PartialSums::Job* jobs, int count, int accumulate, hipStream_t s) {
+  ReduceList<JOBS> list;
   unsigned blocks = 0;
-  for (int j = 0; j < MAX_JOBS; j++) {
+  for (int j = 0; j < JOBS; j++) {
     const bool there = j < count;
     list.partial[j] = there ? jobs[j].partial : nullptr;
     list.out[j] = there ? jobs[j].out : nullptr;
@@ -749,12 +755,18 @@ hipError_t PartialSums::flush(hipStream_t s) {
     list.first[j] = there ? blocks : ~0u;
     if (there) blocks += blocks_for(jobs[j].n, RED_COLS);
   }
-  count = 0;
-  used = 0;
   if (blocks == 0) return hipSuccess;
   ProfScope prof(PROF_ELEMENTWISE, 0.0, s);   // the bytes of a sum are counted with its first stage
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks), dim3(256), 0, s, list, accumulate);
+  hipLaunchKernelGGL(reduce_partials_kernel<JOBS>, dim3(blocks), dim3(256), 0, s, list, accumulate);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t PartialSums::flush(hipStream_t s) {
+  const int waiting = count;
+  count = 0;
+  used = 0;
+  return waiting <= 3 ? launch_reduce<3>(jobs, waiting, accumulate, s) : launch_reduce<MAX_JOBS>(jobs, waiting, accumulate, s);
 }
 
 // Workgroups (= rows of partial sums) of the norm backward.  The wavefront-per-row kernel with two vectors per lane
