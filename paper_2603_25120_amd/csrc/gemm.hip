@@ -290,14 +290,15 @@ hipError_t launch_general(const GemmArgs& g, hipStream_t s) {
 // Tile and number of parts of the K loop.  A problem with few output tiles leaves CUs idle, one with a bit more
 // than a multiple of 256 tiles an almost empty last round; cutting the K loop in `splits` parts (partial
 // products in fp32 in a scratch buffer, summed in a fixed order afterwards) makes as many times more
-// workgroups.  The plan is the cheapest of all choices by an estimate in microseconds whose constants were
-// fitted to every tile and split of 44 shapes (m 128..32768, n 192..12800, k 128..37888): rounds of
-// workgroups times (k-tiles of a part times the time of a k-tile, which grows with the number of
-// workgroups that share power and memory, plus a workgroup's start and end), plus the parts' trip
-// through memory.  Measured against the best choice of a shape it loses 3 % on average; examples (us):
-// 777 x 4096 x 14336 128x128 tiles 104, 256x256 in 4 parts 99; 777 x 4096 x 4096 33 and 47;
-// 2999 x 3584 x 37888 192x256 tiles 731, 256x256 in 3 parts 640; 1024 x 1024 x 26496 256x256 in 12 parts 68, in
-// 16 parts 83.
+// workgroups.  The plan is the cheapest of all choices by an estimate in microseconds: rounds of workgroups times
+// (k-tiles of a part times the time of a k-tile, which grows with the number of workgroups that share power and
+// memory, plus a workgroup's start and end), plus the parts' trip through memory.  The constants were fitted to rank
+// the choices, not to time a product (single products run up to 40 % off the estimate).  Against the best of all tiles and
+// splits, measured with the present kernel on 240 random products of the layers' widths (64 to 33000 tokens) that
+// the fit had not seen, the plan loses 0.7 % on average in forward layout (worst 20 %: 7200 x 18944 x 192, 103 and 86 us),
+// 1.1 % with W stored [N, K] (worst 16 %) and 0.8 % for weight gradients (worst 11 %; 2.8 % and 27 % with the forward row
+// of constants).  Examples (us): 777 x 4096 x 14336 128x128 tiles 104, 256x256 in 4 parts 99; 777 x 4096 x 4096 33 and 47;
+// weight gradient 11008 x 4608 x 296 256x256 tiles 68, 128x128 53; 9600 x 3072 x 1408 81 and 94.
 namespace {
 struct GemmPlan { GemmTile tile; int splits; };
 struct TileCost {
@@ -308,9 +309,14 @@ struct TileCost {
 };
 // split_bytes: scratch for the parts; the cheapest plan that fits it.
 GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes) {
-  static const TileCost costs[] = {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
-                                   {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
-                                   {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}};   // two on a CU from 257 on
+  // [1]: A stored [K, M], the weight gradients: fp32 tiles, twice the bytes to write, make a 256x256 workgroup's end longer
+  static const TileCost table[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}},   // two on a CU from 257 on
+                                       {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 10.5},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},      // not for this layout
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 1.05, 4.0}}};
+  const TileCost (&costs)[3] = table[a_t ? 1 : 0];
   const int64_t nk = (k + BK - 1) / BK;
   GemmPlan best{GemmTile::T256, 1};
   if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
@@ -320,14 +326,17 @@ GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes
   for (const TileCost& c : costs) {
     if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
+    // gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB and more apart (6144 x 28672 x 82
+    // 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473)
+    const double fixed = c.fixed + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0);
     for (int64_t sp = 1; sp <= cap; sp++) {
       const int64_t per = (nk + sp - 1) / sp;
       if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
       const int64_t wgs = tiles * sp, rounds = wgs / c.slots, rest = wgs % c.slots;
-      double cost = (double)rounds * ((double)per * c.k_full + c.fixed);
+      double cost = (double)rounds * ((double)per * c.k_full + fixed);
       if (rest > 0) {
         const double kt = rest <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(rest - c.few) / (c.slots - c.few);
-        cost += (double)per * kt + c.fixed;
+        cost += (double)per * kt + fixed;
       }
       if (sp > 1) cost += 3.0 + (double)m * n * (8.0 * sp + 4.0) * 1e-7;
       if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp}; }
