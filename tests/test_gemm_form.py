@@ -40,3 +40,20 @@ def test_ragged_contraction_examples(B):
     assert B.mllm_gemm_form(4096, 4096, 777, 1, 0)[0] != 0
     assert B.mllm_gemm_form(4096, 4096, 776, 0, 0) == (0, 0, 1)  # k along the rows of only one operand
     assert B.mllm_gemm_form(64, 64, 0, 1, 0) == (0, 0, 1)
+
+
+def test_no_plan_leaves_a_part_empty(B):
+    """A part is a whole number of k-tiles, at least eight, and the last one has some: over shapes of every layout, with
+    all the scratch a plan wants and with less."""
+    cut = 0
+    for m in (72, 777, 1024, 1280, 3200):
+        for n in (192, 1024, 1280, 4096):
+            for k in list(range(64, 8000, 64 * 7)) + [6720, 26496, 37888]:
+                for a_layout, b_layout in ((0, 0), (0, 1), (1, 0)):
+                    for scratch in (1 << 40, 5 * m * n * 4):
+                        parts = B.mllm_gemm_form(m, n, k, a_layout, b_layout, scratch)[2]
+                        tiles = k // 64
+                        per = -(-tiles // parts)
+                        assert (parts - 1) * per < tiles and (parts == 1 or per >= 8) and parts * m * n * 4 <= max(scratch, m * n * 4)
+                        cut += parts > 1
+    assert cut > 100

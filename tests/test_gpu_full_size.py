@@ -44,8 +44,9 @@ def test_vit_l_layer_full(B):
 
 def test_weight_gradient_split_with_empty_last_parts(B):
     """Weight gradient of a 1280 -> 1280 connector over 6720 image tokens (105 k-tiles of 64): the
-    1280 x 1280 product is cut along the tokens into 13 parts of 9 k-tiles, so the last part starts
-    past the end of the contraction and must contribute zeros."""
+    1280 x 1280 product is cut along the tokens into two parts, 53 and 52 k-tiles.  (13 parts of 9 k-tiles would leave the
+    last one empty; the plan takes no such number, test_gemm_form.py.)"""
+    assert B.mllm_gemm_form(1280, 1280, 6720, 1, 0, 1 << 40)[2] == 2
     layers = [W.projector_layer(1280, 1280)]
     batch = W.batch_from_samples([(1, 3)] * 12, img_tokens=560)
     assert batch.img.total_tokens == 105 * 64
@@ -58,9 +59,9 @@ def test_weight_gradient_split_with_empty_last_parts(B):
 
 
 def test_weight_gradient_split_over_ragged_token_count(B):
-    """ViT-L layer on 7 images of 577 tokens: 4039 tokens are 63 k-tiles of 64 and one of 7 rows, and
-    the layer's weight gradients are cut along the tokens into parts, the last of which holds the
-    partial k-tile."""
+    """ViT-L layer on 7 images of 577 tokens: 4039 tokens are 63 k-tiles of 64 and one of 7 rows, and the output
+    projection's weight gradient is cut along the tokens into four parts, the last of which holds the partial k-tile."""
+    assert B.mllm_gemm_form(1024, 1024, 4039, 1, 0, 1 << 40)[2] == 4
     layers = [W.vit_l_layer()]
     batch = W.Batch(W.make_pack([577] * 7, W.MASK_BIDIR), None, None, [])
     wl = W.make_workload("vit_ragged_tokens", layers, batch, 911)

@@ -60,10 +60,63 @@ def test_small_tiles_edges_and_epilogue_terms(B, m, n, k, b_layout, f32):
     assert np.all(got[m:] == 7.0)
 
 
+# sizes that take a tile with one, two, an odd and an even number of k-tiles alike
+TILES = [(256, 2216, 5536, 0, 0), (256, 2216, 5536, 0, 1), (256, 704, 20944, 1, 0), (256, 704, 20944, 1, 1),
+         (192, 5960, 1312, 0, 0), (192, 5960, 1312, 0, 1),
+         (128, 200, 520, 0, 0), (128, 200, 520, 0, 1), (128, 200, 520, 1, 0), (128, 200, 520, 1, 1)]
+
+
+@pytest.mark.parametrize("k", [64, 128, 192, 320])
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("tile,m,n,a_layout,b_layout", TILES)
+def test_every_tile_with_few_k_tiles(B, tile, m, n, a_layout, b_layout, f32, k):
+    """Ragged M and N, every layout and output type of a tile, all epilogue terms."""
+    assert B.mllm_gemm_form(m, n, k, a_layout, b_layout)[0] == tile
+    a = W.draw_tensor(361, m, k)
+    b = W.bf16_round(W.draw_tensor(362, k, n) * np.float32(0.125))
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    bias = W.draw_tensor(363, 1, n)
+    a_dev, b_dev = (dev_bf16(np.ascontiguousarray(t.T) if turned else t) for t, turned in ((a, a_layout), (b, b_layout)))
+    if f32:
+        init = np.random.default_rng(364).standard_normal((m, n)).astype(np.float32)
+        c = torch.from_numpy(init.copy()).cuda()
+        B.mllm_op_gemm(a_dev, b_dev, c, m, n, k, a_layout, b_layout, out_fp32=1, accumulate=1, bias=dev_bf16(bias))
+        assert nmax_err(host_f64(c), ref + bias + init) < 2e-3
+    else:
+        res = W.draw_tensor(365, m, n)
+        c = empty_bf16(m, n)
+        B.mllm_op_gemm(a_dev, b_dev, c, m, n, k, a_layout, b_layout, bias=dev_bf16(bias), residual=dev_bf16(res))
+        assert nmax_err(host_f64(c), ref + bias + res) < 1e-2
+        B.mllm_op_gemm(a_dev, b_dev, c, m, n, k, a_layout, b_layout)
+        assert nmax_err(host_f64(c), ref) < 1e-2
+
+
+@pytest.mark.parametrize("k", [1, 63, 65, 130, 193])
+@pytest.mark.parametrize("f32", [0, 1])
+def test_weight_gradient_large_tiles_short_ragged_contraction(B, k, f32):
+    """256x256 tiles whose last k-tile is partial, also the only one; the rows behind the operands hold large values."""
+    m, n = 704, 20944
+    assert B.mllm_gemm_form(m, n, k, 1, 0)[0] == 256
+    a, b = W.draw_tensor(371, k + 64, m), W.draw_tensor(372, k + 64, n)
+    a[k:], b[k:] = 1000.0, 1000.0
+    ref = a[:k].T.astype(np.float64) @ b[:k].astype(np.float64)
+    c = torch.full((m, n), float("nan"), dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    B.mllm_op_gemm(dev_bf16(a), dev_bf16(b), c, m, n, k, 1, 0, out_fp32=f32)
+    assert nmax_err(host_f64(c), ref) < (2e-3 if f32 else 1e-2)
+
+
+SCRATCH = 1 << 40   # more than any product wants
+
+
 @pytest.mark.parametrize("lengths", [[5], [77, 130], [300, 1, 64]])
 def test_layers_whose_products_split_the_k_loop(B, lengths):
-    """A few tokens against wide matrices: every product has too few tiles to fill the chip, so forward and input
-    gradients (bias, residual) and weight gradients go through partial products."""
+    """A few tokens against wide matrices: products with too few tiles to fill the chip go through partial products, the
+    down projection forward (bias, residual) and the input gradients of the up and QKV projections among them.  (The
+    weight gradients here contract over too few tokens to be cut; the test below has some.)"""
+    T = sum(lengths)
+    assert B.mllm_gemm_form(T, 1024, 4096, 0, 1, SCRATCH)[2] > 1 and B.mllm_gemm_form(T, 1024, 3072, 0, 1, SCRATCH)[2] > 1
+    assert B.mllm_gemm_form(T, 1024, 4096, 0, 0, SCRATCH)[2] > 1                # the down projection: bias, residual
+    assert B.mllm_gemm_form(4096, 1024, T, 1, 0, SCRATCH)[2] == 1
     for layer, pack in ((W.vit_layer(1024, 16, 64, 4096), "img"), (W.decoder_layer(1024, 8, 2, 128, 4096, 10000.0, qkv_bias=1), "seq")):
         p = W.make_pack(lengths, W.MASK_BIDIR if pack == "img" else W.MASK_CAUSAL)
         batch = W.Batch(p, None, None, []) if pack == "img" else W.Batch(None, p, None, [])
@@ -76,6 +129,27 @@ def test_layers_whose_products_split_the_k_loop(B, lengths):
             assert all(torch.equal(x, y) for x, y in zip(got[3], again[3])) and torch.equal(got[0], again[0])
         finally:
             st.close()
+
+
+@pytest.mark.parametrize("d_in,d_out,images,img_tokens,tile,parts", [(512, 1024, 19, 79, 128, 3), (2048, 2560, 5, 1025, 256, 3)])
+def test_split_weight_gradient_over_ragged_tokens_accumulates(B, d_in, d_out, images, img_tokens, tile, parts):
+    """A connector's weight gradient in parts, the last of which ends in a partial k-tile, added to what is there."""
+    T = images * img_tokens
+    assert T % 64 and B.mllm_gemm_form(d_in, d_out, T, 1, 0, SCRATCH) == (tile, tile, parts)
+    layers = [W.projector_layer(d_in, d_out)]
+    wl = W.make_workload("split_dw", layers, W.batch_from_samples([(1, 3)] * images, img_tokens=img_tokens), 331)
+    st = GpuStage(B, layers)
+    try:
+        ref = oracle_run(wl)
+        scale = float(np.max(np.abs(ref[3][0])))
+        rng = np.random.default_rng(332)
+        init = [(rng.standard_normal((r, c)) * scale).astype(np.float32) for _, _, r, c in st.infos]
+        dparams = [torch.from_numpy(t.copy()).cuda() for t in init]
+        got = st.run(wl, accumulate=1, dparams=dparams)
+        compare(st, wl, got, (*ref[:3], [g + t for g, t in zip(ref[3], init)]))
+        assert nmax_err(host_f64(dparams[0]), ref[3][0] + init[0]) < 2e-3      # fp32 sums of bf16 products
+    finally:
+        st.close()
 
 
 def test_ragged_contraction_close_to_4_gib(B):

@@ -56,7 +56,8 @@ def test_gemm_layouts(B, m, n, k, a_layout, b_layout):
 
 @pytest.mark.parametrize("a_layout,b_layout,f32", [(0, 0, 0), (0, 1, 0), (1, 0, 1), (1, 1, 0), (0, 0, 1)])
 def test_gemm_large_ragged(B, a_layout, b_layout, f32):
-    """Enough 256x256 tiles to take the large-tile kernel, with ragged M, N and K edges."""
+    """M, N and K ragged: 256x256 tiles of the general kernel where k is contiguous in an operand, otherwise the
+    tile kernel."""
     m, n, k = 3512, 4104, 264
     a = W.draw_tensor(61, m, k)
     b = W.bf16_round(W.draw_tensor(62, k, n) * np.float32(0.125))
@@ -80,8 +81,9 @@ def test_gemm_large_ragged(B, a_layout, b_layout, f32):
 @pytest.mark.parametrize("a_layout,b_layout,f32", [(0, 0, 0), (0, 1, 0), (1, 0, 0), (1, 1, 0),
                                                    (0, 0, 1), (0, 1, 1), (1, 0, 1), (1, 1, 1)])
 def test_gemm_large_tiles_k_multiple_of_64(B, k, a_layout, b_layout, f32):
-    """The four-wavefront 256x256 kernel (enough tiles, K a multiple of 64): one, two, an odd and
-    an even number of k-tiles, ragged M and N, every layout, with the fused epilogue terms."""
+    """The tile kernel at 238 tiles of 256x256 (K a multiple of 64): one, two, an odd and an even number of k-tiles,
+    ragged M and N, every layout, with the fused epilogue terms.  A stored [K, M] takes 128x128 tiles up to K = 192;
+    256x256 ones with as few k-tiles are in test_gpu_gemm_plan.py."""
     m, n = 3512, 4104
     a = W.draw_tensor(71, m, k)
     b = W.bf16_round(W.draw_tensor(72, k, n) * np.float32(0.125))
@@ -106,8 +108,8 @@ def test_gemm_large_tiles_k_multiple_of_64(B, k, a_layout, b_layout, f32):
 @pytest.mark.parametrize("k", [65, 127, 129, 200, 1000, 2350])
 @pytest.mark.parametrize("f32", [1, 0])
 def test_gemm_large_tiles_weight_gradient_ragged_k(B, k, f32):
-    """The weight-gradient layout (both operands stored [K, .]) keeps the four-wavefront kernel when
-    K is no multiple of 64: the rows of the last k-tile past K must read as zeros.  The operands are
+    """The weight-gradient layout (both operands stored [K, .]) keeps the tile kernel (128x128 tiles up to K = 200, 256x256
+    above) when K is no multiple of 64: the rows of the last k-tile past K must read as zeros.  The operands are
     the leading K rows of longer buffers whose later rows hold large values, so a row read past K
     would show."""
     m, n = 3512, 4104
@@ -192,9 +194,9 @@ def test_gemm_large_tiles_random_shapes(B, seed):
 @pytest.mark.parametrize("k", [64, 192, 1024])
 @pytest.mark.parametrize("b_layout,f32", [(0, 0), (1, 0), (0, 1), (1, 1)])
 def test_gemm_192_row_tiles(B, k, b_layout, f32):
-    """5640 x 4096 outputs are 368 tiles of 256x256 (two rounds of 256 workgroups, the second
-    mostly empty) and 480 tiles of 192x256: the kernel's 192-row form takes these.  Ragged last
-    row tile, both B layouts, both output types, fused epilogue terms."""
+    """5640 x 4096 outputs are 368 tiles of 256x256 (two rounds of 256 workgroups, the second mostly empty) and 480
+    tiles of 192x256: at K = 1024 the 192-row form takes these, below it 128x128 tiles (test_gpu_gemm_plan.py has the
+    192-row form with few k-tiles).  Ragged last row tile, both B layouts, both output types, fused epilogue terms."""
     m, n = 5640, 4096
     a = W.draw_tensor(101, m, k)
     b = W.bf16_round(W.draw_tensor(102, k, n) * np.float32(0.125))
