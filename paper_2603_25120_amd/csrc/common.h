@@ -15,9 +15,6 @@ typedef uint16_t bf16_t;  // raw storage type in global memory
 
 #define MLLM_LDS __attribute__((address_space(3)))
 
-__device__ __forceinline__ float bf16_to_f32(bf16_t b) {
-  return __uint_as_float(((uint32_t)b) << 16);
-}
 // fp32 -> bf16, round to nearest even, through the hardware conversion (v_cvt_pk_bf16_f32).
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2_t;
@@ -26,7 +23,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   const bf16x2_t b = __builtin_convertvector(v, bf16x2_t);
   return __builtin_bit_cast(uint32_t, b);
 }
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)(pack_bf16x2(f, 0.f) & 0xffffu); }
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 

@@ -34,7 +34,7 @@ constexpr int PAD_T = 32;
 // Global -> register -> LDS staging of one operand tile through buffer loads: an out-of-range
 // offset returns zeros, so ragged edges need no branches.  K_ROWS: the tile's rows run along the
 // contraction index (operand stored [K, rows]); otherwise its columns do (stored [rows, K]).
-template <int ROWS, int COLS, int PADC, int NT, bool K_ROWS, int BKT>
+template <int ROWS, int COLS, int PADC, int NT, bool K_ROWS>
 struct TileLoader {
   static constexpr int VEC_PER_ROW = COLS / 8;
   static constexpr int NVEC = ROWS * COLS / 8;
@@ -47,7 +47,7 @@ struct TileLoader {
   uint32_t kstep;             // bytes per BK step
 
   __device__ __forceinline__ void init(int64_t ld, int64_t fixed0, int64_t nfixed, int64_t K, int tid) {
-    kstep = (uint32_t)(K_ROWS ? BKT * ld * 2 : BKT * 2);
+    kstep = (uint32_t)(K_ROWS ? BK * ld * 2 : BK * 2);
 #pragma unroll
     for (int i = 0; i < PER_THREAD; i++) {
       const int v = tid + i * NT, rr = v / VEC_PER_ROW, cc = (v % VEC_PER_ROW) * 8;
@@ -61,7 +61,7 @@ struct TileLoader {
   __device__ __forceinline__ void store(bf16_t* lds, int tid) const { store_part<0, PER_THREAD>(lds, tid); }
   template <int I0, int I1>
   __device__ __forceinline__ void load_part(__amdgpu_buffer_rsrc_t rsrc, int kt) {
-    const int k0 = kt * BKT;
+    const int k0 = kt * BK;
 #pragma unroll
     for (int i = I0; i < I1; i++) {
       const uint32_t o = (off[i] != OOB && k0 < klim[i]) ? off[i] + (uint32_t)kt * kstep : OOB;
@@ -106,13 +106,13 @@ __device__ __forceinline__ void interleave_reads(std::integer_sequence<int, Ms..
   (interleave_slot<PER, N_READS, Ms>(), ...);
 }
 
-template <int BM, int BN, int WM, int WN, bool A_T, bool B_T, bool OUT_F32, int BKT>
+template <int BM, int BN, int WM, int WN, bool A_T, bool B_T, bool OUT_F32>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmParams p) {
   constexpr int NWM = BM / WM, NWN = BN / WN, NT = 64 * NWM * NWN;
   constexpr int TM = WM / 32, TN = WN / 32;
   // A tile: [BM][BK] (contraction contiguous) or [BK][BM] (as stored, transposing reads)
-  constexpr int A_ROWS = A_T ? BKT : BM, A_COLS = A_T ? BM : BKT, A_PAD = A_T ? PAD_T : PAD_K;
-  constexpr int B_ROWS = B_T ? BKT : BN, B_COLS = B_T ? BN : BKT, B_PAD = B_T ? PAD_T : PAD_K;
+  constexpr int A_ROWS = A_T ? BK : BM, A_COLS = A_T ? BM : BK, A_PAD = A_T ? PAD_T : PAD_K;
+  constexpr int B_ROWS = B_T ? BK : BN, B_COLS = B_T ? BN : BK, B_PAD = B_T ? PAD_T : PAD_K;
   constexpr int A_STRIDE = A_COLS + A_PAD, B_STRIDE = B_COLS + B_PAD;
   constexpr int A_SIZE = A_ROWS * A_STRIDE, B_SIZE = B_ROWS * B_STRIDE;
   // two LDS stages: tile kt+1 is written while tile kt is being multiplied
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
   tile_of_block(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
-  TileLoader<A_ROWS, A_COLS, A_PAD, NT, A_T, BKT> la;
-  TileLoader<B_ROWS, B_COLS, B_PAD, NT, B_T, BKT> lb;
+  TileLoader<A_ROWS, A_COLS, A_PAD, NT, A_T> la;
+  TileLoader<B_ROWS, B_COLS, B_PAD, NT, B_T> lb;
   la.init(p.lda, m0, p.M, p.K, tid);
   lb.init(p.ldb, n0, p.N, p.K, tid);
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(p.a, p.a_bytes), rb = make_rsrc(p.b, p.b_bytes);
@@ -143,13 +143,11 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
 
-  // Split-K: workgroup row blockIdx.y owns k-tiles [kt0, kt0 + nk) and writes its own partial C.
-  const int kt0 = blockIdx.y * p.kt_per_split;
-  const int nk = min(p.kt_per_split, (int)((p.K + BKT - 1) / BKT) - kt0);
-  gload(kt0);
+  const int nk = (int)((p.K + BK - 1) / BK);
+  gload(0);
   la.store(As, tid);
   lb.store(Bs, tid);
-  gload(kt0 + 1);
+  gload(1);
   __syncthreads();
 
   // Fragments are double-buffered in registers: those of step kk+1 are fetched from LDS while
@@ -162,19 +160,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
     for (int j = 0; j < TN; j++) bfr[buf][j] = fetch_frag<B_T, B_STRIDE>(bt, wn * WN + 32 * j, kk, lane);
   };
   fetch(0, As, Bs, 0);
-  constexpr int STEPS = BKT / 16;
-  using LA = TileLoader<A_ROWS, A_COLS, A_PAD, NT, A_T, BKT>;
-  using LB = TileLoader<B_ROWS, B_COLS, B_PAD, NT, B_T, BKT>;
-  // EARLY (four k-steps per tile): the tile is moved in the first half of the k-steps and the
-  // barrier sits before the last step's MFMAs, so the next tile's first fragments are fetched
-  // under them.  Otherwise the move is spread over all k-steps and the barrier closes the
-  // iteration.
-  constexpr bool EARLY = STEPS == 4;
-  constexpr int MOVE_STEPS = EARLY ? STEPS / 2 : STEPS;
+  constexpr int STEPS = BK / 16;
+  using LA = TileLoader<A_ROWS, A_COLS, A_PAD, NT, A_T>;
+  using LB = TileLoader<B_ROWS, B_COLS, B_PAD, NT, B_T>;
+  // The next tile is moved in the first half of the k-steps and the barrier sits before the last
+  // step's MFMAs, so that tile's first fragments are fetched under them.
+  constexpr int MOVE_STEPS = STEPS / 2;
   constexpr int A_PER = LA::PER_THREAD / MOVE_STEPS, B_PER = LB::PER_THREAD / MOVE_STEPS;
   static_assert(A_PER * MOVE_STEPS == LA::PER_THREAD && B_PER * MOVE_STEPS == LB::PER_THREAD && A_PER >= 1 && B_PER >= 1,
                 "the moving k-steps must split the tile evenly");
-  static_assert(STEPS == 2 || STEPS == 4, "two or four k-steps per tile");
   for (int kt = 0; kt < nk; kt++) {
     const int cur = kt & 1;
     bf16_t* an = As + (cur ^ 1) * A_SIZE;
@@ -184,7 +178,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
     // Branch-free body.  The moving k-steps each put a share of tile kt+1 from the staging
     // registers into the other LDS stage and at once refill those registers with the same share
     // of tile kt+2 (every prefetch has a whole iteration to land); every step but the last
-    // fetches the next step's fragments before issuing its MFMAs.  With EARLY the barrier comes
+    // fetches the next step's fragments before issuing its MFMAs.  The barrier comes
     // before the last step's MFMAs: by then every fragment of this stage is in registers and
     // every store to the other stage has been issued.  Past the end the prefetch offsets are out
     // of range (zeros, no traffic) and the stored stage is never read.
@@ -193,12 +187,12 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
       if constexpr (kk < MOVE_STEPS) {
         la.template store_part<kk * A_PER, (kk + 1) * A_PER>(an, tid);
         lb.template store_part<kk * B_PER, (kk + 1) * B_PER>(bn, tid);
-        la.template load_part<kk * A_PER, (kk + 1) * A_PER>(ra, kt0 + kt + 2);
-        lb.template load_part<kk * B_PER, (kk + 1) * B_PER>(rb, kt0 + kt + 2);
+        la.template load_part<kk * A_PER, (kk + 1) * A_PER>(ra, kt + 2);
+        lb.template load_part<kk * B_PER, (kk + 1) * B_PER>(rb, kt + 2);
       }
       if constexpr (kk + 1 < STEPS) {
         fetch((kk + 1) & 1, at, bt, kk + 1);
-      } else if constexpr (EARLY) {
+      } else {
         __syncthreads();
         fetch(0, an, bn, 0);
       }
@@ -210,29 +204,19 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_kernel(GemmPa
       // Issue order inside the step: the LDS reads of the next fragments go out one per MFMA from
       // the step's start (left alone, the scheduler puts them after the MFMAs and the wavefront
       // then waits on LDS with nothing queued behind it).
-      if constexpr (kk + 1 < STEPS || EARLY) {
-        constexpr int N_READS = TM * (A_T ? 2 : 1) + TN * (B_T ? 2 : 1), N_MFMA = TM * TN;
-        constexpr int PER = (N_READS + N_MFMA - 1) / N_MFMA;     // reads per MFMA slot
-        interleave_reads<PER, N_READS>(std::make_integer_sequence<int, N_MFMA>{});
-      }
+      constexpr int N_READS = TM * (A_T ? 2 : 1) + TN * (B_T ? 2 : 1), N_MFMA = TM * TN;
+      constexpr int PER = (N_READS + N_MFMA - 1) / N_MFMA;     // reads per MFMA slot
+      interleave_reads<PER, N_READS>(std::make_integer_sequence<int, N_MFMA>{});
       __builtin_amdgcn_sched_barrier(0);
     };
     step(std::integral_constant<int, 0>{});
     step(std::integral_constant<int, 1>{});
-    if constexpr (STEPS == 4) {
-      step(std::integral_constant<int, 2>{});
-      step(std::integral_constant<int, 3>{});
-    }
-    if constexpr (!EARLY) {
-      __syncthreads();
-      fetch(0, an, bn, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 3>{});
   }
 
   constexpr int ST_STRIDE = WN + 4;  // floats
   static_assert(NWM * NWN * 32 * ST_STRIDE * 4 <= 2 * A_SIZE * 2, "staging must fit in the A stages");
-  if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + blockIdx.y * p.c_split_stride;
   store_tile<TM, TN, OUT_F32>(p, acc, reinterpret_cast<float*>(As) + wave * 32 * ST_STRIDE,
                               m0 + wm * WM, n0 + wn * WN, lane);
 }
@@ -263,14 +247,14 @@ hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_
 }
 
 // K no multiple of 64 with an operand whose contiguous dimension is k, or K = 0.
-template <int BM, int BN, int WM, int WN, int BKT = 64>
+template <int BM, int BN, int WM, int WN>
 hipError_t launch_general(const GemmArgs& g, hipStream_t s) {
   const GemmParams p = make_gemm_params(g, BM, BN);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n)), block(64 * (BM / WM) * (BN / WN));
   const bool at = g.a_layout != 0, bt = g.b_layout == 0;
 #define MLLM_GEMM_CASE(AT, BT, F32)                                                      \
   if (at == AT && bt == BT && (g.out_fp32 != 0) == F32) {                                \
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AT, BT, F32, BKT>), grid, block, 0, s, p); \
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, AT, BT, F32>), grid, block, 0, s, p); \
     return hipGetLastError();                                                            \
   }
   MLLM_GEMM_CASE(false, true, false)

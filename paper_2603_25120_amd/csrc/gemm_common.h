@@ -92,9 +92,8 @@ __device__ __forceinline__ void tile_of_block(int pid, int nblk, int tiles_m, in
 // runs of four consecutive columns.  One 32-row band at a time goes through a per-wavefront fp32
 // staging area in LDS (32 x (WN+4) floats at `stage`) and leaves as 16-byte chunks (256 or 512
 // contiguous bytes per row), with bias / residual / accumulate applied in fp32 and a single
-// rounding on the way out.  Every wavefront of the workgroup must call it (it synchronises: once
-// with WAVE_LOCAL, which is valid when each wavefront passes a staging area of its own).
-template <int TM, int TN, bool OUT_F32, bool WAVE_LOCAL = false>
+// rounding on the way out.  Every wavefront of the workgroup must call it (it synchronises).
+template <int TM, int TN, bool OUT_F32>
 __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM][TN], float* stage,
                                            int64_t row0, int64_t col0, int lane) {
   constexpr int WN = 32 * TN, ST_STRIDE = WN + 4;
@@ -131,37 +130,16 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM
   // FULL: the whole sub-tile lies inside C (wavefront-uniform), no per-chunk predicate.
   auto emit = [&](auto full_c) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_c)::value;
-    // WAVE_LOCAL callers have registers to spare: the residual of the whole tile is requested up
-    // front, so one memory latency is exposed instead of one per band
-    constexpr bool RES_AHEAD = WAVE_LOCAL && !OUT_F32;
-    uint4 res_ahead[RES_AHEAD ? TM * PER_BAND : 1];
-    if constexpr (RES_AHEAD) {
-      if (p.res) {
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-          for (int t = 0; t < PER_BAND; t++) {
-            const int r = 32 * i + t * ROWS_PER_PASS;   // + rr0: the lane's row inside the sub-tile
-            const bool ok = FULL || (r + rr0 < rows_left && col_ok);
-            res_ahead[i * PER_BAND + t] =
-                ok ? *reinterpret_cast<const uint4*>(r_base + (r_lane + (uint32_t)r * r_pitch)) : make_uint4(0, 0, 0, 0);
-          }
-      }
-    }
 #pragma unroll
     for (int i = 0; i < TM; i++) {
-      // the band staged before (or the last tile's fragments) has been read; a wavefront's own
-      // LDS accesses execute in order, so after the first band only its own order matters
-      if (!WAVE_LOCAL || i == 0) __syncthreads();
-      else __builtin_amdgcn_wave_barrier();
+      __syncthreads();   // the band staged before (or the last tile's fragments) has been read
 #pragma unroll
       for (int j = 0; j < TN; j++)
 #pragma unroll
         for (int g4 = 0; g4 < 4; g4++)
           *reinterpret_cast<float4*>(stage + cl * ST_STRIDE + 32 * j + 8 * g4 + 4 * h) =
               make_float4(acc[i][j][4 * g4], acc[i][j][4 * g4 + 1], acc[i][j][4 * g4 + 2], acc[i][j][4 * g4 + 3]);
-      if (!WAVE_LOCAL) __syncthreads();
-      else __builtin_amdgcn_wave_barrier();
+      __syncthreads();
 #pragma unroll
       for (int t = 0; t < PER_BAND; t++) {
         const int rr = rr0 + t * ROWS_PER_PASS;
@@ -187,9 +165,7 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM
           *dst = make_float4(f[0], f[1], f[2], f[3]);
         } else {
           if (p.res) {
-            uint4 rv;
-            if constexpr (RES_AHEAD) rv = res_ahead[i * PER_BAND + t];
-            else rv = *reinterpret_cast<const uint4*>(r_base + (r_lane + (uint32_t)r * r_pitch));
+            const uint4 rv = *reinterpret_cast<const uint4*>(r_base + (r_lane + (uint32_t)r * r_pitch));
             f[0] += bf16lo(rv.x); f[1] += bf16hi(rv.x); f[2] += bf16lo(rv.y); f[3] += bf16hi(rv.y);
             f[4] += bf16lo(rv.z); f[5] += bf16hi(rv.z); f[6] += bf16lo(rv.w); f[7] += bf16hi(rv.w);
           }
