@@ -354,9 +354,13 @@ bool gemm_rope_fusable(int64_t m, int64_t n, int64_t k, int32_t head_dim) {
 }
 
 namespace {
-// The plan of a product that takes the tile kernel.
+// The plan of a product that takes the tile kernel.  With both operands k-contiguous the large tiles are loaded straight
+// into LDS, 16 bytes a lane, which is only known to work from addresses that are multiples of 16; operands that start
+// elsewhere (a tensor inside a larger buffer) take 128x128 tiles, whose loads go through registers.
 GemmPlan plan_of(const GemmArgs& g) {
-  if (!takes_tile_kernel(g) || g.swiglu_act || g.swiglu_dpre || g.rope_table) return {GemmTile::T256, 1};   // the fused epilogues exist for this tile
+  if (!takes_tile_kernel(g)) return {GemmTile::T256, 1};
+  if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1};
+  if (g.swiglu_act || g.swiglu_dpre || g.rope_table) return {GemmTile::T256, 1};   // the fused epilogues exist for this tile
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
   return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok ? g.splitk_ws_bytes : 0);
 }

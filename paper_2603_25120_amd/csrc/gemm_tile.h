@@ -389,7 +389,11 @@ hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, in
     if (epi == EPI_ROPE64) { if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_ROPE64); else return hipErrorInvalidValue; }
   }
   if constexpr (!A_T && !B_T) {
-    if (epi == EPI_SWIGLU_BWD) { if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_SWIGLU_BWD); else return hipErrorInvalidValue; }
+    if (epi == EPI_SWIGLU_BWD) {
+      if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_SWIGLU_BWD);
+      if (tile == GemmTile::T128) MLLM_TILE(4, 4, false, EPI_SWIGLU_BWD);   // operands off 16-byte alignment
+      return hipErrorInvalidValue;
+    }
   }
   if (epi != EPI_PLAIN) return hipErrorInvalidValue;
   if constexpr (!A_T) {

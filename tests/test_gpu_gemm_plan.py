@@ -165,3 +165,39 @@ def test_ragged_contraction_close_to_4_gib(B):
     c = torch.empty(w, w, dtype=torch.float32, device="cuda")
     B.mllm_op_gemm(a, b, c, w, w, k, 1, 0, out_fp32=1)
     assert nmax_err(host_f64(c), ref) < 2e-3
+
+
+def placed(x, offset):
+    """The values of x in a contiguous device tensor that starts `offset` elements into its allocation."""
+    flat = torch.zeros(x.size + offset, dtype=torch.bfloat16, device="cuda")
+    flat[offset:] = dev_bf16(x).flatten()
+    return flat[offset:].view(x.shape)
+
+
+@pytest.mark.parametrize("oa,ob", [(1, 0), (0, 1), (3, 6), (8, 4), (0, 0)])
+@pytest.mark.parametrize("m,n,k,a_layout,b_layout", [(2216, 5536, 192, 0, 1), (5960, 1312, 128, 0, 1), (264, 328, 192, 0, 1),
+                                                     (2216, 5536, 192, 0, 0), (704, 20944, 130, 1, 0)])
+def test_operands_anywhere_in_a_buffer(B, m, n, k, a_layout, b_layout, oa, ob):
+    """Tensors that start at any element of a larger buffer, results included; nothing beside the result is written."""
+    a = W.draw_tensor(381, m, k)
+    b = W.bf16_round(W.draw_tensor(382, k, n) * np.float32(0.125))
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    a_dev, b_dev = (placed(np.ascontiguousarray(t.T) if turned else t, o) for t, turned, o in ((a, a_layout, oa), (b, b_layout, ob)))
+    c = torch.full((m * n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+    at = 1 + oa
+    B.mllm_op_gemm(a_dev, b_dev, c[at:at + m * n], m, n, k, a_layout, b_layout)
+    assert nmax_err(host_f64(c[at:at + m * n]).reshape(m, n), ref) < 1e-2
+    assert bool((c[:at] == 7.0).all()) and bool((c[at + m * n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("oa,ob", [(1, 0), (0, 5)])
+def test_swiglu_gradient_of_operands_anywhere_in_a_buffer(B, oa, ob):
+    m, f, k = 4200, 3080, 192
+    dy, w = W.draw_tensor(391, m, k), W.bf16_round(W.draw_tensor(392, f, k) * np.float32(0.125))
+    pre = W.draw_tensor(393, m, 2 * f)
+    da = dy.astype(np.float64) @ w.astype(np.float64).T
+    g, u = pre[:, :f].astype(np.float64), pre[:, f:].astype(np.float64)
+    s = 1.0 / (1.0 + np.exp(-g))
+    dpre = torch.full((m, 2 * f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.mllm_op_gemm_swiglu_bwd(placed(dy, oa), placed(w, ob), dev_bf16(pre), dpre, m, f, k)
+    assert nmax_err(host_f64(dpre), np.concatenate([da * u * s * (1.0 + g * (1.0 - s)), da * g * s], axis=1)) < 2e-2
