@@ -567,7 +567,7 @@ def main():
                     "gemm_dx": "gemm4_kernel<8, 8, false, false, false, *> (dX = dY.W^T, 256x256x64 tiles; plain and SwiGLU-gradient epilogues)",
                     "gemm_dw": "gemm4_kernel<8, 8, true, true, true, 0> (dW = X^T.dY, fp32, 256x256x64 tiles)"}
     traffic, traffic_note = recorded_traffic(gemm_cls, args.workload)
-    # the large-tile kernels stream, per XCD, the 8 A panels and 4 B panels of an 8 x 4 block of 256 x 256 tiles
+    # the large-tile kernels stream, per XCD, the 12 panels of an 8 x 4 block of 256 x 256 tiles (4 x 8 where A is large)
     # through L2 once: 2 M N K (1 / 2048 + 1 / 1024) bytes fetched per launch (bf16 operands)
     traffic_model = (work / n) * (1.0 / 2048 + 1.0 / 1024) if n else None
     out = {

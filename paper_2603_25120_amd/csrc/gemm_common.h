@@ -188,7 +188,8 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, f32x16 (&acc)[TM
 // a row of blocks at a time passes through the wavefront's own part of the LDS that the tiles have left (`stage`,
 // two buffers, no barrier: a wavefront's LDS accesses execute in order) and leaves in row order, 16 bytes a lane, 128 to 512
 // contiguous bytes a row; bf16 operands of the epilogue (residual, gate, up) come in in the same order.  What needs
-// nothing added is staged already rounded.  The padding of 4 words puts the 16 rows on different banks.  Whole products,
+// nothing added is staged already rounded.  The padding of 4 words leaves fp32 rows without bank conflicts
+// and bf16 rows with 384 conflict cycles a wavefront (an exclusive-or order with two thirds of them was no faster).  Whole products,
 // stores from the accumulators -> staged: 5120 x 11008 x 100 weight gradient 53 -> 44 us, 1024 x 12800 x 480 24.4 -> 21.9;
 // forward 7488 x 4096 x 1024 64.8 -> 61.6, 2880 x 4096 x 1024 26.6 -> 25.3.
 // Addresses: a buffer over the wavefront's rows of the matrix that starts at the sub-tile's first
