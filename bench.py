@@ -33,8 +33,10 @@ HBM_PEAK = 8.0e12         # B/s
 
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_full_stage_32k.md")
-TRAFFIC_KERNELS = {"gemm_fwd": "gemm4_kernel<8, 8, false, true, false, 0>", "gemm_dx": "gemm4_kernel<8, 8, false, false, false, 0>",
-                   "gemm_dw": "gemm4_kernel<8, 8, true, true, true, 0>"}
+TRAFFIC_KERNELS = {   # the kernels of a timing class: plain, SwiGLU, rotary epilogue / plain, SwiGLU gradient / plain
+    "gemm_fwd": ["gemm4_kernel<8, 8, false, true, false, %d>" % epi for epi in (0, 1, 3)],
+    "gemm_dx": ["gemm4_kernel<8, 8, false, false, false, %d>" % epi for epi in (0, 2)],
+    "gemm_dw": ["gemm4_kernel<8, 8, true, true, true, 0>"]}
 
 
 def gemm_source_digest():
@@ -48,8 +50,8 @@ def gemm_source_digest():
 
 
 def recorded_traffic(gemm_cls, workload):
-    """L2 <-> fabric bytes per launch of the class's kernel, read from the committed summary of the two
-    `rocprofv3 --pmc` runs (FETCH_SIZE, WRITE_SIZE) of this command.  The summary names the digest of the
+    """L2 <-> fabric bytes per launch, over the launches of the class's kernels, read from the committed summary of
+    the two `rocprofv3 --pmc` runs (FETCH_SIZE, WRITE_SIZE) of this command.  The summary names the digest of the
     kernel sources it was taken with; when the sources have changed since, the figure is withheld (None)."""
     import re
     if workload != "full_stage_32k":
@@ -63,11 +65,15 @@ def recorded_traffic(gemm_cls, workload):
         return None, "the summary names no kernel source digest"
     if m.group(1) != gemm_source_digest():
         return None, "stale: the summary was taken with kernel sources %s, these are %s" % (m.group(1), gemm_source_digest())
-    row = re.search(r"\| `%s` \| \d+ \| (\d+) \| (\d+) \|" % re.escape(TRAFFIC_KERNELS[gemm_cls]), text)
-    if not row:
-        return None, "the summary has no row for %s" % TRAFFIC_KERNELS[gemm_cls]
-    fetch_kib, write_kib = float(row.group(1)), float(row.group(2))
-    return (fetch_kib * 2.0 + write_kib) * 1024.0, "profiles/hbm_traffic_full_stage_32k.md (kernel sources %s)" % m.group(1)
+    launches = kib = 0.0
+    for name in TRAFFIC_KERNELS[gemm_cls]:
+        row = re.search(r"\| `%s` \| (\d+) \| (\d+) \| (\d+) \|" % re.escape(name), text)
+        if not row:
+            return None, "the summary has no row for %s" % name
+        n, fetch_kib, write_kib = (float(v) for v in row.groups())
+        launches += n
+        kib += n * (fetch_kib * 2.0 + write_kib)
+    return kib / launches * 1024.0, "profiles/hbm_traffic_full_stage_32k.md (kernel sources %s)" % m.group(1)
 
 
 def stage_fwd_flops(layers, batch):
