@@ -250,6 +250,22 @@ mllm_status_t mllm_op_gemm_swiglu(const void* x, const void* w_gu, void* pre, vo
 mllm_status_t mllm_op_gemm_swiglu_bwd(const void* dy, const void* w_d, const void* pre, void* dpre,
                                       int64_t m, int64_t f, int64_t k, void* hip_stream);
 
+/* Both gradients of a linear map Y [t, n] = X [t, k] . W [k, n] (bf16, row-major), in one launch where both products take
+ * the tile kernel and dy and w start on 16 bytes, as the stage's backward pass forms them:
+ *   dx [t, k] bf16 = dy . W^T,  dw [k, n] fp32 (+)= X^T . dy (accumulate != 0: added).
+ * swiglu_pre not NULL (the conditions of mllm_op_gemm_swiglu_bwd with m = t, f = k, k = n, else MLLM_ERR_UNSUPPORTED): dx is
+ * [d gate | d up] [t, 2k] instead, from swiglu_pre = [gate | up] [t, 2k].
+ * workspace: scratch_bytes of fp32 scratch (256-byte aligned, may be NULL with 0 bytes) for products cut along their
+ * contraction; the cheapest plan that fits it is taken.  k and n must be multiples of 8. */
+mllm_status_t mllm_op_linear_bwd(const void* dy, const void* x, const void* w, void* dx, void* dw, int64_t t, int64_t k,
+                                 int64_t n, int accumulate, const void* swiglu_pre, void* workspace, size_t scratch_bytes,
+                                 void* hip_stream);
+/* The form that takes (host only): form[0] 1 for one launch, 0 for two; [1..3] tile rows, tile columns and parts of the
+ * input gradient, [4..6] of the weight gradient; [7] 1 if the input gradient's workgroups come first.  scratch_wanted (may be
+ * NULL): what the plan would take without a limit. */
+mllm_status_t mllm_linear_bwd_form(int64_t t, int64_t k, int64_t n, int swiglu, size_t scratch_bytes, int32_t* form,
+                                   size_t* scratch_wanted);
+
 /* Per-instance attention over a packed sequence (Model Profiler, "Throughput Profiling").
  *   q [T, n_q, hd], k, v [T, n_kv, hd] bf16 with row strides (in elements) q_stride / kv_stride,
  *   o [T, n_q, hd] bf16 (row stride o_stride), lse fp32 [n_q, T] (natural log-sum-exp of the
@@ -474,7 +490,7 @@ mllm_status_t mllm_optimize_parallelism(const mllm_module_profile_t* enc, const 
  * mllm_profile_begin(max_records) creates the events and starts recording every kernel launch of
  * the calling process' later mllm_* calls, bracketing each with HIP events on its launch stream.
  * mllm_profile_end stops recording, waits for the recorded events, and sums per class
- * (0 / 1 / 2: the 256x256-tile GEMM kernel in its Y=X.W / dX / dW layouts, 3 attention forward,
+ * (0 / 1 / 2: the 256x256-tile GEMM kernel in its Y=X.W / dX / dW layouts (1 also dX and dW in one launch), 3 attention forward,
  * 4 attention backward, 5 the norm / rotary / activation / reduction / copy kernels, 6 the
  * 128x128-tile GEMM kernel in any layout, 7 the 192x256-tile form of the large GEMM kernel in any
  * layout): launches[8], milliseconds[8] and work[8] (algorithmic FLOPs for the GEMM and attention

@@ -22,7 +22,7 @@ STATUS_NAMES = ["MLLM_OK", "MLLM_ERR_NULL", "MLLM_ERR_DESC", "MLLM_ERR_SHAPE", "
 
 EXPORTS = ["mllm_stage_create", "mllm_stage_destroy", "mllm_stage_param_count", "mllm_stage_param_info",
            "mllm_stage_sizes", "mllm_stage_fwd", "mllm_stage_bwd", "mllm_last_error", "mllm_op_gemm",
-           "mllm_gemm_form", "mllm_op_gemm_swiglu", "mllm_op_gemm_swiglu_bwd", "mllm_op_attn_workspace_bytes", "mllm_attn_work_list", "mllm_op_attn_fwd", "mllm_op_attn_bwd", "mllm_op_norm_fwd",
+           "mllm_gemm_form", "mllm_op_linear_bwd", "mllm_linear_bwd_form", "mllm_op_gemm_swiglu", "mllm_op_gemm_swiglu_bwd", "mllm_op_attn_workspace_bytes", "mllm_attn_work_list", "mllm_op_attn_fwd", "mllm_op_attn_bwd", "mllm_op_norm_fwd",
            "mllm_op_norm_bwd_partial_bytes", "mllm_op_norm_bwd", "mllm_op_norm_bwd_colsum", "mllm_op_rope", "mllm_op_rope_table", "mllm_op_gemm_rope", "mllm_op_attn_bwd_rope", "mllm_op_act_fwd",
            "mllm_op_act_bwd", "mllm_op_colsum_partial_bytes", "mllm_op_colsum", "mllm_op_colsum_static_max_bytes", "mllm_op_colsum_static", "mllm_profile_begin",
            "mllm_profile_end", "mllm_schedule_lpt", "mllm_schedule", "mllm_interp", "mllm_item_durations",
@@ -100,6 +100,8 @@ def lib() -> C.CDLL:
     L.mllm_stage_bwd.argtypes = [vp, C.POINTER(BatchC), C.POINTER(vp), vp, vp, sz, vp, vp, C.POINTER(vp), C.c_int, vp, sz, vp]
     L.mllm_op_gemm.argtypes = [vp, vp, vp, i64, i64, i64, C.c_int, C.c_int, C.c_int, C.c_int, vp, vp, vp]
     L.mllm_op_gemm_swiglu.argtypes = [vp, vp, vp, vp, i64, i64, i64, vp]
+    L.mllm_op_linear_bwd.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, C.c_int, vp, vp, sz, vp]
+    L.mllm_linear_bwd_form.argtypes = [i64, i64, i64, C.c_int, sz, C.POINTER(i32), C.POINTER(sz)]
     L.mllm_gemm_form.argtypes = [i64, i64, i64, C.c_int, C.c_int, sz, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     L.mllm_op_gemm_swiglu_bwd.argtypes = [vp, vp, vp, vp, i64, i64, i64, vp]
     L.mllm_op_attn_workspace_bytes.argtypes = [i32, i32, i32]
@@ -280,6 +282,19 @@ def mllm_gemm_form(m, n, k, a_layout=0, b_layout=0, scratch_bytes=0):
     v = [C.c_int32() for _ in range(3)]
     _check(lib().mllm_gemm_form(m, n, k, a_layout, b_layout, scratch_bytes, *(C.byref(x) for x in v)))
     return tuple(x.value for x in v)
+
+
+def mllm_op_linear_bwd(dy, x, w, dx, dw, t, k, n, accumulate=0, swiglu_pre=None, workspace=None, scratch_bytes=0, stream=None) -> None:
+    _check(lib().mllm_op_linear_bwd(_ptr(dy), _ptr(x), _ptr(w), _ptr(dx), _ptr(dw), t, k, n, accumulate, _ptr(swiglu_pre),
+                                    _ptr(workspace), scratch_bytes, _stream(stream)))
+
+
+def mllm_linear_bwd_form(t, k, n, swiglu=0, scratch_bytes=1 << 40):
+    """((launches in one, dX (rows, cols, parts), dW (rows, cols, parts), dX first), scratch wanted) of a map's gradients."""
+    form, want = (C.c_int32 * 8)(), C.c_size_t()
+    _check(lib().mllm_linear_bwd_form(t, k, n, swiglu, scratch_bytes, form, C.byref(want)))
+    v = list(form)
+    return (bool(v[0]), tuple(v[1:4]), tuple(v[4:7]), bool(v[7])), int(want.value)
 
 
 def mllm_op_gemm_swiglu(x, w_gu, pre, act, m, f, k, stream=None) -> None:

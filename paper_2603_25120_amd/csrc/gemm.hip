@@ -15,6 +15,7 @@
 // workgroup computes a BM x BN tile with (BM/WM)*(BN/WN) wavefronts, each owning a WM x WN sub-tile; the K
 // loop moves BK = 64 at a time: global -> registers (prefetch of the next tile) -> LDS.
 #include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "gemm_common.h"
@@ -232,13 +233,17 @@ bool takes_tile_kernel(const GemmArgs& g) {
   const int64_t rows = (g.k + BK - 1) / BK * BK;
   return rows * g.lda * 2 <= 0xFFFFFFFFll && rows * g.ldb * 2 <= 0xFFFFFFFFll;
 }
-hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
+GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
   const int bm = tile == GemmTile::T256 ? 256 : tile == GemmTile::T192 ? 192 : 128, bn = tile == GemmTile::T128 ? 128 : 256;
   GemmParams p = make_gemm_params(g, bm, bn);
   if (splits > 1) {   // the plan has made sure that no split is empty
     p.kt_per_split = (p.kt_per_split + splits - 1) / splits;
     p.c_split_stride = g.m * g.n;
   }
+  return p;
+}
+hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
+  const GemmParams p = tile_params(g, tile, splits);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
   const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
   const bool at = g.a_layout != 0, bt = g.b_layout == 0, f32 = g.out_fp32 != 0;   // b_layout 0: stored [K, N], transposing reads
@@ -291,16 +296,25 @@ struct TileCost {
   int few;                // up to this many, a k-tile costs k_few; from there on k_more, rising to k_full for a full round
   double k_few, k_more, k_full, fixed;
 };
-// split_bytes: scratch for the parts; the cheapest plan that fits it.
-GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes) {
-  // [1]: A stored [K, M], the weight gradients: fp32 tiles, twice the bytes to write, make a 256x256 workgroup's end longer
-  static const TileCost table[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
+// [1]: A stored [K, M], the weight gradients: fp32 tiles, twice the bytes to write, make a 256x256 workgroup's end longer
+constexpr TileCost TILE_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
                                         {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
                                         {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}},   // two on a CU from 257 on
                                        {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 10.5},
                                         {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},      // not for this layout
                                         {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 1.05, 4.0}}};
-  const TileCost (&costs)[3] = table[a_t ? 1 : 0];
+// A workgroup's start and end.  Gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB and more
+// apart (6144 x 28672 x 82 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473).
+double start_and_end(const TileCost& c, bool a_t, int64_t n) { return c.fixed + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0); }
+// A k-tile's time among `wgs` workgroups of at most a round.
+double k_tile_time(const TileCost& c, int64_t wgs) {
+  return wgs <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(wgs - c.few) / (c.slots - c.few);
+}
+// What the parts cost besides: their trip through memory and a launch.
+double parts_cost(int64_t m, int64_t n, int64_t parts) { return parts > 1 ? 3.0 + (double)m * n * (8.0 * parts + 4.0) * 1e-7 : 0.0; }
+// split_bytes: scratch for the parts; the cheapest plan that fits it.
+GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes) {
+  const TileCost (&costs)[3] = TILE_COSTS[a_t ? 1 : 0];
   const int64_t nk = (k + BK - 1) / BK;
   GemmPlan best{GemmTile::T256, 1};
   if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
@@ -310,24 +324,115 @@ GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes
   for (const TileCost& c : costs) {
     if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
-    // gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB and more apart (6144 x 28672 x 82
-    // 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473)
-    const double fixed = c.fixed + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0);
+    const double fixed = start_and_end(c, a_t, n);
     for (int64_t sp = 1; sp <= cap; sp++) {
       const int64_t per = (nk + sp - 1) / sp;
       if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
       const int64_t wgs = tiles * sp, rounds = wgs / c.slots, rest = wgs % c.slots;
       double cost = (double)rounds * ((double)per * c.k_full + fixed);
-      if (rest > 0) {
-        const double kt = rest <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(rest - c.few) / (c.slots - c.few);
-        cost += (double)per * kt + fixed;
-      }
-      if (sp > 1) cost += 3.0 + (double)m * n * (8.0 * sp + 4.0) * 1e-7;
+      if (rest > 0) cost += (double)per * k_tile_time(c, rest) + fixed;
+      cost += parts_cost(m, n, sp);
       if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp}; }
     }
   }
   return best;
 }
+}  // namespace
+
+namespace {
+// A linear map's input gradient x = dY [T, n] . W^T [n, k] and weight gradient w = X^T [k, T] . dY [T, n] in one launch:
+// neither needs the other, the second starts on the CUs that the first one's last round leaves idle, and a launch and its
+// gap go.  The plan takes tiles, parts and order together, as the cheapest estimate of the whole launch: the workgroups of
+// the first product, then those of the second, each on the first slot that is free.  On 229 maps of the layers' widths (64 to
+// 26000 tokens) it loses 2.2 % on average against the best of all choices (worst 23 %); against two launches with the plans of
+// their own the pair takes 0.87 of the time: 576 x 1024 x 4096 (T, k, n) 26.6 -> 21.7 us, 256 x 256 x 768 14.2 -> 8.4,
+// 2880 x 1024 x 3072 52 -> 43, 5125 x 3200 x 12800 737 -> 628.
+struct PairPlan { GemmPlan x, w; bool x_first, pays; };
+constexpr TileCost PAIR_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.00, 1.00, 1.33, 8.4},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9},
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.70, 0.90, 4.3}},
+                                       {{GemmTile::T256, 256, 256, 256, 0, 1.30, 1.30, 1.45, 10.3},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9},   // not for this layout
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.44, 0.74, 0.94, 4.5}}};
+constexpr double MIXED_128[2] = {0.52, 0.56};   // a k-tile of a 128x128 tile that has its CU to itself beside large tiles
+constexpr double LONGEST = 0.1;                 // workgroups do not all take the same time: long ones delay the end more often
+constexpr int MOST_PARTS = 8;
+struct PairSide {   // one choice for one of the products
+  const TileCost* c; int splits; int64_t per, wgs; double fixed, parts; size_t bytes;
+};
+// The time after which na workgroups of da each and then nb of db each have run on `slots` slots.
+double makespan(int64_t na, double da, int64_t nb, double db, int64_t slots) {
+  const int64_t rounds = na / slots, rest = na % slots, early = slots - rest;   // `early` slots are free one da before the others
+  const double t1 = (double)rounds * da, t2 = t1 + da;
+  const double q = std::floor(da / db);                                         // workgroups that an early slot takes by then
+  const double alone = std::ceil((double)nb / (double)early);
+  double end;
+  if (rest == 0 || alone <= q) {
+    end = t1 + alone * db;
+  } else {
+    const double lag = q + (da > q * db * (1 + 1e-9) ? 1.0 : 0.0);
+    const double i = std::max(1.0, std::ceil(((double)nb + (double)rest * lag) / (double)slots));
+    const double j = std::max(1.0, std::ceil(((double)nb - (double)early * q) / (double)slots));
+    end = std::min(t1 + i * db, t2 + j * db);
+  }
+  return std::max(end, rest > 0 ? t2 : t1);
+}
+int pair_sides(PairSide (&out)[3 * MOST_PARTS], int64_t m, int64_t n, int64_t k, bool a_t, bool only_256, size_t bytes) {
+  const int64_t nk = (k + BK - 1) / BK;
+  int count = 0;
+  for (const TileCost& c : PAIR_COSTS[a_t ? 1 : 0]) {
+    if ((c.tile == GemmTile::T192 && a_t) || (only_256 && c.tile != GemmTile::T256)) continue;
+    const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
+    for (int64_t sp = 1; sp <= MOST_PARTS && (sp == 1 || (!only_256 && sp <= nk / 8 && (sp - 1) * tiles < 512)); sp++) {
+      const int64_t per = (nk + sp - 1) / sp;
+      const size_t need = sp > 1 ? (size_t)sp * (size_t)m * (size_t)n * 4 : 0;
+      if ((nk + per - 1) / per != sp || need > bytes) continue;
+      out[count++] = {&c, (int)sp, per, tiles * sp, c.fixed, parts_cost(m, n, sp), need};
+    }
+  }
+  return count;
+}
+PairPlan plan_pair(int64_t t, int64_t k, int64_t n, bool swiglu, size_t split_bytes) {
+  PairSide xs[3 * MOST_PARTS], ws[3 * MOST_PARTS];
+  const int nx = pair_sides(xs, t, k, n, false, swiglu, split_bytes), nw = pair_sides(ws, k, n, t, true, false, split_bytes);
+  PairPlan best{{GemmTile::T256, 1}, {GemmTile::T256, 1}, true, true};
+  double best_cost = 1e300;
+  for (int i = 0; i < nx; i++)
+    for (int j = 0; j < nw; j++) {
+      const PairSide &x = xs[i], &w = ws[j];
+      if (x.bytes + w.bytes > split_bytes) continue;
+      const bool x128 = x.c->tile == GemmTile::T128, w128 = w.c->tile == GemmTile::T128, both = x128 && w128;
+      const int64_t slots = both ? 512 : 256, wgs = std::min(x.wgs + w.wgs, slots);
+      const double dx = (double)x.per * (x128 && !both ? MIXED_128[0] : k_tile_time(*x.c, wgs)) + x.fixed;
+      const double dw = (double)w.per * (w128 && !both ? MIXED_128[1] : k_tile_time(*w.c, wgs)) + w.fixed;
+      const double besides = x.parts + w.parts + LONGEST * std::max(dx, dw);
+      for (const bool x_first : {true, false}) {
+        const double cost = besides + (x_first ? makespan(x.wgs, dx, w.wgs, dw, slots) : makespan(w.wgs, dw, x.wgs, dx, slots));
+        if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {{x.c->tile, x.splits}, {w.c->tile, w.splits}, x_first, true}; }
+      }
+    }
+  // A long launch runs at the power cap: work packed tighter lowers the clock, and two products side by side evict each
+  // other's panels.  It gains where the two last rounds complement each other (5125 x 3200 x 12800 711 us apart, 630
+  // together in a layer, estimate 1.16x; a 1024-wide layer on 13824 tokens 1555 -> 1510), the longest not by a few per cent of the
+  // estimate: 2999 x 3584 x 37888, estimate 1.065x, makes its layer 0.6-1.7 % slower, 8192 x 4096 x 22016 (1.005x) 2160 -> 2207.
+  // The SwiGLU gradient's epilogue moves three matrices while no matrix core works; beside another product's k-loops that is
+  // hidden (8192 x 11008 x 4096 1226 -> 1119 us, 32768 x 14336 x 4096 6006 -> 5790).
+  if (!swiglu && best_cost > 150) {
+    auto apart = [](const PairSide* side, int count) {
+      double least = 1e300;
+      for (int i = 0; i < count; i++) {
+        const PairSide& p = side[i];
+        const int64_t slots = p.c->slots, rounds = p.wgs / slots, rest = p.wgs % slots;
+        const double longest = (double)p.per * k_tile_time(*p.c, std::min(p.wgs, slots)) + p.fixed;
+        least = std::min(least, (double)rounds * longest + (rest ? (double)p.per * k_tile_time(*p.c, rest) + p.fixed : 0.0) + p.parts + LONGEST * longest);
+      }
+      return least;
+    };
+    best.pays = best_cost * (best_cost > 600 ? 1.07 : 1.02) < apart(xs, nx) + apart(ws, nw) + 2.5;
+  }
+  return best;
+}
+size_t part_bytes(const GemmPlan& p, int64_t m, int64_t n) { return p.splits > 1 ? (size_t)p.splits * (size_t)m * (size_t)n * 4 : 0; }
 }  // namespace
 
 size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t) {
@@ -372,25 +477,47 @@ GemmForm gemm_form(const GemmArgs& g) {
   return {pl.tile == GemmTile::T256 ? 256 : pl.tile == GemmTile::T192 ? 192 : 128, pl.tile == GemmTile::T128 ? 128 : 256, pl.splits};
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  if (g.m <= 0 || g.n <= 0) return hipSuccess;
+namespace {
+// The product as its K parts: partial results to the scratch, everything that the epilogue adds left to the reduction.
+GemmArgs part_of(const GemmArgs& g) {
+  GemmArgs part = g;
+  part.c = g.splitk_ws;
+  part.out_fp32 = 1;
+  part.accumulate = 0;
+  part.bias = nullptr;
+  part.residual = nullptr;
+  return part;
+}
+hipError_t reduce_parts(const GemmArgs& g, int splits, hipStream_t s) {
+  return launch_splitk_reduce((const float*)g.splitk_ws, g.c, splits, g.m, g.n, g.out_fp32, g.accumulate, g.bias, g.residual, g.ldres, s);
+}
+}  // namespace
+
+// What no form of a product accepts.
+static bool refused(const GemmArgs& g) {
   if (g.rope_table && (!g.rope_pos || !gemm_rope_fusable(g.m, g.n, g.k, g.rope_head_dim) || g.a_layout != 0 ||
                        g.b_layout != 0 || g.out_fp32 || g.residual || g.swiglu_act || g.swiglu_dpre || g.ldc != g.n ||
                        g.rope_cols % 128 != 0 || g.rope_cols > g.n))
-    return hipErrorInvalidValue;
+    return true;
   if ((g.swiglu_dpre || g.swiglu_pre) &&
       (!g.swiglu_dpre || !g.swiglu_pre || g.swiglu_act || !gemm_swiglu_bwd_fusable(g.m, g.n, g.k) || g.a_layout != 0 ||
        g.b_layout != 1 || g.out_fp32 || g.bias || g.residual || g.ldc != 2 * g.n))
-    return hipErrorInvalidValue;
+    return true;
   if (g.swiglu_act && (!gemm_swiglu_fusable(g.m, g.n, g.k) || g.a_layout != 0 || g.b_layout != 0 || g.out_fp32 ||
                        g.bias || g.residual || g.ldc != g.n))
-    return hipErrorInvalidValue;
+    return true;
   // operands are addressed through 32-bit buffer offsets
   if ((g.a_layout ? g.k : g.m) * g.lda * 2 > GEMM_MAX_OPERAND_BYTES || (g.b_layout ? g.n : g.k) * g.ldb * 2 > GEMM_MAX_OPERAND_BYTES)
-    return hipErrorInvalidValue;
+    return true;
   // the epilogue addresses a sub-tile of up to 128 rows with 32-bit offsets from its first element
   if (g.ldc * (g.out_fp32 ? 4 : 2) * 128 > 0xFFFFFFFFll || (g.residual && g.ldres * 2 * 128 > 0xFFFFFFFFll))
-    return hipErrorInvalidValue;
+    return true;
+  return false;
+}
+
+hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
+  if (g.m <= 0 || g.n <= 0) return hipSuccess;
+  if (refused(g)) return hipErrorInvalidValue;
   const bool tiled = takes_tile_kernel(g);
   const GemmPlan pl = plan_of(g);
   // timing classes: the three layouts of the large tiles, the 192-row form, and the small tiles
@@ -405,19 +532,64 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     // 128x128 tiles so that more workgroups exist
     return small ? launch_general<128, 128, 64, 64>(g, s) : launch_general<256, 256, 128, 64>(g, s);
   }
-  GemmArgs part = g;
-  part.c = g.splitk_ws;
-  part.out_fp32 = 1;
-  part.accumulate = 0;
-  part.bias = nullptr;
-  part.residual = nullptr;
   hipError_t e;
   {
     ProfScope prof(cls, flops, s);
-    e = launch_tiles(part, pl.tile, pl.splits, s);
+    e = launch_tiles(part_of(g), pl.tile, pl.splits, s);
   }
-  if (e != hipSuccess) return e;
-  return launch_splitk_reduce((const float*)g.splitk_ws, g.c, pl.splits, g.m, g.n, g.out_fp32, g.accumulate, g.bias, g.residual, g.ldres, s);
+  return e != hipSuccess ? e : reduce_parts(g, pl.splits, s);
+}
+
+
+// Whether the two gradients may share a launch: both take the tile kernel, on operands that start on 16 bytes (the input
+// gradient's large tiles are loaded straight to LDS).
+static bool pairable(const GemmArgs& x, const GemmArgs& w) {
+  return x.m > 0 && x.n > 0 && w.m > 0 && w.n > 0 && takes_tile_kernel(x) && takes_tile_kernel(w) && (((uintptr_t)x.a | (uintptr_t)x.b) & 15) == 0;
+}
+
+LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
+  if (!pairable(x, w)) return {false, gemm_form(x), gemm_form(w), false};
+  const PairPlan pl = plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0);
+  if (!pl.pays) return {false, gemm_form(x), gemm_form(w), false};
+  auto form = [](const GemmPlan& p) { return GemmForm{p.tile == GemmTile::T256 ? 256 : p.tile == GemmTile::T192 ? 192 : 128, p.tile == GemmTile::T128 ? 128 : 256, p.splits}; };
+  return {true, form(pl.x), form(pl.w), pl.x_first};
+}
+
+size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu) {
+  if (t <= 0) return 0;
+  const PairPlan pl = plan_pair(t, k, n, swiglu, SIZE_MAX);
+  if (!pl.pays) return std::max(gemm_splitk_ws_bytes(t, k, n, false), gemm_splitk_ws_bytes(k, n, t, true));
+  return part_bytes(pl.x, t, k) + part_bytes(pl.w, k, n);
+}
+
+hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s) {
+  const bool pair = pairable(x, w);
+  const PairPlan pl = pair ? plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0) : PairPlan{};
+  if (!pair || !pl.pays) {
+    const hipError_t e = launch_gemm(w, s);
+    return e != hipSuccess ? e : launch_gemm(x, s);
+  }
+  if (refused(x) || refused(w)) return hipErrorInvalidValue;
+  GemmArgs xa = x, wa = w;   // the parts of both are in the scratch at the same time
+  wa.splitk_ws = (char*)x.splitk_ws + part_bytes(pl.x, x.m, x.n);
+  const GemmArgs xp = pl.x.splits > 1 ? part_of(xa) : xa, wp = pl.w.splits > 1 ? part_of(wa) : wa;
+  GemmPairParams p;
+  p.x = tile_params(xp, pl.x.tile, pl.x.splits);
+  p.w = tile_params(wp, pl.w.tile, pl.w.splits);
+  p.x_tiles = p.x.tiles_m * p.x.tiles_n;
+  p.w_tiles = p.w.tiles_m * p.w.tiles_n;
+  const int x_wgs = p.x_tiles * pl.x.splits, w_wgs = p.w_tiles * pl.w.splits;
+  p.x_first = pl.x_first;
+  p.first = pl.x_first ? x_wgs : w_wgs;
+  hipError_t e;
+  {
+    const bool small = pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128;
+    ProfScope prof(small ? PROF_GEMM_SMALL : PROF_GEMM_DX, 4.0 * (double)x.m * (double)x.n * (double)x.k, s);
+    e = launch_gemm_pair_tiles(p, pl.x.tile, xp.out_fp32 != 0, x.swiglu_dpre ? EPI_SWIGLU_BWD : EPI_PLAIN, pl.w.tile, x_wgs + w_wgs, s);
+  }
+  if (e == hipSuccess && pl.x.splits > 1) e = reduce_parts(xa, pl.x.splits, s);
+  if (e == hipSuccess && pl.w.splits > 1) e = reduce_parts(wa, pl.w.splits, s);
+  return e;
 }
 
 }  // namespace mllm

@@ -71,6 +71,15 @@ enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_R
 template <bool A_T, bool B_T>
 hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
 
+// A linear map's input gradient (x) and weight gradient (w) in one launch (gemm_pair.hip).
+struct GemmPairParams {
+  GemmParams x, w;
+  int x_tiles, w_tiles;   // workgroups of one part of the K loop
+  int first;              // workgroups of the product that comes first
+  int x_first;
+};
+hipError_t launch_gemm_pair_tiles(const GemmPairParams& p, GemmTile x_tile, bool x_f32, int x_epi, GemmTile w_tile, int workgroups, hipStream_t s);
+
 // Workgroups are dealt round-robin to the 8 XCDs.  Renumber so that each XCD gets a contiguous
 // range of tile ids, then walk the tile grid in panels of group_m tile-rows.
 __device__ __forceinline__ void tile_of_block(int pid, int nblk, int tiles_m, int tiles_n, int group_m,

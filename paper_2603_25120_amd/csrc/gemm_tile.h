@@ -141,8 +141,10 @@ __device__ __forceinline__ void mfma_results_ready() {
 
 // K must be a multiple of 64 unless k runs along the rows of both operands (the rows of the last k-tile that lie
 // past K are then past the operands' ends).
+// pid of nblk workgroups of the product, each of them with part `split` of the K loop; As0 .. Bs1: the two LDS stages of
+// both operands (distinct variables of the kernel, so that the compiler can tell their accesses apart).
 template <int WM, int WN, bool A_T, bool B_T, bool OUT_F32, int EPI>
-__device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
+__device__ __forceinline__ void gemm_dma_tile(GemmParams p, int pid, int nblk, int split, bf16_t* As0, bf16_t* As1, bf16_t* Bs0, bf16_t* Bs1) {
   static_assert(EPI == EPI_PLAIN || (!OUT_F32 && !A_T && B_T == (EPI != EPI_SWIGLU_BWD)), "fused epilogues: bf16, forward layout (gradient: W stored [N, K])");
   constexpr int BM = 32 * WM, BN = 32 * WN;
   constexpr int NU = WM + WN;         // fragments per k-step
@@ -158,23 +160,19 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
   constexpr int BAR = RS * (NU - 1) + (NS < 48 ? 4 : DIRECT ? 8 : 10);
   constexpr int BAR2 = DIRECT ? NS - 1 : -1;   // second barrier of a k-tile, direct loads only
   static_assert(BAR < NS, "the first k-step's reads are issued before the barrier");
-  __shared__ __attribute__((aligned(1024))) bf16_t As0[TA::SIZE];
-  __shared__ __attribute__((aligned(1024))) bf16_t As1[TA::SIZE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Bs0[TB::SIZE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Bs1[TB::SIZE];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn;
-  tile_of_block(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+  tile_of_block(pid, nblk, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   TA la;
   TB lb;
   la.init(p.lda, m0, p.M, lane, wave);
   lb.init(p.ldb, n0, p.N, lane, wave, EPI == EPI_SWIGLU ? p.N >> 1 : 0, 8 * WN);
 
-  // Split-K: workgroup row blockIdx.y owns k-tiles [kt0, kt0 + nk) and writes its own partial C.
-  const int kt0 = blockIdx.y * p.kt_per_split;
+  // Split-K: part `split` owns k-tiles [kt0, kt0 + nk) and writes its own partial C.
+  const int kt0 = split * p.kt_per_split;
   const int last_tile = (int)((p.K + BK - 1) / BK) - 1;
   const int nk = min(p.kt_per_split, last_tile + 1 - kt0);   // at least one: the host leaves no split empty
 
@@ -352,7 +350,7 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
   static_assert(2 * 16 * (16 * WN + 4) * 4 <= 2 * (TA::SIZE < TB::SIZE ? TA::SIZE : TB::SIZE), "two staged rows of blocks in a tile's LDS");
 
   const int64_t row0 = m0 + wm * 16 * WM, col0 = n0 + wn * 16 * WN;
-  if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + blockIdx.y * p.c_split_stride;
+  if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + split * p.c_split_stride;
   if constexpr (EPI == EPI_SWIGLU) {
     store_blocks_swiglu<WM, WN>(p, acc, row0, (n0 >> 1) + 8 * WN * wn, lane_out, out_stage);
   } else if constexpr (EPI == EPI_SWIGLU_BWD) {
@@ -364,7 +362,8 @@ __device__ __forceinline__ void gemm_dma_tile(GemmParams p) {
 
 template <int WM, int WN, bool A_T, bool B_T, bool OUT_F32, int EPI>
 __global__ __launch_bounds__(256, WM * WN <= 16 ? 2 : 1) void gemm4_kernel(GemmParams p) {
-  gemm_dma_tile<WM, WN, A_T, B_T, OUT_F32, EPI>(p);
+  __shared__ __attribute__((aligned(1024))) bf16_t As0[32 * WM * BK], As1[32 * WM * BK], Bs0[32 * WN * BK], Bs1[32 * WN * BK];
+  gemm_dma_tile<WM, WN, A_T, B_T, OUT_F32, EPI>(p, blockIdx.x, gridDim.x, blockIdx.y, As0, As1, Bs0, Bs1);
 }
 
 }  // namespace

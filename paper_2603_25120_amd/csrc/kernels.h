@@ -53,6 +53,13 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // What launch_gemm takes for a product: output tile (0 x 0: the general kernel) and parts of the K loop.
 struct GemmForm { int tile_rows, tile_cols, k_parts; };
 GemmForm gemm_form(const GemmArgs& g);
+// Both gradients of a linear map Y [t, n] = X [t, k] . W [k, n] in one launch: x the arguments of dX = dY . W^T (or of its SwiGLU form), w
+// those of dW (+)= X^T . dY.  Both name the same scratch.  Where that does not pay, on operands that the tile kernel does not
+// take and on those that do not start on 16 bytes, two launches.
+hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s);
+struct LinearBwdForm { bool paired; GemmForm x, w; bool x_first; };
+LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w);
+size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu);   // scratch that launch_linear_bwd wants
 // Scratch bytes launch_gemm wants for a product of this shape (0: it will not split the K loop); a_t: A stored
 // [K, M].
 size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t);

@@ -179,6 +179,48 @@ mllm_status_t mllm_gemm_form(int64_t m, int64_t n, int64_t k, int a_layout, int 
   return MLLM_OK;
 }
 
+static void linear_bwd_args(GemmArgs& x, GemmArgs& w, int64_t t, int64_t k, int64_t n) {
+  x.m = t; x.n = k; x.k = n; x.lda = n; x.ldb = n; x.ldc = k; x.a_layout = 0; x.b_layout = 1;
+  w.m = k; w.n = n; w.k = t; w.lda = k; w.ldb = n; w.ldc = n; w.a_layout = 1; w.b_layout = 0; w.out_fp32 = 1;
+}
+
+mllm_status_t mllm_op_linear_bwd(const void* dy, const void* x, const void* w, void* dx, void* dw, int64_t t, int64_t k,
+                                 int64_t n, int accumulate, const void* swiglu_pre, void* workspace, size_t scratch_bytes,
+                                 void* hip_stream) {
+  if (!dy || !x || !w || !dx || !dw) return op_fail(MLLM_ERR_NULL, "a tensor pointer is NULL");
+  if (t < 0 || k <= 0 || n <= 0) return op_fail(MLLM_ERR_SHAPE, "sizes must be positive");
+  if (k % 8 || n % 8) return op_fail(MLLM_ERR_SHAPE, "widths must be multiples of 8");
+  if (scratch_bytes && !workspace) return op_fail(MLLM_ERR_NULL, "workspace is NULL");
+  if ((uintptr_t)workspace % ALIGN) return op_fail(MLLM_ERR_WORKSPACE, "the workspace must be 256-byte aligned");
+  if (swiglu_pre && !gemm_swiglu_bwd_fusable(t, k, n))
+    return op_fail(MLLM_ERR_UNSUPPORTED, "the fused form needs n %% 64 == 0 and at least 200 tiles of 256 x 256");
+  GemmArgs gx{}, gw{};
+  linear_bwd_args(gx, gw, t, k, n);
+  gx.a = dy; gx.b = w; gx.c = dx;
+  if (swiglu_pre) { gx.c = nullptr; gx.ldc = 2 * k; gx.swiglu_pre = swiglu_pre; gx.swiglu_dpre = dx; }
+  gw.a = x; gw.b = dy; gw.c = dw; gw.accumulate = accumulate;
+  gx.splitk_ws = gw.splitk_ws = scratch_bytes ? workspace : nullptr;
+  gx.splitk_ws_bytes = gw.splitk_ws_bytes = scratch_bytes;
+  OP_TRY(launch_linear_bwd(gx, gw, (hipStream_t)hip_stream));
+  return MLLM_OK;
+}
+
+mllm_status_t mllm_linear_bwd_form(int64_t t, int64_t k, int64_t n, int swiglu, size_t scratch_bytes, int32_t* form,
+                                   size_t* scratch_wanted) {
+  if (!form) return op_fail(MLLM_ERR_NULL, "form is NULL");
+  if (t < 0 || k <= 0 || n <= 0) return op_fail(MLLM_ERR_SHAPE, "sizes must be positive");
+  GemmArgs gx{}, gw{};
+  linear_bwd_args(gx, gw, t, k, n);
+  if (swiglu) gx.swiglu_dpre = &gx;                          // only whether there is one
+  gx.splitk_ws = gw.splitk_ws = scratch_bytes ? &gx : nullptr;   // likewise
+  gx.splitk_ws_bytes = gw.splitk_ws_bytes = scratch_bytes;
+  const LinearBwdForm f = linear_bwd_form(gx, gw);
+  const int32_t v[8] = {f.paired, f.x.tile_rows, f.x.tile_cols, f.x.k_parts, f.w.tile_rows, f.w.tile_cols, f.w.k_parts, f.x_first};
+  for (int i = 0; i < 8; i++) form[i] = v[i];
+  if (scratch_wanted) *scratch_wanted = linear_bwd_ws_bytes(t, k, n, swiglu != 0);
+  return MLLM_OK;
+}
+
 mllm_status_t mllm_op_gemm_swiglu(const void* x, const void* w_gu, void* pre, void* act, int64_t m,
                                   int64_t f, int64_t k, void* hip_stream) {
   if (!x || !w_gu || !pre || !act) return op_fail(MLLM_ERR_NULL, "a tensor pointer is NULL");

@@ -254,15 +254,29 @@ size_t layer_partial_bytes(const mllm_layer_desc_t& L, int64_t T) {
   return (size_t)floats * 4;
 }
 
-// Scratch of the three products of a linear map [T, k] -> [T, n]: Y, dX and dW.
-size_t linear_split_bytes(int64_t T, int64_t k, int64_t n) {
-  return std::max(gemm_splitk_ws_bytes(k, n, T, true), std::max(gemm_splitk_ws_bytes(T, n, k, false), gemm_splitk_ws_bytes(T, k, n, false)));
+// Scratch of the three products of a linear map [T, k] -> [T, n]: Y on its own, dX and dW together (dX in its SwiGLU form
+// where that applies).
+size_t linear_split_bytes(int64_t T, int64_t k, int64_t n, bool swiglu = false) {
+  return std::max(gemm_splitk_ws_bytes(T, n, k, false), linear_bwd_ws_bytes(T, k, n, swiglu && gemm_swiglu_bwd_fusable(T, k, n)));
+}
+// The most scratch that a product of the layer asks for.
+size_t layer_split_bytes(const mllm_layer_desc_t& L, int64_t T) {
+  const int64_t d = L.d_model, f = L.d_ff;
+  if (L.kind == MLLM_LAYER_PROJECTOR) {
+    const int64_t d_in = d * std::max(1, (int)L.merge);
+    return f ? std::max(linear_split_bytes(T, d_in, f), linear_split_bytes(T, f, L.d_out)) : linear_split_bytes(T, d_in, L.d_out);
+  }
+  const bool vit = L.kind == MLLM_LAYER_VIT;
+  return std::max(std::max(linear_split_bytes(T, f, d, !vit), linear_split_bytes(T, d, vit ? f : 2 * f)),
+                  std::max(linear_split_bytes(T, d, d), linear_split_bytes(T, d, nqkv_of(L))));
 }
 
 // Bytes of partial dK and dV that a part of the dK/dV pass takes.
 size_t kv_part_bytes(const AttnLists& A, int64_t T) { return (size_t)2 * (size_t)T * A.hkv * A.head_dim * 4; }
 
-Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
+// scratch: also how much of it the products and dK/dV passes would like.  That does not move anything else, so the calls
+// that are given a workspace leave the pricing of plans to the one that sizes it.
+Plan make_plan(const mllm_stage* st, const mllm_batch_t* b, bool scratch = false) {
   Plan P;
   const bool need_img = st->n_vit > 0 || st->proj >= 0;
   const bool need_seq = st->n_dec > 0 || st->proj >= 0;
@@ -346,19 +360,12 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   }
   M.bytes = ws.off;
 
-  size_t part = 0, part_all = 0, a = 0, bb = 0, c = 0, e = 0, delta = 0, g = 0, proj = 0, split = 0, qkn = 0;
+  size_t part = 0, part_all = 0, a = 0, bb = 0, c = 0, e = 0, delta = 0, g = 0, proj = 0, qkn = 0;
   for (const mllm_layer_desc_t& L : st->layers) {
     if (L.kind == MLLM_LAYER_PROJECTOR) {
-      const int64_t d_in = (int64_t)L.d_model * std::max(1, (int)L.merge);
       proj = (size_t)P.T_con * L.d_out * 2;
       P.largest_operand_bytes = std::max<int64_t>(P.largest_operand_bytes, (int64_t)P.T_img * std::max(std::max(L.d_model, L.d_out), L.d_ff) * 2);
-      if (L.d_ff) {
-        split = std::max(split, linear_split_bytes(P.T_con, d_in, L.d_ff));
-        split = std::max(split, linear_split_bytes(P.T_con, L.d_ff, L.d_out));
-        a = std::max(a, (size_t)P.T_con * L.d_ff * 2);
-      } else {
-        split = std::max(split, linear_split_bytes(P.T_con, d_in, L.d_out));
-      }
+      if (L.d_ff) a = std::max(a, (size_t)P.T_con * L.d_ff * 2);
       if (P.pool > 1) c = std::max(c, (size_t)P.T_con * L.d_model * 2);   // gradient of the pooled rows
       const size_t sums = (size_t)colsum_partial_rows(P.T_con) * (L.d_out + L.d_ff) * 4;
       part = std::max(part, sums);
@@ -383,11 +390,6 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
     if (L.qk_norm) qkn = std::max(qkn, T * nq * 2);
     delta = std::max(delta, T * L.n_q_heads * 4);
     g = std::max(g, T * d * 2);
-    const int64_t fup = L.kind == MLLM_LAYER_VIT ? f : 2 * f;
-    split = std::max(split, linear_split_bytes(T, f, d));
-    split = std::max(split, linear_split_bytes(T, d, fup));
-    split = std::max(split, linear_split_bytes(T, d, d));
-    split = std::max(split, linear_split_bytes(T, d, nq));
   }
   P.rope_of.assign(st->layers.size(), -1);
   if (st->n_dec > 0) {
@@ -420,13 +422,22 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b) {
   P.w_g1 = ws.take(g);
   P.w_proj = ws.take(proj);
   P.w_scratch = std::max<size_t>(ws.off, ALIGN);
-  P.scratch_bytes = align_up(std::max(split, dkv));
+  if (scratch) {
+    size_t split = 0;
+    const mllm_layer_desc_t* before = nullptr;   // a stack of equal layers is priced once
+    for (const mllm_layer_desc_t& L : st->layers) {
+      if (before && memcmp(before, &L, sizeof L) == 0) continue;
+      before = &L;
+      split = std::max(split, layer_split_bytes(L, L.kind == MLLM_LAYER_PROJECTOR ? P.T_con : L.kind == MLLM_LAYER_VIT ? P.T_img : P.T_seq));
+    }
+    P.scratch_bytes = align_up(std::max(split, dkv));
+  }
   return P;
 }
 
 // The partial results a workspace of this size has room for (check_io has seen to the rest).
 void fit_scratch(Plan& P, size_t workspace_bytes) {
-  P.scratch_bytes = std::min(P.scratch_bytes, workspace_bytes - P.w_scratch);
+  P.scratch_bytes = workspace_bytes - P.w_scratch;
   for (AttnLists& A : P.meta.attn) {
     const size_t part = kv_part_bytes(A, A.img ? P.T_img : P.T_seq);
     if (part) A.kv_parts = std::max(1, (int)std::min<size_t>(A.kv_parts, P.scratch_bytes / part));
@@ -525,25 +536,22 @@ hipError_t linear_fwd_swiglu(const void* x, const void* w, void* pre, void* act,
   g.swiglu_act = act;
   return launch_gemm(g, s);
 }
-// dX[T,k] = dY[T,n].W[k,n]^T
-hipError_t linear_dx(const void* dy, const void* w, void* dx, int64_t T, int64_t k, int64_t n, hipStream_t s, SplitWs ws) {
-  return gemm(dy, n, 0, w, n, 1, dx, k, T, k, n, 0, 0, nullptr, nullptr, 0, s, ws.p, ws.bytes);
-}
-// [d gate | d up][T,2f] from dY[T,d], W_d[f,d] and pre = [gate | up][T,2f]: dA = dY.W_d^T stays in registers
-hipError_t linear_dx_swiglu(const void* dy, const void* w, const void* pre, void* dpre, int64_t T, int64_t f,
-                            int64_t d, hipStream_t s) {
-  GemmArgs g;
-  g.splitk_ws = nullptr; g.splitk_ws_bytes = 0;
-  g.a = dy; g.b = w; g.c = nullptr; g.m = T; g.n = f; g.k = d; g.lda = d; g.ldb = d; g.ldc = 2 * f;
-  g.a_layout = 0; g.b_layout = 1; g.out_fp32 = 0; g.accumulate = 0;
-  g.bias = nullptr; g.residual = nullptr; g.ldres = 0;
-  g.swiglu_pre = pre; g.swiglu_dpre = dpre;
-  return launch_gemm(g, s);
-}
-// dW[k,n] (+)= X[T,k]^T.dY[T,n]
-hipError_t linear_dw(const void* x, const void* dy, void* dw, int64_t T, int64_t k, int64_t n, int accumulate,
-                     hipStream_t s, SplitWs ws) {
-  return gemm(x, k, 1, dy, n, 0, dw, n, k, n, T, 1, accumulate, nullptr, nullptr, 0, s, ws.p, ws.bytes);
+// dX[T,k] = dY[T,n].W[k,n]^T and dW[k,n] (+)= X[T,k]^T.dY[T,n].  With swiglu_pre = [gate | up][T,2k] the input gradient stays
+// in registers and dX receives [d gate | d up][T,2k].
+hipError_t linear_bwd(const void* dy, const void* x, const void* w, void* dx, void* dw, int64_t T, int64_t k, int64_t n, int accumulate,
+                      hipStream_t s, SplitWs ws, const void* swiglu_pre = nullptr) {
+  GemmArgs gx, gw;
+  gx.splitk_ws = gw.splitk_ws = ws.p; gx.splitk_ws_bytes = gw.splitk_ws_bytes = ws.bytes;
+  gx.bias = gw.bias = gx.residual = gw.residual = nullptr; gx.ldres = gw.ldres = 0;
+  gx.a = dy; gx.b = w; gx.c = dx; gx.m = T; gx.n = k; gx.k = n; gx.lda = n; gx.ldb = n; gx.ldc = k;
+  gx.a_layout = 0; gx.b_layout = 1; gx.out_fp32 = 0; gx.accumulate = 0;
+  if (swiglu_pre) {
+    gx.c = nullptr; gx.ldc = 2 * k;
+    gx.swiglu_pre = swiglu_pre; gx.swiglu_dpre = dx;
+  }
+  gw.a = x; gw.b = dy; gw.c = dw; gw.m = k; gw.n = n; gw.k = T; gw.lda = k; gw.ldb = n; gw.ldc = n;
+  gw.a_layout = 1; gw.b_layout = 0; gw.out_fp32 = 1; gw.accumulate = accumulate;
+  return launch_linear_bwd(gx, gw, s);
 }
 
 // qk: the [T, nq] matrix whose q and k columns attention reads; v: the one whose v columns it reads
@@ -673,20 +681,18 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
   const int64_t fup = vit ? f : 2 * f;
 
   // MLP
-  K_TRY(linear_dw(act, dy, dprm[iwdn], T, f, d, accumulate, s, split));
   if (vit && !dy_colsum_done) K_TRY(launch_colsum(dy, d, (float*)dprm[ibdn], sums, T, d, s));
   char* dpre = vit ? wa : wb;
   if (!vit && gemm_swiglu_bwd_fusable(T, f, d)) {
-    K_TRY(linear_dx_swiglu(dy, prm[iwdn], pre, dpre, T, f, d, s));
+    K_TRY(linear_bwd(dy, act, prm[iwdn], dpre, dprm[iwdn], T, f, d, accumulate, s, split, pre));
   } else {
-    K_TRY(linear_dx(dy, prm[iwdn], wa, T, f, d, s, split));
+    K_TRY(linear_bwd(dy, act, prm[iwdn], wa, dprm[iwdn], T, f, d, accumulate, s, split));
     if (vit)   // the bias gradient (column sums of dpre) comes out of the same pass
       K_TRY(launch_gelu_bwd_colsum(L.act, wa, pre, dpre, (float*)dprm[ibup], sums, T, f, s));
     else
       K_TRY(launch_act_bwd(L.act, wa, pre, dpre, T, f, s));
   }
-  K_TRY(linear_dw(n2, dpre, dprm[iwup], T, d, fup, accumulate, s, split));
-  K_TRY(linear_dx(dpre, prm[iwup], wc, T, d, fup, s, split));
+  K_TRY(linear_bwd(dpre, n2, prm[iwup], wc, dprm[iwup], T, d, fup, accumulate, s, split));
   // the gradient that leaves this norm is that of the output projection's output: its column sums are
   // the projection's bias gradient, formed in the same pass where the row width allows
   const bool bo_fused = vit && norm_bwd_colsum_fusable(d);
@@ -694,9 +700,8 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
                         (float*)dprm[ig2], vit ? (float*)dprm[ib2n] : nullptr, sums, T, d, d, s,
                         bo_fused ? (float*)dprm[ibo] : nullptr));
   // attention block
-  K_TRY(linear_dw(o, wd, dprm[iwo], T, d, d, accumulate, s, split));
   if (vit && !bo_fused) K_TRY(launch_colsum(wd, d, (float*)dprm[ibo], sums, T, d, s));
-  K_TRY(linear_dx(wd, prm[iwo], wc, T, d, d, s, split));
+  K_TRY(linear_bwd(wd, o, prm[iwo], wc, dprm[iwo], T, d, d, accumulate, s, split));
   // With QK normalisation the gradient of the normalised q, k goes to a matrix of its own (same
   // columns as in d qkv); the norm's backward then writes the gradient of the projection's q, k
   // beside dV in d qkv.
@@ -721,9 +726,8 @@ mllm_status_t layer_bwd(const mllm_layer_desc_t& L, const void* const* prm, void
                           nullptr, we + q_cols * 2, (float*)dprm[n_base + 1], nullptr, sums,
                           T, k_cols, nq, s));
   }
-  K_TRY(linear_dw(n1, we, dprm[iwqkv], T, d, nq, accumulate, s, split));
   if (ibqkv >= 0) K_TRY(launch_colsum(we, nq, (float*)dprm[ibqkv], sums, T, nq, s));
-  K_TRY(linear_dx(we, prm[iwqkv], wc, T, d, nq, s, split));
+  K_TRY(linear_bwd(we, n1, prm[iwqkv], wc, dprm[iwqkv], T, d, nq, accumulate, s, split));
   K_TRY(launch_norm_bwd(vit ? 0 : 1, wc, x, prm[ig1], (const float*)(saved + S.stats1), wd, dx,
                         (float*)dprm[ig1], vit ? (float*)dprm[ib1n] : nullptr, sums, T, d, d, s, dx_colsum));
   return MLLM_OK;
@@ -841,7 +845,7 @@ mllm_status_t mllm_stage_sizes(const mllm_stage_t* st, const mllm_batch_t* b, si
                                size_t* workspace_bytes) {
   mllm_status_t r = check_batch(st, b);
   if (r != MLLM_OK) return r;
-  Plan P = make_plan(st, b);
+  Plan P = make_plan(st, b, true);
   if ((r = check_plan(P)) != MLLM_OK) return r;
   // The staging ring grows here, where the caller sizes its own buffers, so that fwd / bwd find it
   // large enough.  Best effort: a failure (no device in this process) is left to fwd / bwd, which
@@ -964,16 +968,13 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
         const char* pre = saved + P.saved[i].pre;
         const char* act = saved + P.saved[i].act;
         char* dh = ws + P.w_a;     // d act, then d pre in place   [T_con, d_ff]
-        K_TRY(linear_dw(act, dproj, dprm[2], P.T_con, L.d_ff, L.d_out, accumulate, s, split));
         K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[3], sums, P.T_con, L.d_out, s));
-        K_TRY(linear_dx(dproj, prm[2], dh, P.T_con, L.d_ff, L.d_out, s, split));
+        K_TRY(linear_bwd(dproj, act, prm[2], dh, dprm[2], P.T_con, L.d_ff, L.d_out, accumulate, s, split));
         K_TRY(launch_gelu_bwd_colsum(L.act, dh, pre, dh, (float*)dprm[1], sums, P.T_con, L.d_ff, s));
-        K_TRY(linear_dw(xin, dh, dprm[0], P.T_con, d_in, L.d_ff, accumulate, s, split));
-        K_TRY(linear_dx(dh, prm[0], dxin, P.T_con, d_in, L.d_ff, s, split));
+        K_TRY(linear_bwd(dh, xin, prm[0], dxin, dprm[0], P.T_con, d_in, L.d_ff, accumulate, s, split));
       } else {
-        K_TRY(linear_dw(xin, dproj, dprm[0], P.T_con, d_in, L.d_out, accumulate, s, split));
         K_TRY(launch_colsum(dproj, L.d_out, (float*)dprm[1], sums, P.T_con, L.d_out, s));
-        K_TRY(linear_dx(dproj, prm[0], dxin, P.T_con, d_in, L.d_out, s, split));
+        K_TRY(linear_bwd(dproj, xin, prm[0], dxin, dprm[0], P.T_con, d_in, L.d_out, accumulate, s, split));
       }
       if (P.pool > 1)
         K_TRY(launch_unpool_rows(dxin, out, (const int32_t*)(ws + P.meta.row_window),
