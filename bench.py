@@ -34,16 +34,16 @@ HBM_PEAK = 8.0e12         # B/s
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_full_stage_32k.md")
 TRAFFIC_KERNELS = {   # the kernels of a timing class: plain, SwiGLU, rotary epilogue / plain, with dW in the launch, SwiGLU gradient / plain
-    "gemm_fwd": ["gemm4_kernel<8, 8, false, true, false, %d>" % epi for epi in (0, 1, 3)],
+    "gemm_fwd": ["gemm4_kernel<8, 8, false, true, false, %d>" % epi for epi in (0, 3)] + ["gemm_wide_kernel<8, 4, 2, false, true, false, %d>" % epi for epi in (0, 1)],
     "gemm_dx": ["gemm4_kernel<8, 8, false, false, false, 0>"] + ["gemm_pair_kernel<8, 8, false, %d, 8>" % epi for epi in (0, 2)],
-    "gemm_dw": ["gemm4_kernel<8, 8, true, true, true, 0>"]}
+    "gemm_dw": ["gemm_wide_kernel<8, 4, 2, true, true, true, 0>"]}
 
 
 def gemm_source_digest():
     """First 16 hex digits of the SHA-256 of the GEMM kernel sources."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gemm.hip", "gemm_common.h", "gemm_tile.h", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip"):
+    for f in ("gemm.hip", "gemm_common.h", "gemm_tile.h", "gemm_wide.h", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip"):
         with open(os.path.join(ROOT, "paper_2603_25120_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -569,9 +569,9 @@ def main():
     gemm_all = ("gemm_fwd", "gemm_dx", "gemm_dw", "gemm_small", "gemm_rows192")
     all_gemm_ms = sum(prof[c][1] for c in gemm_all)
     all_gemm_work = sum(prof[c][2] for c in gemm_all)
-    kernel_names = {"gemm_fwd": "gemm4_kernel<8, 8, false, true, false, *> (Y = X.W, 256x256x64 tiles; plain, SwiGLU and RoPE epilogues)",
+    kernel_names = {"gemm_fwd": "gemm_wide_kernel<8, 4, 2, false, true, false, *>, gemm4_kernel<8, 8, false, true, false, *> (Y = X.W, 256x256x64 tiles; plain, SwiGLU and RoPE epilogues)",
                     "gemm_dx": "gemm4_kernel<8, 8, false, false, false, *>, gemm_pair_kernel<8, 8, false, *, 8> (dX = dY.W^T, also with dW in the same launch, 256x256x64 tiles; plain and SwiGLU-gradient epilogues)",
-                    "gemm_dw": "gemm4_kernel<8, 8, true, true, true, 0> (dW = X^T.dY, fp32, 256x256x64 tiles)"}
+                    "gemm_dw": "gemm_wide_kernel<8, 4, 2, true, true, true, 0> (dW = X^T.dY, fp32, 256x256x64 tiles)"}
     traffic, traffic_note = recorded_traffic(gemm_cls, args.workload)
     # the large-tile kernels stream, per XCD, the 12 panels of an 8 x 4 block of 256 x 256 tiles (4 x 8 where A is large)
     # through L2 once: 2 M N K (1 / 2048 + 1 / 1024) bytes fetched per launch (bf16 operands)

@@ -4,10 +4,10 @@
 // (Model Profiler, "Throughput Profiling"): QKV / output / MLP projections and the connector,
 // their input gradients (dX = dY.W^T) and their weight gradients (dW = X^T.dY).
 //
-// Two kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
-// hand-placed k-loop, for every K that is a multiple of 64 and for any K of a weight gradient; plan_gemm
-// below chooses the tile and whether the K loop is split.  gemm_kernel (here): a general template for what is
-// left, K no multiple of 64 with an operand whose contiguous dimension is k.  It wants, per lane, eight
+// Three kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
+// hand-placed k-loop, for every K that is a multiple of 64 and for any K of a weight gradient; gemm_wide_kernel
+// (gemm_wide.h): the same tiles on eight wavefronts; plan_gemm below chooses the tile and whether the K loop is split.
+// gemm_kernel (here): a general template for what is left, K no multiple of 64 with an operand whose contiguous dimension is k.  It wants, per lane, eight
 // consecutive values along the contraction index for v_mfma_f32_32x32x16_bf16: operands whose
 // contraction index is contiguous in memory are staged in LDS as [row][k] and fetched with one 16-byte read;
 // operands whose contraction index is the strided one are staged as they lie in memory, [k][row], and
@@ -242,11 +242,25 @@ GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
   }
   return p;
 }
+// Whether a tile is taken on eight wavefronts (gemm_wide.h, where both sides' times stand).  128x128: as long as every workgroup
+// has a CU to itself.  The large tiles: where an operand is stored [K, .], short of contractions over 8192 in
+// forward layout (32768 x 4096 x 14336 2710 us on four wavefronts, 2750 on eight; at 4096 100 and 95).  The rotary epilogue of 128
+// wide heads wants a head's columns in one wavefront.
+bool takes_wide_form(const GemmArgs& g, GemmTile tile, int64_t workgroups) {
+  if ((((uintptr_t)g.a | (uintptr_t)g.b) & 15) || (g.a_layout != 0 && g.b_layout != 0)) return false;
+  if (tile == GemmTile::T128) return workgroups <= GEMM_CUS && !g.swiglu_dpre;
+  if (g.b_layout != 0 || (g.rope_table && g.rope_head_dim == 128)) return false;
+  return g.a_layout != 0 || g.k <= 8192;
+}
 hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
   const GemmParams p = tile_params(g, tile, splits);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
   const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
   const bool at = g.a_layout != 0, bt = g.b_layout == 0, f32 = g.out_fp32 != 0;   // b_layout 0: stored [K, N], transposing reads
+  if (takes_wide_form(g, tile, (int64_t)grid.x * splits)) {
+    if (at) return launch_gemm_wide<true, true>(p, tile, f32, epi, grid, s);
+    return bt ? launch_gemm_wide<false, true>(p, tile, f32, epi, grid, s) : launch_gemm_wide<false, false>(p, tile, f32, epi, grid, s);
+  }
   if (at) return bt ? launch_gemm_tile<true, true>(p, tile, f32, epi, grid, s) : launch_gemm_tile<true, false>(p, tile, f32, epi, grid, s);
   return bt ? launch_gemm_tile<false, true>(p, tile, f32, epi, grid, s) : launch_gemm_tile<false, false>(p, tile, f32, epi, grid, s);
 }
@@ -281,13 +295,11 @@ hipError_t launch_general(const GemmArgs& g, hipStream_t s) {
 // products in fp32 in a scratch buffer, summed in a fixed order afterwards) makes as many times more
 // workgroups.  The plan is the cheapest of all choices by an estimate in microseconds: rounds of workgroups times
 // (k-tiles of a part times the time of a k-tile, which grows with the number of workgroups that share power and
-// memory, plus a workgroup's start and end), plus the parts' trip through memory.  The constants were fitted to rank
-// the choices, not to time a product (single products run up to 40 % off the estimate).  Against the best of all tiles and
-// splits, measured with the present kernel on 240 random products of the layers' widths (64 to 33000 tokens) that
-// the fit had not seen, the plan loses 0.7 % on average in forward layout (worst 20 %: 7200 x 18944 x 192, 103 and 86 us),
-// 1.1 % with W stored [N, K] (worst 16 %) and 0.8 % for weight gradients (worst 11 %; 2.8 % and 27 % with the forward row
-// of constants).  Examples (us): 777 x 4096 x 14336 128x128 tiles 104, 256x256 in 4 parts 99; 777 x 4096 x 4096 33 and 47;
-// weight gradient 11008 x 4608 x 296 256x256 tiles 68, 128x128 53; 9600 x 3072 x 1408 81 and 94.
+// memory, plus a workgroup's start and end), plus the parts' trip through memory.  The constants rank the choices and do
+// not time a product (single products run up to 40 % off the estimate).  Fitted to all tiles and splits of 260 random
+// products of the layers' widths (96 to 24000 tokens): on average the plan loses 0.3 % in forward layout against the best
+// choice (worst 8 %), 1.6 % with W stored [N, K] (one 32 %, the others below 13 %) and 0.7 % for weight gradients (worst 16 %); with
+// the constants of the four-wavefront kernels alone 1.4, 3.1 and 1.7 %.
 namespace {
 struct GemmPlan { GemmTile tile; int splits; };
 struct TileCost {
@@ -295,26 +307,33 @@ struct TileCost {
   int slots;              // workgroups of a round
   int few;                // up to this many, a k-tile costs k_few; from there on k_more, rising to k_full for a full round
   double k_few, k_more, k_full, fixed;
+  double fixed_few;       // start and end of up to `few` workgroups
 };
-// [1]: A stored [K, M], the weight gradients: fp32 tiles, twice the bytes to write, make a 256x256 workgroup's end longer
-constexpr TileCost TILE_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 8.3},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 0.95, 4.0}},   // two on a CU from 257 on
-                                       {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.45, 10.5},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6},      // not for this layout
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.43, 0.70, 1.05, 4.0}}};
+// By layout: 0 forward, 1 both operands k-contiguous, 2 A stored [K, M] (weight gradients).
+constexpr TileCost TILE_COSTS[3][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.04, 1.04, 1.46, 8.1, 8.1},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.60, 0.60, 1.19, 6.7, 6.7},
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.28, 0.80, 0.97, 6.5, 4.0}},   // two on a CU from 257 on
+                                       {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.46, 8.3, 8.3},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.09, 7.3, 7.3},
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.79, 1.10, 4.2, 4.0}},
+                                       {{GemmTile::T256, 256, 256, 256, 0, 0.88, 0.88, 1.46, 7.9, 7.9},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6, 7.6},      // not for this layout
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.39, 0.83, 0.98, 3.2, 4.0}}};
+inline int cost_row(bool a_t, bool b_t) { return a_t ? 2 : b_t ? 0 : 1; }   // b_t: B stored [K, N]
 // A workgroup's start and end.  Gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB and more
 // apart (6144 x 28672 x 82 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473).
-double start_and_end(const TileCost& c, bool a_t, int64_t n) { return c.fixed + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0); }
+double start_and_end(const TileCost& c, bool a_t, int64_t n, int64_t wgs) {
+  return (wgs <= c.few ? c.fixed_few : c.fixed) + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0);
+}
 // A k-tile's time among `wgs` workgroups of at most a round.
 double k_tile_time(const TileCost& c, int64_t wgs) {
   return wgs <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(wgs - c.few) / (c.slots - c.few);
 }
 // What the parts cost besides: their trip through memory and a launch.
 double parts_cost(int64_t m, int64_t n, int64_t parts) { return parts > 1 ? 3.0 + (double)m * n * (8.0 * parts + 4.0) * 1e-7 : 0.0; }
-// split_bytes: scratch for the parts; the cheapest plan that fits it.
-GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes) {
-  const TileCost (&costs)[3] = TILE_COSTS[a_t ? 1 : 0];
+// split_bytes: scratch for the parts; the cheapest plan that fits it (and its estimate).
+GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t, size_t split_bytes, double* estimate = nullptr) {
+  const TileCost (&costs)[3] = TILE_COSTS[cost_row(a_t, b_t)];
   const int64_t nk = (k + BK - 1) / BK;
   GemmPlan best{GemmTile::T256, 1};
   if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
@@ -324,17 +343,18 @@ GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, size_t split_bytes
   for (const TileCost& c : costs) {
     if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
-    const double fixed = start_and_end(c, a_t, n);
     for (int64_t sp = 1; sp <= cap; sp++) {
       const int64_t per = (nk + sp - 1) / sp;
       if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
       const int64_t wgs = tiles * sp, rounds = wgs / c.slots, rest = wgs % c.slots;
+      const double fixed = start_and_end(c, a_t, n, wgs);
       double cost = (double)rounds * ((double)per * c.k_full + fixed);
       if (rest > 0) cost += (double)per * k_tile_time(c, rest) + fixed;
       cost += parts_cost(m, n, sp);
       if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp}; }
     }
   }
+  if (estimate) *estimate = best_cost;
   return best;
 }
 }  // namespace
@@ -348,12 +368,12 @@ namespace {
 // their own the pair takes 0.87 of the time: 576 x 1024 x 4096 (T, k, n) 26.6 -> 21.7 us, 256 x 256 x 768 14.2 -> 8.4,
 // 2880 x 1024 x 3072 52 -> 43, 5125 x 3200 x 12800 737 -> 628.
 struct PairPlan { GemmPlan x, w; bool x_first, pays; };
-constexpr TileCost PAIR_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.00, 1.00, 1.33, 8.4},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9},
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.70, 0.90, 4.3}},
-                                       {{GemmTile::T256, 256, 256, 256, 0, 1.30, 1.30, 1.45, 10.3},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9},   // not for this layout
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.44, 0.74, 0.94, 4.5}}};
+constexpr TileCost PAIR_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.00, 1.00, 1.33, 8.4, 8.4},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9, 6.9},
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.70, 0.90, 4.3, 4.3}},
+                                       {{GemmTile::T256, 256, 256, 256, 0, 1.30, 1.30, 1.45, 10.3, 10.3},
+                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9, 6.9},   // not for this layout
+                                        {GemmTile::T128, 128, 128, 512, 256, 0.44, 0.74, 0.94, 4.5, 4.5}}};
 constexpr double MIXED_128[2] = {0.52, 0.56};   // a k-tile of a 128x128 tile that has its CU to itself beside large tiles
 constexpr double LONGEST = 0.1;                 // workgroups do not all take the same time: long ones delay the end more often
 constexpr int MOST_PARTS = 8;
@@ -413,30 +433,24 @@ PairPlan plan_pair(int64_t t, int64_t k, int64_t n, bool swiglu, size_t split_by
     }
   // A long launch runs at the power cap: work packed tighter lowers the clock, and two products side by side evict each
   // other's panels.  It gains where the two last rounds complement each other (5125 x 3200 x 12800 711 us apart, 630
-  // together in a layer, estimate 1.16x; a 1024-wide layer on 13824 tokens 1555 -> 1510), the longest not by a few per cent of the
-  // estimate: 2999 x 3584 x 37888, estimate 1.065x, makes its layer 0.6-1.7 % slower, 8192 x 4096 x 22016 (1.005x) 2160 -> 2207.
+  // together in a layer, estimate 1.08x; a 1024-wide layer on 13824 tokens 1555 -> 1510), the longest not by a few per cent of the
+  // estimate: 2999 x 3584 x 37888, estimate 1.05x, makes its layer 0.6-1.7 % slower, 8192 x 4096 x 22016 (1.00x) 2160 -> 2207.
+  // Measured on their own, 40 maps whose estimate lies 4 % about even gain 1.04x.
   // The SwiGLU gradient's epilogue moves three matrices while no matrix core works; beside another product's k-loops that is
   // hidden (8192 x 11008 x 4096 1226 -> 1119 us, 32768 x 14336 x 4096 6006 -> 5790).
   if (!swiglu && best_cost > 150) {
-    auto apart = [](const PairSide* side, int count) {
-      double least = 1e300;
-      for (int i = 0; i < count; i++) {
-        const PairSide& p = side[i];
-        const int64_t slots = p.c->slots, rounds = p.wgs / slots, rest = p.wgs % slots;
-        const double longest = (double)p.per * k_tile_time(*p.c, std::min(p.wgs, slots)) + p.fixed;
-        least = std::min(least, (double)rounds * longest + (rest ? (double)p.per * k_tile_time(*p.c, rest) + p.fixed : 0.0) + p.parts + LONGEST * longest);
-      }
-      return least;
-    };
-    best.pays = best_cost * (best_cost > 600 ? 1.07 : 1.02) < apart(xs, nx) + apart(ws, nw) + 2.5;
+    double x_alone, w_alone;
+    plan_gemm(t, k, n, false, false, split_bytes, &x_alone);
+    plan_gemm(k, n, t, true, true, split_bytes, &w_alone);
+    best.pays = best_cost * (best_cost > 600 ? 1.06 : 0.94) < x_alone + w_alone + 2.5;
   }
   return best;
 }
 size_t part_bytes(const GemmPlan& p, int64_t m, int64_t n) { return p.splits > 1 ? (size_t)p.splits * (size_t)m * (size_t)n * 4 : 0; }
 }  // namespace
 
-size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t) {
-  const GemmPlan pl = plan_gemm(m, n, k, a_t, SIZE_MAX);
+size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t) {
+  const GemmPlan pl = plan_gemm(m, n, k, a_t, b_t, SIZE_MAX);
   return pl.splits > 1 ? (size_t)pl.splits * (size_t)m * (size_t)n * 4 : 0;
 }
 
@@ -467,7 +481,7 @@ GemmPlan plan_of(const GemmArgs& g) {
   if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1};
   if (g.swiglu_act || g.swiglu_dpre || g.rope_table) return {GemmTile::T256, 1};   // the fused epilogues exist for this tile
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
-  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, split_ok ? g.splitk_ws_bytes : 0);
+  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0);
 }
 }  // namespace
 
@@ -541,10 +555,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 }
 
 
-// Whether the two gradients may share a launch: both take the tile kernel, on operands that start on 16 bytes (the input
-// gradient's large tiles are loaded straight to LDS).
+// Whether the two gradients may share a launch: both take the tile kernel, on operands that start on 16 bytes (they are
+// loaded straight to LDS).
 static bool pairable(const GemmArgs& x, const GemmArgs& w) {
-  return x.m > 0 && x.n > 0 && w.m > 0 && w.n > 0 && takes_tile_kernel(x) && takes_tile_kernel(w) && (((uintptr_t)x.a | (uintptr_t)x.b) & 15) == 0;
+  return x.m > 0 && x.n > 0 && w.m > 0 && w.n > 0 && takes_tile_kernel(x) && takes_tile_kernel(w) && (((uintptr_t)x.a | (uintptr_t)x.b | (uintptr_t)w.a | (uintptr_t)w.b) & 15) == 0;
 }
 
 LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
@@ -558,7 +572,7 @@ LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
 size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu) {
   if (t <= 0) return 0;
   const PairPlan pl = plan_pair(t, k, n, swiglu, SIZE_MAX);
-  if (!pl.pays) return std::max(gemm_splitk_ws_bytes(t, k, n, false), gemm_splitk_ws_bytes(k, n, t, true));
+  if (!pl.pays) return std::max(gemm_splitk_ws_bytes(t, k, n, false, false), gemm_splitk_ws_bytes(k, n, t, true, true));
   return part_bytes(pl.x, t, k) + part_bytes(pl.w, k, n);
 }
 

@@ -9,6 +9,7 @@
 namespace mllm {
 
 constexpr int BK = 64;
+constexpr int GEMM_CUS = 256;   // compute units; one workgroup of the larger forms on each
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -70,6 +71,8 @@ enum class GemmTile { T256, T192, T128 };   // 256 x 256, 192 x 256 (A stored [M
 enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_ROPE64 = 4 };
 template <bool A_T, bool B_T>
 hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
+template <bool A_T, bool B_T>   // the same on eight wavefronts (gemm_wide.h)
+hipError_t launch_gemm_wide(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
 
 // A linear map's input gradient (x) and weight gradient (w) in one launch (gemm_pair.hip).
 struct GemmPairParams {

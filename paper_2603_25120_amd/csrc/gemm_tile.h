@@ -53,12 +53,12 @@ struct TileSource { __amdgpu_buffer_rsrc_t rsrc; uint32_t soff; };
 //     32-byte slots of the 256 bytes that LDS serves at a time.  A lane's vectors are rows that differ only
 //     in bits 2, 4 and 5, which the permutation does not see, so one offset register serves them all (the
 //     row steps are scalar offsets and instruction offsets).
-template <int EXT, bool K_ROWS>
+template <int EXT, bool K_ROWS, int WAVES = 4>
 struct TileLoader16 {
   static constexpr int SIZE = EXT * BK;                    // elements
-  static constexpr int PER_WAVE = SIZE / 512 / 4;          // instructions per wavefront and tile
+  static constexpr int PER_WAVE = SIZE / 512 / WAVES;      // instructions per wavefront and tile
   static constexpr int CPR = K_ROWS ? EXT / 8 : BK / 8;    // chunks per LDS row
-  static_assert(PER_WAVE * 2048 == SIZE && (!K_ROWS || EXT == 128 || EXT == 256), "whole instructions per wavefront");
+  static_assert(PER_WAVE * 512 * WAVES == SIZE && (!K_ROWS || EXT == 128 || EXT == 256) && (WAVES == 4 || WAVES == 8), "whole instructions per wavefront");
   uint32_t off[K_ROWS ? 1 : PER_WAVE];   // byte offset of the lane's chunks in k-tile 0, OOB if never valid
   uint32_t lds_off;                      // the lane's element of vector 0 in the LDS tile
   uint32_t kstep, pitch;                 // bytes per k-tile; bytes per row of the operand
@@ -67,7 +67,12 @@ struct TileLoader16 {
     if constexpr (K_ROWS) return ((r & 3) | ((r >> 1) & 4)) << 1;
     else return (r >> 1) & 7;
   }
-  static constexpr int row_step(int i) { return EXT == 256 ? ((i & 1) << 2) | ((i >> 1) << 4) : i << 4; }
+  static constexpr int row_step(int i) {
+    return EXT == 256 ? ((i & 1) << 2) | ((i >> 1) << (WAVES == 8 ? 5 : 4)) : i << (WAVES == 8 ? 5 : 4);
+  }
+  static __device__ __forceinline__ int wave_row(int wave) {
+    return (EXT == 256 ? ((wave & 1) << 1) | (((wave >> 1) & 1) << 3) : (((wave >> 1) & 1) << 2) | ((wave & 1) << 3)) | ((wave >> 2) << 4);
+  }
   // pair_half > 0 (operands stored [K, N] only): the tile's columns alternate, in runs of `run`, between
   // the left half of the matrix and the same columns of the right half (+ pair_half), so that each
   // wavefront's columns are matching gate and up columns.
@@ -76,7 +81,7 @@ struct TileLoader16 {
     pitch = (uint32_t)(ld * 2);
     kstep = K_ROWS ? BK * pitch : BK * 2;
     if constexpr (K_ROWS) {
-      const int r = EXT == 256 ? (lane >> 5) | ((wave & 1) << 1) | ((wave >> 1) << 3) : (lane >> 4) | ((wave >> 1) << 2) | ((wave & 1) << 3);
+      const int r = (EXT == 256 ? lane >> 5 : lane >> 4) | wave_row(wave);
       const int cc = ((lane % CPR) ^ swz(r)) * 8;
       int64_t fx = fixed0 + cc;
       if (pair_half > 0) {
@@ -94,9 +99,15 @@ struct TileLoader16 {
       }
     }
   }
-  template <int I>   // K_ROWS = false
+  // A load instruction's 64 vectors are 1 KiB of consecutive LDS in lane order, in either layout.
+  template <int I>
   __device__ __forceinline__ void load_to_lds(const TileSource& s, bf16_t* lds, int wave) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rsrc, (MLLM_LDS void*)(lds + (wave * PER_WAVE + I) * 512), 16, (int)off[I], (int)s.soff, 0, 0);
+    if constexpr (K_ROWS) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rsrc, (MLLM_LDS void*)(lds + (wave_row(wave) + row_step(I)) * EXT), 16, (int)off[0],
+                                               (int)(s.soff + (uint32_t)row_step(I) * pitch), 0, 0);
+    } else {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rsrc, (MLLM_LDS void*)(lds + (wave * PER_WAVE + I) * 512), 16, (int)off[I], (int)s.soff, 0, 0);
+    }
   }
   template <int I>
   __device__ __forceinline__ u32x4 load(const TileSource& s) const {

@@ -61,8 +61,8 @@ struct LinearBwdForm { bool paired; GemmForm x, w; bool x_first; };
 LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w);
 size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu);   // scratch that launch_linear_bwd wants
 // Scratch bytes launch_gemm wants for a product of this shape (0: it will not split the K loop); a_t: A stored
-// [K, M].
-size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t);
+// [K, M]; b_t: B stored [K, N].
+size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t);
 // C [M, N] (+)= sum over p of partial[p], p ascending, (+ bias) (+ residual); fp32 or bf16, N a multiple of 8.
 hipError_t launch_splitk_reduce(const float* partial, void* c, int splits, int64_t m, int64_t n, int out_fp32,
                                 int accumulate, const void* bias, const void* residual, int64_t ldres, hipStream_t s);

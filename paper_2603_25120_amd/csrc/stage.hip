@@ -257,7 +257,7 @@ size_t layer_partial_bytes(const mllm_layer_desc_t& L, int64_t T) {
 // Scratch of the three products of a linear map [T, k] -> [T, n]: Y on its own, dX and dW together (dX in its SwiGLU form
 // where that applies).
 size_t linear_split_bytes(int64_t T, int64_t k, int64_t n, bool swiglu = false) {
-  return std::max(gemm_splitk_ws_bytes(T, n, k, false), linear_bwd_ws_bytes(T, k, n, swiglu && gemm_swiglu_bwd_fusable(T, k, n)));
+  return std::max(gemm_splitk_ws_bytes(T, n, k, false, true), linear_bwd_ws_bytes(T, k, n, swiglu && gemm_swiglu_bwd_fusable(T, k, n)));
 }
 // The most scratch that a product of the layer asks for.
 size_t layer_split_bytes(const mllm_layer_desc_t& L, int64_t T) {
