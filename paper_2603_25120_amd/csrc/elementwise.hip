@@ -93,6 +93,85 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
   }
 }
 
+// Rows wider than 1024: a workgroup owns a row, NV 16-byte vectors a thread.  With a wavefront a row, few rows left most of
+// the chip idle behind a chain of 64 values a lane, and many rows did not keep enough loads in flight (us: 777 x 4096 10.3 -> 6.7, 5125 x
+// 3200 LayerNorm 23.9 -> 19.1, 32768 x 4096 123 -> 105, 5.1 TB/s).
+template <int KIND, int NV>
+__global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
+                                                           const bf16_t* __restrict__ beta, bf16_t* __restrict__ y,
+                                                           float* __restrict__ stats, int64_t T, int d, int64_t ld, float eps,
+                                                           bf16_t* __restrict__ x_copy) {
+  __shared__ float red[2][4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t row = blockIdx.x;
+  const int nvec = d >> 3;
+  uint4 u[NV], g4[NV], b4[NV];
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = tid + 256 * j;
+    u[j] = g4[j] = b4[j] = make_uint4(0, 0, 0, 0);
+    if (c < nvec) u[j] = *reinterpret_cast<const uint4*>(x + row * ld + 8 * c);
+  }
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = tid + 256 * j;
+    if (c < nvec) {
+      g4[j] = *reinterpret_cast<const uint4*>(gamma + 8 * c);
+      if (KIND == 0) b4[j] = *reinterpret_cast<const uint4*>(beta + 8 * c);
+    }
+  }
+  float v[NV][8];
+  float sum = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = tid + 256 * j;
+    if (x_copy && c < nvec) *reinterpret_cast<uint4*>(x_copy + row * ld + 8 * c) = u[j];
+    unpack8(u[j], v[j]);
+#pragma unroll
+    for (int e = 0; e < 8; e++) sum += v[j][e];
+  }
+  float mean = 0.f;
+  if (KIND == 0) {
+    sum = wave_sum(sum);
+    if (lane == 0) red[0][wave] = sum;
+    __syncthreads();
+    mean = (red[0][0] + red[0][1] + red[0][2] + red[0][3]) / (float)d;
+  }
+  float sq = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; j++)
+    if (tid + 256 * j < nvec) {
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const float t = v[j][e] - mean;
+        sq += t * t;
+      }
+    }
+  sq = wave_sum(sq);
+  if (lane == 0) red[1][wave] = sq;
+  __syncthreads();
+  const float rstd = rsqrtf((red[1][0] + red[1][1] + red[1][2] + red[1][3]) / (float)d + eps);
+  if (tid == 0) {
+    stats[row] = rstd;
+    stats[T + row] = mean;
+  }
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = tid + 256 * j;
+    if (c < nvec) {
+      float g[8], b[8], o[8];
+      unpack8(g4[j], g);
+      unpack8(b4[j], b);
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        o[e] = (v[j][e] - mean) * rstd * g[e];
+        if (KIND == 0) o[e] += b[e];
+      }
+      *reinterpret_cast<uint4*>(y + row * ld + 8 * c) = pack8(o);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // normalisation backward.  With xhat = (x - mean) * rstd and dxh = dy * gamma:
 //   LayerNorm: dx = (dxh - mean(dxh) - xhat * mean(dxh * xhat)) * rstd
@@ -120,18 +199,40 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
     for (int e = 0; e < 8; e++) { dg[j][e] = 0.f; db[j][e] = 0.f; if (c >= nvec) g[j][e] = 0.f; }
   }
   int parity = 0;
+  uint4 xq[NV], dq[NV], rq[NV];
+  float rstd_n = 0.f, mean_n = 0.f;
+  auto fetch = [&](int64_t row) __attribute__((always_inline)) {   // a row's operands, while the row before is worked on
+    if (row >= T) return;
+    rstd_n = stats[row];
+    if (KIND == 0) mean_n = stats[T + row];
+#pragma unroll
+    for (int j = 0; j < NV; j++) {
+      const int c = tid + 256 * j;
+      if (c < nvec) {
+        xq[j] = *reinterpret_cast<const uint4*>(x + row * ld + 8 * c);
+        dq[j] = *reinterpret_cast<const uint4*>(dy + row * ld + 8 * c);
+        if (dres) rq[j] = *reinterpret_cast<const uint4*>(dres + row * ld + 8 * c);
+      }
+    }
+  };
+  // RMSNorm: one row ahead (777 x 4096 14.4 -> 10.8 us, 2999 x 3584 23.4 -> 18.6; 32768 x 4096 187 -> 191, of which
+  // the second stage gives back 15).  LayerNorm's second set of sums takes the registers: 5125 x 3200 31.3 us, ahead 34.7.
+  constexpr bool AHEAD = KIND == 1;
+  if constexpr (AHEAD) fetch(b);
   for (int64_t row = b; row < T; row += B, parity ^= 1) {
-    const float rstd = stats[row];
-    const float mean = KIND == 0 ? stats[T + row] : 0.f;
+    if constexpr (!AHEAD) fetch(row);
+    const float rstd = rstd_n, mean = mean_n;
     float xh[NV][8], dxh[NV][8];
+    uint4 res[NV];
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int j = 0; j < NV; j++) {
       const int c = tid + 256 * j;
       if (c < nvec) {
         float xv[8], dv[8];
-        unpack8(*reinterpret_cast<const uint4*>(x + row * ld + 8 * c), xv);
-        unpack8(*reinterpret_cast<const uint4*>(dy + row * ld + 8 * c), dv);
+        unpack8(xq[j], xv);
+        unpack8(dq[j], dv);
+        res[j] = rq[j];
 #pragma unroll
         for (int e = 0; e < 8; e++) {
           xh[j][e] = (xv[e] - mean) * rstd;
@@ -143,6 +244,7 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
         }
       }
     }
+    if constexpr (AHEAD) fetch(row + B);
     s2 = wave_sum(s2);
     if (KIND == 0) s1 = wave_sum(s1);
     if (lane == 0) { red[parity][0][wave] = s1; red[parity][1][wave] = s2; }
@@ -155,7 +257,7 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
       const int c = tid + 256 * j;
       if (c < nvec) {
         float o[8], r[8];
-        if (dres) unpack8(*reinterpret_cast<const uint4*>(dres + row * ld + 8 * c), r);
+        if (dres) unpack8(res[j], r);
 #pragma unroll
         for (int e = 0; e < 8; e++) {
           o[e] = (dxh[j][e] - m1 - xh[j][e] * m2) * rstd;
@@ -181,11 +283,13 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
   }
 }
 
-// out[c] (+)= sum_p partial[p][c], for every job of a list.  A workgroup owns 8 columns of one job: 128 row
-// slices x 2 float4 column groups; slice s adds rows s, s+128, ... in order (four loads in flight), then the
-// slice sums are added pairwise (s with s+64, then s with s+32, ...): a fixed association, so the result is
-// bitwise reproducible.
-constexpr int RED_COLS = 8, RED_SLICES = 128;
+// out[c] (+)= sum_p partial[p][c], for every job of a list.  A workgroup owns 32 columns of one job: 32 row
+// slices x 8 float4 column groups; slice s adds rows s, s+32, ... in order (eight loads in flight), then the
+// slice sums are added pairwise (s with s+16, then s with s+8, ...): a fixed association, so the result is
+// bitwise reproducible.  A row's 32 columns are a whole line of 128 bytes: with 8 columns a workgroup, neighbours on
+// different XCDs each fetched it (8 sums of 320 to 1024 rows, 89 MB: 53 us, now
+// 24; 1024 rows of 4096: 22.5 and 7.1).
+constexpr int RED_COLS = 32, RED_SLICES = 32;
 // JOBS: room in the list, which travels as the kernel's argument.  A list of 32 costs each workgroup a walk over 32
 // entries before it knows its job, 0.7 us of a launch of 2-5; one norm or bias (at most 3 jobs) takes the short form.
 template <int JOBS>
@@ -205,21 +309,24 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceList<JOBS> l
   float* __restrict__ out = list.out[job];
   const int P = list.rows[job];
   const int64_t n = list.n[job];
-  const int cg = threadIdx.x & 1, slice = threadIdx.x >> 1;
+  const int cg = threadIdx.x & 7, slice = threadIdx.x >> 3;
   const int64_t c = ((int64_t)(blockIdx.x - list.first[job]) * (RED_COLS / 4) + cg) * 4;
   const bool valid = c < n;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (valid) {
     const float* col = partial + c;
     int p = slice;
-    for (; p + 3 * RED_SLICES < P; p += 4 * RED_SLICES) {
-      const float4 v0 = *reinterpret_cast<const float4*>(col + (int64_t)p * n);
-      const float4 v1 = *reinterpret_cast<const float4*>(col + (int64_t)(p + RED_SLICES) * n);
-      const float4 v2 = *reinterpret_cast<const float4*>(col + (int64_t)(p + 2 * RED_SLICES) * n);
-      const float4 v3 = *reinterpret_cast<const float4*>(col + (int64_t)(p + 3 * RED_SLICES) * n);
-      s.x += (v0.x + v1.x) + (v2.x + v3.x); s.y += (v0.y + v1.y) + (v2.y + v3.y);
-      s.z += (v0.z + v1.z) + (v2.z + v3.z); s.w += (v0.w + v1.w) + (v2.w + v3.w);
+    for (; p + 7 * RED_SLICES < P; p += 8 * RED_SLICES) {
+      float4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) v[q] = *reinterpret_cast<const float4*>(col + (int64_t)(p + q * RED_SLICES) * n);
+#pragma unroll
+      for (int q = 0; q < 8; q += 4) {
+        s.x += (v[q].x + v[q + 1].x) + (v[q + 2].x + v[q + 3].x); s.y += (v[q].y + v[q + 1].y) + (v[q + 2].y + v[q + 3].y);
+        s.z += (v[q].z + v[q + 1].z) + (v[q + 2].z + v[q + 3].z); s.w += (v[q].w + v[q + 1].w) + (v[q + 2].w + v[q + 3].w);
+      }
     }
+#pragma unroll 4
     for (; p < P; p += RED_SLICES) {
       const float4 v = *reinterpret_cast<const float4*>(col + (int64_t)p * n);
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
@@ -587,25 +694,24 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
-#define MLLM_NV_DISPATCH(NVEC, CALL)          \
-  if ((NVEC) <= 64) { CALL(1) }               \
-  else if ((NVEC) <= 128) { CALL(2) }         \
-  else if ((NVEC) <= 256) { CALL(4) }         \
-  else if ((NVEC) <= 512) { CALL(8) }         \
-  else { CALL(16) }
-
 hipError_t launch_norm_fwd(int kind, const void* x, const void* gamma, const void* beta, void* y,
                            float* stats, int64_t t, int64_t d, int64_t ld, float eps, hipStream_t s, void* x_copy) {
   if (t == 0) return hipSuccess;
   if (d % 8 != 0 || d > 8192 || ld < d || ld % 8 != 0) return hipErrorInvalidValue;
   ProfScope prof(PROF_ELEMENTWISE, (x_copy ? 6.0 : 4.0) * (double)t * (double)d, s);
-  dim3 grid(blocks_for(t, ROWS_PER_BLOCK)), block(256);
-#define CALL(NV)                                                                                  \
-  if (kind == 0) hipLaunchKernelGGL((norm_fwd_kernel<0, NV>), grid, block, 0, s, (const bf16_t*)x, \
-      (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy); \
-  else hipLaunchKernelGGL((norm_fwd_kernel<1, NV>), grid, block, 0, s, (const bf16_t*)x,           \
-      (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);
-  MLLM_NV_DISPATCH(d / 8, CALL)
+  const int64_t nvec = d / 8;
+  const bool wide = nvec > 128;
+  dim3 grid(wide ? (unsigned)t : (unsigned)blocks_for(t, ROWS_PER_BLOCK)), block(256);
+#define CALL(K, NV)                                                                                  \
+  if (kind == 0) hipLaunchKernelGGL((K<0, NV>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma, \
+      (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);                     \
+  else hipLaunchKernelGGL((K<1, NV>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma,       \
+      (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);
+  if (nvec <= 64) { CALL(norm_fwd_kernel, 1) }
+  else if (!wide) { CALL(norm_fwd_kernel, 2) }
+  else if (nvec <= 256) { CALL(norm_fwd_row_kernel, 1) }
+  else if (nvec <= 512) { CALL(norm_fwd_row_kernel, 2) }
+  else { CALL(norm_fwd_row_kernel, 4) }
 #undef CALL
   return hipGetLastError();
 }
@@ -769,7 +875,7 @@ hipError_t PartialSums::flush(hipStream_t s) {
   return waiting <= 3 ? launch_reduce<3>(jobs, waiting, accumulate, s) : launch_reduce<MAX_JOBS>(jobs, waiting, accumulate, s);
 }
 
-// Workgroups (= rows of partial sums) of the norm backward.  The wavefront-per-row kernel with two vectors per lane
+// Workgroups (= rows of partial sums) of the norm backward, at most.  The wavefront-per-row kernel with two vectors per lane
 // keeps three workgroups per CU resident: a grid of 768 runs in one round.
 // For few rows the second stage (W x d floats a set) weighs more than the occupancy of the first, so a workgroup
 // then takes several rows: two a wavefront in the wavefront-per-row kernel, three in the other one (777 x 4096: 10.8 + 10.2 us
@@ -789,7 +895,8 @@ hipError_t launch_norm_bwd(int kind, const void* dy, const void* x, const void* 
   if (d % 8 != 0 || d > 8192 || ld < d || ld % 8 != 0) return hipErrorInvalidValue;
   if (dx_colsum && !norm_bwd_colsum_fusable(d)) return hipErrorInvalidValue;
   const int64_t nvec = d / 8;
-  const int64_t W = norm_bwd_workgroups(t, d);
+  // RMSNorm on wide rows keeps the next row's operands in registers, and three workgroups per CU (two with four vectors)
+  const int64_t W = std::min<int64_t>(norm_bwd_workgroups(t, d), kind == 1 && nvec > 128 ? (nvec <= 512 ? 768 : 512) : 1024);
   float* partial = nullptr;
   float* beta_out = kind == 0 ? dbeta : nullptr;
   hipError_t e = dx_colsum ? sums.take(W, d, {dgamma, beta_out, dx_colsum}, s, &partial)
