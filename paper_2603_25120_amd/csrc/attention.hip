@@ -71,17 +71,17 @@ struct AttnParams {
 // The dK/dV pass of a key tile walks (query head of the group, query tile) pairs; with gridDim.y parts a
 // workgroup walks its share of them.
 struct KvRange { int n_it, head, q0; };   // iterations, and where they start: head of the group, first query row
-__device__ __forceinline__ KvRange kv_range(int grp, int q_begin, int seg_len, int tile_rows) {
+__device__ __forceinline__ KvRange kv_range(int grp, int q_begin, int seg_len, int tile_rows, int part, int parts) {
   const int per_head = (seg_len - q_begin + tile_rows - 1) / tile_rows, total = grp * per_head;
-  const int first = total * (int)blockIdx.y / (int)gridDim.y, last = total * ((int)blockIdx.y + 1) / (int)gridDim.y;
+  const int first = total * part / parts, last = total * (part + 1) / parts;
   return {last - first, first / per_head, q_begin + first % per_head * tile_rows};
 }
 // A part's sums of one key row (the lane's), fp32 and unscaled.
 template <int HD>
 __device__ __forceinline__ void store_kv_partial(const AttnParams& p, const f32x16 (&dk)[HD / 32], const f32x16 (&dv)[HD / 32],
-                                                 int64_t row, int kvh, int h) {
+                                                 int64_t row, int kvh, int h, int part) {
   const int64_t width = (int64_t)p.Hkv * HD;
-  float* k = p.dkv_partial + ((int64_t)(2 * blockIdx.y) * p.T + row) * width + kvh * HD + 4 * h;
+  float* k = p.dkv_partial + ((int64_t)(2 * part) * p.T + row) * width + kvh * HD + 4 * h;
   float* v = k + (int64_t)p.T * width;
 #pragma unroll
   for (int d = 0; d < HD / 32; d++)
@@ -118,11 +118,11 @@ __device__ __forceinline__ void rope_unrotate(f32x16 (&acc)[HD / 32], const floa
     }
 }
 
-// The work item of this workgroup (entry blockIdx.x of the list; the host has arranged the entries so
+// The work item of this workgroup (an entry of the list, by default blockIdx.x; the host has arranged the entries so
 // that workgroups sharing rows run on one XCD).  Returns false, for the whole workgroup, on the empty
 // items that pad the shorter XCD lists.
-__device__ __forceinline__ bool work_item(const AttnItem* list, AttnItem& t) {
-  const AttnItem x = list[blockIdx.x];
+__device__ __forceinline__ bool work_item(const AttnItem* list, AttnItem& t, int entry) {
+  const AttnItem x = list[entry];
   // the same for every lane: keep the fields in scalar registers
   t.seg_start = __builtin_amdgcn_readfirstlane(x.seg_start);
   t.seg_len = __builtin_amdgcn_readfirstlane(x.seg_len);
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) bf16_t Vs0[TILE];
   __shared__ __attribute__((aligned(1024))) bf16_t Vs1[TILE];
   AttnItem t;
-  if (!work_item(p.list, t)) return;
+  if (!work_item(p.list, t, blockIdx.x)) return;
   const int head = t.head, kvh = head / (p.Hq / p.Hkv);
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -381,15 +381,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
 // the backward pass and also produces delta[h][t] = sum_d dO[t,h,d] * O[t,h,d] for the dK/dV pass.
 // ---------------------------------------------------------------------------------------------
 template <int HD>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
-  constexpr int NC = HD / 16, ND = HD / 32, TILE = BKV * HD;
+__device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem* list, int entry, bf16_t* Ks0, bf16_t* Ks1, bf16_t* Vs0, bf16_t* Vs1) {
+  constexpr int NC = HD / 16, ND = HD / 32;
   // K and V tiles go straight to LDS, two stages each (as in the forward kernel).
-  __shared__ __attribute__((aligned(1024))) bf16_t Ks0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Ks1[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Vs0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Vs1[TILE];
   AttnItem t;
-  if (!work_item(p.list, t)) return;
+  if (!work_item(list, t, entry)) return;
   const int head = t.head, kvh = head / (p.Hq / p.Hkv);
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -546,6 +542,12 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
     }
 }
 
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(1024))) bf16_t Ks0[BKV * HD], Ks1[BKV * HD], Vs0[BKV * HD], Vs1[BKV * HD];
+  attn_bwd_dq<HD>(p, p.list, blockIdx.x, Ks0, Ks1, Vs0, Vs1);
+}
+
 // ---------------------------------------------------------------------------------------------
 // dK/dV pass: one workgroup per (key tile of 128, kv head); each wavefront owns 32 key rows and
 // loops over the query heads of the group and the query tiles that can see its keys.
@@ -559,16 +561,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
 // ---------------------------------------------------------------------------------------------
 // s_waitcnt vmcnt(0) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
 
-template <int HD>
-__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(AttnParams p) {
-  constexpr int NC = HD / 16, ND = HD / 32, TILE = BQ * HD;
-  __shared__ __attribute__((aligned(1024))) bf16_t Qs0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Qs1[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t dOs0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t dOs1[TILE];
-  __shared__ float lse_s0[BQ], lse_s1[BQ], delta_s0[BQ], delta_s1[BQ];
+// SELF_DELTA: delta is formed here, four threads a query row of the tile, instead of read from the dQ pass.
+struct DkvLds { bf16_t *q0, *q1, *o0, *o1; float *lse0, *lse1, *delta0, *delta1; };
+template <int HD, bool SELF_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem* list, int entry, int part, int parts, const DkvLds& lds) {
+  constexpr int NC = HD / 16, ND = HD / 32;
+  static_assert(!SELF_DELTA || HD == 64, "four threads of 16 columns a row");
+  bf16_t *const Qs0 = lds.q0, *const Qs1 = lds.q1, *const dOs0 = lds.o0, *const dOs1 = lds.o1;
+  float *const lse_s0 = lds.lse0, *const lse_s1 = lds.lse1, *const delta_s0 = lds.delta0, *const delta_s1 = lds.delta1;
   AttnItem t;
-  if (!work_item(p.list, t)) return;
+  if (!work_item(list, t, entry)) return;
   const int kvh = t.head, grp = p.Hq / p.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -591,7 +593,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
 
   const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
   const int wave_first_k = t.tile0 + 32 * wave;
-  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ);
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ, part, parts);
   const int n_it = range.n_it;
 
   constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BQ / RPI / 4;
@@ -610,6 +612,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
   int nj = range.head, nq0 = range.q0;
   float r_lse = 0.f, r_delta = 0.f;   // statistics of the tile in flight, one row per thread (tid < BQ)
   bool r_ok = false;
+  u32x4_t r_o[2], r_do[2];             // SELF_DELTA: the thread's 16 columns of O and dO
   auto issue = [&](bf16_t* qs, bf16_t* dos) {
     const bool valid = nj < grp;
     const int head = kvh * grp + (valid ? nj : 0);
@@ -631,7 +634,18 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
         const_cast<float*>(p.delta + (int64_t)head * p.T + t.seg_start), 0, valid ? t.seg_len * 4 : 0, 0x00020000);
     const uint32_t so = tid < BQ ? (uint32_t)(nq0 + tid) * 4u : 0xFFFFFFFFu;
     r_lse = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, (int)so, 0, 0));
-    r_delta = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, (int)so, 0, 0));
+    if constexpr (SELF_DELTA) {
+      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+          p.o + (int64_t)t.seg_start * p.o_stride + head * HD, 0, valid ? (int)do_bytes : 0, 0x00020000);
+      const uint32_t at = dorow + (uint32_t)(tid >> 2) * (uint32_t)(p.o_stride * 2) + (uint32_t)(tid & 3) * 32u;
+#pragma unroll
+      for (int w = 0; w < 2; w++) {
+        r_o[w] = __builtin_amdgcn_raw_buffer_load_b128(ro, (int)(at + 16u * w), 0, 0);
+        r_do[w] = __builtin_amdgcn_raw_buffer_load_b128(rdo, (int)(at + 16u * w), 0, 0);
+      }
+    } else {
+      r_delta = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, (int)so, 0, 0));
+    }
     r_ok = valid && tid < BQ && nq0 + tid < t.seg_len;
     nq0 += BQ;
     if (nq0 >= t.seg_len) { nq0 = q_begin; nj++; }
@@ -644,7 +658,17 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
                   int q0, bool live) {
     if (tid < BQ) {
       lse_s[tid] = r_ok ? r_lse * LOG2E : INFINITY;   // +inf: probabilities of rows past the segment are 0
-      delta_s[tid] = r_ok ? r_delta : 0.f;
+      if constexpr (!SELF_DELTA) delta_s[tid] = r_ok ? r_delta : 0.f;
+    }
+    if constexpr (SELF_DELTA) {   // rows past the segment, and the tile past the last one, have come as zeros
+      float d = 0.f;
+#pragma unroll
+      for (int w = 0; w < 2; w++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) d += bf16lo(r_o[w][e]) * bf16lo(r_do[w][e]) + bf16hi(r_o[w][e]) * bf16hi(r_do[w][e]);
+      d += __shfl_xor(d, 1, 64);
+      d += __shfl_xor(d, 2, 64);
+      if ((tid & 3) == 0) delta_s[tid >> 2] = d;
     }
     __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
     __syncthreads();
@@ -731,8 +755,8 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
   // can be handed to another one
   __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
   if (!kok) return;
-  if (gridDim.y > 1) {
-    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h);
+  if (parts > 1) {
+    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, part);
     return;
   }
   float out_scale = p.scale;
@@ -755,6 +779,23 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(Att
       *reinterpret_cast<uint2*>(dvp + 32 * d + 8 * g4 + 4 * h) = w;
     }
 }
+
+#define MLLM_DKV_LDS(HD)                                                                                                \
+  __shared__ __attribute__((aligned(1024))) bf16_t T0[BQ * HD], T1[BQ * HD], T2[BQ * HD], T3[BQ * HD];                  \
+  __shared__ float lse0[BQ], lse1[BQ], delta0[BQ], delta1[BQ]
+template <int HD>
+__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(AttnParams p) {
+  MLLM_DKV_LDS(HD);
+  attn_bwd_dkv<HD, false>(p, p.list, blockIdx.x, blockIdx.y, gridDim.y, DkvLds{T0, T1, T2, T3, lse0, lse1, delta0, delta1});
+}
+// Both passes in one launch, the dK/dV pass first.
+__global__ __launch_bounds__(256, 2) void attn_bwd_both_kernel(AttnParams p, const AttnItem* kv_list, int kv_grid, int kv_parts) {
+  MLLM_DKV_LDS(64);
+  const int kv = kv_grid * kv_parts, pid = blockIdx.x;
+  if (pid < kv) attn_bwd_dkv<64, true>(p, kv_list, pid % kv_grid, pid / kv_grid, kv_parts, DkvLds{T0, T1, T2, T3, lse0, lse1, delta0, delta1});
+  else attn_bwd_dq<64>(p, p.list, pid - kv, T0, T1, T2, T3);
+}
+#undef MLLM_DKV_LDS
 
 // ---------------------------------------------------------------------------------------------
 // dK/dV pass, software-pipelined form.  The work of a block of 32 query rows is a chain: scores and
@@ -824,7 +865,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
   constexpr int STATS_AT = NST * STAGE_B;
   __shared__ __attribute__((aligned(1024))) char lds[NST * STAGE_B + NST * STAT_STAGE_B];
   AttnItem t;
-  if (!work_item(p.list, t)) return;
+  if (!work_item(p.list, t, blockIdx.x)) return;
   const int kvh = t.head, grp = p.Hq / p.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -851,7 +892,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
 
   const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
   const int wave_first_k = t.tile0 + 32 * wave;
-  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ);
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ, blockIdx.y, gridDim.y);
   const int n_it = range.n_it;
   const float c2 = p.scale_log2e;
 
@@ -1104,7 +1145,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kerne
   wait_loads<0>();
   if (!kok) return;
   if (gridDim.y > 1) {
-    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h);
+    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, blockIdx.y);
     return;
   }
   float out_scale = p.scale;
@@ -1235,6 +1276,12 @@ int attn_kv_parts(int64_t heaviest, int64_t total, int64_t rows, int head_dim) {
   return best;
 }
 
+// Heads of 64: up to this many workgroups the dQ and the dK/dV pass share a launch.  The dK/dV pass then forms delta itself,
+// some 6 % more instructions a query tile; for that neither waits for the other's last workgroups, and with few
+// workgroups both run side by side.  Whole layers and stages, apart and together (us; workgroups): toy stage 495 and 469,
+// one 576-token image (160) 218.6 and 207.8, five (800) 427 and 421, eight (1280) 662 and 653, 13 (2080) 874 and 868, 20 (3200)
+// 1267 and 1265, 46 (7360) 2548 and 2571.
+constexpr int64_t BOTH_MOST = 3072;
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (a.q_grid == 0) return hipSuccess;
   if (!offsets_fit(a)) return hipErrorInvalidValue;
@@ -1243,12 +1290,16 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   ProfScope prof(PROF_ATTN_BWD, 2.0 * a.fwd_flops, s);
   AttnParams p = make_params(a);
   const dim3 block(256), qgrid((unsigned)a.q_grid), kgrid((unsigned)a.kv_grid, split ? (unsigned)a.kv_parts : 1u);
-  // dQ first: it writes delta, which the dK/dV pass reads
+  // dQ first: it writes delta, which the dK/dV pass of a launch of its own reads
   if (a.head_dim == 128) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, qgrid, block, 0, s, p);
     p.list = (const AttnItem*)a.kv_list;
     hipLaunchKernelGGL(attn_bwd_dkv_pipe_kernel<128>, kgrid, block, 0, s, p);
+  } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST) {
+    p.list = (const AttnItem*)a.q_list;
+    hipLaunchKernelGGL(attn_bwd_both_kernel, dim3((unsigned)a.q_grid + kgrid.x * kgrid.y), block, 0, s, p, (const AttnItem*)a.kv_list,
+                       (int)kgrid.x, (int)kgrid.y);
   } else if (a.head_dim == 64) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, qgrid, block, 0, s, p);
