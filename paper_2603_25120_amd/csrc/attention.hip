@@ -79,7 +79,7 @@ __device__ __forceinline__ KvRange kv_range(int grp, int q_begin, int seg_len, i
 // A part's sums of one key row (the lane's), fp32 and unscaled.
 template <int HD>
 __device__ __forceinline__ void store_kv_partial(const AttnParams& p, const f32x16 (&dk)[HD / 32], const f32x16 (&dv)[HD / 32],
-                                                 int64_t row, int kvh, int h, int part) {
+                                                 int64_t row, int kvh, int h, unsigned part) {
   const int64_t width = (int64_t)p.Hkv * HD;
   float* k = p.dkv_partial + ((int64_t)(2 * part) * p.T + row) * width + kvh * HD + 4 * h;
   float* v = k + (int64_t)p.T * width;
@@ -756,7 +756,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem
   __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
   if (!kok) return;
   if (parts > 1) {
-    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, part);
+    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, (unsigned)part);
     return;
   }
   float out_scale = p.scale;
