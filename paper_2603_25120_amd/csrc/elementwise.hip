@@ -94,13 +94,18 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
 }
 
 // Rows wider than 1024: a workgroup owns a row, NV 16-byte vectors a thread.  With a wavefront a row, few rows left most of
-// the chip idle behind a chain of 64 values a lane, and many rows did not keep enough loads in flight (us: 777 x 4096 10.3 -> 6.7, 5125 x
-// 3200 LayerNorm 23.9 -> 19.1, 32768 x 4096 123 -> 105, 5.1 TB/s).
+// the chip idle behind one wavefront's loads and stores, and many rows did not keep enough loads in flight (us, in a layer: 5125 x 3200
+// LayerNorm 23.9 -> 19.1; alone: 32768 x 4096 RMSNorm 110.6 -> 94.1, LayerNorm 121.7 -> 102.1).
+// RMSNorm: the row passes through LDS and every wavefront forms the sum of all of it by itself, in the order of norm_fwd_kernel, so that a
+// row's statistics have the same bits as with a wavefront a row (sums of quarters 91.7 us at 32768 x 4096, this 94.1).
+// LayerNorm, with two such sums, adds the quarters' (5125 x 3200 13.2 and 18.5 us; rstd's largest error against float64 1.41e-7 and
+// 1.47e-7, at 32768 x 4096 1.42e-7 and 2.83e-7).
 template <int KIND, int NV>
 __global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
                                                            const bf16_t* __restrict__ beta, bf16_t* __restrict__ y,
                                                            float* __restrict__ stats, int64_t T, int d, int64_t ld, float eps,
                                                            bf16_t* __restrict__ x_copy) {
+  __shared__ uint4 whole[KIND == 1 ? 256 * NV : 1];
   __shared__ float red[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t row = blockIdx.x;
@@ -121,36 +126,48 @@ __global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restr
     }
   }
   float v[NV][8];
-  float sum = 0.f;
 #pragma unroll
   for (int j = 0; j < NV; j++) {
     const int c = tid + 256 * j;
+    if (KIND == 1) whole[c] = u[j];
     if (x_copy && c < nvec) *reinterpret_cast<uint4*>(x_copy + row * ld + 8 * c) = u[j];
     unpack8(u[j], v[j]);
-#pragma unroll
-    for (int e = 0; e < 8; e++) sum += v[j][e];
   }
-  float mean = 0.f;
-  if (KIND == 0) {
+  float mean = 0.f, sq = 0.f, rstd;
+  if (KIND == 1) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4 * NV; j++) {
+      float w[8];
+      unpack8(whole[lane + 64 * j], w);   // zeros beyond the row
+#pragma unroll
+      for (int e = 0; e < 8; e++) sq += w[e] * w[e];
+    }
+    rstd = rsqrtf(wave_sum(sq) / (float)d + eps);
+  } else {
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < NV; j++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) sum += v[j][e];
     sum = wave_sum(sum);
     if (lane == 0) red[0][wave] = sum;
     __syncthreads();
     mean = (red[0][0] + red[0][1] + red[0][2] + red[0][3]) / (float)d;
-  }
-  float sq = 0.f;
 #pragma unroll
-  for (int j = 0; j < NV; j++)
-    if (tid + 256 * j < nvec) {
+    for (int j = 0; j < NV; j++)
+      if (tid + 256 * j < nvec) {
 #pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const float t = v[j][e] - mean;
-        sq += t * t;
+        for (int e = 0; e < 8; e++) {
+          const float t = v[j][e] - mean;
+          sq += t * t;
+        }
       }
-    }
-  sq = wave_sum(sq);
-  if (lane == 0) red[1][wave] = sq;
-  __syncthreads();
-  const float rstd = rsqrtf((red[1][0] + red[1][1] + red[1][2] + red[1][3]) / (float)d + eps);
+    sq = wave_sum(sq);
+    if (lane == 0) red[1][wave] = sq;
+    __syncthreads();
+    rstd = rsqrtf((red[1][0] + red[1][1] + red[1][2] + red[1][3]) / (float)d + eps);
+  }
   if (tid == 0) {
     stats[row] = rstd;
     stats[T + row] = mean;
