@@ -295,7 +295,8 @@ mllm_status_t mllm_attn_work_list(const mllm_pack_t* pack, int32_t kv_major, int
                                   size_t out_bytes, size_t* bytes_needed, int32_t* grid_out);
 
 /* Backward of the above from (q, k, v, o, lse, do): dq, dk, dv bf16 with the strides of q / k / v.
- * delta: fp32 scratch [n_q, T] (rowsum(dO * O)), overwritten. */
+ * delta: fp32 scratch [n_q, T] (rowsum(dO * O)), overwritten.
+ * dk may be k, dv may be v and dq may be o (same place, same stride); no other output may overlap an input or another output. */
 mllm_status_t mllm_op_attn_bwd(const void* q, const void* k, const void* v, const void* o,
                                const float* lse, const void* d_o, void* dq, void* dk, void* dv,
                                float* delta, const mllm_pack_t* pack, int32_t n_q_heads,

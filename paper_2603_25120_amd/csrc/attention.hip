@@ -1249,6 +1249,19 @@ static bool offsets_fit(const AttnArgs& a) {
   return ((int64_t)a.total_tokens + 256) * widest * 2 < (int64_t)0xFFFFFFFFll;
 }
 
+// Whether a gradient is written over something that the passes read.  One launch for both passes may then write what the other
+// pass still wants; one after the other, dk may take the place of k, dv that of v and dq that of o.  First to last element, so
+// matrices that are only interleaved count as well: they are served in order, a little slower.
+static bool gradients_over_inputs(const AttnArgs& a) {
+  const auto bytes = [&](int64_t stride, int heads) { return ((a.total_tokens - 1) * stride + (int64_t)heads * a.head_dim) * 2; };
+  const int64_t q = bytes(a.q_stride, a.n_q_heads), kv = bytes(a.kv_stride, a.n_kv_heads), o = bytes(a.o_stride, a.n_q_heads);
+  const struct { const void* p; int64_t n; } out[3] = {{a.dq, q}, {a.dk, kv}, {a.dv, kv}}, in[5] = {{a.q, q}, {a.k, kv}, {a.v, kv}, {a.o, o}, {a.d_o, o}};
+  for (const auto& w : out)
+    for (const auto& r : in)
+      if (ranges_overlap(w.p, w.n, r.p, r.n)) return true;
+  return false;
+}
+
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (a.q_grid == 0) return hipSuccess;
   if (!offsets_fit(a)) return hipErrorInvalidValue;
@@ -1296,7 +1309,7 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, qgrid, block, 0, s, p);
     p.list = (const AttnItem*)a.kv_list;
     hipLaunchKernelGGL(attn_bwd_dkv_pipe_kernel<128>, kgrid, block, 0, s, p);
-  } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST) {
+  } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST && !gradients_over_inputs(a)) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_both_kernel, dim3((unsigned)a.q_grid + kgrid.x * kgrid.y), block, 0, s, p, (const AttnItem*)a.kv_list,
                        (int)kgrid.x, (int)kgrid.y);
