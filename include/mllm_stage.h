@@ -256,7 +256,8 @@ mllm_status_t mllm_op_gemm_swiglu_bwd(const void* dy, const void* w_d, const voi
  * swiglu_pre not NULL (the conditions of mllm_op_gemm_swiglu_bwd with m = t, f = k, k = n, else MLLM_ERR_UNSUPPORTED): dx is
  * [d gate | d up] [t, 2k] instead, from swiglu_pre = [gate | up] [t, 2k].
  * workspace: scratch_bytes of fp32 scratch (256-byte aligned, may be NULL with 0 bytes) for products cut along their
- * contraction; the cheapest plan that fits it is taken.  k and n must be multiples of 8. */
+ * contraction; the cheapest plan that fits it is taken.  k and n must be multiples of 8.
+ * dx may be x (then two launches); no other output may overlap an input, the other output or the workspace. */
 mllm_status_t mllm_op_linear_bwd(const void* dy, const void* x, const void* w, void* dx, void* dw, int64_t t, int64_t k,
                                  int64_t n, int accumulate, const void* swiglu_pre, void* workspace, size_t scratch_bytes,
                                  void* hip_stream);

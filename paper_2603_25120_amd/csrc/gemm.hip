@@ -576,8 +576,19 @@ size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu) {
   return part_bytes(pl.x, t, k) + part_bytes(pl.w, k, n);
 }
 
+// Whether one of the gradients is written over something that the other product reads: as two launches, dW first, dX may take
+// the place of X.
+static bool gradients_over_operands(const GemmArgs& x, const GemmArgs& w) {
+  const int64_t dy = x.m * x.lda * 2, act = w.k * w.lda * 2, weight = x.n * x.ldb * 2;
+  const void* dx = x.swiglu_dpre ? x.swiglu_dpre : x.c;
+  const int64_t dx_bytes = x.m * x.ldc * 2, dw_bytes = w.m * w.ldc * 4;
+  return ranges_overlap(dx, dx_bytes, w.a, act) || ranges_overlap(dx, dx_bytes, w.b, dy) || ranges_overlap(w.c, dw_bytes, x.a, dy) ||
+         ranges_overlap(w.c, dw_bytes, x.b, weight) || ranges_overlap(w.c, dw_bytes, x.swiglu_pre, x.m * 2 * x.n * 2) ||
+         ranges_overlap(dx, dx_bytes, w.c, dw_bytes);
+}
+
 hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s) {
-  const bool pair = pairable(x, w);
+  const bool pair = pairable(x, w) && !gradients_over_operands(x, w);
   const PairPlan pl = pair ? plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0) : PairPlan{};
   if (!pair || !pl.pays) {
     const hipError_t e = launch_gemm(w, s);

@@ -39,3 +39,17 @@ def test_attention_gradients_over_their_inputs(B, head_dim, causal, what):
     B.mllm_op_attn_bwd(q, kin, vin, place[0] if "dq" in what else o, lse, do, *place, delta, *dims)
     for got, want in zip(place, own):
         assert nmax_err(host_f64(got), host_f64(want)) < 3e-2
+
+
+@pytest.mark.parametrize("t,k,n", [(600, 1024, 192), (130, 256, 64), (2050, 640, 3200)])
+def test_input_gradient_over_the_input(B, t, k, n):
+    """Sizes whose gradients share a launch: dX over X makes two.  dX carries one bf16 rounding, dW is an fp32 sum (2e-3)."""
+    (one, *_), want = B.mllm_linear_bwd_form(t, k, n)
+    assert one
+    g = torch.Generator(device="cuda").manual_seed(t + k + n)
+    dy, x = (torch.randn(t, c, generator=g, device="cuda").bfloat16() for c in (n, k))
+    w = (torch.randn(k, n, generator=g, device="cuda") * 0.125).bfloat16()
+    want_dx, want_dw = dy.double() @ w.double().t().contiguous(), x.double().t().contiguous() @ dy.double()
+    dw = torch.full((k, n), float("nan"), device="cuda")
+    B.mllm_op_linear_bwd(dy, x, w, x, dw, t, k, n, workspace=scratch(want), scratch_bytes=want)
+    assert nmax_err(host_f64(x), want_dx.cpu().numpy()) < 1e-2 and nmax_err(host_f64(dw), want_dw.cpu().numpy()) < 2e-3
