@@ -263,7 +263,7 @@ mllm_status_t mllm_op_linear_bwd(const void* dy, const void* x, const void* w, v
                                  void* hip_stream);
 /* The form that takes (host only): form[0] 1 for one launch, 0 for two; [1..3] tile rows, tile columns and parts of the
  * input gradient, [4..6] of the weight gradient; [7] 1 if the input gradient's workgroups come first.  scratch_wanted (may be
- * NULL): what the plan would take without a limit. */
+ * NULL): with this much, and more, the plan is the one without a limit, wherever the operands start. */
 mllm_status_t mllm_linear_bwd_form(int64_t t, int64_t k, int64_t n, int swiglu, size_t scratch_bytes, int32_t* form,
                                    size_t* scratch_wanted);
 

@@ -569,11 +569,17 @@ LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
   return {true, form(pl.x), form(pl.w), pl.x_first};
 }
 
+// Enough for one launch and for two: which it will be also hangs on where the operands start.
 size_t linear_bwd_ws_bytes(int64_t t, int64_t k, int64_t n, bool swiglu) {
   if (t <= 0) return 0;
+  GemmArgs x{}, w{};
+  x.m = t; x.n = k; x.k = n; x.lda = x.ldb = n; x.b_layout = 1;
+  w.m = k; w.n = n; w.k = t; w.lda = k; w.ldb = n; w.a_layout = 1;
+  const size_t apart = std::max(swiglu || !takes_tile_kernel(x) ? 0 : gemm_splitk_ws_bytes(t, k, n, false, false),
+                                takes_tile_kernel(w) ? gemm_splitk_ws_bytes(k, n, t, true, true) : 0);
+  if (!pairable(x, w)) return apart;
   const PairPlan pl = plan_pair(t, k, n, swiglu, SIZE_MAX);
-  if (!pl.pays) return std::max(gemm_splitk_ws_bytes(t, k, n, false, false), gemm_splitk_ws_bytes(k, n, t, true, true));
-  return part_bytes(pl.x, t, k) + part_bytes(pl.w, k, n);
+  return pl.pays ? std::max(apart, part_bytes(pl.x, t, k) + part_bytes(pl.w, k, n)) : apart;
 }
 
 // Whether one of the gradients is written over something that the other product reads: as two launches, dW first, dX may take

@@ -45,3 +45,13 @@ def test_swiglu_form_keeps_the_tile_of_its_epilogue(B):
     for t in (777, 2999, 8192, 32768):
         (one, x, _, _), _ = B.mllm_linear_bwd_form(t, 18944, 3584, swiglu=1)
         assert one and x == (256, 256, 1)
+
+
+@pytest.mark.parametrize("t,k,n", [(20000, 512, 520), (9000, 512, 712), (4000, 256, 72), (671050, 3200, 3200), (2880, 1024, 1024), (200, 4096, 8192)])
+def test_scratch_wanted_is_enough_for_two_launches(B, t, k, n):
+    """Maps whose gradients cannot share a launch (n no multiple of 64, or past 4 GiB) and maps whose operands may start off 16
+    bytes: what the scratch is sized for is the form without a limit, one launch or two."""
+    form, want = B.mllm_linear_bwd_form(t, k, n)
+    assert B.mllm_linear_bwd_form(t, k, n, scratch_bytes=want)[0] == form
+    for m, c, depth, al, bl in ((t, k, n, 0, 1), (k, n, t, 1, 0)):
+        assert B.mllm_gemm_form(m, c, depth, al, bl, want) == B.mllm_gemm_form(m, c, depth, al, bl, 1 << 40)
