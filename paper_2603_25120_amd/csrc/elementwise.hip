@@ -217,11 +217,10 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
   }
   int parity = 0;
   uint4 xq[NV], dq[NV], rq[NV];
-  float rstd_n = 0.f, mean_n = 0.f;
-  auto fetch = [&](int64_t row) __attribute__((always_inline)) {   // a row's operands, while the row before is worked on
+  float rstd_n = 0.f;
+  auto fetch = [&](int64_t row) __attribute__((always_inline)) {   // AHEAD only: a row's operands, while the row before is worked on
     if (row >= T) return;
     rstd_n = stats[row];
-    if (KIND == 0) mean_n = stats[T + row];
 #pragma unroll
     for (int j = 0; j < NV; j++) {
       const int c = tid + 256 * j;
@@ -233,12 +232,13 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
     }
   };
   // RMSNorm: one row ahead (777 x 4096 14.4 -> 10.8 us, 2999 x 3584 23.4 -> 18.6; 32768 x 4096 187 -> 191, of which
-  // the second stage gives back 15).  LayerNorm's second set of sums takes the registers: 5125 x 3200 31.3 us, ahead 34.7.
+  // the second stage gives back 15).  LayerNorm's second set of sums takes the registers, so it loads each operand where it is
+  // used (both stages: 32768 x 3200 126 us, all three loaded in front of the row's work 172; 32768 x 5120 280 and 428).
   constexpr bool AHEAD = KIND == 1;
   if constexpr (AHEAD) fetch(b);
   for (int64_t row = b; row < T; row += B, parity ^= 1) {
-    if constexpr (!AHEAD) fetch(row);
-    const float rstd = rstd_n, mean = mean_n;
+    const float rstd = AHEAD ? rstd_n : stats[row];
+    const float mean = KIND == 0 ? stats[T + row] : 0.f;
     float xh[NV][8], dxh[NV][8];
     uint4 res[NV];
     float s1 = 0.f, s2 = 0.f;
@@ -247,9 +247,9 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
       const int c = tid + 256 * j;
       if (c < nvec) {
         float xv[8], dv[8];
-        unpack8(xq[j], xv);
-        unpack8(dq[j], dv);
-        res[j] = rq[j];
+        unpack8(AHEAD ? xq[j] : *reinterpret_cast<const uint4*>(x + row * ld + 8 * c), xv);
+        unpack8(AHEAD ? dq[j] : *reinterpret_cast<const uint4*>(dy + row * ld + 8 * c), dv);
+        if constexpr (AHEAD) res[j] = rq[j];
 #pragma unroll
         for (int e = 0; e < 8; e++) {
           xh[j][e] = (xv[e] - mean) * rstd;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
       const int c = tid + 256 * j;
       if (c < nvec) {
         float o[8], r[8];
-        if (dres) unpack8(res[j], r);
+        if (dres) unpack8(AHEAD ? res[j] : *reinterpret_cast<const uint4*>(dres + row * ld + 8 * c), r);
 #pragma unroll
         for (int e = 0; e < 8; e++) {
           o[e] = (dxh[j][e] - m1 - xh[j][e] * m2) * rstd;
