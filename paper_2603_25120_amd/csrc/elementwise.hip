@@ -305,7 +305,8 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(
 // slice sums are added pairwise (s with s+16, then s with s+8, ...): a fixed association, so the result is
 // bitwise reproducible.  A row's 32 columns are a whole line of 128 bytes: with 8 columns a workgroup, neighbours on
 // different XCDs each fetched it (8 sums of 320 to 1024 rows, 89 MB: 53 us, now
-// 24; 1024 rows of 4096: 22.5 and 7.1).
+// 24; 1024 rows of 4096: 22.5 and 7.1).  With a quarter of the slices a slice has four times the rows, so the last few are requested
+// four at a time too (94 rows of 1024, both stages of a column sum: 5.34 us one at a time, now 4.82; with 128 slices 5.03).
 constexpr int RED_COLS = 32, RED_SLICES = 32;
 // JOBS: room in the list, which travels as the kernel's argument.  A list of 32 costs each workgroup a walk over 32
 // entries before it knows its job, 0.7 us of a launch of 2-5; one norm or bias (at most 3 jobs) takes the short form.
@@ -343,10 +344,16 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceList<JOBS> l
         s.z += (v[q].z + v[q + 1].z) + (v[q + 2].z + v[q + 3].z); s.w += (v[q].w + v[q + 1].w) + (v[q + 2].w + v[q + 3].w);
       }
     }
-#pragma unroll 4
-    for (; p < P; p += RED_SLICES) {
-      const float4 v = *reinterpret_cast<const float4*>(col + (int64_t)p * n);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+#pragma unroll 1
+    for (; p < P; p += 4 * RED_SLICES) {   // what is left, four rows requested together
+      float4 v[4];
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (p + q * RED_SLICES < P) v[q] = *reinterpret_cast<const float4*>(col + (int64_t)(p + q * RED_SLICES) * n);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; q++) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
     }
   }
   part[slice][cg] = s;
