@@ -108,7 +108,8 @@ __global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restr
   __shared__ uint4 whole[KIND == 1 ? 256 * NV : 1];
   __shared__ float red[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t row = blockIdx.x;
+  const int64_t row = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (row >= T) return;
   const int nvec = d >> 3;
   uint4 u[NV], g4[NV], b4[NV];
 #pragma unroll
@@ -718,6 +719,9 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
+// A grid's x dimension holds fewer than 2^32 threads, 2^24 rows of the row form: beyond this many they go to y.
+constexpr int64_t ROW_FORM_GRID = (int64_t)1 << 20;
+
 hipError_t launch_norm_fwd(int kind, const void* x, const void* gamma, const void* beta, void* y,
                            float* stats, int64_t t, int64_t d, int64_t ld, float eps, hipStream_t s, void* x_copy) {
   if (t == 0) return hipSuccess;
@@ -725,7 +729,8 @@ hipError_t launch_norm_fwd(int kind, const void* x, const void* gamma, const voi
   ProfScope prof(PROF_ELEMENTWISE, (x_copy ? 6.0 : 4.0) * (double)t * (double)d, s);
   const int64_t nvec = d / 8;
   const bool wide = nvec > 128;
-  dim3 grid(wide ? (unsigned)t : (unsigned)blocks_for(t, ROWS_PER_BLOCK)), block(256);
+  const dim3 grid = wide ? dim3((unsigned)std::min(t, ROW_FORM_GRID), (unsigned)((t + ROW_FORM_GRID - 1) / ROW_FORM_GRID))
+                         : dim3(blocks_for(t, ROWS_PER_BLOCK)), block(256);
 #define CALL(K, NV)                                                                                  \
   if (kind == 0) hipLaunchKernelGGL((K<0, NV>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma, \
       (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);                     \

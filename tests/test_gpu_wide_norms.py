@@ -53,3 +53,28 @@ def test_column_sums(B, t, n):
     B.mllm_op_colsum(x, out, 1, scratch(B.mllm_op_colsum_partial_bytes(t, n)), t, n)
     ref = (x.double().sum(0, keepdim=True) + init.double()).cpu().numpy()
     assert nmax_err(host_f64(out), ref) < 2e-3
+
+
+# more rows than a grid's first dimension is given
+@pytest.mark.parametrize("kind,t,d", [(0, (1 << 20) + 3, 2056), (1, (1 << 20) + 3, 2056), (1, (1 << 24) + 3, 1032)])
+def test_norm_at_the_lines_between_its_forms(B, kind, t, d):
+    """The first and last rows, and those around multiples of a million, against float64; the others' results are written by the
+    same code.  y 1e-2 of the maximum (one rounding), rstd and mean 1e-5 (fp32 sums of at most 8192 terms)."""
+    torch.cuda.empty_cache()
+    if t * d * 4 > torch.cuda.mem_get_info()[0] * 3 // 4:
+        pytest.skip("needs %d GB" % (t * d * 4 >> 30))
+    g = torch.Generator(device="cuda").manual_seed(t + d + kind)
+    x, y = (torch.empty(t, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    rows = torch.tensor(sorted({r for c in range(0, t + (1 << 20), 1 << 20) for r in range(c - 2, c + 3) if 0 <= r < t} | {t - 2, t - 1}), device="cuda")
+    x[rows] = torch.randn(len(rows), d, generator=g, device="cuda").bfloat16()
+    gam = (1 + 0.02 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    bet = (0.02 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    stats = torch.full((2, t), float("nan"), device="cuda")
+    B.mllm_op_norm_fwd(kind, x, gam, bet if kind == 0 else None, y, stats, t, d, 1e-5)
+    X = x[rows].double()
+    mean = X.mean(1, keepdim=True) if kind == 0 else torch.zeros(len(rows), 1, dtype=torch.float64, device="cuda")
+    r = torch.rsqrt(((X - mean) ** 2).mean(1, keepdim=True) + 1e-5)
+    want = (X - mean) * r * gam.double() + (bet.double() if kind == 0 else 0.0)
+    assert nmax_err(host_f64(y[rows]), want.cpu().numpy()) < 1e-2
+    assert nmax_err(stats[0][rows].double().cpu().numpy(), r.flatten().cpu().numpy()) < 1e-5
+    assert float((stats[1][rows].double() - mean.flatten()).abs().max()) < 1e-5
