@@ -93,9 +93,10 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
   }
 }
 
-// Rows wider than 1024: a workgroup owns a row, NV 16-byte vectors a thread.  With a wavefront a row, few rows left most of
-// the chip idle behind one wavefront's loads and stores, and many rows did not keep enough loads in flight (us, in a layer: 5125 x 3200
-// LayerNorm 23.9 -> 19.1; alone: 32768 x 4096 RMSNorm 110.6 -> 94.1, LayerNorm 121.7 -> 102.1).
+// The other form for rows wider than 1024 (norm_fwd_row_form chooses): a workgroup owns a row, NV 16-byte vectors a thread.  With
+// a wavefront a row, few rows leave most of the chip idle behind one wavefront's loads and stores, and many rows over 2048 wide do not
+// keep enough loads in flight (us, in a layer: 5125 x 3200 LayerNorm 23.9 -> 19.1; alone: 32768 x 4096 RMSNorm 109 -> 91, LayerNorm
+// 120 -> 97).
 // RMSNorm: the row passes through LDS and every wavefront forms the sum of all of it by itself, in the order of norm_fwd_kernel, so that a
 // row's statistics have the same bits as with a wavefront a row (sums of quarters 91.7 us at 32768 x 4096, this 94.1).
 // LayerNorm, with two such sums, adds the quarters' (5125 x 3200 13.2 and 18.5 us; rstd's largest error against float64 1.41e-7 and
@@ -719,6 +720,17 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
+// Whether a workgroup owns a row (norm_fwd_row_kernel) or a wavefront does (us with a wavefront a row and a workgroup a row).
+// Up to 2048 columns the workgroup's threads have a vector each at most, and many rows are better off with more loads in
+// flight a thread: 400 x 1280 LayerNorm 3.60 and 2.89, 1500 x 1280 3.97 and 3.74, 2048 x 1280 4.15 and 4.24, 2999 x 1280 4.97 and 5.60,
+// 32768 x 1280 28.0 and 34.3, 32768 x 2048 43.6 and 43.0.  Wider rows always gain in LayerNorm (2999 x 2560 7.80 and 7.58, 32768 x 4096
+// 120 and 97); in RMSNorm not between 3/4 d rows and the 5120 that a wavefront a row has resident at once: 2999 x 2560 7.10 and
+// 7.61, 4200 x 3072 9.6 and 10.7, 2500 x 4096 8.8 and 8.3, 3500 x 4096 10.9 and 11.3, 6000 x 3072 15.0 and 13.9.
+static bool norm_fwd_row_form(int kind, int64_t t, int64_t d) {
+  if (d <= 1024) return false;
+  if (d <= 2048) return t <= 1536;
+  return kind == 0 || d > 4096 || 4 * t <= 3 * d || t > 5120;
+}
 // A grid's x dimension holds fewer than 2^32 threads, 2^24 rows of the row form: beyond this many they go to y.
 constexpr int64_t ROW_FORM_GRID = (int64_t)1 << 20;
 
@@ -728,18 +740,22 @@ hipError_t launch_norm_fwd(int kind, const void* x, const void* gamma, const voi
   if (d % 8 != 0 || d > 8192 || ld < d || ld % 8 != 0) return hipErrorInvalidValue;
   ProfScope prof(PROF_ELEMENTWISE, (x_copy ? 6.0 : 4.0) * (double)t * (double)d, s);
   const int64_t nvec = d / 8;
-  const bool wide = nvec > 128;
-  const dim3 grid = wide ? dim3((unsigned)std::min(t, ROW_FORM_GRID), (unsigned)((t + ROW_FORM_GRID - 1) / ROW_FORM_GRID))
-                         : dim3(blocks_for(t, ROWS_PER_BLOCK)), block(256);
+  const bool row = norm_fwd_row_form(kind, t, d);
+  const dim3 grid = row ? dim3((unsigned)std::min(t, ROW_FORM_GRID), (unsigned)((t + ROW_FORM_GRID - 1) / ROW_FORM_GRID))
+                        : dim3(blocks_for(t, ROWS_PER_BLOCK)), block(256);
 #define CALL(K, NV)                                                                                  \
   if (kind == 0) hipLaunchKernelGGL((K<0, NV>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma, \
       (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);                     \
   else hipLaunchKernelGGL((K<1, NV>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma,       \
       (const bf16_t*)beta, (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy);
   if (nvec <= 64) { CALL(norm_fwd_kernel, 1) }
-  else if (!wide) { CALL(norm_fwd_kernel, 2) }
-  else if (nvec <= 256) { CALL(norm_fwd_row_kernel, 1) }
-  else if (nvec <= 512) { CALL(norm_fwd_row_kernel, 2) }
+  else if (nvec <= 128) { CALL(norm_fwd_kernel, 2) }
+  else if (nvec <= 256) { if (row) { CALL(norm_fwd_row_kernel, 1) } else { CALL(norm_fwd_kernel, 4) } }
+  else if (nvec <= 512) {
+    if (row) { CALL(norm_fwd_row_kernel, 2) }
+    else { hipLaunchKernelGGL((norm_fwd_kernel<1, 8>), grid, block, 0, s, (const bf16_t*)x, (const bf16_t*)gamma, (const bf16_t*)beta,
+                              (bf16_t*)y, stats, t, (int)d, ld, eps, (bf16_t*)x_copy); }
+  }
   else { CALL(norm_fwd_row_kernel, 4) }
 #undef CALL
   return hipGetLastError();

@@ -55,8 +55,11 @@ def test_column_sums(B, t, n):
     assert nmax_err(host_f64(out), ref) < 2e-3
 
 
-# more rows than a grid's first dimension is given
-@pytest.mark.parametrize("kind,t,d", [(0, (1 << 20) + 3, 2056), (1, (1 << 20) + 3, 2056), (1, (1 << 24) + 3, 1032)])
+# either side of each line between a wavefront and a workgroup a row: 1536 rows up to 2048 columns; RMSNorm up to 4096 columns
+# between 3/4 of the columns and 5120 rows; and more rows than a grid's first dimension is given
+@pytest.mark.parametrize("kind,t,d", [(0, 1536, 1288), (0, 1537, 1288), (1, 1536, 2048), (1, 1537, 2048), (1, 1728, 2304), (1, 1729, 2304),
+                                      (1, 5120, 2056), (1, 5121, 2056), (1, 3073, 4096), (0, 3073, 4096), (1, 4000, 4104),
+                                      (0, (1 << 20) + 3, 2056), (1, (1 << 20) + 3, 2056), (1, (1 << 24) + 3, 1032)])
 def test_norm_at_the_lines_between_its_forms(B, kind, t, d):
     """The first and last rows, and those around multiples of a million, against float64; the others' results are written by the
     same code.  y 1e-2 of the maximum (one rounding), rstd and mean 1e-5 (fp32 sums of at most 8192 terms)."""
