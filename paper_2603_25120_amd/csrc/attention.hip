@@ -1293,8 +1293,12 @@ int attn_kv_parts(int64_t heaviest, int64_t total, int64_t rows, int head_dim) {
 // some 6 % more instructions a query tile; for that neither waits for the other's last workgroups, and with few
 // workgroups both run side by side.  Whole layers and stages, apart and together (us; workgroups): toy stage 495 and 469,
 // one 576-token image (160) 218.6 and 207.8, five (800) 427 and 421, eight (1280) 662 and 653, 13 (2080) 874 and 868, 20 (3200)
-// 1267 and 1265, 46 (7360) 2548 and 2571.
+// 1267 and 1265, 46 (7360) 2548 and 2571.  With more than four query heads a kv head a few long dK/dV workgroups set the time, and those
+// of dQ beside them slow them down (causal, backward alone: 16 / 2 heads, 577 tokens 140 and 143, 2048 413 and 429, 4134 821 and
+// 868; 28 / 4, 4134 775 and 790; with four, 16 / 4 454 and 450, 32 / 8 513 and 486), other than for a few tokens, where a launch
+// counts for more (forward and backward of 16 / 2: 110 tokens 46.5 and 43.3, 342 47.6 and 43.9).
 constexpr int64_t BOTH_MOST = 3072;
+constexpr int BOTH_GROUP = 4, BOTH_FEW_TOKENS = 512;
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (a.q_grid == 0) return hipSuccess;
   if (!offsets_fit(a)) return hipErrorInvalidValue;
@@ -1309,7 +1313,8 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, qgrid, block, 0, s, p);
     p.list = (const AttnItem*)a.kv_list;
     hipLaunchKernelGGL(attn_bwd_dkv_pipe_kernel<128>, kgrid, block, 0, s, p);
-  } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST && !gradients_over_inputs(a)) {
+  } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST && (a.n_q_heads <= BOTH_GROUP * a.n_kv_heads || a.total_tokens <= BOTH_FEW_TOKENS) &&
+             !gradients_over_inputs(a)) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_both_kernel, dim3((unsigned)a.q_grid + kgrid.x * kgrid.y), block, 0, s, p, (const AttnItem*)a.kv_list,
                        (int)kgrid.x, (int)kgrid.y);
