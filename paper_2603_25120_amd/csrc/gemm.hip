@@ -242,22 +242,17 @@ GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
   }
   return p;
 }
-// Whether a tile is taken on eight wavefronts (gemm_wide.h, where both sides' times stand).  128x128: as long as every workgroup
-// has a CU to itself.  The large tiles: where an operand is stored [K, .], short of contractions over 8192 in
-// forward layout (32768 x 4096 x 14336 2710 us on four wavefronts, 2750 on eight; at 4096 100 and 95).  The rotary epilogue of 128
-// wide heads wants a head's columns in one wavefront.
-bool takes_wide_form(const GemmArgs& g, GemmTile tile, int64_t workgroups) {
-  if ((((uintptr_t)g.a | (uintptr_t)g.b) & 15) || (g.a_layout != 0 && g.b_layout != 0)) return false;
-  if (tile == GemmTile::T128) return workgroups <= GEMM_CUS && !g.swiglu_dpre;
-  if (g.b_layout != 0 || (g.rope_table && g.rope_head_dim == 128)) return false;
-  return g.a_layout != 0 || g.k <= 8192;
+// Whether the kernel on eight wavefronts (gemm_wide.h) can take the operands: it loads both straight to LDS.  The rotary epilogue of
+// 128 wide heads wants a head's columns in one wavefront.
+bool fits_wide_form(const GemmArgs& g) {
+  return (((uintptr_t)g.a | (uintptr_t)g.b) & 15) == 0 && !(g.a_layout != 0 && g.b_layout != 0) && !(g.rope_table && g.rope_head_dim == 128);
 }
-hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, hipStream_t s) {
+hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, bool wide, hipStream_t s) {
   const GemmParams p = tile_params(g, tile, splits);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
   const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
   const bool at = g.a_layout != 0, bt = g.b_layout == 0, f32 = g.out_fp32 != 0;   // b_layout 0: stored [K, N], transposing reads
-  if (takes_wide_form(g, tile, (int64_t)grid.x * splits)) {
+  if (wide && fits_wide_form(g)) {
     if (at) return launch_gemm_wide<true, true>(p, tile, f32, epi, grid, s);
     return bt ? launch_gemm_wide<false, true>(p, tile, f32, epi, grid, s) : launch_gemm_wide<false, false>(p, tile, f32, epi, grid, s);
   }
@@ -296,62 +291,93 @@ hipError_t launch_general(const GemmArgs& g, hipStream_t s) {
 // workgroups.  The plan is the cheapest of all choices by an estimate in microseconds: rounds of workgroups times
 // (k-tiles of a part times the time of a k-tile, which grows with the number of workgroups that share power and
 // memory, plus a workgroup's start and end), plus the parts' trip through memory.  The constants rank the choices and do
-// not time a product (single products run up to 40 % off the estimate).  Fitted to all tiles and splits of 260 random
-// products of the layers' widths (96 to 24000 tokens): on average the plan loses 0.3 % in forward layout against the best
-// choice (worst 8 %), 1.6 % with W stored [N, K] (one 32 %, the others below 13 %) and 0.7 % for weight gradients (worst 16 %); with
-// the constants of the four-wavefront kernels alone 1.4, 3.1 and 1.7 %.
+// not time a product (single products run up to 40 % off the estimate).  They are fitted to all tiles, parts and kernels of 1500
+// random products of the layers' widths (96 to 24000 tokens), with weights (dW: the saved X) that are not in the memory-side
+// cache, as a layer finds them; constants from products repeated on the same operands had sent a decoder's down projection to
+// uncut 128x128 tiles (763 x 3584 x 18944: its forward pass 400 -> 468 us).  On 600 other products the plan's tile and parts lose
+// 0.6 % in forward layout against the best measured (worst 22 %), 0.8 % with W stored [N, K] (worst 19 %) and 1.0 % for weight
+// gradients (worst 14 %), on 200 whose operands stay in the cache 0.8, 1.0 and 1.2 %.
 namespace {
-struct GemmPlan { GemmTile tile; int splits; };
+struct GemmPlan { GemmTile tile; int splits; bool wide; };   // wide: on eight wavefronts, where the operands allow it
 struct TileCost {
-  GemmTile tile; int bm, bn;
+  GemmTile tile; bool wide; int bm, bn;
   int slots;              // workgroups of a round
   int few;                // up to this many, a k-tile costs k_few; from there on k_more, rising to k_full for a full round
-  double k_few, k_more, k_full, fixed;
-  double fixed_few;       // start and end of up to `few` workgroups
+  double k_few, k_more, k_full, fixed;   // fixed: start and end
 };
 // By layout: 0 forward, 1 both operands k-contiguous, 2 A stored [K, M] (weight gradients).
-constexpr TileCost TILE_COSTS[3][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.04, 1.04, 1.46, 8.1, 8.1},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.60, 0.60, 1.19, 6.7, 6.7},
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.28, 0.80, 0.97, 6.5, 4.0}},   // two on a CU from 257 on
-                                       {{GemmTile::T256, 256, 256, 256, 0, 1.08, 1.08, 1.46, 8.3, 8.3},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.09, 7.3, 7.3},
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.79, 1.10, 4.2, 4.0}},
-                                       {{GemmTile::T256, 256, 256, 256, 0, 0.88, 0.88, 1.46, 7.9, 7.9},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.18, 7.6, 7.6},      // not for this layout
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.39, 0.83, 0.98, 3.2, 4.0}}};
+constexpr TileCost TILE_COSTS[3][6] = {{{GemmTile::T256, false, 256, 256, 256, 0, 0.83, 0.83, 1.35, 8.2},
+                                        {GemmTile::T256, true, 256, 256, 256, 0, 1.16, 1.16, 1.25, 6.8},
+                                        {GemmTile::T192, false, 192, 256, 256, 0, 0.74, 0.74, 1.06, 8.1},
+                                        {GemmTile::T192, true, 192, 256, 256, 0, 0.76, 0.76, 1.12, 6.9},
+                                        {GemmTile::T128, false, 128, 128, 512, 256, 0.51, 0.85, 0.95, 5.0},   // two on a CU from 257 on
+                                        {GemmTile::T128, true, 128, 128, 256, 0, 0.26, 0.26, 0.49, 3.9}},
+                                       {{GemmTile::T256, false, 256, 256, 256, 0, 0.91, 0.91, 1.29, 9.8},
+                                        {GemmTile::T256, true, 256, 256, 256, 0, 0, 0, 0, 0},   // not for this layout
+                                        {GemmTile::T192, false, 192, 256, 256, 0, 0.83, 0.83, 1.13, 6.8},
+                                        {GemmTile::T192, true, 192, 256, 256, 0, 0, 0, 0, 0},   // not for this layout
+                                        {GemmTile::T128, false, 128, 128, 512, 256, 0.49, 0.82, 0.98, 5.5},
+                                        {GemmTile::T128, true, 128, 128, 256, 0, 0.28, 0.28, 0.49, 4.0}},
+                                       {{GemmTile::T256, false, 256, 256, 256, 0, 1.04, 1.04, 1.42, 11.7},
+                                        {GemmTile::T256, true, 256, 256, 256, 0, 0.88, 0.88, 1.44, 10.3},
+                                        {GemmTile::T192, false, 192, 256, 256, 0, 0, 0, 0, 0},   // not for this layout
+                                        {GemmTile::T192, true, 192, 256, 256, 0, 0, 0, 0, 0},   // not for this layout
+                                        {GemmTile::T128, false, 128, 128, 512, 256, 0.47, 0.79, 1.00, 4.2},
+                                        {GemmTile::T128, true, 128, 128, 256, 0, 0.37, 0.37, 0.48, 3.8}}};
 inline int cost_row(bool a_t, bool b_t) { return a_t ? 2 : b_t ? 0 : 1; }   // b_t: B stored [K, N]
-// A workgroup's start and end.  Gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB and more
-// apart (6144 x 28672 x 82 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473).
-double start_and_end(const TileCost& c, bool a_t, int64_t n, int64_t wgs) {
-  return (wgs <= c.few ? c.fixed_few : c.fixed) + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0);
+// Where a tile may go to eight wavefronts at all; below these lines the estimate decides, but for more than a round of large tiles in
+// forward layout, which then always do.  128x128: as long as every workgroup has a CU to itself (gain up to there 1.02-1.15 in every
+// layout, loss of 2-10 % beyond).  The large tiles: not with both operands k-contiguous; else only for short contractions, as two
+// stages do not cover the latency of weights that come from memory.  Time on four wavefronts / on eight, geomeans by k-tiles of
+// a part: forward 192x256 up to 16 1.02-1.13, up to 32 0.93-1.0 below 1024 workgroups, beyond 0.79-0.99 (up to 64 with weights of up to 64 MB
+// 0.83-0.96 for few workgroups, 1.0-1.04 from two rounds on); forward 256x256 up to 16
+// 1.04-1.15, up to 32 0.98-1.10, up to 64 0.96-0.98 for at most a round and 1.01-1.04 for more, beyond 0.89-1.0; weight gradients
+// up to 64 0.95-1.2, beyond 1.0-1.05 for a round or more of a matrix at least as wide as it is high (4096 x 28672 x 32768 5420 us and
+// 5230), 0.85-1.0 for others.  Weights near the size of the memory-side cache, 256 MB, leave it before the next tile-rows
+// come to them: more than a round of 256x256 tiles over 50 to 64 k-tiles 1.05 up to 192 MB, over that 0.99-1.02, but 1.07 where
+// the last round is almost empty (forward pass of a decoder with 4096 x 28672 SwiGLU weights 0.94-0.995 at 300 to 28000 tokens, 1.04 at
+// 1561, 784 workgroups; 4096 x 22016 1.00-1.03).  Gradients 37888 wide 0.95-0.98, 28672 1.04-1.08.
+bool takes_wide_form(int row, GemmTile tile, int64_t m, int64_t n, int64_t k, int64_t k_tiles, int64_t workgroups) {
+  if (tile == GemmTile::T128) return workgroups <= GEMM_CUS;
+  if (row == 1) return false;
+  if (row == 2) return n <= 32768 && (k_tiles <= 64 || (workgroups >= GEMM_CUS && n >= m));
+  if (tile == GemmTile::T192) return k_tiles <= 24 || (k_tiles <= 64 && workgroups > 2 * GEMM_CUS && 2 * n * k <= (int64_t)64 << 20);
+  return k_tiles <= 32 || (k_tiles <= 64 && workgroups > GEMM_CUS && (2 * n * k <= (int64_t)192 << 20 || workgroups % GEMM_CUS <= 16));
 }
 // A k-tile's time among `wgs` workgroups of at most a round.
 double k_tile_time(const TileCost& c, int64_t wgs) {
   return wgs <= c.few ? c.k_few : c.k_more + (c.k_full - c.k_more) * (double)(wgs - c.few) / (c.slots - c.few);
 }
+// Estimate of `wgs` workgroups of k_tiles each.  Gradients of very wide matrices: the rows of 512 bytes of a 128x128 tile lie 80 KB
+// and more apart (6144 x 28672 x 82 170 us with 128x128 tiles, 160 with 256x256; 14336 x 28672 x 294 632 and 473).
+double workgroups_time(const TileCost& c, bool a_t, int64_t n, int64_t k_tiles, int64_t wgs) {
+  const int64_t rounds = wgs / c.slots, rest = wgs % c.slots;
+  const double fixed = c.fixed + (a_t && n > 20000 && c.tile == GemmTile::T128 ? 1.0 : 0.0);
+  return (double)rounds * ((double)k_tiles * c.k_full + fixed) + (rest > 0 ? (double)k_tiles * k_tile_time(c, rest) + fixed : 0.0);
+}
 // What the parts cost besides: their trip through memory and a launch.
-double parts_cost(int64_t m, int64_t n, int64_t parts) { return parts > 1 ? 3.0 + (double)m * n * (8.0 * parts + 4.0) * 1e-7 : 0.0; }
-// split_bytes: scratch for the parts; the cheapest plan that fits it (and its estimate).
-GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t, size_t split_bytes, double* estimate = nullptr) {
-  const TileCost (&costs)[3] = TILE_COSTS[cost_row(a_t, b_t)];
+double parts_cost(int64_t m, int64_t n, int64_t parts) { return parts > 1 ? 3.0 + (double)m * n * (8.0 * parts + 4.0) * 1.15e-7 : 0.0; }
+// split_bytes: scratch for the parts; the cheapest plan that fits it (and its estimate).  fused: only uncut 256x256 tiles, the ones that
+// the fused epilogues exist for.
+GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t, size_t split_bytes, double* estimate = nullptr, bool fused = false) {
+  const int row = cost_row(a_t, b_t);
   const int64_t nk = (k + BK - 1) / BK;
-  GemmPlan best{GemmTile::T256, 1};
+  GemmPlan best{GemmTile::T256, 1, false};
   if (m <= 0 || n <= 0 || k <= 0) return best;   // an empty product
   const int64_t most = std::min<int64_t>(16, std::min<int64_t>(nk / 8, (int64_t)(split_bytes / 4 / ((uint64_t)m * (uint64_t)n))));
-  const int64_t cap = std::max<int64_t>(1, most);   // at least 8 k-tiles a part
+  const int64_t cap = fused ? 1 : std::max<int64_t>(1, most);   // at least 8 k-tiles a part
   double best_cost = 1e300;
-  for (const TileCost& c : costs) {
-    if (c.tile == GemmTile::T192 && a_t) continue;   // only for A stored [M, K]
+  for (const TileCost& c : TILE_COSTS[row]) {
+    if ((c.tile == GemmTile::T192 && a_t) || (fused && c.tile != GemmTile::T256)) continue;   // T192: only for A stored [M, K]
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
     for (int64_t sp = 1; sp <= cap; sp++) {
       const int64_t per = (nk + sp - 1) / sp;
       if ((nk + per - 1) / per != sp) continue;   // would leave a part empty
-      const int64_t wgs = tiles * sp, rounds = wgs / c.slots, rest = wgs % c.slots;
-      const double fixed = start_and_end(c, a_t, n, wgs);
-      double cost = (double)rounds * ((double)per * c.k_full + fixed);
-      if (rest > 0) cost += (double)per * k_tile_time(c, rest) + fixed;
-      cost += parts_cost(m, n, sp);
-      if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp}; }
+      if ((sp - 1) * tiles >= 512) break;         // the chip is full without
+      const bool eight = takes_wide_form(row, c.tile, m, n, k, per, tiles * sp);
+      if (c.wide ? !eight : eight && row == 0 && c.tile != GemmTile::T128 && tiles * sp > GEMM_CUS) continue;
+      const double cost = workgroups_time(c, a_t, n, per, tiles * sp) + parts_cost(m, n, sp);
+      if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp, c.wide}; }
     }
   }
   if (estimate) *estimate = best_cost;
@@ -363,19 +389,21 @@ namespace {
 // A linear map's input gradient x = dY [T, n] . W^T [n, k] and weight gradient w = X^T [k, T] . dY [T, n] in one launch:
 // neither needs the other, the second starts on the CUs that the first one's last round leaves idle, and a launch and its
 // gap go.  The plan takes tiles, parts and order together, as the cheapest estimate of the whole launch: the workgroups of
-// the first product, then those of the second, each on the first slot that is free.  On 229 maps of the layers' widths (64 to
-// 26000 tokens) it loses 2.2 % on average against the best of all choices (worst 23 %); against two launches with the plans of
-// their own the pair takes 0.87 of the time: 576 x 1024 x 4096 (T, k, n) 26.6 -> 21.7 us, 256 x 256 x 768 14.2 -> 8.4,
+// the first product, then those of the second, each on the first slot that is free.  Constants fitted to 780 maps of the layers'
+// widths (64 to 30000 tokens), weights and saved X not in the memory-side cache; on 150 others the plan loses 0.7 % against the best of
+// all choices (worst 40 %: 2479 x 1280 x 3840 (T, k, n) 75 us and 53), and on 442 that it pairs one launch takes
+// 0.83 of the time of two with the plans of their own.  Examples (us): 576 x 1024 x 4096 26.6 -> 21.7, 256 x 256 x 768 14.2 -> 8.4,
 // 2880 x 1024 x 3072 52 -> 43, 5125 x 3200 x 12800 737 -> 628.
 struct PairPlan { GemmPlan x, w; bool x_first, pays; };
-constexpr TileCost PAIR_COSTS[2][3] = {{{GemmTile::T256, 256, 256, 256, 0, 1.00, 1.00, 1.33, 8.4, 8.4},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9, 6.9},
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.40, 0.70, 0.90, 4.3, 4.3}},
-                                       {{GemmTile::T256, 256, 256, 256, 0, 1.30, 1.30, 1.45, 10.3, 10.3},
-                                        {GemmTile::T192, 192, 256, 256, 0, 0.88, 0.88, 1.12, 6.9, 6.9},   // not for this layout
-                                        {GemmTile::T128, 128, 128, 512, 256, 0.44, 0.74, 0.94, 4.5, 4.5}}};
-constexpr double MIXED_128[2] = {0.52, 0.56};   // a k-tile of a 128x128 tile that has its CU to itself beside large tiles
-constexpr double LONGEST = 0.1;                 // workgroups do not all take the same time: long ones delay the end more often
+constexpr TileCost PAIR_COSTS[2][3] = {{{GemmTile::T256, false, 256, 256, 256, 0, 0.66, 0.66, 1.21, 9.9},
+                                        {GemmTile::T192, false, 192, 256, 256, 0, 0.61, 0.61, 1.07, 6.6},
+                                        {GemmTile::T128, false, 128, 128, 512, 256, 0.31, 0.41, 0.93, 4.7}},
+                                       {{GemmTile::T256, false, 256, 256, 256, 0, 1.08, 1.08, 1.26, 8.3},
+                                        {GemmTile::T192, false, 192, 256, 256, 0, 0, 0, 0, 0},   // not for this layout
+                                        {GemmTile::T128, false, 128, 128, 512, 256, 0.41, 0.70, 0.84, 2.7}}};
+constexpr double FEW_128[2] = {4.8, 3.8};       // start and end of both in 128x128 tiles on eight wavefronts (up to 256 workgroups)
+constexpr double MIXED_128[2] = {0.62, 0.52};   // a k-tile of a 128x128 tile that has its CU to itself beside large tiles
+constexpr double LONGEST = 0.07;                // workgroups do not all take the same time: long ones delay the end more often
 constexpr int MOST_PARTS = 8;
 struct PairSide {   // one choice for one of the products
   const TileCost* c; int splits; int64_t per, wgs; double fixed, parts; size_t bytes;
@@ -415,7 +443,7 @@ int pair_sides(PairSide (&out)[3 * MOST_PARTS], int64_t m, int64_t n, int64_t k,
 PairPlan plan_pair(int64_t t, int64_t k, int64_t n, bool swiglu, size_t split_bytes) {
   PairSide xs[3 * MOST_PARTS], ws[3 * MOST_PARTS];
   const int nx = pair_sides(xs, t, k, n, false, swiglu, split_bytes), nw = pair_sides(ws, k, n, t, true, false, split_bytes);
-  PairPlan best{{GemmTile::T256, 1}, {GemmTile::T256, 1}, true, true};
+  PairPlan best{{GemmTile::T256, 1, false}, {GemmTile::T256, 1, false}, true, true};
   double best_cost = 1e300;
   for (int i = 0; i < nx; i++)
     for (int j = 0; j < nw; j++) {
@@ -423,26 +451,27 @@ PairPlan plan_pair(int64_t t, int64_t k, int64_t n, bool swiglu, size_t split_by
       if (x.bytes + w.bytes > split_bytes) continue;
       const bool x128 = x.c->tile == GemmTile::T128, w128 = w.c->tile == GemmTile::T128, both = x128 && w128;
       const int64_t slots = both ? 512 : 256, wgs = std::min(x.wgs + w.wgs, slots);
-      const double dx = (double)x.per * (x128 && !both ? MIXED_128[0] : k_tile_time(*x.c, wgs)) + x.fixed;
-      const double dw = (double)w.per * (w128 && !both ? MIXED_128[1] : k_tile_time(*w.c, wgs)) + w.fixed;
+      const bool few = both && wgs <= GEMM_CUS;
+      const double dx = (double)x.per * (x128 && !both ? MIXED_128[0] : k_tile_time(*x.c, wgs)) + (few ? FEW_128[0] : x.fixed);
+      const double dw = (double)w.per * (w128 && !both ? MIXED_128[1] : k_tile_time(*w.c, wgs)) + (few ? FEW_128[1] : w.fixed);
       const double besides = x.parts + w.parts + LONGEST * std::max(dx, dw);
       for (const bool x_first : {true, false}) {
         const double cost = besides + (x_first ? makespan(x.wgs, dx, w.wgs, dw, slots) : makespan(w.wgs, dw, x.wgs, dx, slots));
-        if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {{x.c->tile, x.splits}, {w.c->tile, w.splits}, x_first, true}; }
+        if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {{x.c->tile, x.splits, false}, {w.c->tile, w.splits, false}, x_first, true}; }
       }
     }
   // A long launch runs at the power cap: work packed tighter lowers the clock, and two products side by side evict each
-  // other's panels.  It gains where the two last rounds complement each other (5125 x 3200 x 12800 711 us apart, 630
-  // together in a layer, estimate 1.08x; a 1024-wide layer on 13824 tokens 1555 -> 1510), the longest not by a few per cent of the
-  // estimate: 2999 x 3584 x 37888, estimate 1.05x, makes its layer 0.6-1.7 % slower, 8192 x 4096 x 22016 (1.00x) 2160 -> 2207.
-  // Measured on their own, 40 maps whose estimate lies 4 % about even gain 1.04x.
+  // other's panels.  Two launches / one, by the ratio of the estimates, alone: over 540 us 1.05-1.1 below 0.86, 1.02-1.05 up to 0.92,
+  // 1.0 beyond; in a layer 5125 x 3200 x 12800 (0.79) 711 -> 630, but 2999 x 3584 x 37888 (0.87) makes it 0.6-1.7 % slower and
+  // 8192 x 4096 x {12288, 22016} (0.92, 0.93) 1.0 %.  From 140 to 540 us 1.05-1.2 below 0.9, 1.0-1.04 up to 1.0; a 1024-wide layer on
+  // 13824 tokens (0.87-0.95) 1555 -> 1510.  Shorter ones always gain by the launch that goes.
   // The SwiGLU gradient's epilogue moves three matrices while no matrix core works; beside another product's k-loops that is
   // hidden (8192 x 11008 x 4096 1226 -> 1119 us, 32768 x 14336 x 4096 6006 -> 5790).
-  if (!swiglu && best_cost > 150) {
+  if (!swiglu && best_cost > 140) {
     double x_alone, w_alone;
     plan_gemm(t, k, n, false, false, split_bytes, &x_alone);
     plan_gemm(k, n, t, true, true, split_bytes, &w_alone);
-    best.pays = best_cost * (best_cost > 600 ? 1.06 : 0.94) < x_alone + w_alone + 2.5;
+    best.pays = best_cost * (best_cost > 540 ? 1.16 : 1.0) < x_alone + w_alone + 2.5;
   }
   return best;
 }
@@ -477,11 +506,11 @@ namespace {
 // into LDS, 16 bytes a lane, which is only known to work from addresses that are multiples of 16; operands that start
 // elsewhere (a tensor inside a larger buffer) take 128x128 tiles, whose loads go through registers.
 GemmPlan plan_of(const GemmArgs& g) {
-  if (!takes_tile_kernel(g)) return {GemmTile::T256, 1};
-  if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1};
-  if (g.swiglu_act || g.swiglu_dpre || g.rope_table) return {GemmTile::T256, 1};   // the fused epilogues exist for this tile
+  if (!takes_tile_kernel(g)) return {GemmTile::T256, 1, false};
+  if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1, false};
+  const bool fused = g.swiglu_act || g.swiglu_dpre || g.rope_table;
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
-  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0);
+  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0, nullptr, fused);
 }
 }  // namespace
 
@@ -541,7 +570,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const double flops = 2.0 * (double)g.m * (double)g.n * (double)g.k;
   if (pl.splits == 1) {
     ProfScope prof(cls, flops, s);
-    if (tiled) return launch_tiles(g, pl.tile, 1, s);
+    if (tiled) return launch_tiles(g, pl.tile, 1, pl.wide, s);
     // 256x256 tiles (8 wavefronts of 128x64) once they fill the chip; smaller problems keep
     // 128x128 tiles so that more workgroups exist
     return small ? launch_general<128, 128, 64, 64>(g, s) : launch_general<256, 256, 128, 64>(g, s);
@@ -549,7 +578,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   hipError_t e;
   {
     ProfScope prof(cls, flops, s);
-    e = launch_tiles(part_of(g), pl.tile, pl.splits, s);
+    e = launch_tiles(part_of(g), pl.tile, pl.splits, pl.wide, s);
   }
   return e != hipSuccess ? e : reduce_parts(g, pl.splits, s);
 }

@@ -57,3 +57,12 @@ def test_no_plan_leaves_a_part_empty(B):
                         assert (parts - 1) * per < tiles and (parts == 1 or per >= 8) and parts * m * n * 4 <= max(scratch, m * n * 4)
                         cut += parts > 1
     assert cut > 100
+
+
+# rows x columns x contraction of a decoder's down projection for a few hundred tokens: fewer tiles than compute units over a long
+# contraction
+@pytest.mark.parametrize("m", [444, 600, 763, 900])
+@pytest.mark.parametrize("n,k", [(3584, 18944), (4096, 14336), (4096, 11008)])
+def test_long_contractions_of_few_tiles_are_cut(B, m, n, k):
+    """Uncut they take 1.1 to 1.4 times as long with weights that come from memory."""
+    assert B.mllm_gemm_form(m, n, k, 0, 0, 1 << 40)[2] > 1

@@ -70,3 +70,56 @@ def test_large_tiles_on_eight_wavefronts_stored_by_k(B, k):
     assert B.mllm_gemm_form(704, 20944, k, 1, 0)[0] == 256
     for offset in (0, 5):
         assert product(B, 704, 20944, k, 1, 0, 1, offset) < 2e-3
+
+
+# k-tiles either side of the lines between four and eight wavefronts: 192-row tiles 24 (64 from two rounds on), 256-row tiles 32 for at most a
+# round and 64 beyond, weight gradients 64 (any number from a round of a matrix wider than high on)
+@pytest.mark.parametrize("m,n,k,a_layout", [(5960, 1312, 1536, 0), (5960, 1312, 1600, 0), (2216, 5536, 2048, 0), (2216, 5536, 2112, 0),
+                                            (6000, 7000, 4096, 0), (6000, 7000, 4160, 0), (640, 20944, 4096, 1), (640, 20944, 4097, 1),
+                                            (20944, 640, 4096, 1), (20944, 640, 4100, 1)])
+def test_either_side_of_the_lines_of_the_large_tiles(B, m, n, k, a_layout):
+    assert B.mllm_gemm_form(m, n, k, a_layout, 0)[0] == (192 if n == 1312 else 256)
+    for offset in (0, 3):
+        assert product(B, m, n, k, a_layout, 0, a_layout, offset) < (2e-3 if a_layout else 1e-2)
+
+
+def shifted(t, offset):
+    """The same values, `offset` elements behind an allocation's start."""
+    flat = torch.zeros(t.numel() + offset, dtype=t.dtype, device="cuda")
+    flat[offset:] = t.flatten()
+    return flat[offset:]
+
+
+# operands off 16 bytes and contractions over 4096 keep the fused epilogues on four wavefronts
+@pytest.mark.parametrize("x_at,w_at", [(0, 0), (0, 1), (3, 0), (3, 3)])
+@pytest.mark.parametrize("m,f,k", [(4200, 1536, 320), (6401, 1024, 64), (2900, 2304, 4160)])
+def test_swiglu_epilogue_on_four_wavefronts(B, m, f, k, x_at, w_at):
+    """[gate | up] carries one rounding (1e-2), silu(gate) * up another (2e-2)."""
+    g = torch.Generator(device="cuda").manual_seed(m + k)
+    x = torch.randn(m, k, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(k, 2 * f, generator=g, device="cuda") * 0.125).bfloat16()
+    pre, act = (torch.full((m, c), float("nan"), dtype=torch.bfloat16, device="cuda") for c in (2 * f, f))
+    B.mllm_op_gemm_swiglu(shifted(x, x_at), shifted(w, w_at), pre, act, m, f, k)
+    ref = x.double() @ w.double()
+    gate, up = ref[:, :f], ref[:, f:]
+    assert nmax_err(host_f64(pre), ref.cpu().numpy()) < 1e-2
+    assert nmax_err(host_f64(act), (gate * torch.sigmoid(gate) * up).cpu().numpy()) < 2e-2
+
+
+@pytest.mark.parametrize("x_at,w_at", [(0, 0), (0, 1), (3, 0)])
+@pytest.mark.parametrize("k", [64, 320, 4160])
+def test_rotary_epilogue_of_64_wide_heads_on_four_wavefronts(B, k, x_at, w_at):
+    m, n, rot, hd = 4101, 3584, 2560, 64
+    g = torch.Generator(device="cuda").manual_seed(k)
+    x = torch.randn(m, k, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(k, n, generator=g, device="cuda") * 0.06).bfloat16()
+    pos = torch.arange(m, device="cuda", dtype=torch.int32)
+    table = torch.empty(m, hd, device="cuda")
+    B.mllm_op_rope_table(table, m, hd, 10000.0)
+    y = torch.zeros(m, n, dtype=torch.bfloat16, device="cuda")
+    B.mllm_op_gemm_rope(shifted(x, x_at), shifted(w, w_at), None, y, m, n, k, pos, table, rot, hd)
+    ref = x.double() @ w.double()
+    cos, sin = (t.double()[:, None, :] for t in table.split(hd // 2, dim=1))
+    a, b = ref[:, :rot].reshape(m, rot // hd, 2, hd // 2).unbind(2)
+    want = torch.cat([torch.stack([a * cos - b * sin, b * cos + a * sin], dim=2).reshape(m, rot), ref[:, rot:]], dim=1)
+    assert nmax_err(host_f64(y), want.cpu().numpy()) < 1e-2
