@@ -250,8 +250,8 @@ mllm_status_t mllm_op_gemm_swiglu(const void* x, const void* w_gu, void* pre, vo
 mllm_status_t mllm_op_gemm_swiglu_bwd(const void* dy, const void* w_d, const void* pre, void* dpre,
                                       int64_t m, int64_t f, int64_t k, void* hip_stream);
 
-/* Both gradients of a linear map Y [t, n] = X [t, k] . W [k, n] (bf16, row-major), in one launch where both products take
- * the tile kernel and dy and w start on 16 bytes, as the stage's backward pass forms them:
+/* Both gradients of a linear map Y [t, n] = X [t, k] . W [k, n] (bf16, row-major), as the stage's backward pass forms them: in
+ * one launch where both products take the tile kernel, dy, x and w start on 16 bytes and the plan expects a gain, else in two:
  *   dx [t, k] bf16 = dy . W^T,  dw [k, n] fp32 (+)= X^T . dy (accumulate != 0: added).
  * swiglu_pre not NULL (the conditions of mllm_op_gemm_swiglu_bwd with m = t, f = k, k = n, else MLLM_ERR_UNSUPPORTED): dx is
  * [d gate | d up] [t, 2k] instead, from swiglu_pre = [gate | up] [t, 2k].
@@ -492,7 +492,8 @@ mllm_status_t mllm_optimize_parallelism(const mllm_module_profile_t* enc, const 
  * mllm_profile_begin(max_records) creates the events and starts recording every kernel launch of
  * the calling process' later mllm_* calls, bracketing each with HIP events on its launch stream.
  * mllm_profile_end stops recording, waits for the recorded events, and sums per class
- * (0 / 1 / 2: the 256x256-tile GEMM kernel in its Y=X.W / dX / dW layouts (1 also dX and dW in one launch), 3 attention forward,
+ * (0 / 1 / 2: the 256x256-tile GEMM kernel in its Y=X.W / dX / dW layouts, 1 also every launch that forms dX and dW together unless both
+ * are in 128x128 tiles (then 6): its FLOPs are those of both, its tiles may be 256x256, 192x256 and 128x128; 3 attention forward,
  * 4 attention backward, 5 the norm / rotary / activation / reduction / copy kernels, 6 the
  * 128x128-tile GEMM kernel in any layout, 7 the 192x256-tile form of the large GEMM kernel in any
  * layout): launches[8], milliseconds[8] and work[8] (algorithmic FLOPs for the GEMM and attention

@@ -12,8 +12,10 @@ namespace {
 // fragment reads, LDS stores, loads and scalar work of a k-tile take as long as its MFMAs, and no order of them hides
 // that.  With two, one issues under the other's MFMAs, the staging registers and their LDS stores go, and direct loads of
 // operands stored [K, .] are no longer late.  The price is LDS reads: 192 KB a k-tile of 256x256 where four wavefronts of
-// 128x128 read 128 KB, which on long contractions at the power cap costs more than it gives.
-// Four wavefronts -> eight, one card, in turn (us):
+// 128x128 read 128 KB, which on long contractions at the power cap costs more than it gives; and two stages look one k-tile
+// ahead, which does not cover the latency of operands that come from memory (where the line lies then: takes_wide_form in
+// gemm.hip).  No SwiGLU gradient: its product has both operands k-contiguous and 256x256 tiles.
+// Four wavefronts -> eight, one card, in turn, operands in the memory-side cache (us):
 //   256x256, B stored [K, N]: 26496 x 4096 x 1024 206 -> 188, 5125 x 12800 x 3200 357 -> 335, 4096 x 4096 x 4096 100 -> 95, 32768 x 28672 x
 //   4096 5550 -> 5330, 32768 x 4096 x 14336 2710 -> 2750; both [K, .]: 4096 x 28672 x 32768 5420 -> 5230, 3200 x 12800 x 5125
 //   347 -> 332; both k-contiguous: 26496 x 4096 x 1024 187 -> 186, 32768 x 4096 x 28672 4990 -> 5400.
@@ -148,7 +150,6 @@ __device__ __forceinline__ void gemm_wide_tile(GemmParams p, int pid, int nblk, 
   if constexpr (OUT_F32) p.c = reinterpret_cast<float*>(p.c) + split * p.c_split_stride;
   const int64_t row0 = m0 + wm * 16 * WM, col0 = n0 + wn * 16 * WN;
   if constexpr (EPI == EPI_SWIGLU) store_blocks_swiglu<WM, WN>(p, acc, row0, (n0 >> 1) + 8 * WN * wn, lane_out, out_stage);
-  else if constexpr (EPI == EPI_SWIGLU_BWD) store_blocks_swiglu_bwd<WM, WN>(p, acc, row0, col0, lane_out, out_stage);
   else store_blocks<WM, WN, OUT_F32, EPI == EPI_ROPE64 ? 64 : 0>(p, acc, row0, col0, lane_out, out_stage);
 }
 

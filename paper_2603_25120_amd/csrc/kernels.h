@@ -41,7 +41,8 @@ struct GemmArgs {
   int32_t rope_head_dim = 0;
 };
 // Whether launch_gemm can rotate the q and k columns of a forward product in its epilogue (large-tile
-// kernel, K a multiple of 64, heads of 64 or 128 so that a wavefront's 128 columns hold whole heads).
+// kernel, K a multiple of 64, heads of 64 or 128: a wavefront owns 128 columns, 64 in the form on eight wavefronts, which
+// therefore leaves heads of 128 to the other).
 bool gemm_rope_fusable(int64_t m, int64_t n, int64_t k, int32_t head_dim);
 bool gemm_swiglu_bwd_fusable(int64_t m, int64_t n, int64_t k);
 // Whether launch_gemm can write the SwiGLU activation of a forward product X[M,K].W[K,N] along
