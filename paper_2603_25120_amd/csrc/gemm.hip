@@ -326,7 +326,7 @@ constexpr TileCost TILE_COSTS[3][6] = {{{GemmTile::T256, false, 256, 256, 256, 0
                                         {GemmTile::T128, true, 128, 128, 256, 0, 0.37, 0.37, 0.48, 3.8}}};
 inline int cost_row(bool a_t, bool b_t) { return a_t ? 2 : b_t ? 0 : 1; }   // b_t: B stored [K, N]
 // Where a tile may go to eight wavefronts at all; below these lines the estimate decides, but for more than a round of large tiles in
-// forward layout, which then always do.  128x128: as long as every workgroup has a CU to itself (gain up to there 1.02-1.15 in every
+// forward layout and weight gradients over more than 64 k-tiles, which then always do.  128x128: as long as every workgroup has a CU to itself (gain up to there 1.02-1.15 in every
 // layout, loss of 2-10 % beyond).  The large tiles: not with both operands k-contiguous; else only for short contractions, as two
 // stages do not cover the latency of weights that come from memory.  Time on four wavefronts / on eight, geomeans by k-tiles of
 // a part: forward 192x256 up to 16 1.02-1.13, up to 32 0.93-1.0 below 1024 workgroups, beyond 0.79-0.99 (up to 64 with weights of up to 64 MB
@@ -380,6 +380,9 @@ GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t, size_t s
       if (cost < best_cost * (1 - 1e-9)) { best_cost = cost; best = {c.tile, (int)sp, c.wide}; }
     }
   }
+  // Long weight gradients: the estimates of the two kernels lie within 1 % of each other, the times do not (takes_wide_form).
+  const int64_t per = (nk + best.splits - 1) / best.splits, wgs = ((m + 255) / 256) * ((n + 255) / 256) * best.splits;
+  if (row == 2 && best.tile == GemmTile::T256 && per > 64) best.wide = takes_wide_form(row, best.tile, m, n, k, per, wgs);
   if (estimate) *estimate = best_cost;
   return best;
 }

@@ -76,7 +76,7 @@ def test_large_tiles_on_eight_wavefronts_stored_by_k(B, k):
 # round and 64 beyond, weight gradients 64 (any number from a round of a matrix wider than high on)
 @pytest.mark.parametrize("m,n,k,a_layout", [(5960, 1312, 1536, 0), (5960, 1312, 1600, 0), (2216, 5536, 2048, 0), (2216, 5536, 2112, 0),
                                             (6000, 7000, 4096, 0), (6000, 7000, 4160, 0), (640, 20944, 4096, 1), (640, 20944, 4097, 1),
-                                            (20944, 640, 4096, 1), (20944, 640, 4100, 1)])
+                                            (20944, 640, 4096, 1), (20944, 640, 4100, 1), (1024, 20736, 4161, 1), (20736, 1024, 4161, 1)])
 def test_either_side_of_the_lines_of_the_large_tiles(B, m, n, k, a_layout):
     assert B.mllm_gemm_form(m, n, k, a_layout, 0)[0] == (192 if n == 1312 else 256)
     for offset in (0, 3):
