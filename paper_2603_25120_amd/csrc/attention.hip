@@ -7,19 +7,17 @@
 // the LLM).  The host turns the segments into lists of (segment, tile, head) work items, one list
 // per XCD, in which workgroups that share rows sit together (attn_items.h).
 //
-// All three kernels compute score blocks TRANSPOSED so that a lane owns one query (or one key)
-// column of the 32x32 MFMA result: row statistics are then per-lane scalars plus one exchange
-// between the two half-wavefronts, and the probability block can be fed straight back as the
-// B operand of the next MFMA without leaving registers (the contraction-slot order of that
-// operand is a fixed permutation of the key/query rows, applied identically to the A operand,
-// which is fetched from LDS with the transposing read).
+// All kernels compute score blocks TRANSPOSED so that a lane owns one column of a 16x16 MFMA result, a query (a key in the
+// dK/dV pass) of its wavefront: row statistics are then per-lane scalars, summed over the four lanes of a column at the end,
+// and the probability block can be fed straight back as the B operand of the next MFMA without leaving registers (the
+// contraction-slot order of that operand is a fixed permutation of the key/query rows, applied identically to the A
+// operand, which is fetched from LDS with the transposing read).
 //
 //   forward:  S^T = K.Q^T, online softmax, O^T += V^T.P^T
 //   dQ pass:  delta = rowsum(dO*O); S^T, dP^T = V.dO^T, dS^T = P^T*(dP^T - delta), dQ^T += K^T.dS^T
 //   dK/dV:    S = Q.K^T, dP = dO.V^T, dV^T += dO^T.P, dK^T += Q^T.dS, looping the query tiles
 //             and the query heads of the GQA group, so dK/dV need no atomics.
 #include <algorithm>
-#include <utility>
 
 #include "common.h"
 #include "kernels.h"
@@ -28,29 +26,21 @@ namespace mllm {
 
 namespace {
 
-#define MLLM_LDS_VOID(ptr) ((MLLM_LDS void*)(ptr))
-constexpr int WAIT_VMCNT_0 = (0x7 << 4) | (0xF << 8);
 constexpr int BKV = 64;   // key rows staged per step (forward, dQ)
-constexpr int BQ = 64;    // query rows staged per step (dK/dV)
+constexpr int BQ = 64;    // query rows staged per step (dK/dV, heads of 64)
 
-// LDS tiles are [rows][HD] bf16 without padding; 16-byte chunk c of row r lives at chunk position
-// c ^ swz<HD>(r).  LDS serves 256 B per clock: a 16-byte read is processed 16 lanes at a time (16
-// consecutive rows, same logical chunk) and a transposing 8-byte read 32 lanes at a time (4
-// consecutive rows x 64 B).  The permutations below make both patterns conflict-free on the same
-// tile: HD = 128 (256-byte rows) maps the 16 rows to 16 different chunks and the 4 rows of a
-// transposing read to the 4 quarters of the row; HD = 64 (128-byte rows, two rows per 256-byte
-// window) does the same over row pairs.
+// LDS tiles are [rows][HD] bf16 without padding; 16-byte chunk c of row r lives at chunk position c ^ swz<HD>(r).  LDS serves
+// 256 B per clock.  A transposing 8-byte read is processed 32 lanes at a time (here 8 consecutive rows x 32 B), a 16-byte read
+// 16 lanes at a time, lanes 0-3, 12-15, 20-23 and 24-27 of each 32, then the other 16 (here rows 0-3 and 12-15 at an even chunk
+// and rows 4-11 at the next one, or the other way round).  The permutations make both patterns conflict-free on the same
+// tile: HD = 128 (256-byte rows) gives rows 0-7 the 8 pairs of chunks and rows 8-15 the other halves of the pairs, those of
+// 12-15 beside 0-3; HD = 64 (128-byte rows, two rows per 256-byte window) does the same over row pairs.
 template <int HD>
 __device__ __forceinline__ int swz(int r) {
-  if constexpr (HD == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-  else { const int t = (r >> 1) & 7; return ((t & 1) << 2) | (t >> 1); }
+  if constexpr (HD == 128) return (((r & 7) ^ ((r >> 1) & 4)) << 1) | ((r >> 3) & 1);
+  else { const int t = (r >> 1) & 7; return (((t & 3) ^ ((t >> 1) & 2)) << 1) | (t >> 2); }
 }
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-// Descriptor over rows [0, rows) of a row-major bf16 matrix slice of `width` columns.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const bf16_t* base, int64_t stride, int rows, int width) {
-  const uint32_t bytes = rows > 0 ? (uint32_t)(((int64_t)(rows - 1) * stride + width) * 2) : 0u;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
-}
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
@@ -76,47 +66,6 @@ __device__ __forceinline__ KvRange kv_range(int grp, int q_begin, int seg_len, i
   const int first = total * part / parts, last = total * (part + 1) / parts;
   return {last - first, first / per_head, q_begin + first % per_head * tile_rows};
 }
-// A part's sums of one key row (the lane's), fp32 and unscaled.
-template <int HD>
-__device__ __forceinline__ void store_kv_partial(const AttnParams& p, const f32x16 (&dk)[HD / 32], const f32x16 (&dv)[HD / 32],
-                                                 int64_t row, int kvh, int h, unsigned part) {
-  const int64_t width = (int64_t)p.Hkv * HD;
-  float* k = p.dkv_partial + ((int64_t)(2 * part) * p.T + row) * width + kvh * HD + 4 * h;
-  float* v = k + (int64_t)p.T * width;
-#pragma unroll
-  for (int d = 0; d < HD / 32; d++)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      *reinterpret_cast<float4*>(k + 32 * d + 8 * g4) = make_float4(dk[d][4 * g4], dk[d][4 * g4 + 1], dk[d][4 * g4 + 2], dk[d][4 * g4 + 3]);
-      *reinterpret_cast<float4*>(v + 32 * d + 8 * g4) = make_float4(dv[d][4 * g4], dv[d][4 * g4 + 1], dv[d][4 * g4 + 2], dv[d][4 * g4 + 3]);
-    }
-}
-
-// Gradient of the rotary positions on an accumulator of ND = HD/32 blocks whose lane owns row `pos`
-// of its segment: the pair (c, c + HD/2) sits in blocks (d, d + ND/2) of the same lane.  Forward was
-// y1 = x1 cos - x2 sin, y2 = x2 cos + x1 sin, so dx1 = dy1 cos + dy2 sin, dx2 = dy2 cos - dy1 sin.
-// `scale` multiplies the result.
-template <int HD>
-__device__ __forceinline__ void rope_unrotate(f32x16 (&acc)[HD / 32], const float* table, int pos, int h, float scale) {
-  constexpr int ND = HD / 32, HALF = HD / 2;
-  const float* trow = table + (int64_t)pos * HD;
-#pragma unroll
-  for (int d = 0; d < ND / 2; d++)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      const int f0 = 32 * d + 8 * g4 + 4 * h;
-      const float4 c = *reinterpret_cast<const float4*>(trow + f0);
-      const float4 sn = *reinterpret_cast<const float4*>(trow + HALF + f0);
-      const float cs[4] = {c.x * scale, c.y * scale, c.z * scale, c.w * scale};
-      const float ss[4] = {sn.x * scale, sn.y * scale, sn.z * scale, sn.w * scale};
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const float y1 = acc[d][4 * g4 + e], y2 = acc[d + ND / 2][4 * g4 + e];
-        acc[d][4 * g4 + e] = y1 * cs[e] + y2 * ss[e];
-        acc[d + ND / 2][4 * g4 + e] = y2 * cs[e] - y1 * ss[e];
-      }
-    }
-}
 
 // The work item of this workgroup (an entry of the list, by default blockIdx.x; the host has arranged the entries so
 // that workgroups sharing rows run on one XCD).  Returns false, for the whole workgroup, on the empty
@@ -132,685 +81,22 @@ __device__ __forceinline__ bool work_item(const AttnItem* list, AttnItem& t, int
   return t.seg_len > 0;
 }
 
-// Natural-layout operand: row (r0 + lane%32), contraction values 16c + 8*(lane/32) .. +7.
-template <int HD>
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_t* tile, int r0, int c, int lane) {
-  Frag8 f;
-  const int r = r0 + (lane & 31);
-  f.u = *reinterpret_cast<const uint4*>(tile + r * HD + 8 * ((2 * c + (lane >> 5)) ^ swz<HD>(r)));
-  return f.v;
-}
-// Transposed operand for the register-resident B operand built from a 32x32 accumulator:
-// output row (n0 + lane%32) of the tile's columns, contraction slots e = 0..7 standing for tile
-// rows k16 + 8*(e/4) + 4*(lane/32) + e%4.  Each transposing read returns tile[k0 + e][n] for
-// e = 0..3 when lane i of a 16-lane group addresses tile[k0 + i/4][n0' + 4*(i%4)].
-template <int HD>
-__device__ __forceinline__ bf16x8 frag_cols_permuted(const bf16_t* tile, int k16, int n0, int lane) {
-  Frag8 f;
-  const int h = lane >> 5, i16 = lane & 15;
-  const int n = n0 + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-  const int k = k16 + 4 * h + (i16 >> 2);
-  const bf16_t* p0 = tile + k * HD + 8 * ((n >> 3) ^ swz<HD>(k)) + (n & 7);
-  const bf16_t* p1 = tile + (k + 8) * HD + 8 * ((n >> 3) ^ swz<HD>(k + 8)) + (n & 7);
-  f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLLM_LDS s16x4*)p0);
-  f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLLM_LDS s16x4*)p1);
-  return f.v;
-}
-// Accumulator values 8*cc .. 8*cc+7 of a 32x32 block as a bf16 B operand.
-__device__ __forceinline__ bf16x8 acc_to_frag(const f32x16& a, int cc) {
-  Frag8 f;
-#pragma unroll
-  for (int e = 0; e < 4; e++) f.w[e] = pack_bf16x2(a[8 * cc + 2 * e], a[8 * cc + 2 * e + 1]);
-  return f.v;
-}
-__device__ __forceinline__ bf16x8 global_frag(const bf16_t* p, bool ok) {
-  Frag8 f;
-  f.u = ok ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
-  return f.v;
-}
-// Row index inside a 32x32 accumulator block held at position v by a lane of half h.
-__device__ __forceinline__ int acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
-
-// Scheduling patterns (one call per slot): an MFMA followed by N LDS reads; four LDS reads
-// followed by a pair of MFMAs.
-template <int N, int... Is>
-__device__ __forceinline__ void reads_behind_mfmas(std::integer_sequence<int, Is...>) {
-  ((__builtin_amdgcn_sched_group_barrier(0x008, 1, 0), __builtin_amdgcn_sched_group_barrier(0x100, N, 0), (void)Is), ...);
-}
-// An MFMA followed by one LDS read and one load from memory.
-template <int... Is>
-__device__ __forceinline__ void reads_and_loads_behind_mfmas(std::integer_sequence<int, Is...>) {
-  ((__builtin_amdgcn_sched_group_barrier(0x008, 1, 0), __builtin_amdgcn_sched_group_barrier(0x100, 1, 0),
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0), (void)Is), ...);
-}
-// N LDS reads followed by one MFMA.
-template <int N, int... Is>
-__device__ __forceinline__ void reads_before_mfmas(std::integer_sequence<int, Is...>) {
-  ((__builtin_amdgcn_sched_group_barrier(0x100, N, 0), __builtin_amdgcn_sched_group_barrier(0x008, 1, 0), (void)Is), ...);
-}
-template <int... Is>
-__device__ __forceinline__ void reads_before_mfma_pairs(std::integer_sequence<int, Is...>) {
-  ((__builtin_amdgcn_sched_group_barrier(0x100, 4, 0), __builtin_amdgcn_sched_group_barrier(0x008, 2, 0), (void)Is), ...);
-}
-
-// ---------------------------------------------------------------------------------------------
-// forward
-// ---------------------------------------------------------------------------------------------
-template <int HD>
-__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
-  constexpr int NC = HD / 16, ND = HD / 32, NB = BKV / 32, TILE = BKV * HD;
-  // K and V tiles go from global memory straight into LDS (`buffer_load ... lds`), two stages
-  // each in arrays of their own so that every access names its stage statically.
-  __shared__ __attribute__((aligned(1024))) bf16_t Ks0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Ks1[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Vs0[TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Vs1[TILE];
-  AttnItem t;
-  if (!work_item(p.list, t, blockIdx.x)) return;
-  const int head = t.head, kvh = head / (p.Hq / p.Hkv);
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qrow = t.tile0 + 32 * wave + (lane & 31);
-  const bool qok = qrow < t.seg_len;
-  const bf16_t* qp = p.q + (int64_t)(t.seg_start + qrow) * p.q_stride + head * HD + 8 * h;
-  bf16x8 qf[NC];
-#pragma unroll
-  for (int c = 0; c < NC; c++) qf[c] = global_frag(qp + 16 * c, qok);
-
-  const bf16_t* kbase = p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD;
-  const bf16_t* vbase = p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD;
-  const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
-  const int wave_first_q = t.tile0 + 32 * wave, wave_last_q = wave_first_q + 31;
-
-  f32x16 oacc[ND];
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) oacc[d][v] = 0.f;
-  // Running maximum in units of log2: m = max(score) * scale * log2(e); l = sum of exp2(...).
-  float m = -INFINITY, l = 0.f;
-  const float c2 = p.scale_log2e;
-
-  // One direct-to-LDS instruction moves 64 lanes x 16 bytes = RPI rows of the tile; lane l's
-  // chunk lands at position l of that 1 KiB, so the lane fetches the global chunk that the
-  // permutation puts there.  Rows past kv_end are outside the descriptor: zeros, no traffic.
-  const __amdgpu_buffer_rsrc_t rk = rows_rsrc(kbase, p.kv_stride, kv_end, HD), rv = rows_rsrc(vbase, p.kv_stride, kv_end, HD);
-  constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BKV / RPI / 4;
-  uint32_t kv_off[PER_WAVE];
-#pragma unroll
-  for (int i = 0; i < PER_WAVE; i++) {
-    const int r = (wave * PER_WAVE + i) * RPI + lane / CPR, c = (lane % CPR) ^ swz<HD>(r);
-    kv_off[i] = (uint32_t)((r * p.kv_stride + 8 * c) * 2);
-  }
-  const uint32_t tile_bytes = (uint32_t)(BKV * p.kv_stride * 2);
-  auto issue = [&](int kv0, bf16_t* kn, bf16_t* vn) {
-    const uint32_t row = (uint32_t)(kv0 / BKV) * tile_bytes;
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; i++) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, MLLM_LDS_VOID(kn + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)kv_off[i], (int)row, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, MLLM_LDS_VOID(vn + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)kv_off[i], (int)row, 0, 0);
-    }
-  };
-
-  // One key tile: wait for its loads (enqueued a tile ago), barrier (every wavefront is now done
-  // with the other stage), multiply; the loads of the next tile into the other stage go out one
-  // behind each of the first score MFMAs, so the wavefront does not stand still while the memory
-  // pipeline takes them (issued in one run behind the barrier they held it for 0.2 us per tile).
-  auto tile = [&](const bf16_t* Ks, const bf16_t* Vs, bf16_t* Kn, bf16_t* Vn, int kv0, bool live) {
-    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-    __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
-    f32x16 s[NB];
-#pragma unroll
-    for (int b = 0; b < NB; b++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) s[b][v] = 0.f;
-    // Scores: the LDS reads of the K fragments run four ahead of their MFMAs.
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < NC; c++)
-#pragma unroll
-      for (int b = 0; b < NB; b++)
-        s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Ks, 32 * b, c, lane), qf[c], s[b], 0, 0, 0);
-    issue(kv0 + BKV, Kn, Vn);
-    static_assert(NC * NB >= 4 + 2 * PER_WAVE, "a slot behind an MFMA for every load");
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-    reads_and_loads_behind_mfmas(std::make_integer_sequence<int, 2 * PER_WAVE>{});
-    reads_behind_mfmas<1>(std::make_integer_sequence<int, NC * NB - 4 - 2 * PER_WAVE>{});
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    // A tile past the end, or wholly above the diagonal of this wavefront's rows (wavefront-uniform):
-    // its score MFMAs have carried the next tile's loads, their results are dropped.  (Leaving
-    // before them would need a second copy of the loads on that path, which costs the main path
-    // some fifty registers.)
-    if (!live || (t.causal && kv0 > wave_last_q)) return;
-    // First V fragment: its LDS latency runs under the softmax.
-    bf16x8 fv = frag_cols_permuted<HD>(Vs, 0, 0, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    // Only tiles that cross the segment end or the diagonal need the mask (wavefront-uniform).
-    const bool need_mask = (kv0 + BKV > t.seg_len) || (t.causal && kv0 + BKV - 1 > wave_first_q);
-    if (need_mask) {
-#pragma unroll
-      for (int b = 0; b < NB; b++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const int kv = kv0 + 32 * b + acc_row(v, h);
-          const bool vis = kv < t.seg_len && (!t.causal || kv <= qrow);
-          s[b][v] = vis ? s[b][v] : -INFINITY;
-        }
-    }
-    float mx = s[0][0];
-#pragma unroll
-    for (int b = 0; b < NB; b++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[b][v]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
-    // The reference maximum follows the row maximum lazily: it moves only when a tile exceeds it by
-    // more than 8 (log2 units).  Probabilities then reach 2^8 at most, which fp32 sums and the bf16
-    // operand carry at the same relative precision, and the 64-value rescaling of the output
-    // accumulator below is needed on a few tiles instead of on nearly every one (with 64 query rows
-    // per wavefront some row finds a slightly larger score in almost every tile).
-    const float m_new = mx > m + 8.f ? mx : m;
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = fast_exp2(m - m_use);
-    float rs = 0.f;
-#pragma unroll
-    for (int b = 0; b < NB; b++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        s[b][v] = fast_exp2(fmaf(s[b][v], c2, -m_use));
-        rs += s[b][v];
-      }
-    l = l * alpha + rs;
-    if (__any(m_new != m)) {  // the accumulator only needs rescaling when some row's maximum moved
-#pragma unroll
-      for (int d = 0; d < ND; d++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) oacc[d][v] *= alpha;
-    }
-    m = m_new;
-    bf16x8 pf[NB][2];
-#pragma unroll
-    for (int b = 0; b < NB; b++)
-#pragma unroll
-      for (int cc = 0; cc < 2; cc++) pf[b][cc] = acc_to_frag(s[b], cc);
-    __builtin_amdgcn_sched_barrier(0);
-    // O^T += V^T.P^T: each MFMA is preceded by the two LDS reads of the next V fragment.
-    constexpr int NPV = NB * 2 * ND;
-#pragma unroll
-    for (int i = 0; i < NPV; i++) {
-      const int bc = i / ND, d = i % ND;          // bc = 2 b + cc
-      bf16x8 nv = fv;
-      if (i + 1 < NPV) nv = frag_cols_permuted<HD>(Vs, 16 * ((i + 1) / ND), 32 * ((i + 1) % ND), lane);
-      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv, pf[bc / 2][bc % 2], oacc[d], 0, 0, 0);
-      fv = nv;
-    }
-    reads_before_mfmas<2>(std::make_integer_sequence<int, NPV - 1>{});
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-
-  issue(0, Ks0, Vs0);
-  for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
-    tile(Ks0, Vs0, Ks1, Vs1, kv0, true);
-    tile(Ks1, Vs1, Ks0, Vs0, kv0 + BKV, kv0 + BKV < kv_end);
-  }
-  // the last enqueued loads (rows past the end: zeros) must have landed before this workgroup's
-  // LDS can be handed to another one
-  __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-  l += __shfl_xor(l, 32, 64);
-  if (!qok) return;
-  const float inv = 1.f / l;
-  bf16_t* op = p.o + (int64_t)(t.seg_start + qrow) * p.o_stride + head * HD;
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      uint2 w;
-      w.x = pack_bf16x2(oacc[d][4 * g4] * inv, oacc[d][4 * g4 + 1] * inv);
-      w.y = pack_bf16x2(oacc[d][4 * g4 + 2] * inv, oacc[d][4 * g4 + 3] * inv);
-      *reinterpret_cast<uint2*>(op + 32 * d + 8 * g4 + 4 * h) = w;
-    }
-  if (h == 0) p.lse[(int64_t)head * p.T + t.seg_start + qrow] = (m + log2f(l)) * LN2;
-}
-
-// ---------------------------------------------------------------------------------------------
-// dQ pass: one workgroup per (query tile of 128, head), looping over key tiles.  It runs first in
-// the backward pass and also produces delta[h][t] = sum_d dO[t,h,d] * O[t,h,d] for the dK/dV pass.
-// ---------------------------------------------------------------------------------------------
-template <int HD>
-__device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem* list, int entry, bf16_t* Ks0, bf16_t* Ks1, bf16_t* Vs0, bf16_t* Vs1) {
-  constexpr int NC = HD / 16, ND = HD / 32;
-  // K and V tiles go straight to LDS, two stages each (as in the forward kernel).
-  AttnItem t;
-  if (!work_item(list, t, entry)) return;
-  const int head = t.head, kvh = head / (p.Hq / p.Hkv);
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qrow = t.tile0 + 32 * wave + (lane & 31);
-  const bool qok = qrow < t.seg_len;
-  const int64_t grow = t.seg_start + (qok ? qrow : 0);
-  const bf16_t* qp = p.q + grow * p.q_stride + head * HD + 8 * h;
-  const bf16_t* dop = p.d_o + grow * p.o_stride + head * HD + 8 * h;
-  bf16x8 qf[NC], dof[NC];
-#pragma unroll
-  for (int c = 0; c < NC; c++) {
-    qf[c] = global_frag(qp + 16 * c, qok);
-    dof[c] = global_frag(dop + 16 * c, qok);
-  }
-  // Rows beyond the segment get lse = +inf, so their probabilities are exp2(-inf) = 0.
-  const float lse2 = qok ? p.lse[(int64_t)head * p.T + grow] * LOG2E : INFINITY;
-  // delta = rowsum(dO * O) of the lane's query row: each half-wavefront holds half of the row's
-  // columns (the dO fragments above, O fetched the same way).  The dK/dV pass, which runs after this
-  // kernel, reads it from p.delta.
-  float delta = 0.f;
-  {
-    const bf16_t* op = p.o + grow * p.o_stride + head * HD + 8 * h;
-#pragma unroll
-    for (int c = 0; c < NC; c++) {
-      Frag8 fo, fd;
-      fo.v = global_frag(op + 16 * c, qok);
-      fd.v = dof[c];
-#pragma unroll
-      for (int w = 0; w < 4; w++) delta += bf16lo(fo.w[w]) * bf16lo(fd.w[w]) + bf16hi(fo.w[w]) * bf16hi(fd.w[w]);
-    }
-    delta += __shfl_xor(delta, 32, 64);
-    if (qok && h == 0) p.delta[(int64_t)head * p.T + grow] = delta;
-  }
-  const int wave_first_q = t.tile0 + 32 * wave;
-
-  const bf16_t* kbase = p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD;
-  const bf16_t* vbase = p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD;
-  const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
-  const int wave_last_q = t.tile0 + 32 * wave + 31;
-
-  f32x16 dqacc[ND];
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) dqacc[d][v] = 0.f;
-
-  const __amdgpu_buffer_rsrc_t rk = rows_rsrc(kbase, p.kv_stride, kv_end, HD), rv = rows_rsrc(vbase, p.kv_stride, kv_end, HD);
-  constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BKV / RPI / 4;
-  uint32_t kv_off[PER_WAVE];
-#pragma unroll
-  for (int i = 0; i < PER_WAVE; i++) {
-    const int r = (wave * PER_WAVE + i) * RPI + lane / CPR, c = (lane % CPR) ^ swz<HD>(r);
-    kv_off[i] = (uint32_t)((r * p.kv_stride + 8 * c) * 2);
-  }
-  const uint32_t tile_bytes = (uint32_t)(BKV * p.kv_stride * 2);
-  auto issue = [&](int kv0, bf16_t* kn, bf16_t* vn) {   // rows past kv_end: zeros, no traffic
-    const uint32_t row = (uint32_t)(kv0 / BKV) * tile_bytes;
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; i++) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, MLLM_LDS_VOID(kn + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)kv_off[i], (int)row, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, MLLM_LDS_VOID(vn + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)kv_off[i], (int)row, 0, 0);
-    }
-  };
-  auto tile = [&](const bf16_t* Ks, const bf16_t* Vs, bf16_t* Kn, bf16_t* Vn, int kv0, bool live) {
-    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-    __syncthreads();
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int b = 0; b < BKV / 32; b++) {
-      f32x16 s, dp;
-#pragma unroll
-      for (int v = 0; v < 16; v++) { s[v] = 0.f; dp[v] = 0.f; }
-      // Scores and dP: the LDS reads run AHEAD fragments in front of their MFMAs.  At head_dim 128 the
-      // kernel stands at the 256 registers that two wavefronts per SIMD allow, and a request for four
-      // fragments ahead is not refused but dropped as a whole: every MFMA then waits for a read
-      // issued right in front of it (measured 4 % slower than two ahead, which fits).
-      constexpr int AHEAD = HD == 128 ? 2 : 4;
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int c = 0; c < NC; c++) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Ks, 32 * b, c, lane), qf[c], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Vs, 32 * b, c, lane), dof[c], dp, 0, 0, 0);
-      }
-      if (b == 0) {
-        // the next tile's loads go out one behind each of the first MFMAs (see the forward kernel)
-        issue(kv0 + BKV, Kn, Vn);
-        static_assert(2 * NC >= AHEAD + 2 * PER_WAVE, "a slot behind an MFMA for every load");
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
-        reads_and_loads_behind_mfmas(std::make_integer_sequence<int, 2 * PER_WAVE>{});
-        reads_behind_mfmas<1>(std::make_integer_sequence<int, 2 * NC - AHEAD - 2 * PER_WAVE>{});
-        __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
-      } else {
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
-        reads_behind_mfmas<1>(std::make_integer_sequence<int, 2 * NC - AHEAD>{});
-        __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // a tile past the end or wholly above this wavefront's diagonal: only the loads were wanted
-      if (b == 0 && (!live || (t.causal && kv0 > wave_last_q))) return;
-      // First K^T fragment of the dQ product: its LDS latency runs under the vector work.
-      bf16x8 fk = frag_cols_permuted<HD>(Ks, 32 * b, 0, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      const bool need_mask = (kv0 + 32 * b + 32 > t.seg_len) || (t.causal && kv0 + 32 * b + 31 > wave_first_q);
-      if (need_mask) {
-#pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const int kv = kv0 + 32 * b + acc_row(v, h);
-          const bool vis = kv < t.seg_len && (!t.causal || kv <= qrow);
-          s[v] = vis ? s[v] : -INFINITY;
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < 16; v++) s[v] = fast_exp2(fmaf(s[v], p.scale_log2e, -lse2)) * (dp[v] - delta);   // dS^T
-      bf16x8 dsf[2];
-#pragma unroll
-      for (int cc = 0; cc < 2; cc++) dsf[cc] = acc_to_frag(s, cc);
-      __builtin_amdgcn_sched_barrier(0);
-      constexpr int NDQ = 2 * ND;
-#pragma unroll
-      for (int i = 0; i < NDQ; i++) {
-        bf16x8 nk = fk;
-        if (i + 1 < NDQ) nk = frag_cols_permuted<HD>(Ks, 32 * b + 16 * ((i + 1) / ND), 32 * ((i + 1) % ND), lane);
-        dqacc[i % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk, dsf[i / ND], dqacc[i % ND], 0, 0, 0);
-        fk = nk;
-      }
-      reads_before_mfmas<2>(std::make_integer_sequence<int, NDQ - 1>{});
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  issue(0, Ks0, Vs0);
-  for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
-    tile(Ks0, Vs0, Ks1, Vs1, kv0, true);
-    tile(Ks1, Vs1, Ks0, Vs0, kv0 + BKV, kv0 + BKV < kv_end);
-  }
-  __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);   // the last enqueued tile (zeros) has landed
-  if (!qok) return;
-  float out_scale = p.scale;
-  if (p.rope_table) {   // the scale rides on the rotation's factors
-    rope_unrotate<HD>(dqacc, p.rope_table, qrow, h, p.scale);
-    out_scale = 1.f;
-  }
-  bf16_t* dqp = p.dq + grow * p.q_stride + head * HD;
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      uint2 w;
-      w.x = pack_bf16x2(dqacc[d][4 * g4] * out_scale, dqacc[d][4 * g4 + 1] * out_scale);
-      w.y = pack_bf16x2(dqacc[d][4 * g4 + 2] * out_scale, dqacc[d][4 * g4 + 3] * out_scale);
-      *reinterpret_cast<uint2*>(dqp + 32 * d + 8 * g4 + 4 * h) = w;
-    }
-}
-
-template <int HD>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
-  __shared__ __attribute__((aligned(1024))) bf16_t Ks0[BKV * HD], Ks1[BKV * HD], Vs0[BKV * HD], Vs1[BKV * HD];
-  attn_bwd_dq<HD>(p, p.list, blockIdx.x, Ks0, Ks1, Vs0, Vs1);
-}
-
-// ---------------------------------------------------------------------------------------------
-// dK/dV pass: one workgroup per (key tile of 128, kv head); each wavefront owns 32 key rows and
-// loops over the query heads of the group and the query tiles that can see its keys.
-//
-// The query-side tiles (Q, dO) are double-buffered in LDS and filled by buffer loads that write
-// LDS directly (no staging registers, no LDS store instructions): the loads of tile i+1 are
-// enqueued right after the barrier that opens tile i and have all of tile i's MFMAs to land.
-// One such instruction moves 64 chunks of 16 bytes into 1 KiB of LDS, lane l to chunk position
-// l % CPR of row l / CPR; the lane therefore asks for the global chunk that the XOR swizzle keeps
-// at that position.  Rows past the segment are out of the descriptor's range and arrive as zeros.
-// ---------------------------------------------------------------------------------------------
-// s_waitcnt vmcnt(0) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-
-// SELF_DELTA: delta is formed here, four threads a query row of the tile, instead of read from the dQ pass.
-struct DkvLds { bf16_t *q0, *q1, *o0, *o1; float *lse0, *lse1, *delta0, *delta1; };
-template <int HD, bool SELF_DELTA>
-__device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem* list, int entry, int part, int parts, const DkvLds& lds) {
-  constexpr int NC = HD / 16, ND = HD / 32;
-  static_assert(!SELF_DELTA || HD == 64, "four threads of 16 columns a row");
-  bf16_t *const Qs0 = lds.q0, *const Qs1 = lds.q1, *const dOs0 = lds.o0, *const dOs1 = lds.o1;
-  float *const lse_s0 = lds.lse0, *const lse_s1 = lds.lse1, *const delta_s0 = lds.delta0, *const delta_s1 = lds.delta1;
-  AttnItem t;
-  if (!work_item(list, t, entry)) return;
-  const int kvh = t.head, grp = p.Hq / p.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int krow = t.tile0 + 32 * wave + (lane & 31);
-  const bool kok = krow < t.seg_len;
-  const int64_t gkrow = t.seg_start + (kok ? krow : 0);
-  const bf16_t* kp = p.k + gkrow * p.kv_stride + kvh * HD + 8 * h;
-  const bf16_t* vp = p.v + gkrow * p.kv_stride + kvh * HD + 8 * h;
-  bf16x8 kf[NC], vf[NC];
-#pragma unroll
-  for (int c = 0; c < NC; c++) {
-    kf[c] = global_frag(kp + 16 * c, kok);
-    vf[c] = global_frag(vp + 16 * c, kok);
-  }
-  f32x16 dkacc[ND], dvacc[ND];
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) { dkacc[d][v] = 0.f; dvacc[d][v] = 0.f; }
-
-  const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
-  const int wave_first_k = t.tile0 + 32 * wave;
-  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ, part, parts);
-  const int n_it = range.n_it;
-
-  constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BQ / RPI / 4;
-  uint32_t q_off[PER_WAVE], do_off[PER_WAVE];
-#pragma unroll
-  for (int i = 0; i < PER_WAVE; i++) {
-    const int r = (wave * PER_WAVE + i) * RPI + lane / CPR, c = (lane % CPR) ^ swz<HD>(r);
-    q_off[i] = (uint32_t)((r * p.q_stride + 8 * c) * 2);
-    do_off[i] = (uint32_t)((r * p.o_stride + 8 * c) * 2);
-  }
-  const uint32_t q_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.q_stride + HD) * 2);
-  const uint32_t do_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.o_stride + HD) * 2);
-
-  // The tile to be loaded next: query head nj of the group, query rows from nq0.  Past the last
-  // tile the descriptors are empty and the loads write zeros.
-  int nj = range.head, nq0 = range.q0;
-  float r_lse = 0.f, r_delta = 0.f;   // statistics of the tile in flight, one row per thread (tid < BQ)
-  bool r_ok = false;
-  u32x4_t r_o[2], r_do[2];             // SELF_DELTA: the thread's 16 columns of O and dO
-  auto issue = [&](bf16_t* qs, bf16_t* dos) {
-    const bool valid = nj < grp;
-    const int head = kvh * grp + (valid ? nj : 0);
-    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.q + (int64_t)t.seg_start * p.q_stride + head * HD), 0, valid ? (int)q_bytes : 0, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rdo = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(p.d_o + (int64_t)t.seg_start * p.o_stride + head * HD), 0, valid ? (int)do_bytes : 0, 0x00020000);
-    const uint32_t qrow = (uint32_t)nq0 * (uint32_t)(p.q_stride * 2), dorow = (uint32_t)nq0 * (uint32_t)(p.o_stride * 2);
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; i++) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, MLLM_LDS_VOID(qs + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)(q_off[i] + qrow), 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rdo, MLLM_LDS_VOID(dos + (wave * PER_WAVE + i) * 512), 16,
-                                               (int)(do_off[i] + dorow), 0, 0, 0);
-    }
-    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(p.lse + (int64_t)head * p.T + t.seg_start), 0, valid ? t.seg_len * 4 : 0, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(p.delta + (int64_t)head * p.T + t.seg_start), 0, valid ? t.seg_len * 4 : 0, 0x00020000);
-    const uint32_t so = tid < BQ ? (uint32_t)(nq0 + tid) * 4u : 0xFFFFFFFFu;
-    r_lse = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, (int)so, 0, 0));
-    if constexpr (SELF_DELTA) {
-      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-          p.o + (int64_t)t.seg_start * p.o_stride + head * HD, 0, valid ? (int)do_bytes : 0, 0x00020000);
-      const uint32_t at = dorow + (uint32_t)(tid >> 2) * (uint32_t)(p.o_stride * 2) + (uint32_t)(tid & 3) * 32u;
-#pragma unroll
-      for (int w = 0; w < 2; w++) {
-        r_o[w] = __builtin_amdgcn_raw_buffer_load_b128(ro, (int)(at + 16u * w), 0, 0);
-        r_do[w] = __builtin_amdgcn_raw_buffer_load_b128(rdo, (int)(at + 16u * w), 0, 0);
-      }
-    } else {
-      r_delta = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, (int)so, 0, 0));
-    }
-    r_ok = valid && tid < BQ && nq0 + tid < t.seg_len;
-    nq0 += BQ;
-    if (nq0 >= t.seg_len) { nq0 = q_begin; nj++; }
-  };
-
-  // One tile: publish the statistics of the tile whose loads were enqueued a tile ago, wait for
-  // those loads, barrier (every wavefront is now done with the other stage), enqueue the next
-  // tile into the other stage, multiply.
-  auto tile = [&](const bf16_t* Qs, const bf16_t* dOs, float* lse_s, float* delta_s, bf16_t* Qn, bf16_t* dOn,
-                  int q0, bool live) {
-    if (tid < BQ) {
-      lse_s[tid] = r_ok ? r_lse * LOG2E : INFINITY;   // +inf: probabilities of rows past the segment are 0
-      if constexpr (!SELF_DELTA) delta_s[tid] = r_ok ? r_delta : 0.f;
-    }
-    if constexpr (SELF_DELTA) {   // rows past the segment, and the tile past the last one, have come as zeros
-      float d = 0.f;
-#pragma unroll
-      for (int w = 0; w < 2; w++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) d += bf16lo(r_o[w][e]) * bf16lo(r_do[w][e]) + bf16hi(r_o[w][e]) * bf16hi(r_do[w][e]);
-      d += __shfl_xor(d, 1, 64);
-      d += __shfl_xor(d, 2, 64);
-      if ((tid & 3) == 0) delta_s[tid >> 2] = d;
-    }
-    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-    __syncthreads();
-    issue(Qn, dOn);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!live || (t.causal && q0 + BQ - 1 < wave_first_k)) return;  // no query here sees this wave's keys
-#pragma unroll
-    for (int b = 0; b < BQ / 32; b++) {
-      f32x16 s, dp;
-#pragma unroll
-      for (int v = 0; v < 16; v++) { s[v] = 0.f; dp[v] = 0.f; }
-      // Scores: 2 NC MFMAs, their LDS reads issued four ahead (left alone, the scheduler reads
-      // each fragment into the same registers right before its MFMA and waits for it every time).
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int c = 0; c < NC; c++) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Qs, 32 * b, c, lane), kf[c], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(dOs, 32 * b, c, lane), vf[c], dp, 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-      reads_behind_mfmas<1>(std::make_integer_sequence<int, 2 * NC - 4>{});
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      // First fragments of the dV / dK products: their LDS latency runs under the vector work.
-      constexpr int NPV = 2 * ND;            // (cc, d) pairs, two MFMAs each
-      bf16x8 fdo = frag_cols_permuted<HD>(dOs, 32 * b, 0, lane), fq = frag_cols_permuted<HD>(Qs, 32 * b, 0, lane);
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 pr;
-      // The scores are consumed by the vector ALU: keep them out of the accumulation registers
-      // (with the whole register file available the allocator otherwise parks them there and
-      // copies every value back and forth).
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        float a = s[v], c = dp[v];
-        asm volatile("" : "+v"(a), "+v"(c));
-        s[v] = a;
-        dp[v] = c;
-      }
-      if (t.causal && q0 + 32 * b <= wave_first_k + 31) {   // block touches the diagonal
-#pragma unroll
-        for (int v = 0; v < 16; v++) s[v] = (krow <= q0 + 32 * b + acc_row(v, h)) ? s[v] : -INFINITY;
-      }
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const int qi = 32 * b + acc_row(v, h);
-        pr[v] = fast_exp2(fmaf(s[v], p.scale_log2e, -lse_s[qi]));
-        s[v] = pr[v] * (dp[v] - delta_s[qi]);   // dS
-      }
-      bf16x8 pf[2], dsf[2];
-#pragma unroll
-      for (int cc = 0; cc < 2; cc++) { pf[cc] = acc_to_frag(pr, cc); dsf[cc] = acc_to_frag(s, cc); }
-      __builtin_amdgcn_sched_barrier(0);
-      // dV, dK: every pair of MFMAs is preceded by the four LDS reads of the next pair's fragments.
-#pragma unroll
-      for (int i = 0; i < NPV; i++) {
-        const int cc = i / ND, d = i % ND;
-        bf16x8 ndo = fdo, nq = fq;
-        if (i + 1 < NPV) {
-          const int cc1 = (i + 1) / ND, d1 = (i + 1) % ND;
-          ndo = frag_cols_permuted<HD>(dOs, 32 * b + 16 * cc1, 32 * d1, lane);
-          nq = frag_cols_permuted<HD>(Qs, 32 * b + 16 * cc1, 32 * d1, lane);
-        }
-        dvacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fdo, pf[cc], dvacc[d], 0, 0, 0);
-        dkacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq, dsf[cc], dkacc[d], 0, 0, 0);
-        fdo = ndo;
-        fq = nq;
-      }
-      reads_before_mfma_pairs(std::make_integer_sequence<int, NPV - 1>{});
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  issue(Qs0, dOs0);
-  int q0 = range.q0;
-  auto advance = [&]() { q0 += BQ; if (q0 >= t.seg_len) q0 = q_begin; };
-  for (int it = 0; it < n_it; it += 2) {
-    tile(Qs0, dOs0, lse_s0, delta_s0, Qs1, dOs1, q0, true);
-    advance();
-    tile(Qs1, dOs1, lse_s1, delta_s1, Qs0, dOs0, q0, it + 1 < n_it);
-    advance();
-  }
-  // the last enqueued loads (an empty tile: zeros) must have landed before this workgroup's LDS
-  // can be handed to another one
-  __builtin_amdgcn_s_waitcnt(WAIT_VMCNT_0);
-  if (!kok) return;
-  if (parts > 1) {
-    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, (unsigned)part);
-    return;
-  }
-  float out_scale = p.scale;
-  if (p.rope_table) {
-    rope_unrotate<HD>(dkacc, p.rope_table, krow, h, p.scale);
-    out_scale = 1.f;
-  }
-  bf16_t* dkp = p.dk + gkrow * p.kv_stride + kvh * HD;
-  bf16_t* dvp = p.dv + gkrow * p.kv_stride + kvh * HD;
-#pragma unroll
-  for (int d = 0; d < ND; d++)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      uint2 w;
-      w.x = pack_bf16x2(dkacc[d][4 * g4] * out_scale, dkacc[d][4 * g4 + 1] * out_scale);
-      w.y = pack_bf16x2(dkacc[d][4 * g4 + 2] * out_scale, dkacc[d][4 * g4 + 3] * out_scale);
-      *reinterpret_cast<uint2*>(dkp + 32 * d + 8 * g4 + 4 * h) = w;
-      w.x = pack_bf16x2(dvacc[d][4 * g4], dvacc[d][4 * g4 + 1]);
-      w.y = pack_bf16x2(dvacc[d][4 * g4 + 2], dvacc[d][4 * g4 + 3]);
-      *reinterpret_cast<uint2*>(dvp + 32 * d + 8 * g4 + 4 * h) = w;
-    }
-}
-
-#define MLLM_DKV_LDS(HD)                                                                                                \
-  __shared__ __attribute__((aligned(1024))) bf16_t T0[BQ * HD], T1[BQ * HD], T2[BQ * HD], T3[BQ * HD];                  \
-  __shared__ float lse0[BQ], lse1[BQ], delta0[BQ], delta1[BQ]
-template <int HD>
-__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_kernel(AttnParams p) {
-  MLLM_DKV_LDS(HD);
-  attn_bwd_dkv<HD, false>(p, p.list, blockIdx.x, blockIdx.y, gridDim.y, DkvLds{T0, T1, T2, T3, lse0, lse1, delta0, delta1});
-}
-// Both passes in one launch, the dK/dV pass first.
-__global__ __launch_bounds__(256, 2) void attn_bwd_both_kernel(AttnParams p, const AttnItem* kv_list, int kv_grid, int kv_parts) {
-  MLLM_DKV_LDS(64);
-  const int kv = kv_grid * kv_parts, pid = blockIdx.x;
-  if (pid < kv) attn_bwd_dkv<64, true>(p, kv_list, pid % kv_grid, pid / kv_grid, kv_parts, DkvLds{T0, T1, T2, T3, lse0, lse1, delta0, delta1});
-  else attn_bwd_dq<64>(p, p.list, pid - kv, T0, T1, T2, T3);
-}
-#undef MLLM_DKV_LDS
-
-// ---------------------------------------------------------------------------------------------
-// dK/dV pass, software-pipelined form.  The work of a block of 32 query rows is a chain: scores and
-// dP (MFMA) -> probabilities and dS (vector ALU, 1/4 of it the exponential) -> dV and dK (MFMA).
-// Run as a chain, with one wavefront per SIMD at head_dim 128, the matrix pipe idles during the
-// vector stage and the vector ALU during the other two.  Here every step works on two blocks: the
-// score MFMAs of block n+1 are issued one per slot and the vector work of block n is cut into as
-// many slices, one behind each MFMA (the matrix pipe runs an MFMA for 32 clocks while the wavefront
-// goes on issuing independent instructions); the dV/dK MFMAs of block n follow, carrying the LDS
-// reads of the next steps.  The Q / dO tiles rotate through NST stages of LDS: a tile is still
-// being read (dV/dK of its second block) after the barrier that opens the next tile, so the tile
-// after that is loaded into a third stage.  The stage base is part of the address registers, which
-// are advanced once per tile; block and operand offsets ride in the instructions' offset fields.
-// ---------------------------------------------------------------------------------------------
+// ---- operands -----------------------------------------------------------------------------------
+// All products are v_mfma_f32_16x16x32_bf16.  A wavefront owns 32 rows (queries, or keys in the dK/dV pass) as the columns of
+// the results, in two groups j of 16: lane l holds column l%16 of group j, and with g = l/16 the rows 4g .. 4g+3 of each
+// 16-row group i of the other side's block of 32.  The 32x32x16 form does the same work in half the MFMAs and reads and
+// writes its accumulator twice as often per multiply-add, and that is power, which bounds these kernels at head_dim 128: 13255
+// causal tokens, 32/8 heads of 128, MFMA busy 61 % of the cycles in the forward pass and 72 % in dQ at 1.76 and 1.66 GHz with
+// it, 62 % and 69 % at 1.88 and 1.87 GHz with this form (of 2.4): 1245 -> 1121 and 1672 -> 1544 us on one card.  The order in
+// which a wavefront issues its reads and vector work no longer shows there (reads one to four fragments ahead, vector work
+// between the MFMAs or behind them: within 1 %, behind them where not).  At head_dim 64 the vector ALU bounds them, at 2.2 GHz
+// (46 x 576 tokens, 16 heads: forward 109 -> 97 us, dK/dV 211 -> 187).
+struct Lane {
+  int lane, g, c16;
+  __device__ __forceinline__ explicit Lane(int tid) : lane(tid & 63), g((tid & 63) >> 4), c16(tid & 15) {}
+};
 typedef MLLM_LDS const char* lds_cptr;
+typedef MLLM_LDS char* lds_ptr;
 __device__ __forceinline__ bf16x8 lds_b128(lds_cptr base, uint32_t off) {
   return __builtin_bit_cast(bf16x8, *(MLLM_LDS const u32x4_t*)(base + off));
 }
@@ -818,16 +104,50 @@ __device__ __forceinline__ s16x4 lds_tr(lds_cptr base, uint32_t off) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLLM_LDS s16x4*)(base + off));
 }
 __device__ __forceinline__ f32x4 lds_f4(lds_cptr base, uint32_t off) { return *(MLLM_LDS const f32x4*)(base + off); }
-template <int V> using Int = std::integral_constant<int, V>;
-// Loads from global memory straight into LDS, written as assembly so that the compiler does not
-// know them for what they are.  Told (through the builtin), it makes LDS reads wait for every such
-// load in flight into the same LDS variable, which turns a queue of several tiles on their way
-// into one tile at a time; it cannot see that the loads go to a stage nobody reads when the stage
-// numbers are run-time values.  The kernel that uses these waits for its loads by count and
-// separates writers from readers with barriers, as it has to anyway.
+// Natural-layout operand of the score-like products: row l%16 of a 16-row group, columns 32c + 8g .. +7.  Byte offset in the
+// tile; 16 rows further on are 16 * HD * 2 bytes.
+template <int HD>
+__device__ __forceinline__ uint32_t row_offset(const Lane& L, int c) { return (uint32_t)(L.c16 * HD + 8 * ((4 * c + L.g) ^ swz<HD>(L.c16))) * 2u; }
+// Transposed operand for the register-resident operand made of two 16-row groups of a result: column 16n + l%16 of the tile,
+// contraction slots e = 0..7 standing for tile rows 4g + e%4 (+16 for e >= 4).  Each transposing read returns tile[k0 + e][n0 + i]
+// for e = 0..3 when lane i of a 16-lane group addresses tile[k0 + i/4][n0 + 4*(i%4)].
+template <int HD>
+__device__ __forceinline__ uint32_t col_offset(const Lane& L, int n) {
+  const int k = 4 * L.g + (L.c16 >> 2), chunk = 2 * n + ((L.c16 & 3) >> 1);
+  return (uint32_t)(k * HD + 8 * (chunk ^ swz<HD>(k)) + 4 * (L.c16 & 1)) * 2u;
+}
+template <int HD>
+__device__ __forceinline__ bf16x8 read_col(lds_cptr base, uint32_t off) {
+  Frag8 f;
+  f.h[0] = lds_tr(base, off);
+  f.h[1] = lds_tr(base, off + 16 * HD * 2);
+  return f.v;
+}
+__device__ __forceinline__ bf16x8 global_frag(const bf16_t* p, bool ok) {
+  Frag8 f;
+  f.u = ok ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
+  return f.v;
+}
+__device__ __forceinline__ bf16x8 negated(bf16x8 x) {
+  Frag8 f;
+  f.v = x;
+#pragma unroll
+  for (int w = 0; w < 4; w++) f.w[w] ^= 0x80008000u;
+  return f.v;
+}
+__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+// Keeps what a slot (a few MFMAs and what is to be issued beside them) holds apart from the next one's.
+#define MLLM_SLOT_END __builtin_amdgcn_sched_barrier(0)
+
+// ---- loads from memory straight into LDS -----------------------------------------------------------
+// Written as assembly so that the compiler does not know them for what they are.  Told (through the builtin), it makes LDS
+// reads wait for every such load in flight into the same LDS variable, which turns a queue of several tiles on their way
+// into one tile at a time; it cannot see that the loads go to a stage nobody reads.  The kernels wait for their loads by
+// count and separate writers from readers with barriers, as they have to anyway.
 // The 64 lanes' 16 (or 4) bytes land side by side from LDS address `lds_addr` (wavefront-uniform).
 // The statements set M0 themselves; M0 is a reserved register that the compiler holds no value in and
 // sets anew in front of each of its own uses, so overwriting it here disturbs nothing.
+// `row_off` (wavefront-uniform) is added to the lanes' offsets, and the range check covers the sum.
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4_t raw_rsrc(const void* base, uint32_t bytes) {   // untyped buffer over [base, base + bytes)
   const uint64_t b = (uint64_t)base;
@@ -838,335 +158,1012 @@ __device__ __forceinline__ i32x4_t raw_rsrc(const void* base, uint32_t bytes) { 
   r[3] = 0x00020000;
   return r;
 }
-__device__ __forceinline__ void load_to_lds_b128(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc) : "memory");
+// Descriptor over rows [0, rows) of a row-major bf16 matrix slice of `width` columns.
+__device__ __forceinline__ i32x4_t rows_rsrc(const bf16_t* base, int64_t stride, int rows, int width) {
+  return raw_rsrc(base, rows > 0 ? (uint32_t)(((int64_t)(rows - 1) * stride + width) * 2) : 0u);
 }
-__device__ __forceinline__ void load_to_lds_b32(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc) : "memory");
+__device__ __forceinline__ void load_to_lds_b128(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
+}
+__device__ __forceinline__ void load_to_lds_b32(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
 }
 __device__ __forceinline__ uint32_t lds_address(MLLM_LDS const void* p) { return (uint32_t)(size_t)p; }
 // At most N of the loads above still in flight (the compiler does not count them, so neither can its builtin).
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
-
+// The workgroup's barrier, in its place; LDS writes issued before it are visible behind it.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int V> using Int = std::integral_constant<int, V>;
+// One such instruction moves 64 lanes x 16 bytes = RPI rows of a tile; lane l's chunk lands at position l of that 1 KiB, so the
+// lane fetches the global chunk that the permutation puts there.  Byte offset of the lane's chunk, instruction `ins` of the tile.
 template <int HD>
-__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_pipe_kernel(AttnParams p) {
-  constexpr int NC = HD / 16, ND = HD / 32, TILE = BQ * HD, NST = 4;
-  constexpr int TILE_B = TILE * 2;                          // a stage: the Q tile, then the dO tile
-  constexpr int ROWS32_B = 32 * HD * 2, ROWS16_B = 16 * HD * 2;
-  constexpr int STAGE_B = 2 * TILE_B, STAT_STAGE_B = 2 * BQ * 4;
-  // NST stages of tiles, then NST stages of row statistics (lse of the tile's rows, then delta).  ONE
-  // array on purpose: the compiler tags LDS accesses with the variable they belong to and makes every
-  // read of a variable wait for all loads in flight into the same variable; it cannot tell the stages
-  // of one array apart when their numbers are run-time values.  With a single variable there is
-  // nothing to tag, and the waits below (which know the stages) are the only ones.
-  constexpr int STATS_AT = NST * STAGE_B;
-  __shared__ __attribute__((aligned(1024))) char lds[NST * STAGE_B + NST * STAT_STAGE_B];
+__device__ __forceinline__ uint32_t load_offset(const Lane& L, int ins, int64_t stride) {
+  constexpr int CPR = HD / 8, RPI = 64 / CPR;
+  const int r = ins * RPI + L.lane / CPR, c = (L.lane % CPR) ^ swz<HD>(r);
+  return (uint32_t)((r * stride + 8 * c) * 2);
+}
+
+// ---- results -----------------------------------------------------------------------------------------
+// acc[n][j]: columns 16n + 4g .. +3 of the head, own row 16j + l%16.
+// Gradient of the rotary positions on row group j, whose lanes own row `pos` of their segment: the pair (c, c + HD/2) sits in
+// groups (n, n + HD/32) of the same lane.  Forward was y1 = x1 cos - x2 sin, y2 = x2 cos + x1 sin, so
+// dx1 = dy1 cos + dy2 sin, dx2 = dy2 cos - dy1 sin.  `scale` multiplies the result.
+template <int HD>
+__device__ __forceinline__ void rope_unrotate(f32x4 (&acc)[HD / 16][2], int j, const float* table, int pos, int g, float scale) {
+  constexpr int HALF = HD / 2;
+  const float* trow = table + (int64_t)pos * HD;
+#pragma unroll
+  for (int n = 0; n < HD / 32; n++) {
+    const int f0 = 16 * n + 4 * g;
+    const float4 c = *reinterpret_cast<const float4*>(trow + f0);
+    const float4 sn = *reinterpret_cast<const float4*>(trow + HALF + f0);
+    const float cs[4] = {c.x * scale, c.y * scale, c.z * scale, c.w * scale};
+    const float ss[4] = {sn.x * scale, sn.y * scale, sn.z * scale, sn.w * scale};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float y1 = acc[n][j][e], y2 = acc[n + HD / 32][j][e];
+      acc[n][j][e] = y1 * cs[e] + y2 * ss[e];
+      acc[n + HD / 32][j][e] = y2 * cs[e] - y1 * ss[e];
+    }
+  }
+}
+// Row group j in bf16, times `scale`; dst: the row's first column of the head, plus 4g.
+template <int HD>
+__device__ __forceinline__ void store_row(bf16_t* dst, const f32x4 (&acc)[HD / 16][2], int j, float scale) {
+#pragma unroll
+  for (int n = 0; n < HD / 16; n++) {
+    uint2 w;
+    w.x = pack_bf16x2(acc[n][j][0] * scale, acc[n][j][1] * scale);
+    w.y = pack_bf16x2(acc[n][j][2] * scale, acc[n][j][3] * scale);
+    *reinterpret_cast<uint2*>(dst + 16 * n) = w;
+  }
+}
+// A part's sums of row group j, fp32 and without the softmax scale; which: 0 dK, 1 dV.
+template <int HD>
+__device__ __forceinline__ void store_kv_partial(const AttnParams& p, const f32x4 (&acc)[HD / 16][2], int j, int which, float sign, int64_t row, int kvh, int g,
+                                                 unsigned part) {
+  float* dst = p.dkv_partial + ((int64_t)(2 * part + which) * p.T + row) * ((int64_t)p.Hkv * HD) + kvh * HD + 4 * g;
+#pragma unroll
+  for (int n = 0; n < HD / 16; n++)
+    *reinterpret_cast<float4*>(dst + 16 * n) = make_float4(sign * acc[n][j][0], sign * acc[n][j][1], sign * acc[n][j][2], sign * acc[n][j][3]);
+}
+// dK (negated in acc) or dV of the lane's two rows: partial sums, or bf16 with scale and rotation.
+template <int HD>
+__device__ __forceinline__ void store_dk(const AttnParams& p, f32x4 (&acc)[HD / 16][2], int j, int krow, int64_t gkrow, int kvh, int g, bool split, unsigned part) {
+  if (split) return store_kv_partial<HD>(p, acc, j, 0, -1.f, gkrow, kvh, g, part);
+  bf16_t* dst = p.dk + gkrow * p.kv_stride + kvh * HD + 4 * g;
+  if (p.rope_table) rope_unrotate<HD>(acc, j, p.rope_table, krow, g, -p.scale);
+  store_row<HD>(dst, acc, j, p.rope_table ? 1.f : -p.scale);
+}
+template <int HD>
+__device__ __forceinline__ void store_dv(const AttnParams& p, const f32x4 (&acc)[HD / 16][2], int j, int64_t gkrow, int kvh, int g, bool split, unsigned part) {
+  if (split) return store_kv_partial<HD>(p, acc, j, 1, 1.f, gkrow, kvh, g, part);
+  store_row<HD>(p.dv + gkrow * p.kv_stride + kvh * HD + 4 * g, acc, j, 1.f);
+}
+// Sum over the four lanes that hold parts of one own row.
+__device__ __forceinline__ float own_row_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ __forceinline__ float own_row_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+
+// ---------------------------------------------------------------------------------------------
+// forward: one workgroup per (query tile of 128, head), looping over key tiles of 64: two blocks b of 32 keys.
+// ---------------------------------------------------------------------------------------------
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
+  constexpr int NC = HD / 32, NN = HD / 16, NS = 2 * NC, TILE_B = BKV * HD * 2, BLOCK_B = 32 * HD * 2, GROUP_B = 16 * HD * 2;
+  // two stages of a K tile and a V tile
+  __shared__ __attribute__((aligned(1024))) char lds[4 * TILE_B];
   AttnItem t;
   if (!work_item(p.list, t, blockIdx.x)) return;
-  const int kvh = t.head, grp = p.Hq / p.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int krow = t.tile0 + 32 * wave + (lane & 31);
-  const bool kok = krow < t.seg_len;
-  const int64_t gkrow = t.seg_start + (kok ? krow : 0);
-  const bf16_t* kp = p.k + gkrow * p.kv_stride + kvh * HD + 8 * h;
-  const bf16_t* vp = p.v + gkrow * p.kv_stride + kvh * HD + 8 * h;
-  bf16x8 kf[NC], vf[NC];
+  const int head = t.head, kvh = head / (p.Hq / p.Hkv);
+  const Lane L(threadIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_first_q = t.tile0 + 32 * wave, wave_last_q = wave_first_q + 31;
+  int qrow[2];
+  bf16x8 qf[2][NC];
 #pragma unroll
-  for (int c = 0; c < NC; c++) {
-    kf[c] = global_frag(kp + 16 * c, kok);
-    vf[c] = global_frag(vp + 16 * c, kok);
+  for (int j = 0; j < 2; j++) {
+    qrow[j] = wave_first_q + 16 * j + L.c16;
+    const bf16_t* qp = p.q + (int64_t)(t.seg_start + qrow[j]) * p.q_stride + head * HD + 8 * L.g;
+#pragma unroll
+    for (int c = 0; c < NC; c++) qf[j][c] = global_frag(qp + 32 * c, qrow[j] < t.seg_len);
   }
-  // MFMA operands may sit in accumulation registers: park these 64 there for the whole kernel and
-  // leave the vector registers to the values that the vector ALU touches
+  const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
+
+  f32x4 acc[NN][2];
 #pragma unroll
-  for (int c = 0; c < NC; c++) asm volatile("" : "+a"(kf[c]), "+a"(vf[c]));
-  f32x16 dkacc[ND], dvacc[ND];
+  for (int n = 0; n < NN; n++) acc[n][0] = acc[n][1] = f32x4{0, 0, 0, 0};
+  const float c2 = p.scale_log2e;
+  // Reference maximum m (in units of log2: score * scale * log2(e)) and sum l = sum of exp2(... - m).  The reference is the
+  // row's maximum over the first tile and stays: probabilities above 1 carry the same relative precision in fp32 sums and
+  // in the bf16 operand.  Only a tile whose sum comes out above `limit` (some probability near or above 2^12, or past the range
+  // of fp32) has its scores formed again and moves the reference (`again`); so neither the maximum of a tile's scores, nor its
+  // exchange between lanes, nor the rescaling of the accumulator is on the path.
+  constexpr float LIMIT = 4096.f;
+  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f}, limit[2] = {-1.f, -1.f};   // -1: no reference yet
+
+  // Rows past kv_end are outside the descriptors: zeros, no traffic.
+  const i32x4_t rk = rows_rsrc(p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  const i32x4_t rv = rows_rsrc(p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  constexpr int PER_WAVE = BKV * HD / 8 / 64 / 4;
+  uint32_t kv_off[PER_WAVE];
 #pragma unroll
-  for (int d = 0; d < ND; d++)
+  for (int i = 0; i < PER_WAVE; i++) kv_off[i] = load_offset<HD>(L, wave * PER_WAVE + i, p.kv_stride);
+  const uint32_t row_bytes = (uint32_t)(p.kv_stride * 2);
+  const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_address((MLLM_LDS const void*)lds) + wave * PER_WAVE * 1024);
+  auto issue_part = [&](int st, int kv0, int j) {   // j even: K, odd: V
+    load_to_lds_b128(j % 2 ? rv : rk, lds_b + (uint32_t)(st * 2 * TILE_B + j % 2 * TILE_B + j / 2 * 1024), kv_off[j / 2], (uint32_t)kv0 * row_bytes);
+  };
+  const lds_cptr M = (lds_cptr)lds;
+  uint32_t rows[NC], cols[NN];
 #pragma unroll
-    for (int v = 0; v < 16; v++) { dkacc[d][v] = 0.f; dvacc[d][v] = 0.f; }
+  for (int c = 0; c < NC; c++) rows[c] = row_offset<HD>(L, c);
+#pragma unroll
+  for (int n = 0; n < NN; n++) cols[n] = col_offset<HD>(L, n) + TILE_B;
+
+  f32x4 s[2][2][2];      // scores, then probabilities: [block][row group][own group]
+  Frag8 pb[2][2];        // probabilities as MFMA operand: [block][own group]
+  auto mask = [&](int kv0) {
+    if ((kv0 + BKV > t.seg_len) || (t.causal && kv0 + BKV - 1 > wave_first_q)) {   // the tile crosses the segment end or the diagonal
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              const int kv = kv0 + 32 * b + 16 * i + 4 * L.g + e;
+              s[b][i][j][e] = (kv < t.seg_len && (!t.causal || kv <= qrow[j])) ? s[b][i][j][e] : -INFINITY;
+            }
+    }
+  };
+  auto tile_max = [&](int j) {
+    float mx = s[0][0][j][0];
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) mx = fmaxf(mx, s[b][i][j][e]);
+    return own_row_max(mx) * c2;
+  };
+  float mu[2] = {0.f, 0.f};   // m, or 0 where there is none yet
+  auto set_reference = [&](int j, float to) {
+    m[j] = to;
+    mu[j] = to == -INFINITY ? 0.f : to;
+    limit[j] = to == -INFINITY ? -1.f : LIMIT;
+  };
+  float rs[2];   // the tile's sums
+  auto probs = [&]() {
+    rs[0] = rs[1] = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            s[b][i][j][e] = fast_exp2(fmaf(s[b][i][j][e], c2, -mu[j]));
+            rs[j] += s[b][i][j][e];
+          }
+          pb[b][j].w[2 * i] = pack_bf16x2(s[b][i][j][0], s[b][i][j][1]);
+          pb[b][j].w[2 * i + 1] = pack_bf16x2(s[b][i][j][2], s[b][i][j][3]);
+        }
+  };
+  auto again = [&](int st, int kv0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      const uint32_t at = (uint32_t)(st * 2 * TILE_B + b * BLOCK_B);
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) s[b][i][j] = f32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int c = 0; c < NC; c++)
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int j = 0; j < 2; j++) s[b][i][j] = mfma(lds_b128(M, rows[c] + at + i * GROUP_B), qf[j][c], s[b][i][j]);
+    }
+    mask(kv0);
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const float mx = tile_max(j), old = m[j];
+      if (mx > old + 8.f) set_reference(j, mx);
+      const float alpha = fast_exp2(old - mu[j]);
+      l[j] *= alpha;
+#pragma unroll
+      for (int n = 0; n < NN; n++) acc[n][j] *= alpha;
+    }
+    probs();
+  };
+
+  constexpr int AHEAD = 4;    // natural-layout fragments read ahead of their MFMAs
+  constexpr int VAHEAD = 2;   // transposed fragments
+  auto tile = [&](auto STt, int kv0, bool live) {
+    constexpr int ST = decltype(STt)::value;
+    constexpr uint32_t AT = ST * 2 * TILE_B;
+    wait_loads<0>();
+    phase_barrier();   // the tile has landed, and every wavefront is done with the other stage
+    bf16x8 fr[2 * NS], fv[2 * NN];
+    // fragment x: block x / NS, column chunk x % NS / 2, row group x % 2
+    auto read_row = [&](int x) { fr[x] = lds_b128(M, rows[x % NS / 2] + AT + x / NS * BLOCK_B + x % 2 * GROUP_B); };
+    auto read_v = [&](int x) { fv[x] = read_col<HD>(M, cols[x % NN] + AT + x / NN * BLOCK_B); };
+    // A tile past the end, or wholly above the diagonal of this wavefront's rows, or a wavefront without a row (uniform over
+    // the wavefront): only the next tile's loads are wanted.
+    if (!live || (t.causal && kv0 > wave_last_q) || wave_first_q >= t.seg_len) {
+#pragma unroll
+      for (int x = 0; x < 2 * PER_WAVE; x++) issue_part(1 - ST, kv0 + BKV, x);
+      return;
+    }
+#pragma unroll
+    for (int x = 0; x < AHEAD; x++) read_row(x);
+    // Scores; the next tile's loads go out one behind each of the first slots, so the wavefront does not stand still while the
+    // memory pipeline takes them.
+#pragma unroll
+    for (int x = 0; x < 2 * NS; x++) {
+      if (x + AHEAD < 2 * NS) read_row(x + AHEAD);
+      const int b = x / NS, c = x % NS / 2, i = x % 2;
+#pragma unroll
+      for (int j = 0; j < 2; j++) s[b][i][j] = mfma(fr[x], qf[j][c], c == 0 ? f32x4{0, 0, 0, 0} : s[b][i][j]);
+      if (x < 2 * PER_WAVE) issue_part(1 - ST, kv0 + BKV, x);
+      MLLM_SLOT_END;
+    }
+#pragma unroll
+    for (int x = 0; x < VAHEAD; x++) read_v(x);   // their latency runs under the vector work
+    MLLM_SLOT_END;
+    mask(kv0);
+    if (kv0 == 0) {
+#pragma unroll
+      for (int j = 0; j < 2; j++) set_reference(j, tile_max(j));
+    }
+    probs();
+    if (__any(rs[0] > limit[0] || rs[1] > limit[1])) again(ST, kv0);
+    l[0] += rs[0];
+    l[1] += rs[1];
+    MLLM_SLOT_END;
+#pragma unroll
+    for (int x = 0; x < 2 * NN; x++) {
+      if (x + VAHEAD < 2 * NN) read_v(x + VAHEAD);
+#pragma unroll
+      for (int j = 0; j < 2; j++) acc[x % NN][j] = mfma(fv[x], pb[x / NN][j].v, acc[x % NN][j]);
+      MLLM_SLOT_END;
+    }
+  };
+
+#pragma unroll
+  for (int j = 0; j < 2 * PER_WAVE; j++) issue_part(0, 0, j);
+  for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
+    tile(Int<0>{}, kv0, true);
+    tile(Int<1>{}, kv0 + BKV, kv0 + BKV < kv_end);
+  }
+  // the last enqueued loads (rows past the end: zeros) must have landed before this workgroup's
+  // LDS can be handed to another one
+  wait_loads<0>();
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const float sum = own_row_sum(l[j]);
+    if (qrow[j] >= t.seg_len) continue;
+    const int64_t row = t.seg_start + qrow[j];
+    store_row<HD>(p.o + row * p.o_stride + head * HD + 4 * L.g, acc, j, 1.f / sum);
+    if (L.g == 0) p.lse[(int64_t)head * p.T + row] = (m[j] + log2f(sum)) * LN2;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// dQ pass: one workgroup per (query tile of 128, head), looping over key tiles.  It runs first in
+// the backward pass and also produces delta[h][t] = sum_d dO[t,h,d] * O[t,h,d] for the dK/dV pass.
+// dO enters negated and the dP products start from delta, so that they end as delta - dP: the subtraction costs no
+// instruction, and dQ, which comes out negated, takes its sign back with the softmax scale.
+// ---------------------------------------------------------------------------------------------
+template <int HD>
+__device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem* list, int entry, char* lds) {
+  constexpr int NC = HD / 32, NN = HD / 16, NS = 2 * NC, TILE_B = BKV * HD * 2, BLOCK_B = 32 * HD * 2, GROUP_B = 16 * HD * 2;
+  AttnItem t;
+  if (!work_item(list, t, entry)) return;
+  const int head = t.head, kvh = head / (p.Hq / p.Hkv);
+  const Lane L(threadIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_first_q = t.tile0 + 32 * wave, wave_last_q = wave_first_q + 31;
+  int qrow[2];
+  bf16x8 qf[2][NC], dof[2][NC];
+  float lse2[2], delta[2];
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    qrow[j] = wave_first_q + 16 * j + L.c16;
+    const bool ok = qrow[j] < t.seg_len;
+    const int64_t row = t.seg_start + (ok ? qrow[j] : 0);
+    const bf16_t* qp = p.q + row * p.q_stride + head * HD + 8 * L.g;
+    const bf16_t* dop = p.d_o + row * p.o_stride + head * HD + 8 * L.g;
+    const bf16_t* op = p.o + row * p.o_stride + head * HD + 8 * L.g;
+    float d = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      qf[j][c] = global_frag(qp + 32 * c, ok);
+      Frag8 fo, fd;
+      fo.v = global_frag(op + 32 * c, ok);
+      fd.v = global_frag(dop + 32 * c, ok);
+#pragma unroll
+      for (int w = 0; w < 4; w++) d += bf16lo(fo.w[w]) * bf16lo(fd.w[w]) + bf16hi(fo.w[w]) * bf16hi(fd.w[w]);
+      dof[j][c] = negated(fd.v);
+    }
+    delta[j] = own_row_sum(d);
+    // Rows beyond the segment get lse = +inf, so their probabilities are exp2(-inf) = 0.
+    lse2[j] = ok ? p.lse[(int64_t)head * p.T + row] * LOG2E : INFINITY;
+    if (ok && L.g == 0) p.delta[(int64_t)head * p.T + row] = delta[j];
+  }
+  const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
+  const float c2 = p.scale_log2e;
+
+  f32x4 acc[NN][2], start[2];
+#pragma unroll
+  for (int n = 0; n < NN; n++) acc[n][0] = acc[n][1] = f32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 2; j++) start[j] = f32x4{delta[j], delta[j], delta[j], delta[j]};
+
+  const i32x4_t rk = rows_rsrc(p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  const i32x4_t rv = rows_rsrc(p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  constexpr int PER_WAVE = BKV * HD / 8 / 64 / 4;
+  uint32_t kv_off[PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < PER_WAVE; i++) kv_off[i] = load_offset<HD>(L, wave * PER_WAVE + i, p.kv_stride);
+  const uint32_t row_bytes = (uint32_t)(p.kv_stride * 2);
+  const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_address((MLLM_LDS const void*)lds) + wave * PER_WAVE * 1024);
+  auto issue_part = [&](int st, int kv0, int j) {   // j even: K, odd: V; rows past kv_end: zeros, no traffic
+    load_to_lds_b128(j % 2 ? rv : rk, lds_b + (uint32_t)(st * 2 * TILE_B + j % 2 * TILE_B + j / 2 * 1024), kv_off[j / 2], (uint32_t)kv0 * row_bytes);
+  };
+  const lds_cptr M = (lds_cptr)lds;
+  uint32_t rows[NC], cols[NN];
+#pragma unroll
+  for (int c = 0; c < NC; c++) rows[c] = row_offset<HD>(L, c);
+#pragma unroll
+  for (int n = 0; n < NN; n++) cols[n] = col_offset<HD>(L, n);
+
+  f32x4 s[2][2], dp[2][2];   // a block's scores and delta - dP: [row group][own group]
+  constexpr int AHEAD = HD == 128 ? 2 : 4, CAHEAD = 2;   // fragments (pairs of them in the score stage) read ahead of their MFMAs
+  auto tile = [&](auto STt, int kv0, bool live) {
+    constexpr int ST = decltype(STt)::value;
+    wait_loads<0>();
+    phase_barrier();
+    if (!live || (t.causal && kv0 > wave_last_q) || wave_first_q >= t.seg_len) {   // only the loads are wanted (see the forward kernel)
+#pragma unroll
+      for (int x = 0; x < 2 * PER_WAVE; x++) issue_part(1 - ST, kv0 + BKV, x);
+      return;
+    }
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      constexpr uint32_t AT0 = ST * 2 * TILE_B;
+      const uint32_t AT = AT0 + b * BLOCK_B;
+      bf16x8 fk[NS], fv[NS], fc[NN];
+      auto read_row = [&](int x) {
+        const uint32_t o = rows[x / 2] + AT + x % 2 * GROUP_B;
+        fk[x] = lds_b128(M, o);
+        fv[x] = lds_b128(M, o + TILE_B);
+      };
+      auto read_c = [&](int x) { fc[x] = read_col<HD>(M, cols[x] + AT); };
+#pragma unroll
+      for (int x = 0; x < AHEAD; x++) read_row(x);
+#pragma unroll
+      for (int x = 0; x < NS; x++) {
+        if (x + AHEAD < NS) read_row(x + AHEAD);
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          s[x % 2][j] = mfma(fk[x], qf[j][x / 2], x < 2 ? f32x4{0, 0, 0, 0} : s[x % 2][j]);
+          dp[x % 2][j] = mfma(fv[x], dof[j][x / 2], x < 2 ? start[j] : dp[x % 2][j]);
+        }
+        static_assert(2 * PER_WAVE == NS, "one load a slot");
+        if (b == 0) issue_part(1 - ST, kv0 + BKV, x);   // the next tile's loads, one a slot (see the forward kernel)
+        MLLM_SLOT_END;
+      }
+#pragma unroll
+      for (int x = 0; x < CAHEAD; x++) read_c(x);   // their latency runs under the vector work
+      MLLM_SLOT_END;
+      const int k0 = kv0 + 32 * b;
+      if ((k0 + 32 > t.seg_len) || (t.causal && k0 + 31 > wave_first_q)) {
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              const int kv = k0 + 16 * i + 4 * L.g + e;
+              s[i][j][e] = (kv < t.seg_len && (!t.causal || kv <= qrow[j])) ? s[i][j][e] : -INFINITY;
+            }
+      }
+      Frag8 db[2];   // dS negated as MFMA operand
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          float ds[4];
+#pragma unroll
+          for (int e = 0; e < 4; e++) ds[e] = fast_exp2(fmaf(s[i][j][e], c2, -lse2[j])) * dp[i][j][e];
+          db[j].w[2 * i] = pack_bf16x2(ds[0], ds[1]);
+          db[j].w[2 * i + 1] = pack_bf16x2(ds[2], ds[3]);
+        }
+      MLLM_SLOT_END;
+#pragma unroll
+      for (int x = 0; x < NN; x++) {
+        if (x + CAHEAD < NN) read_c(x + CAHEAD);
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[x][j] = mfma(fc[x], db[j].v, acc[x][j]);
+        MLLM_SLOT_END;
+      }
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < 2 * PER_WAVE; j++) issue_part(0, 0, j);
+  for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
+    tile(Int<0>{}, kv0, true);
+    tile(Int<1>{}, kv0 + BKV, kv0 + BKV < kv_end);
+  }
+  wait_loads<0>();   // the last enqueued tile (zeros) has landed
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    if (qrow[j] >= t.seg_len) continue;
+    if (p.rope_table) rope_unrotate<HD>(acc, j, p.rope_table, qrow[j], L.g, -p.scale);   // the scale rides on the rotation's factors
+    store_row<HD>(p.dq + (int64_t)(t.seg_start + qrow[j]) * p.q_stride + head * HD + 4 * L.g, acc, j, p.rope_table ? 1.f : -p.scale);
+  }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * BKV * HD * 2];
+  attn_bwd_dq<HD>(p, p.list, blockIdx.x, lds);
+}
+
+// ---------------------------------------------------------------------------------------------
+// dK/dV pass at head_dim 64: one workgroup per (key tile of 128, kv head); each wavefront owns 32 key rows and
+// loops over the query heads of the group and the query tiles of 64 that can see its keys, in the same four steps of two
+// blocks.  The query-side tiles (Q, dO) have two stages in LDS, the row statistics beside them: lse times log2(e), delta.
+// V enters negated (see the dQ pass).
+// SELF_DELTA: delta is formed here, four threads a query row of the tile, instead of read from the dQ pass.
+// ---------------------------------------------------------------------------------------------
+constexpr int DKV_STAT_AT = 4 * BQ * 64 * 2, DKV_LDS_B = DKV_STAT_AT + 4 * BQ * 4;
+template <bool SELF_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem* list, int entry, int part, int parts, char* lds) {
+  constexpr int HD = 64, NC = HD / 32, NN = HD / 16, NS = 2 * NC, TILE_B = BQ * HD * 2, BLOCK_B = 32 * HD * 2, GROUP_B = 16 * HD * 2;
+  AttnItem t;
+  if (!work_item(list, t, entry)) return;
+  const int kvh = t.head, grp = p.Hq / p.Hkv;
+  const int tid = threadIdx.x;
+  const Lane L(tid);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_first_k = t.tile0 + 32 * wave;
+  int krow[2];
+  bf16x8 kf[2][NC], vf[2][NC];
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    krow[j] = wave_first_k + 16 * j + L.c16;
+    const bool ok = krow[j] < t.seg_len;
+    const int64_t at = (int64_t)(t.seg_start + (ok ? krow[j] : 0)) * p.kv_stride + kvh * HD + 8 * L.g;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      kf[j][c] = global_frag(p.k + at + 32 * c, ok);
+      vf[j][c] = negated(global_frag(p.v + at + 32 * c, ok));
+    }
+  }
+  f32x4 dk[NN][2], dv[NN][2];
+#pragma unroll
+  for (int n = 0; n < NN; n++) dk[n][0] = dk[n][1] = dv[n][0] = dv[n][1] = f32x4{0, 0, 0, 0};
 
   const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
-  const int wave_first_k = t.tile0 + 32 * wave;
-  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ, blockIdx.y, gridDim.y);
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, BQ, part, parts);
   const int n_it = range.n_it;
   const float c2 = p.scale_log2e;
 
-  // ---- loads ------------------------------------------------------------------------------------
-  constexpr int CPR = HD / 8, RPI = 64 / CPR, PER_WAVE = BQ / RPI / 4;
-  constexpr int PT = 2 * PER_WAVE + 1;   // load instructions per wavefront and tile
+  constexpr int PER_WAVE = BQ * HD / 8 / 64 / 4;
   uint32_t q_off[PER_WAVE], do_off[PER_WAVE];
 #pragma unroll
   for (int i = 0; i < PER_WAVE; i++) {
-    const int r = (wave * PER_WAVE + i) * RPI + lane / CPR, c = (lane % CPR) ^ swz<HD>(r);
-    q_off[i] = (uint32_t)((r * p.q_stride + 8 * c) * 2);
-    do_off[i] = (uint32_t)((r * p.o_stride + 8 * c) * 2);
+    q_off[i] = load_offset<HD>(L, wave * PER_WAVE + i, p.q_stride);
+    do_off[i] = load_offset<HD>(L, wave * PER_WAVE + i, p.o_stride);
   }
   const uint32_t q_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.q_stride + HD) * 2);
   const uint32_t do_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * p.o_stride + HD) * 2);
-  int nj = range.head, nq0 = range.q0;   // the tile to be loaded next: query head nj of the group, rows from nq0
-  // Past the last tile the descriptors are empty and the loads write zeros.
-  const uint32_t lds_b = lds_address((MLLM_LDS const void*)lds);
-  // A tile's loads are enqueued in PT parts so that they can be spread over the MFMAs of a stage.
-  i32x4_t rq, rdo, rst;
-  uint32_t qrow, dorow, dst_t, dst_s;
-  auto issue_begin = [&](int stage) {
+  const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_address((MLLM_LDS const void*)lds) + wave * PER_WAVE * 1024);
+
+  // The tile to be loaded next: query head nj of the group, query rows from nq0.  Past the last
+  // tile the descriptors are empty and the loads write zeros.
+  int nj = range.head, nq0 = range.q0;
+  float r_lse = 0.f, r_delta = 0.f;   // statistics of the tile in flight, one row per thread (tid < BQ)
+  bool r_ok = false;
+  u32x4_t r_o[2], r_do[2];             // SELF_DELTA: the thread's 16 columns of O and dO
+  auto issue = [&](int st) {
     const bool valid = nj < grp;
     const int head = kvh * grp + (valid ? nj : 0);
-    rq = raw_rsrc(p.q + (int64_t)t.seg_start * p.q_stride + head * HD, valid ? q_bytes : 0u);
-    rdo = raw_rsrc(p.d_o + (int64_t)t.seg_start * p.o_stride + head * HD, valid ? do_bytes : 0u);
-    // lse and delta of the tile's rows, 64 floats each, one instruction each: even wavefronts bring
-    // lse, odd ones delta (twice the same bytes, so that every wavefront counts the same loads).
-    // Rows past the segment read as zero; their dO rows are zero too, so they add nothing.
-    rst = raw_rsrc(((wave & 1) ? p.delta : p.lse) + (int64_t)head * p.T + t.seg_start, valid ? (uint32_t)t.seg_len * 4u : 0u);
-    qrow = (uint32_t)nq0 * (uint32_t)(p.q_stride * 2);
-    dorow = (uint32_t)nq0 * (uint32_t)(p.o_stride * 2);
-    dst_t = lds_b + (uint32_t)(stage * STAGE_B + (wave * PER_WAVE) * 1024);
-    dst_s = lds_b + (uint32_t)(STATS_AT + stage * STAT_STAGE_B + (wave & 1) * BQ * 4);
-  };
-  auto issue_part = [&](int j) {
-    if (j < PER_WAVE) load_to_lds_b128(rq, dst_t + j * 1024, q_off[j] + qrow);
-    else if (j < 2 * PER_WAVE) load_to_lds_b128(rdo, dst_t + TILE_B + (j - PER_WAVE) * 1024, do_off[j - PER_WAVE] + dorow);
-    else load_to_lds_b32(rst, dst_s, (uint32_t)(nq0 + lane) * 4u);
-  };
-  auto issue_end = [&]() {
+    const bf16_t* dos = p.d_o + (int64_t)t.seg_start * p.o_stride + head * HD;
+    const i32x4_t rq = raw_rsrc(p.q + (int64_t)t.seg_start * p.q_stride + head * HD, valid ? q_bytes : 0u);
+    const i32x4_t rdo = raw_rsrc(dos, valid ? do_bytes : 0u);
+    const uint32_t qrow = (uint32_t)nq0 * (uint32_t)(p.q_stride * 2), dorow = (uint32_t)nq0 * (uint32_t)(p.o_stride * 2);
+    const uint32_t so = tid < BQ ? (uint32_t)(nq0 + tid) * 4u : 0xFFFFFFFFu;
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.lse + (int64_t)head * p.T + t.seg_start), 0, valid ? t.seg_len * 4 : 0, 0x00020000);
+    r_lse = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rl, (int)so, 0, 0));
+    if constexpr (SELF_DELTA) {
+      const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(dos), 0, valid ? (int)do_bytes : 0, 0x00020000);
+      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+          p.o + (int64_t)t.seg_start * p.o_stride + head * HD, 0, valid ? (int)do_bytes : 0, 0x00020000);
+      const uint32_t at = dorow + (uint32_t)(tid >> 2) * (uint32_t)(p.o_stride * 2) + (uint32_t)(tid & 3) * 32u;
+#pragma unroll
+      for (int w = 0; w < 2; w++) {
+        r_o[w] = __builtin_amdgcn_raw_buffer_load_b128(ro, (int)(at + 16u * w), 0, 0);
+        r_do[w] = __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(at + 16u * w), 0, 0);
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(p.delta + (int64_t)head * p.T + t.seg_start), 0, valid ? t.seg_len * 4 : 0, 0x00020000);
+      r_delta = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, (int)so, 0, 0));
+    }
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; i++) {
+      load_to_lds_b128(rq, lds_b + (uint32_t)(st * 2 * TILE_B + i * 1024), q_off[i], qrow);
+      load_to_lds_b128(rdo, lds_b + (uint32_t)(st * 2 * TILE_B + TILE_B + i * 1024), do_off[i], dorow);
+    }
+    r_ok = valid && tid < BQ && nq0 + tid < t.seg_len;
     nq0 += BQ;
     if (nq0 >= t.seg_len) { nq0 = q_begin; nj++; }
   };
-  auto issue = [&](int stage) {
-    issue_begin(stage);
+  const lds_cptr M = (lds_cptr)lds;
+  float* const stats = (float*)(lds + DKV_STAT_AT);   // [stage][lse * log2(e), delta][BQ]
+  uint32_t rows[NC], cols[NN];
 #pragma unroll
-    for (int j = 0; j < PT; j++) issue_part(j);
-    issue_end();
-  };
+  for (int c = 0; c < NC; c++) rows[c] = row_offset<HD>(L, c);
+#pragma unroll
+  for (int n = 0; n < NN; n++) cols[n] = col_offset<HD>(L, n);
+  const uint32_t stat_rows = DKV_STAT_AT + 16u * L.g;
 
-  // ---- lane parts of the LDS offsets, stage included (advanced once per tile); block and operand ride
-  // in the instructions' offset fields ------------------------------------------------------------
-  // natural-layout fragment (frag_rows): tile row lane%32 of a 32-row block, 16-byte chunk 2c + h
-  // transposed fragment (frag_cols_permuted): rows 4h + i16/4 (+8), columns 32d + 16*(lane/16 % 2) + 4*(i16 % 4)
-  uint32_t rows_c[NC], rows_n[NC], cols_c[ND][2];   // _c: stage of the current tile, _n: of the next
-  {
-    const int r = lane & 31, i16 = lane & 15;
+  f32x4 s[2][2][2], dp[2][2][2];   // [block][row group][own group]: scores, delta - dP
+  f32x4 ls[2][2], de[2][2];        // [block][row group]: statistics of the lane's rows
+  Frag8 pb[2][2], db[2][2];        // P and dS (negated) as MFMA operands: [block][own group]
+  auto mask = [&](int b, int q0) {
+    const int r0 = q0 + 32 * b;
+    if (t.causal && r0 <= wave_first_k + 31) {   // block touches the diagonal
 #pragma unroll
-    for (int c = 0; c < NC; c++) {
-      rows_c[c] = (uint32_t)(r * HD + 8 * ((2 * c + h) ^ swz<HD>(r))) * 2u;
-      rows_n[c] = rows_c[c] + STAGE_B;
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) s[b][i][j][e] = (krow[j] <= r0 + 16 * i + 4 * L.g + e) ? s[b][i][j][e] : -INFINITY;
     }
-#pragma unroll
-    for (int d = 0; d < ND; d++)
-#pragma unroll
-      for (int e = 0; e < 2; e++) {
-        const int k = 4 * h + (i16 >> 2) + 8 * e;
-        const int n = 32 * d + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-        cols_c[d][e] = (uint32_t)(k * HD + 8 * ((n >> 3) ^ swz<HD>(k)) + (n & 7)) * 2u;
-      }
-  }
-  uint32_t sa_c = STATS_AT + 16u * h, sa_n = sa_c + STAT_STAGE_B;
-  int st_c = 0;   // stage of the current tile
+  };
+  auto grad = [&](int b, int v) {   // elements v, v+1 of a block
+    const int i = v >> 3, j = (v >> 2) & 1, e = v & 3;
+    const float x = fast_exp2(fmaf(s[b][i][j][e], c2, -ls[b][i][e])), y = fast_exp2(fmaf(s[b][i][j][e + 1], c2, -ls[b][i][e + 1]));
+    pb[b][j].w[2 * i + (e >> 1)] = pack_bf16x2(x, y);
+    db[b][j].w[2 * i + (e >> 1)] = pack_bf16x2(x * dp[b][i][j][e], y * dp[b][i][j][e + 1]);
+  };
+  constexpr int AHEAD = 2, CAHEAD = 1;
+  constexpr int EPS = 16 / NS, EPV = 16 / NN;
 
-  // ---- the two stages of a step ------------------------------------------------------------------
-  const lds_cptr rt = (lds_cptr)lds, rs = (lds_cptr)lds;
-  constexpr int NM = 2 * NC, EPS = 16 / NM, NPV = 2 * ND;
-  constexpr int RD = NM < 8 ? NM / 2 : 8;   // score fragments are read RD slots ahead of their MFMA
-  constexpr int PD = NPV < 8 ? NPV / 2 : 3;   // dV / dK fragments PD pairs ahead
-  constexpr int SP = NPV / 4;               // pairs of the second stage that fetch the next block's statistics
-  // carried from stage to stage
-  bf16x8 pre[RD];            // the first fragments of the next score stage
-  f32x16 s_n, dp_n;          // scores and dP of the block after the current one
-  float xs[16], ts[16];      // current block: exponent (s scale - lse) log2 e, and dP - delta
-  Frag8 pf[2], dsf[2];       // current block: P and dS as MFMA operands
-  Frag8 fdo[NPV], fq[NPV];   // current block: transposed dO and Q fragments
-  // transposing reads of pair i of the dV / dK products: rows 32 BC + 16 cc .. +15 of the current tile, columns 32 d .. +31
-  auto pair_reads = [&](int BC, int i, int part) {   // part 0: the dO fragment, 1: the Q fragment
-    const int cc = i / ND, d = i % ND;
-    const uint32_t o = BC * ROWS32_B + cc * ROWS16_B;
-    if (part == 0) { fdo[i].h[0] = lds_tr(rt, cols_c[d][0] + o + TILE_B); fdo[i].h[1] = lds_tr(rt, cols_c[d][1] + o + TILE_B); }
-    else { fq[i].h[0] = lds_tr(rt, cols_c[d][0] + o); fq[i].h[1] = lds_tr(rt, cols_c[d][1] + o); }
-  };
-  // Score stage: S and dP of block BN of the tile at offsets rows_x, one MFMA per slot; behind each
-  // MFMA a slice of the current block's (BC) vector work, P = exp2(xs), dS = P * ts, packed to bf16.
-  // An MFMA has no side effect the compiler must keep in place: left alone, those whose results are
-  // needed only later all move to the end of the loop body, out of their slots.  Passing each result
-  // through an empty volatile statement ties it between its neighbours.
-  auto sx = [&](auto BCt, auto BNt, const uint32_t (&rows_x)[NC]) {
-    constexpr int BC = decltype(BCt)::value, BN = decltype(BNt)::value;
-    bf16x8 fr[NM];
-#pragma unroll
-    for (int m = 0; m < RD; m++) fr[m] = pre[m];
-    float prv[16], dsv[16];
-    f32x16 zero;
-#pragma unroll
-    for (int v = 0; v < 16; v++) zero[v] = 0.f;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int m = 0; m < NM; m++) {
-      if (m + RD < NM) {
-        fr[m + RD] = lds_b128(rt, rows_x[(m + RD) / 2] + ((m + RD) % 2) * TILE_B + BN * ROWS32_B);
-      } else {   // the last 2 PD slots fetch the fragments of the first PD pairs, one fragment per slot
-        const int j = m - (NM - 2 * PD);
-        if (j >= 0) pair_reads(BC, j / 2, j % 2);
-      }
-      if (m % 2 == 0) {
-        s_n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m], kf[m / 2], m == 0 ? zero : s_n, 0, 0, 0);
-        asm volatile("" : "+a"(s_n));
-      } else {
-        dp_n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[m], vf[m / 2], m == 1 ? zero : dp_n, 0, 0, 0);
-        asm volatile("" : "+a"(dp_n));
-      }
-#pragma unroll
-      for (int e = 0; e < EPS; e++) {
-        const int v = m * EPS + e;
-        prv[v] = fast_exp2(xs[v]);
-        dsv[v] = prv[v] * ts[v];
-        if (v & 1) {
-          pf[v >> 3].w[(v >> 1) & 3] = pack_bf16x2(prv[v - 1], prv[v]);
-          dsf[v >> 3].w[(v >> 1) & 3] = pack_bf16x2(dsv[v - 1], dsv[v]);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
+  // One tile: publish the statistics of the tile whose loads were enqueued a tile ago, wait for
+  // those loads, barrier (every wavefront is now done with the other stage), enqueue the next
+  // tile into the other stage, multiply.
+  auto tile = [&](auto STt, int q0, bool live) {
+    constexpr int ST = decltype(STt)::value;
+    constexpr uint32_t AT = ST * 2 * TILE_B;
+    if (tid < BQ) {
+      stats[ST * 2 * BQ + tid] = r_ok ? r_lse * LOG2E : INFINITY;   // +inf: probabilities of rows past the segment are 0
+      if constexpr (!SELF_DELTA) stats[ST * 2 * BQ + BQ + tid] = r_ok ? r_delta : 0.f;
     }
-  };
-  // dV / dK stage of block BC: dV += dO^T.P, dK += Q^T.dS, a pair of MFMAs at a time.  Each pair
-  // follows the transposing reads of the pair PD further on; the last pairs carry the first reads
-  // of the next score stage instead (from rows_x, block BT).  The first pairs fetch the statistics of
-  // the next block (offset sa_x, block BN), the later ones turn them and the fresh scores into xs, ts;
-  // with ISSUE, the parts of a tile's loads ride along as well.
-  auto dx = [&](auto BCt, auto BNt, auto BTt, auto ISSUEt, const uint32_t (&rows_x)[NC], uint32_t sa_x) {
-    constexpr int BC = decltype(BCt)::value, BN = decltype(BNt)::value, BT = decltype(BTt)::value;
-    constexpr bool ISSUE = decltype(ISSUEt)::value != 0;
-    f32x4 st[8];   // lse of row groups 0..3, delta of row groups 0..3
+    if constexpr (SELF_DELTA) {   // rows past the segment, and the tile past the last one, have come as zeros
+      float d = 0.f;
 #pragma unroll
-    for (int i = 0; i < NPV; i++) {
-      const int cc = i / ND, d = i % ND;
-      if (i + PD < NPV) {
-        pair_reads(BC, i + PD, 0);
-        pair_reads(BC, i + PD, 1);
-      } else {
-        constexpr int PER = (RD + PD - 1) / PD;
-        const int j0 = (i - (NPV - PD)) * PER;
+      for (int w = 0; w < 2; w++)
 #pragma unroll
-        for (int m = j0; m < j0 + PER && m < RD; m++) pre[m] = lds_b128(rt, rows_x[m / 2] + (m % 2) * TILE_B + BT * ROWS32_B);
-      }
-      if (i < SP) {
-#pragma unroll
-        for (int g = i * 8 / SP; g < (i + 1) * 8 / SP; g++)
-          st[g] = lds_f4(rs, sa_x + (g >= 4 ? BQ * 4 : 0) + (32 * BN + 8 * (g & 3)) * 4);
-      } else {
-#pragma unroll
-        for (int v = (i - SP) * 16 / (NPV - SP); v < (i - SP + 1) * 16 / (NPV - SP); v++) {
-          xs[v] = fmaf(s_n[v], c2, -(st[v >> 2][v & 3] * LOG2E));
-          ts[v] = dp_n[v] - st[4 + (v >> 2)][v & 3];
-        }
-      }
-      if (ISSUE) {
-#pragma unroll
-        for (int j = i * PT / NPV; j < (i + 1) * PT / NPV; j++) issue_part(j);
-      }
-      dvacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fdo[i].v, pf[cc].v, dvacc[d], 0, 0, 0);
-      asm volatile("" : "+a"(dvacc[d]));
-      dkacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[i].v, dsf[cc].v, dkacc[d], 0, 0, 0);
-      asm volatile("" : "+a"(dkacc[d]));
-      __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < 4; e++) d += bf16lo(r_o[w][e]) * bf16lo(r_do[w][e]) + bf16hi(r_o[w][e]) * bf16hi(r_do[w][e]);
+      d += __shfl_xor(d, 1, 64);
+      d += __shfl_xor(d, 2, 64);
+      if ((tid & 3) == 0) stats[ST * 2 * BQ + BQ + (tid >> 2)] = d;
     }
-  };
-  // Causal blocks on or above the diagonal: masked pairs get exponent -inf, i.e. probability zero.
-  auto mask_diag = [&](int q0b) {
-    if (t.causal && q0b <= wave_first_k + 31) {
+    wait_loads<0>();
+    phase_barrier();
+    issue(1 - ST);
+    MLLM_SLOT_END;
+    if (!live || (t.causal && q0 + BQ - 1 < wave_first_k) || wave_first_k >= t.seg_len) return;   // no query here sees this wavefront's keys, or it has none
+    bf16x8 fq[2 * NS], fo[2 * NS], cq[2 * NN], co[2 * NN];
+    auto read_row = [&](int x) {
+      const uint32_t o = rows[x % NS / 2] + AT + x / NS * BLOCK_B + x % 2 * GROUP_B;
+      fq[x] = lds_b128(M, o);
+      fo[x] = lds_b128(M, o + TILE_B);
+    };
+    auto read_c = [&](int x) {
+      const uint32_t o = cols[x % NN] + AT + x / NN * BLOCK_B;
+      cq[x] = read_col<HD>(M, o);
+      co[x] = read_col<HD>(M, o + TILE_B);
+    };
+    auto read_stats = [&](int b) {
 #pragma unroll
-      for (int v = 0; v < 16; v++) xs[v] = (krow <= q0b + acc_row(v, h)) ? xs[v] : -INFINITY;
+      for (int i = 0; i < 2; i++) {
+        de[b][i] = lds_f4(M, stat_rows + (uint32_t)((ST * 2 * BQ + BQ + 32 * b + 16 * i) * 4));
+        ls[b][i] = lds_f4(M, stat_rows + (uint32_t)((ST * 2 * BQ + 32 * b + 16 * i) * 4));
+      }
+    };
+    auto score = [&](int x) {
+      const int b = x / NS, c = x % NS / 2, i = x % 2;
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        s[b][i][j] = mfma(fq[x], kf[j][c], c == 0 ? f32x4{0, 0, 0, 0} : s[b][i][j]);
+        dp[b][i][j] = mfma(fo[x], vf[j][c], c == 0 ? de[b][i] : dp[b][i][j]);
+      }
+    };
+    auto output = [&](int x) {
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        dv[x % NN][j] = mfma(co[x], pb[x / NN][j].v, dv[x % NN][j]);
+        dk[x % NN][j] = mfma(cq[x], db[x / NN][j].v, dk[x % NN][j]);
+      }
+    };
+    read_stats(0);
+#pragma unroll
+    for (int x = 0; x < AHEAD; x++) read_row(x);
+#pragma unroll
+    for (int x = 0; x < NS; x++) {
+      read_row(x + AHEAD);
+      if (x == NS - 1) read_stats(1);
+      score(x);
+      MLLM_SLOT_END;
+    }
+    mask(0, q0);
+    MLLM_SLOT_END;
+#pragma unroll
+    for (int x = NS; x < 2 * NS; x++) {
+      if (x + AHEAD < 2 * NS) read_row(x + AHEAD);
+      else if (x - (2 * NS - AHEAD) < CAHEAD) read_c(x - (2 * NS - AHEAD));
+      score(x);
+#pragma unroll
+      for (int v = (x - NS) * EPS; v < (x - NS + 1) * EPS; v += 2) grad(0, v);
+      MLLM_SLOT_END;
+    }
+    mask(1, q0);
+    MLLM_SLOT_END;
+#pragma unroll
+    for (int x = 0; x < NN; x++) {
+      read_c(x + CAHEAD);
+      output(x);
+#pragma unroll
+      for (int v = x * EPV; v < (x + 1) * EPV; v += 2) grad(1, v);
+      MLLM_SLOT_END;
+    }
+#pragma unroll
+    for (int x = NN; x < 2 * NN; x++) {
+      if (x + CAHEAD < 2 * NN) read_c(x + CAHEAD);
+      output(x);
+      MLLM_SLOT_END;
     }
   };
 
+  issue(0);
   int q0 = range.q0;
-  // ---- prologue: tile 0 lands, its first block's scores are formed on their own ----------------
-#pragma unroll
-  for (int st = 0; st < NST - 1; st++) issue(st);
-  wait_loads<(NST - 2) * PT>();
-  __syncthreads();
-  __builtin_amdgcn_sched_barrier(0);
-  {
-#pragma unroll
-    for (int v = 0; v < 16; v++) { s_n[v] = 0.f; dp_n[v] = 0.f; }
-#pragma unroll
-    for (int c = 0; c < NC; c++) {
-      s_n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(rt, rows_c[c]), kf[c], s_n, 0, 0, 0);
-      dp_n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_b128(rt, rows_c[c] + TILE_B), vf[c], dp_n, 0, 0, 0);
-    }
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      const f32x4 x = lds_f4(rs, sa_c + 8 * g * 4), y = lds_f4(rs, sa_c + BQ * 4 + 8 * g * 4);
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        xs[4 * g + e] = fmaf(s_n[4 * g + e], c2, -(x[e] * LOG2E));
-        ts[4 * g + e] = dp_n[4 * g + e] - y[e];
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < RD; m++) pre[m] = lds_b128(rt, rows_c[m / 2] + (m % 2) * TILE_B + ROWS32_B);
+  auto advance = [&]() { q0 += BQ; if (q0 >= t.seg_len) q0 = q_begin; };
+  for (int it = 0; it < n_it; it += 2) {
+    tile(Int<0>{}, q0, true);
+    advance();
+    tile(Int<1>{}, q0, it + 1 < n_it);
+    advance();
   }
-  __builtin_amdgcn_sched_barrier(0);
-
-  // One tile per iteration.  Block 0: P, dS against the scores of block 1; then tile it+1 must have
-  // landed (the NST-3 tiles enqueued after it may still be on their way) and every wavefront must have
-  // left tile it-1, whose stage takes tile it+NST-1, enqueued under dV, dK of block 0.  Block 1: P, dS
-  // against the scores of block 0 of tile it+1, then its dV, dK.
-  for (int it = 0; it < n_it; it++) {
-    mask_diag(q0);
-    sx(Int<0>{}, Int<1>{}, rows_c);
-    wait_loads<(NST - 3) * PT>();
-    __syncthreads();
-    issue_begin(st_c == 0 ? NST - 1 : st_c - 1);
-    __builtin_amdgcn_sched_barrier(0);
-    dx(Int<0>{}, Int<1>{}, Int<0>{}, Int<1>{}, rows_n, sa_c);
-    issue_end();
-    mask_diag(q0 + 32);
-    sx(Int<1>{}, Int<0>{}, rows_n);
-    dx(Int<1>{}, Int<0>{}, Int<1>{}, Int<0>{}, rows_n, sa_n);
-    // rotate the stages
-    q0 += BQ;
-    if (q0 >= t.seg_len) q0 = q_begin;
-    const int st_n = st_c + 1 == NST ? 0 : st_c + 1, st_nn = st_n + 1 == NST ? 0 : st_n + 1;
-    const uint32_t dc = st_n == 0 ? (uint32_t)(-(NST - 1) * STAGE_B) : (uint32_t)STAGE_B;
-    const uint32_t dn = st_nn == 0 ? (uint32_t)(-(NST - 1) * STAGE_B) : (uint32_t)STAGE_B;
-#pragma unroll
-    for (int c = 0; c < NC; c++) { rows_c[c] += dc; rows_n[c] += dn; }
-#pragma unroll
-    for (int d = 0; d < ND; d++) { cols_c[d][0] += dc; cols_c[d][1] += dc; }
-    sa_c += st_n == 0 ? (uint32_t)(-(NST - 1) * STAT_STAGE_B) : (uint32_t)STAT_STAGE_B;
-    sa_n += st_nn == 0 ? (uint32_t)(-(NST - 1) * STAT_STAGE_B) : (uint32_t)STAT_STAGE_B;
-    st_c = st_n;
-  }
-  // the loads enqueued last (tiles past the end: zeros) must have landed before this workgroup's LDS
+  // the last enqueued loads (an empty tile: zeros) must have landed before this workgroup's LDS
   // can be handed to another one
   wait_loads<0>();
-  if (!kok) return;
-  if (gridDim.y > 1) {
-    store_kv_partial<HD>(p, dkacc, dvacc, gkrow, kvh, h, blockIdx.y);
-    return;
-  }
-  float out_scale = p.scale;
-  if (p.rope_table) {
-    rope_unrotate<HD>(dkacc, p.rope_table, krow, h, p.scale);
-    out_scale = 1.f;
-  }
-  bf16_t* dkp = p.dk + gkrow * p.kv_stride + kvh * HD;
-  bf16_t* dvp = p.dv + gkrow * p.kv_stride + kvh * HD;
 #pragma unroll
-  for (int d = 0; d < ND; d++)
+  for (int j = 0; j < 2; j++) {
+    if (krow[j] >= t.seg_len) continue;
+    const int64_t row = t.seg_start + krow[j];
+    store_dk<HD>(p, dk, j, krow[j], row, kvh, L.g, parts > 1, (unsigned)part);
+    store_dv<HD>(p, dv, j, row, kvh, L.g, parts > 1, (unsigned)part);
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkv_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(1024))) char lds[DKV_LDS_B];
+  attn_bwd_dkv<false>(p, p.list, blockIdx.x, blockIdx.y, gridDim.y, lds);
+}
+// Both passes in one launch, the dK/dV pass first.
+__global__ __launch_bounds__(256, 2) void attn_bwd_both_kernel(AttnParams p, const AttnItem* kv_list, int kv_grid, int kv_parts) {
+  __shared__ __attribute__((aligned(1024))) char lds[DKV_LDS_B];
+  const int kv = kv_grid * kv_parts, pid = blockIdx.x;
+  if (pid < kv) attn_bwd_dkv<true>(p, kv_list, pid % kv_grid, pid / kv_grid, kv_parts, lds);
+  else attn_bwd_dq<64>(p, p.list, pid - kv, lds);
+}
+
+// ---------------------------------------------------------------------------------------------
+// dK/dV pass at head_dim 128: one workgroup of eight wavefronts per (key tile of 128, kv head), two wavefronts on a
+// SIMD.  The work of a block of 32 query rows falls into two halves that hold one accumulator each, so that two
+// wavefronts fit where one that does all of it needs the whole register file:
+//   wavefronts 0..3 (keys 32 w ..):  S = Q.K^T, P = exp2(S scale log2 e - lse log2 e), dV^T += dO^T.P
+//   wavefronts 4..7 (the same keys): dP = dO.V^T - delta, dS = P * dP, dK^T += Q^T.dS
+// P goes from the one to the other through LDS in fp32, lane for lane.  Both are pipelined over phases of one block, a
+// barrier each; in phase n
+//   the first:  dV of block n-1 (exponents of n formed under it), then S of n+1 (P of n formed and written under it)
+//   the second: dK of block n-2 (P of n-1 read under it), then dP of n (dS of n-1 formed under it)
+// so every product is formed from operands that have been at hand since the phase before, and a block passes through in
+// three phases.  Q blocks rotate through 8 stages of LDS (n-2 .. n+1 are read, n+2 .. n+4 on their way), dO blocks through 4
+// (n-1 and n, n+1 and n+2); eight phases are unrolled, so that a stage is an offset in the instruction.
+// One wavefront per SIMD that did both halves was bound by its own instruction issue, 11 instructions a 32x32x16 MFMA at one
+// every 4 to 6 clocks: 13255 causal tokens, 32/8 heads, 5.93 M cycles with the MFMAs busy 47 %, now 5.10 M and 55 %, 2915 -> 2467
+// us on one card.  What is left is spread evenly: without the exchange of P 9 % less time, without the loads 9 %, without the
+// natural reads 7 %, the transposing ones 15 %, the exponentials 5 %, without all of them 25 %.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(512, 2) void attn_bwd_dkv_duo_kernel(AttnParams p) {
+  constexpr int HD = 128, NC = HD / 32, NN = HD / 16, NS = 2 * NC, QB = 32;   // QB: query rows of a block
+  constexpr int BLOCK_B = QB * HD * 2, GROUP_B = 16 * HD * 2;
+  constexpr int NQ = 8, NO = 4;                                  // stages of Q and of dO
+  constexpr int DO_AT = NQ * BLOCK_B, P_AT = DO_AT + NO * BLOCK_B, P_SLOT = 4 * 4096, STAT_AT = P_AT + 2 * P_SLOT;
+  constexpr int STAT_B = 256, WAVE_STAT_B = NQ * STAT_B;         // a wavefront's own row statistics, a stage each
+  // One array on purpose: the compiler tags LDS accesses with the variable they belong to, and with a single one there is
+  // nothing to tag.
+  __shared__ __attribute__((aligned(1024))) char lds[STAT_AT + 8 * WAVE_STAT_B];
+  AttnItem t;
+  if (!work_item(p.list, t, blockIdx.x)) return;
+  const int kvh = t.head, grp = p.Hq / p.Hkv;
+  const int tid = threadIdx.x;
+  const Lane L(tid);
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
+  const bool second = wave8 >= 4;
+  const int wave_first_k = t.tile0 + 32 * wave;
+  int krow[2];
+  // The wavefront's K, or V negated: dP products that start from delta end as delta - dP, and dK takes its sign back with the scale.
+  bf16x8 kvf[2][NC];
 #pragma unroll
-    for (int g4 = 0; g4 < 4; g4++) {
-      uint2 w;
-      w.x = pack_bf16x2(dkacc[d][4 * g4] * out_scale, dkacc[d][4 * g4 + 1] * out_scale);
-      w.y = pack_bf16x2(dkacc[d][4 * g4 + 2] * out_scale, dkacc[d][4 * g4 + 3] * out_scale);
-      *reinterpret_cast<uint2*>(dkp + 32 * d + 8 * g4 + 4 * h) = w;
-      w.x = pack_bf16x2(dvacc[d][4 * g4], dvacc[d][4 * g4 + 1]);
-      w.y = pack_bf16x2(dvacc[d][4 * g4 + 2], dvacc[d][4 * g4 + 3]);
-      *reinterpret_cast<uint2*>(dvp + 32 * d + 8 * g4 + 4 * h) = w;
+  for (int j = 0; j < 2; j++) {
+    krow[j] = wave_first_k + 16 * j + L.c16;
+    const bool ok = krow[j] < t.seg_len;
+    const bf16_t* kvp = (second ? p.v : p.k) + (int64_t)(t.seg_start + (ok ? krow[j] : 0)) * p.kv_stride + kvh * HD + 8 * L.g;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      kvf[j][c] = global_frag(kvp + 32 * c, ok);
+      if (second) kvf[j][c] = negated(kvf[j][c]);
     }
+  }
+  f32x4 acc[NN][2];   // dV, or dK negated
+#pragma unroll
+  for (int n = 0; n < NN; n++) acc[n][0] = acc[n][1] = f32x4{0, 0, 0, 0};
+
+  const int q_begin = t.causal ? (t.tile0 / BQ) * BQ : 0;
+  const KvRange range = kv_range(grp, q_begin, t.seg_len, QB, blockIdx.y, gridDim.y);
+  const int n_it = range.n_it;
+  const float c2 = p.scale_log2e;
+
+  // ---- loads: the first wavefronts bring Q and lse, the second dO and delta, 8 rows each -----------
+  constexpr int PER_WAVE = QB * HD / 8 / 64 / 4, PT = PER_WAVE + 1;   // PT: instructions per wavefront and block
+  const int64_t in_stride = second ? p.o_stride : p.q_stride;
+  const bf16_t* const in = (second ? p.d_o : p.q) + (int64_t)t.seg_start * in_stride;
+  const float* const in_stat = (second ? p.delta : p.lse) + t.seg_start;
+  uint32_t in_off[PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < PER_WAVE; i++) in_off[i] = load_offset<HD>(L, wave * PER_WAVE + i, in_stride);
+  const uint32_t in_bytes = (uint32_t)(((int64_t)(t.seg_len - 1) * in_stride + HD) * 2);
+  const uint32_t in_row = (uint32_t)(in_stride * 2);
+  int nj = range.head, nq0 = range.q0, to_load = n_it;   // the block to be loaded next: query head nj of the group, rows from nq0
+  const uint32_t lds_b = lds_address((MLLM_LDS const void*)lds);
+  const uint32_t load_at = __builtin_amdgcn_readfirstlane(lds_b + (second ? DO_AT : 0) + wave * PER_WAVE * 1024);
+  const uint32_t stat_off = STAT_AT + (uint32_t)wave8 * WAVE_STAT_B;
+  const uint32_t stat_at = __builtin_amdgcn_readfirstlane(lds_b + stat_off);
+  // Past the last block the descriptors are empty and the loads write zeros.  Rows past the segment read as zero as well
+  // (their lse and delta too): they add nothing, as their dO rows are zero.
+  i32x4_t rin, rst;
+  auto set_head = [&]() {
+    const bool valid = to_load > 0;
+    const int head = kvh * grp + (valid ? nj : 0);
+    rin = raw_rsrc(in + head * HD, valid ? in_bytes : 0u);
+    rst = raw_rsrc(in_stat + (int64_t)head * p.T, valid ? (uint32_t)t.seg_len * 4u : 0u);
+  };
+  set_head();
+  auto issue_part = [&](int stage, int j) {
+    if (j < PER_WAVE) load_to_lds_b128(rin, load_at + (uint32_t)(stage * BLOCK_B + j * 1024), in_off[j], (uint32_t)nq0 * in_row);
+    else load_to_lds_b32(rst, stat_at + (uint32_t)(stage * STAT_B), (uint32_t)L.lane * 4u, (uint32_t)nq0 * 4u);
+  };
+  auto issue_end = [&]() {
+    nq0 += QB;
+    to_load--;
+    if (nq0 >= t.seg_len || to_load == 0) {
+      if (nq0 >= t.seg_len) { nq0 = q_begin; nj++; }
+      set_head();
+    }
+  };
+  auto issue = [&](int stage) {
+#pragma unroll
+    for (int j = 0; j < PT; j++) issue_part(stage, j);
+    issue_end();
+  };
+
+  // ---- lane parts of the LDS offsets; stage, block half and operand ride in the instructions' offset fields ----
+  // rows: of the block that the score-like product reads; cols: of the block that the accumulating product reads
+  uint32_t rows[NC], cols[NN];
+#pragma unroll
+  for (int c = 0; c < NC; c++) rows[c] = row_offset<HD>(L, c) + (second ? DO_AT : 0);
+#pragma unroll
+  for (int n = 0; n < NN; n++) cols[n] = col_offset<HD>(L, n) + (second ? 0 : DO_AT);
+  const uint32_t p_at = P_AT + (uint32_t)(wave * 4096 + L.lane * 16), stat_rows = stat_off + 16u * L.g;
+  const lds_cptr M = (lds_cptr)lds;
+  const lds_ptr Mw = (lds_ptr)lds;
+
+  // What phases 0 and 1 read of blocks -2 and -1 is zero: the last two stages of Q, the last of dO, the second slot of P.
+  for (int i = tid * 16; i < 2 * BLOCK_B; i += 512 * 16) *(MLLM_LDS u32x4_t*)(Mw + (NQ - 2) * BLOCK_B + i) = u32x4_t{0, 0, 0, 0};
+  *(MLLM_LDS u32x4_t*)(Mw + DO_AT + (NO - 1) * BLOCK_B + tid * 16) = u32x4_t{0, 0, 0, 0};
+  for (int i = tid * 16; i < P_SLOT; i += 512 * 16) *(MLLM_LDS u32x4_t*)(Mw + P_AT + P_SLOT + i) = u32x4_t{0, 0, 0, 0};
+
+  constexpr int RD = 4, CD = 4;   // fragments read ahead of their MFMAs
+  Frag8 pb[2];            // P, or dS negated, of a block as MFMA operand, an own group each
+#pragma unroll
+  for (int j = 0; j < 2; j++)
+#pragma unroll
+    for (int w = 0; w < 4; w++) pb[j].w[w] = 0;
+  bf16x8 fc[NN], fr[NS];   // transposed and natural-layout fragments
+  auto read_cols = [&](int stage, int n) { fc[n] = read_col<HD>(M, cols[n] + (uint32_t)(stage * BLOCK_B)); };
+  auto read_rows = [&](int stage, int x) { fr[x] = lds_b128(M, rows[x / 2] + (uint32_t)(stage * BLOCK_B + x % 2 * GROUP_B)); };
+  auto accumulate = [&](int n) {
+#pragma unroll
+    for (int j = 0; j < 2; j++) acc[n][j] = mfma(fc[n], pb[j].v, acc[n][j]);
+  };
+  // elements 2x, 2x+1 of a block: row group i, own group j, rows e, e+1
+  struct El { int i, j, e; };
+  auto element = [](int v) { return El{v >> 3, (v >> 2) & 1, v & 3}; };
+
+  const bool idle = wave_first_k >= t.seg_len;   // a wavefront without a key: only its share of the loads is wanted
+  if (!second) {
+    f32x4 s[2][2];          // scores of the block after the current one: [row group][own group]
+    f32x4 xs[2][2];         // exponents of the current block
+    auto scale_lse = [&](int stage) {   // the lse rows of a stage times log2(e), in place (they are this wavefront's own)
+      const uint32_t at = stat_off + (uint32_t)(stage * STAT_B + 4 * L.lane);
+      *(MLLM_LDS float*)(Mw + at) = *(MLLM_LDS const float*)(M + at) * LOG2E;
+    };
+    int q0 = range.q0;
+#pragma unroll
+    for (int st = 0; st < 4; st++) issue(st);
+    wait_loads<3 * PT>();
+    phase_barrier();
+#pragma unroll
+    for (int x = 0; x < NS; x++) {
+      read_rows(0, x);
+#pragma unroll
+      for (int j = 0; j < 2; j++) s[x % 2][j] = mfma(fr[x], kvf[j][x / 2], x < 2 ? f32x4{0, 0, 0, 0} : s[x % 2][j]);
+    }
+    scale_lse(0);
+#pragma unroll
+    for (int n = 0; n < CD; n++) read_cols(NO - 1, n);
+    auto phase = [&](auto Ut) {
+      constexpr int U = decltype(Ut)::value;   // phase number modulo 8
+      wait_loads<2 * PT>();
+      phase_barrier();
+      if (idle) return issue((U + 4) & 7);
+      f32x4 ls[2];
+      // dV of block n-1; exponents of block n; the first fragments of Q of block n+1; the loads of Q of block n+4
+#pragma unroll
+      for (int n = 0; n < NN; n++) {
+        if (n + CD < NN) read_cols((U + 3) & 3, n + CD);
+        else if (n - (NN - CD) < RD) read_rows((U + 1) & 7, n - (NN - CD));
+        if (n < 2) ls[n] = lds_f4(M, stat_rows + (uint32_t)(U * STAT_B + 64 * n));
+        if (n >= 1 && n - 1 < PT) issue_part((U + 4) & 7, n - 1);
+        accumulate(n);
+        if (n >= 2) {
+#pragma unroll
+          for (int v = (n - 2) * 16 / (NN - 2); v < (n - 1) * 16 / (NN - 2); v++) {
+            const El x = element(v);
+            xs[x.i][x.j][x.e] = fmaf(s[x.i][x.j][x.e], c2, -ls[x.i][x.e]);
+          }
+        }
+        MLLM_SLOT_END;
+      }
+      issue_end();
+      if (t.causal && q0 <= wave_first_k + 31) {   // the block touches the diagonal: masked pairs get probability zero
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const El x = element(v);
+          xs[x.i][x.j][x.e] = (krow[x.j] <= q0 + 16 * x.i + 4 * L.g + x.e) ? xs[x.i][x.j][x.e] : -INFINITY;
+        }
+      }
+      q0 += QB;
+      if (q0 >= t.seg_len) q0 = q_begin;
+      // S of block n+1; P of block n, written for the partner; the first fragments of dO of block n
+      f32x4 pr;
+      MLLM_SLOT_END;
+#pragma unroll
+      for (int x = 0; x < NS; x++) {
+        if (x + RD < NS) read_rows((U + 1) & 7, x + RD);
+        else read_cols(U & 3, x - (NS - RD));
+        if (x == 1) scale_lse((U + 1) & 7);
+#pragma unroll
+        for (int j = 0; j < 2; j++) s[x % 2][j] = mfma(fr[x], kvf[j][x / 2], x < 2 ? f32x4{0, 0, 0, 0} : s[x % 2][j]);
+        constexpr int SL = 6;   // slots that the 16 exponentials are spread over
+#pragma unroll
+        for (int v = x * 16 / SL; v < (x + 1) * 16 / SL && v < 16; v++) {
+          const El y = element(v);
+          pr[y.e] = fast_exp2(xs[y.i][y.j][y.e]);
+          if (v & 1) pb[y.j].w[2 * y.i + (y.e >> 1)] = pack_bf16x2(pr[y.e - 1], pr[y.e]);
+          if (y.e == 3) *(MLLM_LDS f32x4*)(Mw + p_at + (U & 1) * P_SLOT + (v >> 2) * 1024) = pr;
+        }
+        MLLM_SLOT_END;
+      }
+    };
+    for (int n = 0;;) {
+      phase(Int<0>{}); if (++n == n_it + 2) break;
+      phase(Int<1>{}); if (++n == n_it + 2) break;
+      phase(Int<2>{}); if (++n == n_it + 2) break;
+      phase(Int<3>{}); if (++n == n_it + 2) break;
+      phase(Int<4>{}); if (++n == n_it + 2) break;
+      phase(Int<5>{}); if (++n == n_it + 2) break;
+      phase(Int<6>{}); if (++n == n_it + 2) break;
+      phase(Int<7>{}); if (++n == n_it + 2) break;
+    }
+  } else {
+    f32x4 dp[2][2][2];      // delta - dP of even and odd blocks: [row group][own group]
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) dp[0][i][j] = dp[1][i][j] = f32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int st = 0; st < 2; st++) issue(st);
+    phase_barrier();
+#pragma unroll
+    for (int n = 0; n < CD; n++) read_cols(NQ - 2, n);
+    auto phase = [&](auto Ut) {
+      constexpr int U = decltype(Ut)::value;
+      wait_loads<PT>();
+      phase_barrier();
+      if (idle) return issue((U + 2) & 3);
+      f32x4 pq[4], de[2];
+      // dK of block n-2; P of block n-1; delta and the first fragments of dO of block n; the loads of dO of block n+2
+#pragma unroll
+      for (int n = 0; n < NN; n++) {
+        if (n + CD < NN) read_cols((U + 6) & 7, n + CD);
+        else if (n - (NN - CD) < RD) read_rows(U & 3, n - (NN - CD));
+        if (n < 4) pq[n] = lds_f4(M, p_at + (uint32_t)(((U + 1) & 1) * P_SLOT + n * 1024));
+        else if (n < 6) de[n - 4] = lds_f4(M, stat_rows + (uint32_t)((U & 3) * STAT_B + 64 * (n - 4)));
+        if (n >= 1 && n - 1 < PT) issue_part((U + 2) & 3, n - 1);
+        accumulate(n);
+        MLLM_SLOT_END;
+      }
+      issue_end();
+      // dP of block n; dS of block n-1; the first fragments of Q of block n-1
+      MLLM_SLOT_END;
+#pragma unroll
+      for (int x = 0; x < NS; x++) {
+        if (x + RD < NS) read_rows(U & 3, x + RD);
+        else read_cols((U + 7) & 7, x - (NS - RD));
+#pragma unroll
+        for (int j = 0; j < 2; j++) dp[U & 1][x % 2][j] = mfma(fr[x], kvf[j][x / 2], x < 2 ? de[x % 2] : dp[U & 1][x % 2][j]);
+        const El y = element(2 * x);
+        const f32x4& dc = dp[(U + 1) & 1][y.i][y.j];
+        pb[y.j].w[2 * y.i + (y.e >> 1)] = pack_bf16x2(pq[x >> 1][y.e] * dc[y.e], pq[x >> 1][y.e + 1] * dc[y.e + 1]);
+        MLLM_SLOT_END;
+      }
+    };
+    for (int n = 0;;) {
+      phase(Int<0>{}); if (++n == n_it + 2) break;
+      phase(Int<1>{}); if (++n == n_it + 2) break;
+      phase(Int<2>{}); if (++n == n_it + 2) break;
+      phase(Int<3>{}); if (++n == n_it + 2) break;
+      phase(Int<4>{}); if (++n == n_it + 2) break;
+      phase(Int<5>{}); if (++n == n_it + 2) break;
+      phase(Int<6>{}); if (++n == n_it + 2) break;
+      phase(Int<7>{}); if (++n == n_it + 2) break;
+    }
+  }
+  // the loads enqueued last (blocks past the end: zeros) must have landed before this workgroup's LDS
+  // can be handed to another one
+  wait_loads<0>();
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    if (krow[j] >= t.seg_len) continue;
+    const int64_t row = t.seg_start + krow[j];
+    if (second) store_dk<HD>(p, acc, j, krow[j], row, kvh, L.g, gridDim.y > 1, blockIdx.y);
+    else store_dv<HD>(p, acc, j, row, kvh, L.g, gridDim.y > 1, blockIdx.y);
+  }
 }
 
 // dK and dV from the parts' sums, added in their order; dK scaled and rotated back.  A thread takes eight
@@ -1312,7 +1309,7 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_dq_kernel<128>, qgrid, block, 0, s, p);
     p.list = (const AttnItem*)a.kv_list;
-    hipLaunchKernelGGL(attn_bwd_dkv_pipe_kernel<128>, kgrid, block, 0, s, p);
+    hipLaunchKernelGGL(attn_bwd_dkv_duo_kernel, kgrid, dim3(512), 0, s, p);
   } else if (a.head_dim == 64 && a.q_grid + (int64_t)kgrid.x * kgrid.y <= BOTH_MOST && (a.n_q_heads <= BOTH_GROUP * a.n_kv_heads || a.total_tokens <= BOTH_FEW_TOKENS) &&
              !gradients_over_inputs(a)) {
     p.list = (const AttnItem*)a.q_list;
@@ -1322,7 +1319,7 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     p.list = (const AttnItem*)a.q_list;
     hipLaunchKernelGGL(attn_bwd_dq_kernel<64>, qgrid, block, 0, s, p);
     p.list = (const AttnItem*)a.kv_list;
-    hipLaunchKernelGGL(attn_bwd_dkv_kernel<64>, kgrid, block, 0, s, p);
+    hipLaunchKernelGGL(attn_bwd_dkv_kernel, kgrid, block, 0, s, p);
   } else {
     return hipErrorInvalidValue;
   }
