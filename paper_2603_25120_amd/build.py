@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmllm_stage.so")
 BUILD = os.path.join(ROOT, "_build")
 
-SOURCES = ["gemm.hip", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip", "attention.hip", "elementwise.hip", "stage.hip", "ops_abi.hip", "profile.hip", "scheduler.hip", "planner.hip"]
+SOURCES = ["gemm.hip", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip", "gemm_small.hip", "attention.hip", "elementwise.hip", "stage.hip", "ops_abi.hip", "profile.hip", "scheduler.hip", "planner.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=fast",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]

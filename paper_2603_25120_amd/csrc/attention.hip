@@ -139,41 +139,11 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __bu
 // Keeps what a slot (a few MFMAs and what is to be issued beside them) holds apart from the next one's.
 #define MLLM_SLOT_END __builtin_amdgcn_sched_barrier(0)
 
-// ---- loads from memory straight into LDS -----------------------------------------------------------
-// Written as assembly so that the compiler does not know them for what they are.  Told (through the builtin), it makes LDS
-// reads wait for every such load in flight into the same LDS variable, which turns a queue of several tiles on their way
-// into one tile at a time; it cannot see that the loads go to a stage nobody reads.  The kernels wait for their loads by
-// count and separate writers from readers with barriers, as they have to anyway.
-// The 64 lanes' 16 (or 4) bytes land side by side from LDS address `lds_addr` (wavefront-uniform).
-// The statements set M0 themselves; M0 is a reserved register that the compiler holds no value in and
-// sets anew in front of each of its own uses, so overwriting it here disturbs nothing.
-// `row_off` (wavefront-uniform) is added to the lanes' offsets, and the range check covers the sum.
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ i32x4_t raw_rsrc(const void* base, uint32_t bytes) {   // untyped buffer over [base, base + bytes)
-  const uint64_t b = (uint64_t)base;
-  i32x4_t r;
-  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu));
-  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
-  r[3] = 0x00020000;
-  return r;
-}
+// ---- loads from memory straight into LDS (common.h) --------------------------------------------------
 // Descriptor over rows [0, rows) of a row-major bf16 matrix slice of `width` columns.
 __device__ __forceinline__ i32x4_t rows_rsrc(const bf16_t* base, int64_t stride, int rows, int width) {
   return raw_rsrc(base, rows > 0 ? (uint32_t)(((int64_t)(rows - 1) * stride + width) * 2) : 0u);
 }
-__device__ __forceinline__ void load_to_lds_b128(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
-}
-__device__ __forceinline__ void load_to_lds_b32(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
-}
-__device__ __forceinline__ uint32_t lds_address(MLLM_LDS const void* p) { return (uint32_t)(size_t)p; }
-// At most N of the loads above still in flight (the compiler does not count them, so neither can its builtin).
-template <int N>
-__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 // The workgroup's barrier, in its place; LDS writes issued before it are visible behind it.
 __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);

@@ -79,6 +79,37 @@ __device__ __forceinline__ float gelu_grad_f(int act, float z) {
          z * __builtin_amdgcn_exp2f(-0.7213475204444817f * z * z) * 0.3989422804014327f;
 }
 
+// Loads from memory straight into LDS, written as assembly so that the compiler does not know them for what they are.  Told (through the builtin), it makes LDS
+// reads wait for every such load in flight into the same LDS variable, which turns a queue of several tiles on their way
+// into one tile at a time; it cannot see that the loads go to a stage nobody reads.  The kernels wait for their loads by
+// count and separate writers from readers with barriers, as they have to anyway.
+// The 64 lanes' 16 (or 4) bytes land side by side from LDS address `lds_addr` (wavefront-uniform).
+// The statements set M0 themselves; M0 is a reserved register that the compiler holds no value in and
+// sets anew in front of each of its own uses, so overwriting it here disturbs nothing.
+// `row_off` (wavefront-uniform) is added to the lanes' offsets, and the range check covers the sum.
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ i32x4_t raw_rsrc(const void* base, uint32_t bytes) {   // untyped buffer over [base, base + bytes)
+  const uint64_t b = (uint64_t)base;
+  i32x4_t r;
+  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu));
+  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00020000;
+  return r;
+}
+__device__ __forceinline__ void load_to_lds_b128(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
+}
+__device__ __forceinline__ void load_to_lds_b32(i32x4_t rsrc, uint32_t lds_addr, uint32_t byte_off, uint32_t row_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(byte_off), "s"(rsrc), "s"(row_off) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(MLLM_LDS const void* p) { return (uint32_t)(size_t)p; }
+// At most N of the loads above still in flight (the compiler does not count them, so neither can its builtin).
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

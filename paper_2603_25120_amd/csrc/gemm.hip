@@ -4,9 +4,10 @@
 // (Model Profiler, "Throughput Profiling"): QKV / output / MLP projections and the connector,
 // their input gradients (dX = dY.W^T) and their weight gradients (dW = X^T.dY).
 //
-// Three kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
+// Four kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
 // hand-placed k-loop, for every K that is a multiple of 64 and for any K of a weight gradient; gemm_wide_kernel
-// (gemm_wide.h): the same tiles on eight wavefronts; plan_gemm below chooses the tile and whether the K loop is split.
+// (gemm_wide.h): the same tiles on eight wavefronts; gemm_small_kernel (gemm_small.h): quarters of the small tiles, the K loop dealt
+// to eight wavefronts, for products of few tiles; plan_gemm below chooses the tile and whether the K loop is split.
 // gemm_kernel (here): a general template for what is left, K no multiple of 64 with an operand whose contiguous dimension is k.  It wants, per lane, eight
 // consecutive values along the contraction index for v_mfma_f32_32x32x16_bf16: operands whose
 // contraction index is contiguous in memory are staged in LDS as [row][k] and fetched with one 16-byte read;
@@ -234,8 +235,7 @@ bool takes_tile_kernel(const GemmArgs& g) {
   return rows * g.lda * 2 <= 0xFFFFFFFFll && rows * g.ldb * 2 <= 0xFFFFFFFFll;
 }
 GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
-  const int bm = tile == GemmTile::T256 ? 256 : tile == GemmTile::T192 ? 192 : 128, bn = tile == GemmTile::T128 ? 128 : 256;
-  GemmParams p = make_gemm_params(g, bm, bn);
+  GemmParams p = make_gemm_params(g, tile_rows(tile), tile_cols(tile));
   if (splits > 1) {   // the plan has made sure that no split is empty
     p.kt_per_split = (p.kt_per_split + splits - 1) / splits;
     p.c_split_stride = g.m * g.n;
@@ -247,11 +247,20 @@ GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
 bool fits_wide_form(const GemmArgs& g) {
   return (((uintptr_t)g.a | (uintptr_t)g.b) & 15) == 0 && !(g.a_layout != 0 && g.b_layout != 0) && !(g.rope_table && g.rope_head_dim == 128);
 }
+// Quarters of 128x128 tiles, each with eight wavefronts that share out the K loop (gemm_small.h): in place of uncut 128x128 tiles as
+// long as every quarter has a CU to itself.  152 products of the layers' widths (64 to 1728 tokens, weights from memory): up to 64
+// quarters 1.27x (least 1.14), 65 to 256 1.06 to 1.77x, 257 to 320 0.83x, up to 640 0.82 to 0.56x.
+int64_t quarters(int64_t m, int64_t n) { return ((m + 63) / 64) * ((n + 63) / 64); }
+bool takes_small_form(const GemmArgs& g) {
+  return fits_wide_form(g) && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && quarters(g.m, g.n) <= GEMM_CUS;
+}
 hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, bool wide, hipStream_t s) {
+  if (tile == GemmTile::T128 && splits == 1 && takes_small_form(g)) tile = GemmTile::T64;
   const GemmParams p = tile_params(g, tile, splits);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
   const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
   const bool at = g.a_layout != 0, bt = g.b_layout == 0, f32 = g.out_fp32 != 0;   // b_layout 0: stored [K, N], transposing reads
+  if (tile == GemmTile::T64) return launch_gemm_small(p, at, bt, f32, grid, s);
   if (wide && fits_wide_form(g)) {
     if (at) return launch_gemm_wide<true, true>(p, tile, f32, epi, grid, s);
     return bt ? launch_gemm_wide<false, true>(p, tile, f32, epi, grid, s) : launch_gemm_wide<false, false>(p, tile, f32, epi, grid, s);
@@ -520,7 +529,7 @@ GemmPlan plan_of(const GemmArgs& g) {
 GemmForm gemm_form(const GemmArgs& g) {
   if (!takes_tile_kernel(g)) return {0, 0, 1};
   const GemmPlan pl = plan_of(g);
-  return {pl.tile == GemmTile::T256 ? 256 : pl.tile == GemmTile::T192 ? 192 : 128, pl.tile == GemmTile::T128 ? 128 : 256, pl.splits};
+  return {tile_rows(pl.tile), tile_cols(pl.tile), pl.splits};
 }
 
 namespace {
@@ -597,7 +606,7 @@ LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
   if (!pairable(x, w)) return {false, gemm_form(x), gemm_form(w), false};
   const PairPlan pl = plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0);
   if (!pl.pays) return {false, gemm_form(x), gemm_form(w), false};
-  auto form = [](const GemmPlan& p) { return GemmForm{p.tile == GemmTile::T256 ? 256 : p.tile == GemmTile::T192 ? 192 : 128, p.tile == GemmTile::T128 ? 128 : 256, p.splits}; };
+  auto form = [](const GemmPlan& p) { return GemmForm{tile_rows(p.tile), tile_cols(p.tile), p.splits}; };
   return {true, form(pl.x), form(pl.w), pl.x_first};
 }
 
@@ -625,14 +634,24 @@ static bool gradients_over_operands(const GemmArgs& x, const GemmArgs& w) {
          ranges_overlap(dx, dx_bytes, w.c, dw_bytes);
 }
 
+// Both gradients in quarters of 128x128 tiles (takes_small_form), in place of a plan with both in 128x128 tiles and dW uncut.  64 to 1728
+// tokens, 11 maps of 192 to 3584 columns, up to 256 quarters: 1.12 to 1.55x; with dX in parts 0.92 and 0.98x at 64 and 128 tokens,
+// 1.06 to 1.48x from 200 on; 257 to 350 quarters 1.0 to 1.3x, but 0.81x for 400 (576 x 1024 x 1024).
+static bool takes_small_pair(const GemmArgs& x, const GemmArgs& w, const PairPlan& pl) {
+  return pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128 && pl.w.splits == 1 && (pl.x.splits == 1 || x.m > 128) && !x.swiglu_dpre &&
+         quarters(x.m, x.n) + quarters(w.m, w.n) <= GEMM_CUS;
+}
+
 hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s) {
   const bool pair = pairable(x, w) && !gradients_over_operands(x, w);
-  const PairPlan pl = pair ? plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0) : PairPlan{};
+  PairPlan pl = pair ? plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0) : PairPlan{};
   if (!pair || !pl.pays) {
     const hipError_t e = launch_gemm(w, s);
     return e != hipSuccess ? e : launch_gemm(x, s);
   }
   if (refused(x) || refused(w)) return hipErrorInvalidValue;
+  const bool in_quarters = takes_small_pair(x, w, pl);
+  if (in_quarters) pl = {{GemmTile::T64, 1, false}, {GemmTile::T64, 1, false}, pl.x_first, true};
   GemmArgs xa = x, wa = w;   // the parts of both are in the scratch at the same time
   wa.splitk_ws = (char*)x.splitk_ws + part_bytes(pl.x, x.m, x.n);
   const GemmArgs xp = pl.x.splits > 1 ? part_of(xa) : xa, wp = pl.w.splits > 1 ? part_of(wa) : wa;
@@ -646,9 +665,10 @@ hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s
   p.first = pl.x_first ? x_wgs : w_wgs;
   hipError_t e;
   {
-    const bool small = pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128;
+    const bool small = in_quarters || (pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128);
     ProfScope prof(small ? PROF_GEMM_SMALL : PROF_GEMM_DX, 4.0 * (double)x.m * (double)x.n * (double)x.k, s);
-    e = launch_gemm_pair_tiles(p, pl.x.tile, xp.out_fp32 != 0, x.swiglu_dpre ? EPI_SWIGLU_BWD : EPI_PLAIN, pl.w.tile, x_wgs + w_wgs, s);
+    e = in_quarters ? launch_gemm_pair_small(p, x_wgs + w_wgs, s)
+                    : launch_gemm_pair_tiles(p, pl.x.tile, xp.out_fp32 != 0, x.swiglu_dpre ? EPI_SWIGLU_BWD : EPI_PLAIN, pl.w.tile, x_wgs + w_wgs, s);
   }
   if (e == hipSuccess && pl.x.splits > 1) e = reduce_parts(xa, pl.x.splits, s);
   if (e == hipSuccess && pl.w.splits > 1) e = reduce_parts(wa, pl.w.splits, s);

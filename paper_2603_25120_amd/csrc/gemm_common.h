@@ -67,12 +67,16 @@ inline GemmParams make_gemm_params(const GemmArgs& g, int bm, int bn) {
 }
 
 // Output tiles of the MFMA kernel (gemm_tile.h) and its epilogues.
-enum class GemmTile { T256, T192, T128 };   // 256 x 256, 192 x 256 (A stored [M, K]), 128 x 128
+enum class GemmTile { T256, T192, T128, T64 };   // 256 x 256, 192 x 256 (A stored [M, K]), 128 x 128, 64 x 64 (gemm_small.h)
+inline int tile_rows(GemmTile t) { return t == GemmTile::T256 ? 256 : t == GemmTile::T192 ? 192 : t == GemmTile::T128 ? 128 : 64; }
+inline int tile_cols(GemmTile t) { return t == GemmTile::T128 ? 128 : t == GemmTile::T64 ? 64 : 256; }
 enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_ROPE64 = 4 };
 template <bool A_T, bool B_T>
 hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
 template <bool A_T, bool B_T>   // the same on eight wavefronts (gemm_wide.h)
 hipError_t launch_gemm_wide(const GemmParams& p, GemmTile tile, bool out_f32, int epi, dim3 grid, hipStream_t s);
+
+hipError_t launch_gemm_small(const GemmParams& p, bool a_t, bool b_t, bool out_f32, dim3 grid, hipStream_t s);   // 64 x 64 tiles (gemm_small.hip)
 
 // A linear map's input gradient (x) and weight gradient (w) in one launch (gemm_pair.hip).
 struct GemmPairParams {
@@ -82,6 +86,7 @@ struct GemmPairParams {
   int x_first;
 };
 hipError_t launch_gemm_pair_tiles(const GemmPairParams& p, GemmTile x_tile, bool x_f32, int x_epi, GemmTile w_tile, int workgroups, hipStream_t s);
+hipError_t launch_gemm_pair_small(const GemmPairParams& p, int workgroups, hipStream_t s);   // both in 64 x 64 tiles (gemm_small.hip)
 
 // Workgroups are dealt round-robin to the 8 XCDs.  Renumber so that each XCD gets a contiguous
 // range of tile ids, then walk the tile grid in panels of group_m tile-rows.
