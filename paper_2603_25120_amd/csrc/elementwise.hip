@@ -422,9 +422,8 @@ __global__ void rope_kernel(bf16_t* __restrict__ qk, const int32_t* __restrict__
 // Table of the rotary angles for the kernels that rotate in their own epilogue: row `pos` holds
 // cos(pos * base^(-2i/hd)) for i < hd/2, then the sines (fp32; angles and sincos in fp64, as in
 // rope_kernel, so both forms of the rotation use the same factors).
-__global__ void rope_table_kernel(float* __restrict__ table, int64_t n_pos, int hd, double log2_base) {
+__device__ __forceinline__ void rope_table_entry(float* __restrict__ table, int64_t n_pos, int hd, double log2_base, int64_t gid) {
   const int half = hd >> 1;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= n_pos * half) return;
   const int64_t pos = gid / half;
   const int i = (int)(gid % half);
@@ -433,6 +432,33 @@ __global__ void rope_table_kernel(float* __restrict__ table, int64_t n_pos, int 
   sincos((double)pos * inv, &sn, &cs);
   table[pos * hd + i] = (float)cs;
   table[pos * hd + half + i] = (float)sn;
+}
+__global__ void rope_table_kernel(float* __restrict__ table, int64_t n_pos, int hd, double log2_base) {
+  rope_table_entry(table, n_pos, hd, log2_base, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+// The beginning of a stage's pass (launch_begin): workgroups of the metadata, then of each table, then of the copied rows.  A
+// launch of its own for each cost 4 us of a small stage's pass, of which 1.5 to 2.5 are the kernel: launches are what bounds it.
+struct BeginArgs {
+  const uint4* meta_src; uint4* meta; int64_t meta_vec;
+  struct { float* table; double log2_base; int hd; int first; } table[BEGIN_TABLES];   // first workgroup of each
+  int64_t n_pos;
+  const uint4* copy_src; uint4* copy_dst; int64_t copy_vec;
+  int n_tables, copy_first;
+};
+__global__ __launch_bounds__(256) void begin_kernel(BeginArgs a) {
+  const int b = blockIdx.x;
+  if (b >= a.copy_first) {
+    const int64_t i = (int64_t)(b - a.copy_first) * 256 + threadIdx.x;
+    if (i < a.copy_vec) a.copy_dst[i] = a.copy_src[i];
+    return;
+  }
+  for (int t = a.n_tables - 1; t >= 0; t--)
+    if (b >= a.table[t].first) {
+      rope_table_entry(a.table[t].table, a.n_pos, a.table[t].hd, a.table[t].log2_base, (int64_t)(b - a.table[t].first) * 256 + threadIdx.x);
+      return;
+    }
+  const int64_t i = (int64_t)b * 256 + threadIdx.x;
+  if (i < a.meta_vec) a.meta[i] = a.meta_src[i];
 }
 
 // The same rotation from the table (forward only): a thread takes eight pairs of one head of one token, so that a
@@ -658,12 +684,24 @@ __global__ void unpool_rows_kernel(const bf16_t* __restrict__ src, bf16_t* __res
   for (int e = 0; e < 8; e++) v[e] *= inv;
   reinterpret_cast<uint4*>(dst)[r * vec_per_row + c] = pack8(v);
 }
-__global__ void zero_rows_kernel(bf16_t* __restrict__ dst, const int32_t* __restrict__ rows,
-                                 int64_t n_rows, int64_t vec_per_row) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_rows * vec_per_row) return;
-  const int64_t r = rows[i / vec_per_row], c = i % vec_per_row;
-  reinterpret_cast<uint4*>(dst)[r * vec_per_row + c] = make_uint4(0, 0, 0, 0);
+// Gradient of the connector's scatter (launch_connector_grad).  The workgroups of the scattered rows take a row's gradient and
+// leave zeros in its place, both in one thread, so that dx_seq may be dy; the others copy the rows in between.
+__global__ __launch_bounds__(256) void connector_grad_kernel(const uint4* dy, uint4* __restrict__ dproj, uint4* dx_seq, const int32_t* __restrict__ rows,
+                                                             const uint32_t* __restrict__ scattered, int64_t n_rows, int64_t n_seq, int64_t vec_per_row,
+                                                             int copy_first) {
+  const int b = blockIdx.x;
+  if (b < copy_first) {
+    const int64_t i = (int64_t)b * 256 + threadIdx.x;
+    if (i >= n_rows * vec_per_row) return;
+    const int64_t at = (int64_t)rows[i / vec_per_row] * vec_per_row + i % vec_per_row;
+    dproj[i] = dy[at];
+    dx_seq[at] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  const int64_t i = (int64_t)(b - copy_first) * 256 + threadIdx.x;
+  if (i >= n_seq * vec_per_row) return;
+  const int64_t r = i / vec_per_row;
+  if (!((scattered[r >> 5] >> (r & 31)) & 1)) dx_seq[i] = dy[i];
 }
 // Sum of the partial products of a split K loop, in their order, four of their loads in flight at a time; then
 // the epilogue terms of the product.  A thread takes eight consecutive columns of a row.
@@ -1002,6 +1040,37 @@ hipError_t launch_rope_table(float* table, int64_t n_pos, int32_t head_dim, floa
   return hipGetLastError();
 }
 
+hipError_t launch_begin(const void* meta_src, void* meta, size_t meta_bytes, const RopeTableSpec* tables, int n_tables, int64_t n_pos,
+                        const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t s) {
+  if (meta_bytes % 16 != 0 || copy_bytes % 16 != 0) return hipErrorInvalidValue;
+  BeginArgs a;
+  a.meta_src = (const uint4*)meta_src; a.meta = (uint4*)meta; a.meta_vec = (int64_t)(meta_bytes / 16);
+  a.copy_src = (const uint4*)copy_src; a.copy_dst = (uint4*)copy_dst; a.copy_vec = (int64_t)(copy_bytes / 16);
+  a.n_pos = n_pos;
+  a.n_tables = std::min(n_tables, BEGIN_TABLES);
+  unsigned blocks = blocks_for(a.meta_vec, 256);
+  double bytes = 2.0 * (double)(meta_bytes + copy_bytes);
+  for (int t = 0; t < a.n_tables; t++) {
+    if (tables[t].head_dim % 16 != 0) return hipErrorInvalidValue;
+    a.table[t] = {tables[t].table, log2((double)tables[t].base), tables[t].head_dim, (int)blocks};
+    blocks += blocks_for(n_pos * (tables[t].head_dim / 2), 256);
+    bytes += 4.0 * (double)n_pos * (double)tables[t].head_dim;
+  }
+  a.copy_first = (int)blocks;
+  blocks += blocks_for(a.copy_vec, 256);
+  if (blocks > 0) {
+    ProfScope prof(PROF_ELEMENTWISE, bytes, s);
+    hipLaunchKernelGGL(begin_kernel, dim3(blocks), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  for (int t = a.n_tables; t < n_tables; t++) {
+    const hipError_t e = launch_rope_table(tables[t].table, n_pos, tables[t].head_dim, tables[t].base, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_act_fwd(int act, const void* pre, void* a, int64_t t, int64_t f, hipStream_t s) {
   if (t == 0) return hipSuccess;
   if (f % 8 != 0) return hipErrorInvalidValue;
@@ -1094,13 +1163,14 @@ hipError_t launch_unpool_rows(const void* src, void* dst, const int32_t* window,
   return hipGetLastError();
 }
 
-hipError_t launch_zero_rows(void* dst, const int32_t* rows, int64_t n_rows, int64_t d,
-                            hipStream_t s) {
-  if (n_rows == 0) return hipSuccess;
+hipError_t launch_connector_grad(const void* dy, void* dproj, void* dx_seq, const int32_t* rows, const uint32_t* scattered, int64_t n_rows,
+                                 int64_t n_seq, int64_t d, hipStream_t s) {
+  if (n_seq == 0) return hipSuccess;
   if (d % 8 != 0) return hipErrorInvalidValue;
-  const int64_t n = n_rows * (d / 8);
-  hipLaunchKernelGGL(zero_rows_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, (bf16_t*)dst,
-                     rows, n_rows, d / 8);
+  const unsigned first = blocks_for(n_rows * (d / 8), 256), rest = blocks_for(n_seq * (d / 8), 256);
+  ProfScope prof(PROF_ELEMENTWISE, 4.0 * (double)(n_rows + n_seq) * (double)d, s);
+  hipLaunchKernelGGL(connector_grad_kernel, dim3(first + rest), dim3(256), 0, s, (const uint4*)dy, (uint4*)dproj, (uint4*)dx_seq, rows, scattered, n_rows,
+                     n_seq, d / 8, (int)first);
   return hipGetLastError();
 }
 

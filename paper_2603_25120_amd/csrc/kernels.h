@@ -150,6 +150,12 @@ hipError_t launch_rope(void* qk, const int32_t* pos, int64_t t, int64_t row_stri
 hipError_t launch_rope_from_table(void* qk, const int32_t* pos, const float* table, int64_t t, int64_t row_stride,
                                   int32_t n_heads, int32_t head_dim, hipStream_t s);
 // table [n_pos, head_dim] fp32: cos then sin of pos * rope_base^(-2i/head_dim), i < head_dim / 2.
+// What a stage's pass begins with, in one launch: the call's metadata from pinned host memory (its device address), the tables
+// of the rotary angles, and a copy of rows that depends on nothing (all but the tables may be absent).
+struct RopeTableSpec { float* table; int32_t head_dim; float base; };
+constexpr int BEGIN_TABLES = 4;
+hipError_t launch_begin(const void* meta_src, void* meta, size_t meta_bytes, const RopeTableSpec* tables, int n_tables, int64_t n_pos,
+                        const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t s);
 hipError_t launch_rope_table(float* table, int64_t n_pos, int32_t head_dim, float rope_base, hipStream_t s);
 hipError_t launch_act_fwd(int act, const void* pre, void* a, int64_t t, int64_t f, hipStream_t s);
 hipError_t launch_act_bwd(int act, const void* da, const void* pre, void* dpre, int64_t t,
@@ -169,9 +175,10 @@ hipError_t launch_pool_rows(const void* src, void* dst, const int32_t* first, co
 // dst[i, :] = src[window[i], :] / count[window[i]]: the gradient of launch_pool_rows.
 hipError_t launch_unpool_rows(const void* src, void* dst, const int32_t* window, const int32_t* count,
                               int64_t n_rows, int64_t d, hipStream_t s);
-// Zero the rows named by rows[] of a bf16 [*, d] matrix.
-hipError_t launch_zero_rows(void* dst, const int32_t* rows, int64_t n_rows, int64_t d,
-                            hipStream_t s);
+// Gradient of the scattered connector rows: dproj[j] = dy[rows[j]], and dx_seq = dy with those rows zero.  scattered: a bit for
+// every row of dy.  dx_seq may be dy.
+hipError_t launch_connector_grad(const void* dy, void* dproj, void* dx_seq, const int32_t* rows, const uint32_t* scattered, int64_t n_rows,
+                                 int64_t n_seq, int64_t d, hipStream_t s);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
 
 // Optional per-launch timing with HIP events on the launch stream (off by default).  Classes:

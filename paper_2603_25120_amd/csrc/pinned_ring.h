@@ -11,6 +11,7 @@ struct PinnedRing {
   static constexpr int SLOTS = 4;
   struct Slot {
     void* p = nullptr;
+    void* device = nullptr;   // the same memory as kernels address it
     size_t bytes = 0;
     hipEvent_t done = nullptr;
     bool pending = false;
@@ -40,7 +41,7 @@ struct PinnedRing {
     return hipSuccess;
   }
 
-  // Call after the asynchronous copy out of the slot has been enqueued on `stream`.
+  // Call after the copy out of the slot (or the kernel that reads it) has been enqueued on `stream`.
   hipError_t commit(Slot* s, hipStream_t stream) {
     hipError_t e = hipEventRecord(s->done, stream);
     if (e == hipSuccess) s->pending = true;
@@ -68,10 +69,11 @@ struct PinnedRing {
     if (s.bytes >= bytes) return hipSuccess;
     if ((e = settle(s)) != hipSuccess) return e;
     if (s.p) (void)hipHostFree(s.p);
-    s.p = nullptr;
+    s.p = s.device = nullptr;
     s.bytes = 0;
     const size_t want = bytes + bytes / 2 + 4096;    // headroom: microbatches of one run differ a little
-    if ((e = hipHostMalloc(&s.p, want, hipHostMallocDefault)) != hipSuccess) return e;
+    if ((e = hipHostMalloc(&s.p, want, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess) return e;
+    if ((e = hipHostGetDevicePointer(&s.device, s.p, 0)) != hipSuccess) return e;
     s.bytes = want;
     return hipSuccess;
   }

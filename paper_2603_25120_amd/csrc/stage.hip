@@ -190,7 +190,7 @@ struct LayerSaved {  // byte offsets into `saved`
 struct AttnLists {
   bool img;
   int hq, hkv, head_dim;
-  // byte offsets into the metadata blob and grid sizes, known once the lists are built (upload_meta)
+  // byte offsets into the metadata blob and grid sizes, known once the lists are built (begin_pass)
   size_t q_off = 0, kv_off = 0;
   int q_grid = 0, kv_grid = 0;
   int kv_parts = 1;                 // parts of the dK/dV pass
@@ -198,6 +198,7 @@ struct AttnLists {
 
 struct Meta {  // byte offsets into the metadata blob at the head of the workspace
   size_t pos = 0, i2s = 0;
+  size_t scattered = 0;             // a bit for every row of the sequence: set where a connector row is scattered to
   size_t pool_first = 0, pool_count = 0, row_window = 0;   // pooling connector: window tables
   size_t lists = 0;                 // where the attention lists begin, one behind the other
   std::vector<AttnLists> attn;
@@ -328,7 +329,10 @@ Plan make_plan(const mllm_stage* st, const mllm_batch_t* b, bool scratch = false
   Meta& M = P.meta;
   size_t dkv = 0;
   if (st->n_dec > 0) M.pos = ws.take(sizeof(int32_t) * P.T_seq);
-  if (st->proj >= 0) M.i2s = ws.take(sizeof(int32_t) * P.T_con);
+  if (st->proj >= 0) {
+    M.i2s = ws.take(sizeof(int32_t) * P.T_con);
+    M.scattered = ws.take((size_t)(P.T_seq + 31) / 32 * 4);
+  }
   if (st->proj >= 0 && P.pool > 1) {
     M.pool_first = ws.take(sizeof(int32_t) * P.T_con);
     M.pool_count = ws.take(sizeof(int32_t) * P.T_con);
@@ -451,10 +455,16 @@ void fit_scratch(Plan& P, size_t workspace_bytes) {
 // two for heads of 64 and one for heads of 128.
 int kv_residents(int head_dim) { return head_dim == 64 ? 64 : 32; }
 
-mllm_status_t upload_meta(mllm_stage* st, const mllm_batch_t* b, Plan& P, void* workspace,
-                          hipStream_t s) {
+// Begins a pass: the metadata, the tables of the rotary angles and, if given, a copy of rows, in one launch.
+mllm_status_t begin_pass(mllm_stage* st, const mllm_batch_t* b, Plan& P, char* workspace, const void* copy_src, void* copy_dst, size_t copy_bytes,
+                         hipStream_t s) {
   Meta& M = P.meta;
-  if (M.bytes == 0) return MLLM_OK;
+  std::vector<RopeTableSpec> tables;
+  for (const Plan::RopeTable& t : P.rope_tables) tables.push_back({(float*)(workspace + t.off), t.head_dim, t.base});
+  if (M.bytes == 0) {
+    HIP_TRY(launch_begin(nullptr, nullptr, 0, tables.data(), (int)tables.size(), P.longest_seq, copy_src, copy_dst, copy_bytes, s));
+    return MLLM_OK;
+  }
   PinnedRing::Slot* slot = nullptr;
   HIP_TRY(st->staging.acquire(M.bytes, &slot));
   char* h = (char*)slot->p;
@@ -474,7 +484,11 @@ mllm_status_t upload_meta(mllm_stage* st, const mllm_batch_t* b, Plan& P, void* 
       for (int t = b->seq.cu_seqlens_host[sgm]; t < b->seq.cu_seqlens_host[sgm + 1]; t++)
         pos[t] = t - b->seq.cu_seqlens_host[sgm];
   }
-  if (st->proj >= 0 && P.T_con > 0) memcpy(h + M.i2s, b->img_to_seq_row_host, sizeof(int32_t) * P.T_con);
+  if (st->proj >= 0 && P.T_con > 0) {
+    memcpy(h + M.i2s, b->img_to_seq_row_host, sizeof(int32_t) * P.T_con);
+    uint32_t* scattered = (uint32_t*)(h + M.scattered);
+    for (int64_t i = 0; i < P.T_con; i++) scattered[b->img_to_seq_row_host[i] >> 5] |= 1u << (b->img_to_seq_row_host[i] & 31);
+  }
   if (st->proj >= 0 && P.pool > 1) {
     int32_t* first = (int32_t*)(h + M.pool_first);
     int32_t* count = (int32_t*)(h + M.pool_count);
@@ -489,9 +503,9 @@ mllm_status_t upload_meta(mllm_stage* st, const mllm_batch_t* b, Plan& P, void* 
       }
     }
   }
-  // Space is reserved for the lists' upper bounds; they are packed one behind the other, so that one copy
-  // moves everything (three to five took 2-4 us each on the stream, plus the gaps between them).
-  if (used > 0) HIP_TRY(hipMemcpyAsync(workspace, h, used, hipMemcpyHostToDevice, s));
+  // Space is reserved for the lists' upper bounds; they are packed one behind the other, so that one run of
+  // vectors moves everything.
+  HIP_TRY(launch_begin(slot->device, workspace, used, tables.data(), (int)tables.size(), P.longest_seq, copy_src, copy_dst, copy_bytes, s));
   HIP_TRY(st->staging.commit(slot, s));
   return MLLM_OK;
 }
@@ -874,11 +888,14 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
   hipStream_t s = (hipStream_t)hip_stream;
   char* saved = (char*)saved_v;
   char* ws = (char*)workspace;
-  if ((r = upload_meta(st, b, P, workspace, s)) != MLLM_OK) return r;
-  for (const Plan::RopeTable& t : P.rope_tables)
-    K_TRY(launch_rope_table((float*)(ws + t.off), P.longest_seq, t.head_dim, t.base, s));
-
   const int n = (int)st->layers.size();
+  // The text rows go to the sequence that the connector's rows are scattered into; into `saved`, nothing reads or writes there
+  // before the connector.
+  const bool seq_early = st->proj >= 0 && st->proj < n - 1;
+  if ((r = begin_pass(st, b, P, ws, seq_early ? x_seq : nullptr, seq_early ? saved + P.saved[st->proj + 1].x : nullptr,
+                      seq_early ? (size_t)P.T_seq * st->layers[st->proj].d_out * 2 : 0, s)) != MLLM_OK)
+    return r;
+
   for (int i = 0; i < n; i++) {
     const mllm_layer_desc_t& L = st->layers[i];
     const bool last = i == n - 1;
@@ -888,7 +905,7 @@ mllm_status_t mllm_stage_fwd(mllm_stage_t* st, const mllm_batch_t* b, const void
       // previous ViT layer already wrote its output into S.x
       if (i == 0) K_TRY(launch_copy(x_img, saved + P.saved[i].x, (size_t)P.T_img * L.d_model * 2, s));
       void* dst = last ? y : (void*)(saved + P.saved[i + 1].x);
-      K_TRY(launch_copy(x_seq, dst, (size_t)P.T_seq * L.d_out * 2, s));
+      if (!seq_early) K_TRY(launch_copy(x_seq, dst, (size_t)P.T_seq * L.d_out * 2, s));
       const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
       const char* xin = saved + P.saved[i].x;
       // token merging: the [T_img, d] rows read as [T_img / r, r d] rows (no data movement)
@@ -937,9 +954,7 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
   hipStream_t s = (hipStream_t)hip_stream;
   const char* saved = (const char*)saved_v;
   char* ws = (char*)workspace;
-  if ((r = upload_meta(st, b, P, workspace, s)) != MLLM_OK) return r;
-  for (const Plan::RopeTable& t : P.rope_tables)
-    K_TRY(launch_rope_table((float*)(ws + t.off), P.longest_seq, t.head_dim, t.base, s));
+  if ((r = begin_pass(st, b, P, ws, nullptr, nullptr, 0, s)) != MLLM_OK) return r;
 
   const int n = (int)st->layers.size();
   const void* cur = dy;  // gradient w.r.t. the output of layer i
@@ -954,11 +969,10 @@ mllm_status_t mllm_stage_bwd(mllm_stage_t* st, const mllm_batch_t* b, const void
     if (L.kind == MLLM_LAYER_PROJECTOR) {
       const int32_t* i2s = (const int32_t*)(ws + P.meta.i2s);
       char* dproj = ws + P.w_proj;
-      K_TRY(launch_scatter_rows(cur, dproj, i2s, P.T_con, L.d_out, 1, s));
-      if (dx_seq) {
-        K_TRY(launch_copy(cur, dx_seq, (size_t)P.T_seq * L.d_out * 2, s));
-        K_TRY(launch_zero_rows(dx_seq, i2s, P.T_con, L.d_out, s));
-      }
+      if (dx_seq)
+        K_TRY(launch_connector_grad(cur, dproj, dx_seq, i2s, (const uint32_t*)(ws + P.meta.scattered), P.T_con, P.T_seq, L.d_out, s));
+      else
+        K_TRY(launch_scatter_rows(cur, dproj, i2s, P.T_con, L.d_out, 1, s));
       const SplitWs split{ws + P.w_scratch, P.scratch_bytes};
       void* out = (i == 0 && dx_img) ? dx_img : (void*)pp[flip];
       const char* xin = P.pool > 1 ? saved + P.saved[i].n1 : saved + P.saved[i].x;
