@@ -67,8 +67,8 @@ inline GemmParams make_gemm_params(const GemmArgs& g, int bm, int bn) {
 }
 
 // Output tiles of the MFMA kernel (gemm_tile.h) and its epilogues.
-enum class GemmTile { T256, T192, T128, T64 };   // 256 x 256, 192 x 256 (A stored [M, K]), 128 x 128, 64 x 64 (gemm_small.h)
-inline int tile_rows(GemmTile t) { return t == GemmTile::T256 ? 256 : t == GemmTile::T192 ? 192 : t == GemmTile::T128 ? 128 : 64; }
+enum class GemmTile { T256, T224, T192, T128, T64 };   // 256 x 256, 224 and 192 x 256 (A stored [M, K]), 128 x 128, 64 x 64 (gemm_small.h)
+inline int tile_rows(GemmTile t) { return t == GemmTile::T256 ? 256 : t == GemmTile::T224 ? 224 : t == GemmTile::T192 ? 192 : t == GemmTile::T128 ? 128 : 64; }
 inline int tile_cols(GemmTile t) { return t == GemmTile::T128 ? 128 : t == GemmTile::T64 ? 64 : 256; }
 enum { EPI_PLAIN = 0, EPI_SWIGLU = 1, EPI_SWIGLU_BWD = 2, EPI_ROPE128 = 3, EPI_ROPE64 = 4 };
 template <bool A_T, bool B_T>

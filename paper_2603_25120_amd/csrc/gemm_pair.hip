@@ -55,13 +55,19 @@ hipError_t launch_gemm_pair_tiles(const GemmPairParams& p, GemmTile x_tile, bool
     if (w_tile == GemmTile::T256) MLLM_PAIR(XM, XN, F32, EPI, 8); \
     if (w_tile == GemmTile::T128) MLLM_PAIR(XM, XN, F32, EPI, 4); \
   } while (0)
-  if (x_epi == EPI_SWIGLU_BWD) { if (x_tile == GemmTile::T256) MLLM_PAIR_X(8, 8, false, EPI_SWIGLU_BWD); return hipErrorInvalidValue; }
+  if (x_epi == EPI_SWIGLU_BWD) {
+    if (x_tile == GemmTile::T256) MLLM_PAIR_X(8, 8, false, EPI_SWIGLU_BWD);
+    if (x_tile == GemmTile::T224) MLLM_PAIR_X(7, 8, false, EPI_SWIGLU_BWD);
+    return hipErrorInvalidValue;
+  }
   if (x_f32) {
     if (x_tile == GemmTile::T256) MLLM_PAIR_X(8, 8, true, EPI_PLAIN);
+    if (x_tile == GemmTile::T224) MLLM_PAIR_X(7, 8, true, EPI_PLAIN);
     if (x_tile == GemmTile::T192) MLLM_PAIR_X(6, 8, true, EPI_PLAIN);
     if (x_tile == GemmTile::T128) MLLM_PAIR_X(4, 4, true, EPI_PLAIN);
   } else {
     if (x_tile == GemmTile::T256) MLLM_PAIR_X(8, 8, false, EPI_PLAIN);
+    if (x_tile == GemmTile::T224) MLLM_PAIR_X(7, 8, false, EPI_PLAIN);
     if (x_tile == GemmTile::T192) MLLM_PAIR_X(6, 8, false, EPI_PLAIN);
     if (x_tile == GemmTile::T128) MLLM_PAIR_X(4, 4, false, EPI_PLAIN);
   }

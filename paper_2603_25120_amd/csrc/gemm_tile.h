@@ -394,13 +394,21 @@ hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, in
     else MLLM_TILE(WM, WN, false, EPI_PLAIN);  \
   } while (0)
   if constexpr (!A_T && B_T) {
-    if (epi == EPI_SWIGLU) { if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_SWIGLU); else return hipErrorInvalidValue; }
-    if (epi == EPI_ROPE128) { if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_ROPE128); else return hipErrorInvalidValue; }
-    if (epi == EPI_ROPE64) { if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_ROPE64); else return hipErrorInvalidValue; }
+#define MLLM_TILE_FUSED(E)                                                 \
+    if (epi == E) {                                                        \
+      if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, E);               \
+      if (tile == GemmTile::T224) MLLM_TILE(7, 8, false, E);               \
+      return hipErrorInvalidValue;                                         \
+    }
+    MLLM_TILE_FUSED(EPI_SWIGLU)
+    MLLM_TILE_FUSED(EPI_ROPE128)
+    MLLM_TILE_FUSED(EPI_ROPE64)
+#undef MLLM_TILE_FUSED
   }
   if constexpr (!A_T && !B_T) {
     if (epi == EPI_SWIGLU_BWD) {
       if (tile == GemmTile::T256) MLLM_TILE(8, 8, false, EPI_SWIGLU_BWD);
+      if (tile == GemmTile::T224) MLLM_TILE(7, 8, false, EPI_SWIGLU_BWD);
       if (tile == GemmTile::T128) MLLM_TILE(4, 4, false, EPI_SWIGLU_BWD);   // operands off 16-byte alignment
       return hipErrorInvalidValue;
     }
@@ -408,6 +416,7 @@ hipError_t launch_gemm_tile(const GemmParams& p, GemmTile tile, bool out_f32, in
   if (epi != EPI_PLAIN) return hipErrorInvalidValue;
   if constexpr (!A_T) {
     if (tile == GemmTile::T192) MLLM_TILE_TYPES(6, 8);
+    if (tile == GemmTile::T224) MLLM_TILE_TYPES(7, 8);
   }
   if (tile == GemmTile::T256) MLLM_TILE_TYPES(8, 8);
   if (tile == GemmTile::T128) MLLM_TILE_TYPES(4, 4);
