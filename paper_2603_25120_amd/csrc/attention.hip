@@ -29,16 +29,19 @@ namespace {
 constexpr int BKV = 64;   // key rows staged per step (forward, dQ)
 constexpr int BQ = 64;    // query rows staged per step (dK/dV, heads of 64)
 
-// LDS tiles are [rows][HD] bf16 without padding; 16-byte chunk c of row r lives at chunk position c ^ swz<HD>(r).  LDS serves
-// 256 B per clock.  A transposing 8-byte read is processed 32 lanes at a time (here 8 consecutive rows x 32 B), a 16-byte read
-// 16 lanes at a time, lanes 0-3, 12-15, 20-23 and 24-27 of each 32, then the other 16 (here rows 0-3 and 12-15 at an even chunk
-// and rows 4-11 at the next one, or the other way round).  The permutations make both patterns conflict-free on the same
-// tile: HD = 128 (256-byte rows) gives rows 0-7 the 8 pairs of chunks and rows 8-15 the other halves of the pairs, those of
-// 12-15 beside 0-3; HD = 64 (128-byte rows, two rows per 256-byte window) does the same over row pairs.
-template <int HD>
+// LDS tiles are [rows][HD] bf16 without padding; 16-byte chunk c of row r lives at chunk position c ^ swz<HD, BLOCK>(r), BLOCK the
+// rows of an MFMA operand.  LDS serves 256 B per clock.  A transposing 8-byte read is processed 32 lanes at a time (8 consecutive
+// rows x 32 B with operands of 16 rows, 4 x 64 B with 32), a 16-byte read 16 lanes at a time, lanes 0-3, 12-15, 20-23 and 24-27 of
+// each 32, then the other 16 (operands of 16 rows: rows 0-3 and 12-15 at an even chunk and rows 4-11 at the next one, or the other
+// way round; of 32: 16 rows at one chunk).  The permutations make both patterns conflict-free on the same tile: HD = 128 (256-byte
+// rows), operands of 16 rows: rows 0-7 take the 8 pairs of chunks and rows 8-15 the other halves of the pairs, those of 12-15
+// beside 0-3; of 32: 16 rows take 16 chunks, the 4 rows of a transposing read the 4 quarters of the row.  HD = 64 (128-byte rows,
+// two rows per 256-byte window) does the same over row pairs.
+template <int HD, int BLOCK = 16>
 __device__ __forceinline__ int swz(int r) {
-  if constexpr (HD == 128) return (((r & 7) ^ ((r >> 1) & 4)) << 1) | ((r >> 3) & 1);
-  else { const int t = (r >> 1) & 7; return (((t & 3) ^ ((t >> 1) & 2)) << 1) | (t >> 2); }
+  const int t = (r >> 1) & 7;
+  if constexpr (BLOCK == 32) return HD == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : ((t & 1) << 2) | (t >> 1);
+  else return HD == 128 ? (((r & 7) ^ ((r >> 1) & 4)) << 1) | ((r >> 3) & 1) : (((t & 3) ^ ((t >> 1) & 2)) << 1) | (t >> 2);
 }
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 constexpr float LOG2E = 1.4426950408889634f;
@@ -82,15 +85,15 @@ __device__ __forceinline__ bool work_item(const AttnItem* list, AttnItem& t, int
 }
 
 // ---- operands -----------------------------------------------------------------------------------
-// All products are v_mfma_f32_16x16x32_bf16.  A wavefront owns 32 rows (queries, or keys in the dK/dV pass) as the columns of
-// the results, in two groups j of 16: lane l holds column l%16 of group j, and with g = l/16 the rows 4g .. 4g+3 of each
+// All products but those of the forward pass at head_dim 64 are v_mfma_f32_16x16x32_bf16.  A wavefront owns 32 rows (queries, or
+// keys in the dK/dV pass) as the columns of the results, in two groups j of 16: lane l holds column l%16 of group j, and with g = l/16 the rows 4g .. 4g+3 of each
 // 16-row group i of the other side's block of 32.  The 32x32x16 form does the same work in half the MFMAs and reads and
 // writes its accumulator twice as often per multiply-add, and that is power, which bounds these kernels at head_dim 128: 13255
 // causal tokens, 32/8 heads of 128, MFMA busy 61 % of the cycles in the forward pass and 72 % in dQ at 1.76 and 1.66 GHz with
 // it, 62 % and 69 % at 1.88 and 1.87 GHz with this form (of 2.4): 1245 -> 1121 and 1672 -> 1544 us on one card.  The order in
 // which a wavefront issues its reads and vector work no longer shows there (reads one to four fragments ahead, vector work
-// between the MFMAs or behind them: within 1 %, behind them where not).  At head_dim 64 the vector ALU bounds them, at 2.2 GHz
-// (46 x 576 tokens, 16 heads: forward 109 -> 97 us, dK/dV 211 -> 187).
+// between the MFMAs or behind them: within 1 %, behind them where not).  At head_dim 64 the vector ALU and latency bound them, at 2.2 GHz
+// (46 x 576 tokens, 16 heads: dK/dV 211 -> 187).
 struct Lane {
   int lane, g, c16;
   __device__ __forceinline__ explicit Lane(int tid) : lane(tid & 63), g((tid & 63) >> 4), c16(tid & 15) {}
@@ -153,10 +156,10 @@ __device__ __forceinline__ void phase_barrier() {
 template <int V> using Int = std::integral_constant<int, V>;
 // One such instruction moves 64 lanes x 16 bytes = RPI rows of a tile; lane l's chunk lands at position l of that 1 KiB, so the
 // lane fetches the global chunk that the permutation puts there.  Byte offset of the lane's chunk, instruction `ins` of the tile.
-template <int HD>
+template <int HD, int BLOCK = 16>
 __device__ __forceinline__ uint32_t load_offset(const Lane& L, int ins, int64_t stride) {
   constexpr int CPR = HD / 8, RPI = 64 / CPR;
-  const int r = ins * RPI + L.lane / CPR, c = (L.lane % CPR) ^ swz<HD>(r);
+  const int r = ins * RPI + L.lane / CPR, c = (L.lane % CPR) ^ swz<HD, BLOCK>(r);
   return (uint32_t)((r * stride + 8 * c) * 2);
 }
 
@@ -217,7 +220,7 @@ __device__ __forceinline__ void store_dv(const AttnParams& p, const f32x4 (&acc)
   if (split) return store_kv_partial<HD>(p, acc, j, 1, 1.f, gkrow, kvh, g, part);
   store_row<HD>(p.dv + gkrow * p.kv_stride + kvh * HD + 4 * g, acc, j, 1.f);
 }
-// Sum over the four lanes that hold parts of one own row.
+// Sum and maximum over the four lanes that hold parts of one own row.
 __device__ __forceinline__ float own_row_sum(float v) {
   v += __shfl_xor(v, 16, 64);
   return v + __shfl_xor(v, 32, 64);
@@ -228,11 +231,10 @@ __device__ __forceinline__ float own_row_max(float v) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// forward: one workgroup per (query tile of 128, head), looping over key tiles of 64: two blocks b of 32 keys.
+// forward, head_dim 128: one workgroup per (query tile of 128, head), looping over key tiles of 64: two blocks b of 32 keys.
 // ---------------------------------------------------------------------------------------------
-template <int HD>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
-  constexpr int NC = HD / 32, NN = HD / 16, NS = 2 * NC, TILE_B = BKV * HD * 2, BLOCK_B = 32 * HD * 2, GROUP_B = 16 * HD * 2;
+  constexpr int HD = 128, NC = HD / 32, NN = HD / 16, NS = 2 * NC, TILE_B = BKV * HD * 2, BLOCK_B = 32 * HD * 2, GROUP_B = 16 * HD * 2;
   // two stages of a K tile and a V tile
   __shared__ __attribute__((aligned(1024))) char lds[4 * TILE_B];
   AttnItem t;
@@ -432,6 +434,214 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
     store_row<HD>(p.o + row * p.o_stride + head * HD + 4 * L.g, acc, j, 1.f / sum);
     if (L.g == 0) p.lse[(int64_t)head * p.T + row] = (m[j] + log2f(sum)) * LN2;
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// forward, head_dim 64: the same walk with v_mfma_f32_32x32x16_bf16: lane l owns query l%32, and with h = l/32 the keys
+// 8i + 4h .. +3 of a block.  Here the vector ALU is the bound and the clock 2.2 GHz, so the 16x16x32 form gives little (46 x 576 tokens, 16
+// heads: 109 us at first, 95 with the maximum off the path and without the wavefronts that have no row, 92 with that form as well),
+// and it adds up in another order: through the roundings of a stage of 24 encoder and 8 decoder layers that moves the gradients by
+// 0.044 of their norm, as much as they are from exact ones, where this order leaves the encoder's outputs to the bit (0.020 with the
+// other kernels' orders alone).
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256, 2) void attn_fwd_64_kernel(AttnParams p) {
+  constexpr int HD = 64, NC = HD / 16, ND = HD / 32, NB = BKV / 32, TILE_B = BKV * HD * 2, BLOCK_B = 32 * HD * 2, HALF_B = 16 * HD * 2;
+  // two stages of a K tile and a V tile
+  __shared__ __attribute__((aligned(1024))) char lds[4 * TILE_B];
+  AttnItem t;
+  if (!work_item(p.list, t, blockIdx.x)) return;
+  const int head = t.head, kvh = head / (p.Hq / p.Hkv);
+  const Lane L(threadIdx.x);
+  const int h = L.lane >> 5, c32 = L.lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_first_q = t.tile0 + 32 * wave, wave_last_q = wave_first_q + 31;
+  const int qrow = wave_first_q + c32;
+  const bool qok = qrow < t.seg_len;
+  const bf16_t* qp = p.q + (int64_t)(t.seg_start + qrow) * p.q_stride + head * HD + 8 * h;
+  bf16x8 qf[NC];
+#pragma unroll
+  for (int c = 0; c < NC; c++) qf[c] = global_frag(qp + 16 * c, qok);
+  const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
+
+  f32x16 oacc[ND];
+#pragma unroll
+  for (int d = 0; d < ND; d++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) oacc[d][v] = 0.f;
+  const float c2 = p.scale_log2e;
+  // Reference maximum m (in units of log2: score * scale * log2(e)) and sum l of exp2(... - m).  The reference is the row's maximum
+  // over the first tile and moves when a later tile exceeds it by more than 8: probabilities reach 2^8 at most, at the same relative
+  // precision in fp32 sums and in the bf16 operand.  A tile that exceeds it shows in its sum: only one above 2^8 (or past the
+  // range of fp32) has its scores formed again, its maximum taken and the accumulator rescaled (`again`); so neither the
+  // maximum of a tile's scores nor its exchange between the halves is on the path.
+  constexpr float LIMIT = 256.f;
+  float m = -INFINITY, mu = 0.f, l = 0.f, limit = -1.f;   // mu: m, or 0 where there is none yet; limit -1: no reference yet
+
+  // Rows past kv_end are outside the descriptors: zeros, no traffic.
+  const i32x4_t rk = rows_rsrc(p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  const i32x4_t rv = rows_rsrc(p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
+  constexpr int PER_WAVE = BKV * HD / 8 / 64 / 4;
+  uint32_t kv_off[PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < PER_WAVE; i++) kv_off[i] = load_offset<HD, 32>(L, wave * PER_WAVE + i, p.kv_stride);
+  const uint32_t row_bytes = (uint32_t)(p.kv_stride * 2);
+  const uint32_t lds_b = __builtin_amdgcn_readfirstlane(lds_address((MLLM_LDS const void*)lds) + wave * PER_WAVE * 1024);
+  auto issue_part = [&](int st, int kv0, int j) {   // j even: K, odd: V
+    load_to_lds_b128(j % 2 ? rv : rk, lds_b + (uint32_t)(st * 2 * TILE_B + j % 2 * TILE_B + j / 2 * 1024), kv_off[j / 2], (uint32_t)kv0 * row_bytes);
+  };
+  const lds_cptr M = (lds_cptr)lds;
+  // natural-layout operand: row l%32 of a block, columns 16c + 8h .. +7; transposed operand: column 32d + l%32 of the tile, contraction
+  // slots e = 0..7 standing for rows 4h + e%4 (+8 for e >= 4) of half a block
+  uint32_t rows[NC], cols[ND][2];
+#pragma unroll
+  for (int c = 0; c < NC; c++) rows[c] = (uint32_t)(c32 * HD + 8 * ((2 * c + h) ^ swz<HD, 32>(c32))) * 2u;
+#pragma unroll
+  for (int d = 0; d < ND; d++)
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+      const int k = 4 * h + (L.c16 >> 2) + 8 * e, n = 32 * d + 16 * (L.g & 1) + 4 * (L.c16 & 3);
+      cols[d][e] = (uint32_t)(k * HD + 8 * ((n >> 3) ^ swz<HD, 32>(k)) + (n & 7)) * 2u + TILE_B;
+    }
+  auto mfma32 = [](bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); };
+
+  f32x16 s[NB];          // scores, then probabilities
+  Frag8 pf[NB][2];       // probabilities as MFMA operand
+  float rs;              // the tile's sum over the lane's keys
+  auto mask = [&](int kv0) {
+    if ((kv0 + BKV > t.seg_len) || (t.causal && kv0 + BKV - 1 > wave_first_q)) {   // the tile crosses the segment end or the diagonal
+#pragma unroll
+      for (int b = 0; b < NB; b++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int kv = kv0 + 32 * b + 8 * (v >> 2) + 4 * h + (v & 3);
+          s[b][v] = (kv < t.seg_len && (!t.causal || kv <= qrow)) ? s[b][v] : -INFINITY;
+        }
+    }
+  };
+  auto tile_max = [&]() {
+    float mx = s[0][0];
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[b][v]);
+    return fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
+  };
+  auto set_reference = [&](float to) {
+    m = to;
+    mu = to == -INFINITY ? 0.f : to;
+    limit = to == -INFINITY ? -1.f : LIMIT;
+  };
+  auto probs = [&]() {
+    rs = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        s[b][v] = fast_exp2(fmaf(s[b][v], c2, -mu));
+        rs += s[b][v];
+      }
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int w = 0; w < 8; w++) pf[b][w >> 2].w[w & 3] = pack_bf16x2(s[b][2 * w], s[b][2 * w + 1]);
+  };
+  auto again = [&](int st, int kv0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+#pragma unroll
+      for (int v = 0; v < 16; v++) s[b][v] = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; c++) s[b] = mfma32(lds_b128(M, rows[c] + (uint32_t)(st * 2 * TILE_B + b * BLOCK_B)), qf[c], s[b]);
+    }
+    mask(kv0);
+    const float mx = tile_max(), old = m;
+    if (mx > old + 8.f) set_reference(mx);
+    const float alpha = fast_exp2(old - mu);
+    l *= alpha;
+#pragma unroll
+    for (int d = 0; d < ND; d++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) oacc[d][v] *= alpha;
+    probs();
+  };
+
+  constexpr int AHEAD = 4, VAHEAD = 1;   // natural-layout and transposed fragments read ahead of their MFMAs
+  auto tile = [&](auto STt, int kv0, bool live) {
+    constexpr int ST = decltype(STt)::value;
+    constexpr uint32_t AT = ST * 2 * TILE_B;
+    wait_loads<0>();
+    phase_barrier();   // the tile has landed, and every wavefront is done with the other stage
+    // A tile past the end, or wholly above the diagonal of this wavefront's rows, or a wavefront without a row (uniform over
+    // the wavefront): only the next tile's loads are wanted.
+    if (!live || (t.causal && kv0 > wave_last_q) || wave_first_q >= t.seg_len) {
+#pragma unroll
+      for (int x = 0; x < 2 * PER_WAVE; x++) issue_part(1 - ST, kv0 + BKV, x);
+      return;
+    }
+    constexpr int NSC = NC * NB, NPV = NB * 2 * ND;
+    bf16x8 fr[NSC];        // fragment x: column chunk x / NB, block x % NB
+    Frag8 fv[NPV];         // fragment x: half block x / ND, columns x % ND
+    auto read_row = [&](int x) { fr[x] = lds_b128(M, rows[x / NB] + AT + x % NB * BLOCK_B); };
+    auto read_v = [&](int x) {
+#pragma unroll
+      for (int e = 0; e < 2; e++) fv[x].h[e] = lds_tr(M, cols[x % ND][e] + AT + x / ND * HALF_B);
+    };
+#pragma unroll
+    for (int x = 0; x < AHEAD; x++) read_row(x);
+    // Scores; the next tile's loads go out one behind each of the first slots, so the wavefront does not stand still while the
+    // memory pipeline takes them.
+#pragma unroll
+    for (int x = 0; x < NSC; x++) {
+      if (x + AHEAD < NSC) read_row(x + AHEAD);
+      if (x < NB) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) s[x][v] = 0.f;
+      }
+      s[x % NB] = mfma32(fr[x], qf[x / NB], s[x % NB]);
+      static_assert(2 * PER_WAVE <= NSC, "a slot for every load");
+      if (x < 2 * PER_WAVE) issue_part(1 - ST, kv0 + BKV, x);
+      MLLM_SLOT_END;
+    }
+#pragma unroll
+    for (int x = 0; x < VAHEAD; x++) read_v(x);   // their latency runs under the vector work
+    MLLM_SLOT_END;
+    mask(kv0);
+    if (kv0 == 0) set_reference(tile_max());
+    probs();
+    if (__any(rs > limit)) again(ST, kv0);
+    l += rs;
+    MLLM_SLOT_END;
+#pragma unroll
+    for (int x = 0; x < NPV; x++) {
+      if (x + VAHEAD < NPV) read_v(x + VAHEAD);
+      oacc[x % ND] = mfma32(fv[x].v, pf[x / ND / 2][x / ND % 2].v, oacc[x % ND]);
+      MLLM_SLOT_END;
+    }
+  };
+
+#pragma unroll
+  for (int j = 0; j < 2 * PER_WAVE; j++) issue_part(0, 0, j);
+  for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
+    tile(Int<0>{}, kv0, true);
+    tile(Int<1>{}, kv0 + BKV, kv0 + BKV < kv_end);
+  }
+  // the last enqueued loads (rows past the end: zeros) must have landed before this workgroup's
+  // LDS can be handed to another one
+  wait_loads<0>();
+  l += __shfl_xor(l, 32, 64);
+  if (!qok) return;
+  const float inv = 1.f / l;
+  bf16_t* op = p.o + (int64_t)(t.seg_start + qrow) * p.o_stride + head * HD;
+#pragma unroll
+  for (int d = 0; d < ND; d++)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; g4++) {
+      uint2 w;
+      w.x = pack_bf16x2(oacc[d][4 * g4] * inv, oacc[d][4 * g4 + 1] * inv);
+      w.y = pack_bf16x2(oacc[d][4 * g4 + 2] * inv, oacc[d][4 * g4 + 3] * inv);
+      *reinterpret_cast<uint2*>(op + 32 * d + 8 * g4 + 4 * h) = w;
+    }
+  if (h == 0) p.lse[(int64_t)head * p.T + t.seg_start + qrow] = (m + log2f(l)) * LN2;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1236,8 +1446,8 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   AttnParams p = make_params(a);
   p.list = (const AttnItem*)a.q_list;
   const dim3 grid((unsigned)a.q_grid), block(256);
-  if (a.head_dim == 128) hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, block, 0, s, p);
-  else if (a.head_dim == 64) hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, block, 0, s, p);
+  if (a.head_dim == 128) hipLaunchKernelGGL(attn_fwd_kernel, grid, block, 0, s, p);
+  else if (a.head_dim == 64) hipLaunchKernelGGL(attn_fwd_64_kernel, grid, block, 0, s, p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
