@@ -43,7 +43,7 @@ def gemm_source_digest():
     """First 16 hex digits of the SHA-256 of the GEMM kernel sources."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("gemm.hip", "gemm_common.h", "gemm_tile.h", "gemm_wide.h", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip"):
+    for f in ("gemm.hip", "gemm_common.h", "gemm_tile.h", "gemm_wide.h", "gemm_fwd.hip", "gemm_dx.hip", "gemm_dw.hip", "gemm_pair.hip", "gemm_small.h", "gemm_small.hip"):
         with open(os.path.join(ROOT, "paper_2603_25120_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

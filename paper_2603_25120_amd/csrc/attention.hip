@@ -661,7 +661,8 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem*
   const int wave_first_q = t.tile0 + 32 * wave, wave_last_q = wave_first_q + 31;
   int qrow[2];
   bf16x8 qf[2][NC], dof[2][NC];
-  float lse2[2], delta[2];
+  Frag8 of[2][NC];
+  float lse[2];
 #pragma unroll
   for (int j = 0; j < 2; j++) {
     qrow[j] = wave_first_q + 16 * j + L.c16;
@@ -670,31 +671,15 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem*
     const bf16_t* qp = p.q + row * p.q_stride + head * HD + 8 * L.g;
     const bf16_t* dop = p.d_o + row * p.o_stride + head * HD + 8 * L.g;
     const bf16_t* op = p.o + row * p.o_stride + head * HD + 8 * L.g;
-    float d = 0.f;
 #pragma unroll
     for (int c = 0; c < NC; c++) {
       qf[j][c] = global_frag(qp + 32 * c, ok);
-      Frag8 fo, fd;
-      fo.v = global_frag(op + 32 * c, ok);
-      fd.v = global_frag(dop + 32 * c, ok);
-#pragma unroll
-      for (int w = 0; w < 4; w++) d += bf16lo(fo.w[w]) * bf16lo(fd.w[w]) + bf16hi(fo.w[w]) * bf16hi(fd.w[w]);
-      dof[j][c] = negated(fd.v);
+      of[j][c].v = global_frag(op + 32 * c, ok);
+      dof[j][c] = global_frag(dop + 32 * c, ok);
     }
-    delta[j] = own_row_sum(d);
-    // Rows beyond the segment get lse = +inf, so their probabilities are exp2(-inf) = 0.
-    lse2[j] = ok ? p.lse[(int64_t)head * p.T + row] * LOG2E : INFINITY;
-    if (ok && L.g == 0) p.delta[(int64_t)head * p.T + row] = delta[j];
+    lse[j] = p.lse[(int64_t)head * p.T + row];
   }
   const int kv_end = t.causal ? min(t.seg_len, t.tile0 + ATTN_FWD_Q_TILE) : t.seg_len;
-  const float c2 = p.scale_log2e;
-
-  f32x4 acc[NN][2], start[2];
-#pragma unroll
-  for (int n = 0; n < NN; n++) acc[n][0] = acc[n][1] = f32x4{0, 0, 0, 0};
-#pragma unroll
-  for (int j = 0; j < 2; j++) start[j] = f32x4{delta[j], delta[j], delta[j], delta[j]};
-
   const i32x4_t rk = rows_rsrc(p.k + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
   const i32x4_t rv = rows_rsrc(p.v + (int64_t)t.seg_start * p.kv_stride + kvh * HD, p.kv_stride, kv_end, HD);
   constexpr int PER_WAVE = BKV * HD / 8 / 64 / 4;
@@ -706,6 +691,35 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem*
   auto issue_part = [&](int st, int kv0, int j) {   // j even: K, odd: V; rows past kv_end: zeros, no traffic
     load_to_lds_b128(j % 2 ? rv : rk, lds_b + (uint32_t)(st * 2 * TILE_B + j % 2 * TILE_B + j / 2 * 1024), kv_off[j / 2], (uint32_t)kv0 * row_bytes);
   };
+#pragma unroll
+  for (int j = 0; j < 2 * PER_WAVE; j++) issue_part(0, 0, j);   // before anything waits for the rows above (5 x 576 tokens, 16 heads, both passes: 43.8 -> 42.9 us)
+
+  float lse2[2], delta[2];
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const bool ok = qrow[j] < t.seg_len;
+    float d = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+      Frag8 fd;
+      fd.v = dof[j][c];
+#pragma unroll
+      for (int w = 0; w < 4; w++) d += bf16lo(of[j][c].w[w]) * bf16lo(fd.w[w]) + bf16hi(of[j][c].w[w]) * bf16hi(fd.w[w]);
+      dof[j][c] = negated(fd.v);
+    }
+    delta[j] = own_row_sum(d);
+    // Rows beyond the segment get lse = +inf, so their probabilities are exp2(-inf) = 0.
+    lse2[j] = ok ? lse[j] * LOG2E : INFINITY;
+    if (ok && L.g == 0) p.delta[(int64_t)head * p.T + t.seg_start + qrow[j]] = delta[j];
+  }
+  const float c2 = p.scale_log2e;
+
+  f32x4 acc[NN][2], start[2];
+#pragma unroll
+  for (int n = 0; n < NN; n++) acc[n][0] = acc[n][1] = f32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 2; j++) start[j] = f32x4{delta[j], delta[j], delta[j], delta[j]};
+
   const lds_cptr M = (lds_cptr)lds;
   uint32_t rows[NC], cols[NN];
 #pragma unroll
@@ -785,8 +799,6 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnParams& p, const AttnItem*
       }
     }
   };
-#pragma unroll
-  for (int j = 0; j < 2 * PER_WAVE; j++) issue_part(0, 0, j);
   for (int kv0 = 0; kv0 < kv_end; kv0 += 2 * BKV) {
     tile(Int<0>{}, kv0, true);
     tile(Int<1>{}, kv0 + BKV, kv0 + BKV < kv_end);
@@ -834,7 +846,7 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem
 #pragma unroll
     for (int c = 0; c < NC; c++) {
       kf[j][c] = global_frag(p.k + at + 32 * c, ok);
-      vf[j][c] = negated(global_frag(p.v + at + 32 * c, ok));
+      vf[j][c] = global_frag(p.v + at + 32 * c, ok);
     }
   }
   f32x4 dk[NN][2], dv[NN][2];
@@ -1028,6 +1040,10 @@ __device__ __forceinline__ void attn_bwd_dkv(const AttnParams& p, const AttnItem
   };
 
   issue(0);
+#pragma unroll
+  for (int j = 0; j < 2; j++)
+#pragma unroll
+    for (int c = 0; c < NC; c++) vf[j][c] = negated(vf[j][c]);   // once the first tile is on its way
   int q0 = range.q0;
   auto advance = [&]() { q0 += BQ; if (q0 >= t.seg_len) q0 = q_begin; };
   for (int it = 0; it < n_it; it += 2) {
@@ -1106,7 +1122,6 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_duo_kernel(AttnParams p) 
 #pragma unroll
     for (int c = 0; c < NC; c++) {
       kvf[j][c] = global_frag(kvp + 32 * c, ok);
-      if (second) kvf[j][c] = negated(kvf[j][c]);
     }
   }
   f32x4 acc[NN][2];   // dV, or dK negated
@@ -1288,6 +1303,10 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkv_duo_kernel(AttnParams p) 
       for (int j = 0; j < 2; j++) dp[0][i][j] = dp[1][i][j] = f32x4{0, 0, 0, 0};
 #pragma unroll
     for (int st = 0; st < 2; st++) issue(st);
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int c = 0; c < NC; c++) kvf[j][c] = negated(kvf[j][c]);
     phase_barrier();
 #pragma unroll
     for (int n = 0; n < CD; n++) read_cols(NQ - 2, n);
