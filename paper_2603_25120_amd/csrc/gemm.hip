@@ -248,13 +248,16 @@ bool fits_wide_form(const GemmArgs& g) {
   return (((uintptr_t)g.a | (uintptr_t)g.b) & 15) == 0 && !(g.a_layout != 0 && g.b_layout != 0) && !(g.rope_table && g.rope_head_dim == 128);
 }
 // Quarters of 128x128 tiles, each with eight wavefronts that share out the K loop (gemm_small.h): in place of uncut 128x128 tiles as
-// long as every quarter has a CU to itself and half the CUs suffice.  152 products of the layers' widths (64 to 1728 tokens, weights
-// from memory): up to 64 quarters 1.27x (least 1.14), 65 to 128 1.31x (1.06 to 1.71), 129 to 256 1.30x (1.09 to 1.77), 257 to 320 0.83x, up
-// to 640 0.82 to 0.56x.  The line lies at 128 because a whole image's output projection (576 x 1024 x 1024, 144 quarters, 9.3 and 7.9 us)
-// would add up in another order: through a deep stage's roundings that moves the outputs by 0.03 of their norm, for 1 us a layer.
+// long as every quarter has a CU to itself.  152 products of the layers' widths (64 to 1728 tokens, weights from memory): up to 64
+// quarters 1.27x (least 1.14), 65 to 256 1.06 to 1.77x, 257 to 320 0.83x, up to 640 0.82 to 0.56x.  A row's sums are then in another order
+// than in a tile of 128, and which of them a product takes hangs on its rows; so the form is left to weights of less than 2^20
+// elements (1.05 to 1.50x), whose products stay on one side with what is usually packed together.  An image's output projection
+// (576 x 1024 x 1024, 9.3 and 7.9 us) keeps its order: through the roundings of a stage of 33 layers another one moves the outputs by
+// 0.03 of their norm.
+constexpr int64_t SMALL_WEIGHT = (int64_t)1 << 20;
 int64_t quarters(int64_t m, int64_t n) { return ((m + 63) / 64) * ((n + 63) / 64); }
 bool takes_small_form(const GemmArgs& g) {
-  return fits_wide_form(g) && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && quarters(g.m, g.n) <= GEMM_CUS / 2;
+  return fits_wide_form(g) && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && (g.a_layout || g.n * g.k < SMALL_WEIGHT) && quarters(g.m, g.n) <= GEMM_CUS;
 }
 // Rows that fill as many tiles of 224 as of 256 (so at most 1568 of them) take those, on four wavefronts, in place of a plan of 256x256
 // tiles, cut or not: the same tiles with an eighth less of padding (777 rows: 3.5 tile-rows of 256 in place of 4).  Products of the

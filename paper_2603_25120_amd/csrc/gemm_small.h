@@ -13,8 +13,8 @@ namespace {
 // requested at once, a wavefront asks for its next one when it has read the last.  The eight partial sums meet in LDS and are
 // added in the order of the wavefronts; each wavefront then writes a 16 x 32 part of the tile.  The loop is short code on
 // purpose: in a row of small launches a kernel's instructions come from L2.
-// Against the 128x128 form, back to back, weights from memory (us): 148 x 768 x 256 4.8 -> 4.1, 128 x 3072 x 1024 10.0 -> 7.9, 450 x
-// 1024 x 4096 25.6 -> 15.3; both gradients of a map, 148 tokens x 192 x 768 7.4 -> 5.6, 576 x 512 x 512 7.6 -> 6.0.  A k-tile of all
+// Against the 128x128 form, back to back, weights from memory (us): 148 x 768 x 256 4.8 -> 4.1, 450 x 256 x 1024 9.1 -> 6.0, 576 x
+// 512 x 512 6.7 -> 6.0; both gradients of a map, 148 tokens x 192 x 768 7.4 -> 5.6, 576 x 512 x 512 7.6 -> 6.0.  A k-tile of all
 // eight wavefronts is 128 KB, 1.4 us of what a CU takes from L2, so with more tiles than CUs the larger tiles, which read half
 // as much for their work, are better (where the line lies: takes_small_form in gemm.hip).
 // ---------------------------------------------------------------------------------------------

@@ -1,5 +1,5 @@
 """Products in quarters of 128x128 tiles (64 x 64, the K loop dealt to eight wavefronts) at their edges: rows and columns around 16, 32
-and 64, fewer k-tiles than wavefronts, as many and more, a ragged last k-tile of weight gradients, as many quarters as are taken and one row more;
+and 64, fewer k-tiles than wavefronts, as many and more, a ragged last k-tile of weight gradients, as many quarters as are taken and one row more, weights of 2^20 elements and just less;
 bias, residual, accumulation; operands off 16 bytes (another kernel).  Against float64 products of the same operands: one bf16 rounding
 of the result (1e-2 of the maximum), or fp32 sums of bf16 products (2e-3)."""
 import pytest
@@ -44,13 +44,13 @@ def product(B, m, n, k, a_layout, b_layout, out_fp32, extras=False, offset=0):
 @pytest.mark.parametrize("extras", [False, True])
 @pytest.mark.parametrize("b_layout", [0, 1])
 @pytest.mark.parametrize("m,n,k", [(1, 8, 64), (15, 16, 128), (16, 24, 192), (17, 64, 448), (63, 72, 512), (64, 136, 576), (65, 128, 1024), (200, 264, 1088),
-                                   (512, 1024, 64), (513, 1024, 64), (1024, 1024, 64), (450, 1024, 4096)])
+                                   (1024, 1024, 64), (1025, 1024, 64), (64, 1016, 1024), (64, 1024, 1024)])
 def test_forward_and_input_gradient(B, m, n, k, b_layout, extras):
     product(B, m, n, k, 0, b_layout, 0, extras)
 
 
 @pytest.mark.parametrize("extras", [False, True])
-@pytest.mark.parametrize("m,n,k", [(8, 8, 1), (16, 72, 63), (64, 64, 64), (72, 136, 65), (128, 40, 511), (192, 576, 513), (512, 1024, 77), (520, 1024, 200)])
+@pytest.mark.parametrize("m,n,k", [(8, 8, 1), (16, 72, 63), (64, 64, 64), (72, 136, 65), (128, 40, 511), (192, 576, 513), (1024, 1000, 77), (1032, 1000, 200)])
 def test_weight_gradient(B, m, n, k, extras):
     product(B, m, n, k, 1, 0, 1, extras)
 
