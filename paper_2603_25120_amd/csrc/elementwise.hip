@@ -41,21 +41,30 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
   const int64_t row = (int64_t)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
   if (row >= T) return;
   const int nvec = d >> 3;
+  // The row, gamma and beta are requested before any of them is used (with load and use of a vector in one conditional block they came
+  // one after the other: 576 x 1024 3.19 -> 2.93 us, 26496 x 1024 23.8 -> 22.7, 24000 x 1280 29.5 -> 25.6, 3000 x 3584 RMSNorm 12.5 -> 10.5).
+  uint4 u[NV];
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = lane + 64 * j;
+    u[j] = c < nvec ? *reinterpret_cast<const uint4*>(x + row * ld + 8 * c) : make_uint4(0, 0, 0, 0);
+  }
+  uint4 g4[NV], b4[NV];
+#pragma unroll
+  for (int j = 0; j < NV; j++) {
+    const int c = lane + 64 * j;
+    g4[j] = c < nvec ? *reinterpret_cast<const uint4*>(gamma + 8 * c) : make_uint4(0, 0, 0, 0);
+    b4[j] = KIND == 0 && c < nvec ? *reinterpret_cast<const uint4*>(beta + 8 * c) : make_uint4(0, 0, 0, 0);
+  }
   float v[NV][8];
   float sum = 0.f;
 #pragma unroll
   for (int j = 0; j < NV; j++) {
-    int c = lane + 64 * j;
-    if (c < nvec) {
-      uint4 u = *reinterpret_cast<const uint4*>(x + row * ld + 8 * c);
-      if (x_copy) *reinterpret_cast<uint4*>(x_copy + row * ld + 8 * c) = u;
-      unpack8(u, v[j]);
+    const int c = lane + 64 * j;
+    if (x_copy && c < nvec) *reinterpret_cast<uint4*>(x_copy + row * ld + 8 * c) = u[j];
+    unpack8(u[j], v[j]);
 #pragma unroll
-      for (int e = 0; e < 8; e++) sum += v[j][e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; e++) v[j][e] = 0.f;
-    }
+    for (int e = 0; e < 8; e++) sum += v[j][e];
   }
   float mean = 0.f;
   if (KIND == 0) mean = wave_sum(sum) / (float)d;
@@ -81,8 +90,8 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
     int c = lane + 64 * j;
     if (c < nvec) {
       float g[8], b[8], o[8];
-      unpack8(*reinterpret_cast<const uint4*>(gamma + 8 * c), g);
-      if (KIND == 0) unpack8(*reinterpret_cast<const uint4*>(beta + 8 * c), b);
+      unpack8(g4[j], g);
+      if (KIND == 0) unpack8(b4[j], b);
 #pragma unroll
       for (int e = 0; e < 8; e++) {
         o[e] = (v[j][e] - mean) * rstd * g[e];
@@ -758,16 +767,17 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
-// Whether a workgroup owns a row (norm_fwd_row_kernel) or a wavefront does (us with a wavefront a row and a workgroup a row).
-// Up to 2048 columns the workgroup's threads have a vector each at most, and many rows are better off with more loads in
-// flight a thread: 400 x 1280 LayerNorm 3.60 and 2.89, 1500 x 1280 3.97 and 3.74, 2048 x 1280 4.15 and 4.24, 2999 x 1280 4.97 and 5.60,
-// 32768 x 1280 28.0 and 34.3, 32768 x 2048 43.6 and 43.0.  Wider rows always gain in LayerNorm (2999 x 2560 7.80 and 7.58, 32768 x 4096
-// 120 and 97); in RMSNorm not between 3/4 d rows and the 5120 that a wavefront a row has resident at once: 2999 x 2560 7.10 and
-// 7.61, 4200 x 3072 9.6 and 10.7, 2500 x 4096 8.8 and 8.3, 3500 x 4096 10.9 and 11.3, 6000 x 3072 15.0 and 13.9.
+// Whether a workgroup owns a row (norm_fwd_row_kernel) or a wavefront does (us with a wavefront a row and a workgroup a row, rows
+// from memory).  Up to 2048 columns the workgroup's threads have a vector each at most, and many rows are better off with more loads in
+// flight a thread: 400 x 1280 LayerNorm 3.18 and 3.02, 1500 x 1280 4.32 and 4.29, 2048 x 1280 4.89 and 4.95, 2999 x 1280 5.72 and 6.39,
+// 32768 x 1280 32.8 and 46, 32768 x 2048 48 and 55.  Wider rows always gain in LayerNorm (32768 x 4096 120 and 97); in RMSNorm not
+// between 3/4 d rows and the 3072 (five vectors a lane and fewer: 5120) that a wavefront a row has resident at once: 600 x 4096 4.56 and 4.58,
+// 2999 x 2560 7.5 and 8.4, 3072 x 4096 12.4 and 12.8, 3800 x 2560 10.2 and 11.3, 3300 x 3584 12.9 and 12.3, 4200 x 3072 13.9 and 13.3,
+// 6000 x 3072 17.3 and 16.8.
 static bool norm_fwd_row_form(int kind, int64_t t, int64_t d) {
   if (d <= 1024) return false;
   if (d <= 2048) return t <= 1536;
-  return kind == 0 || d > 4096 || 4 * t <= 3 * d || t > 5120;
+  return kind == 0 || d > 4096 || 4 * t <= 3 * d || t > (d > 2560 ? 3072 : 5120);
 }
 // A grid's x dimension holds fewer than 2^32 threads, 2^24 rows of the row form: beyond this many they go to y.
 constexpr int64_t ROW_FORM_GRID = (int64_t)1 << 20;
