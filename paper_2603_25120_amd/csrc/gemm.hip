@@ -4,10 +4,11 @@
 // (Model Profiler, "Throughput Profiling"): QKV / output / MLP projections and the connector,
 // their input gradients (dX = dY.W^T) and their weight gradients (dW = X^T.dY).
 //
-// Four kernels.  gemm4_kernel (gemm_tile.h): 256x256, 192x256 and 128x128 tiles on four wavefronts with a
+// Four kernels.  gemm4_kernel (gemm_tile.h): 256x256, 224x256, 192x256 and 128x128 tiles on four wavefronts with a
 // hand-placed k-loop, for every K that is a multiple of 64 and for any K of a weight gradient; gemm_wide_kernel
-// (gemm_wide.h): the same tiles on eight wavefronts; gemm_small_kernel (gemm_small.h): quarters of the small tiles, the K loop dealt
-// to eight wavefronts, for products of few tiles; plan_gemm below chooses the tile and whether the K loop is split.
+// (gemm_wide.h): all of these but 224x256 on eight wavefronts; gemm_small_kernel (gemm_small.h): quarters of the small tiles, for
+// products of few tiles; plan_gemm below chooses the tile and whether the K loop is split.  A part of the K loop is summed in the
+// same order in all of their tiles.
 // gemm_kernel (here): a general template for what is left, K no multiple of 64 with an operand whose contiguous dimension is k.  It wants, per lane, eight
 // consecutive values along the contraction index for v_mfma_f32_32x32x16_bf16: operands whose
 // contraction index is contiguous in memory are staged in LDS as [row][k] and fetched with one 16-byte read;
@@ -247,17 +248,14 @@ GemmParams tile_params(const GemmArgs& g, GemmTile tile, int splits) {
 bool fits_wide_form(const GemmArgs& g) {
   return (((uintptr_t)g.a | (uintptr_t)g.b) & 15) == 0 && !(g.a_layout != 0 && g.b_layout != 0) && !(g.rope_table && g.rope_head_dim == 128);
 }
-// Quarters of 128x128 tiles, each with eight wavefronts that share out the K loop (gemm_small.h): in place of uncut 128x128 tiles as
-// long as every quarter has a CU to itself.  152 products of the layers' widths (64 to 1728 tokens, weights from memory): up to 64
-// quarters 1.27x (least 1.14), 65 to 256 1.06 to 1.77x, 257 to 320 0.83x, up to 640 0.82 to 0.56x.  A row's sums are then in another order
-// than in a tile of 128, and which of them a product takes hangs on its rows; so the form is left to weights of less than 2^20
-// elements (1.05 to 1.50x), whose products stay on one side with what is usually packed together.  An image's output projection
-// (576 x 1024 x 1024, 9.3 and 7.9 us) keeps its order: through the roundings of a stage of 33 layers another one moves the outputs by
-// 0.03 of their norm.
-constexpr int64_t SMALL_WEIGHT = (int64_t)1 << 20;
-int64_t quarters(int64_t m, int64_t n) { return ((m + 63) / 64) * ((n + 63) / 64); }
-bool takes_small_form(const GemmArgs& g) {
-  return fits_wide_form(g) && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && (g.a_layout || g.n * g.k < SMALL_WEIGHT) && quarters(g.m, g.n) <= GEMM_CUS;
+// Quarters of 128x128 tiles (gemm_small.h) in place of these, cut or not, as long as every quarter has a CU to itself.
+// 508 products of 18 maps 192 to 4096 wide, 64 to 1728 tokens, operands from memory, in either layout: up to 256 quarters
+// (439 products) 1.16x at least, geomean 1.29x, whatever the weight; beyond, where a CU takes two one after the other, 0.73 to
+// 0.94x up to 340 and 0.54 to 0.98x up to 640: the larger tiles read half as much for their work.
+constexpr int64_t QUARTERS_MOST = GEMM_CUS;
+int64_t quarters(const GemmArgs& g, int splits) { return ((g.m + 63) / 64) * ((g.n + 63) / 64) * splits; }
+bool takes_quarters(const GemmArgs& g, int splits) {
+  return fits_wide_form(g) && !g.swiglu_act && !g.swiglu_dpre && !g.rope_table && quarters(g, splits) <= QUARTERS_MOST;
 }
 // Rows that fill as many tiles of 224 as of 256 (so at most 1568 of them) take those, on four wavefronts, in place of a plan of 256x256
 // tiles, cut or not: the same tiles with an eighth less of padding (777 rows: 3.5 tile-rows of 256 in place of 4).  Products of the
@@ -266,8 +264,6 @@ bool takes_small_form(const GemmArgs& g) {
 // 4096 193 -> 184).
 bool takes_224_rows(const GemmArgs& g) { return g.a_layout == 0 && (g.m + 223) / 224 == (g.m + 255) / 256; }
 hipError_t launch_tiles(const GemmArgs& g, GemmTile tile, int splits, bool wide, hipStream_t s) {
-  if (tile == GemmTile::T256 && takes_224_rows(g)) { tile = GemmTile::T224; wide = false; }
-  if (tile == GemmTile::T128 && splits == 1 && takes_small_form(g)) tile = GemmTile::T64;
   const GemmParams p = tile_params(g, tile, splits);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)splits);
   const int epi = g.swiglu_act ? EPI_SWIGLU : g.swiglu_dpre ? EPI_SWIGLU_BWD : !g.rope_table ? EPI_PLAIN : g.rope_head_dim == 128 ? EPI_ROPE128 : EPI_ROPE64;
@@ -529,18 +525,25 @@ namespace {
 // The plan of a product that takes the tile kernel.  With both operands k-contiguous the large tiles are loaded straight
 // into LDS, 16 bytes a lane, which is only known to work from addresses that are multiples of 16; operands that start
 // elsewhere (a tensor inside a larger buffer) take 128x128 tiles, whose loads go through registers.
-GemmPlan plan_of(const GemmArgs& g) {
+GemmPlan planned(const GemmArgs& g) {
   if (!takes_tile_kernel(g)) return {GemmTile::T256, 1, false};
   if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1, false};
   const bool fused = g.swiglu_act || g.swiglu_dpre || g.rope_table;
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
   return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0, nullptr, fused);
 }
+// The same with the tiles that run in place of the planned ones.
+GemmPlan plan_of(const GemmArgs& g) {
+  GemmPlan pl = planned(g);
+  if (pl.tile == GemmTile::T256 && takes_224_rows(g)) pl = {GemmTile::T224, pl.splits, false};
+  if (pl.tile == GemmTile::T128 && takes_quarters(g, pl.splits)) pl.tile = GemmTile::T64;
+  return pl;
+}
 }  // namespace
 
 GemmForm gemm_form(const GemmArgs& g) {
   if (!takes_tile_kernel(g)) return {0, 0, 1};
-  const GemmPlan pl = plan_of(g);
+  const GemmPlan pl = planned(g);
   return {tile_rows(pl.tile), tile_cols(pl.tile), pl.splits};
 }
 
@@ -588,7 +591,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const bool tiled = takes_tile_kernel(g);
   const GemmPlan pl = plan_of(g);
   // timing classes: the three layouts of the large tiles, the 192-row form, and the small tiles
-  const bool small = tiled ? pl.tile == GemmTile::T128 : !fills_chip(g.m, g.n);
+  const bool small = tiled ? pl.tile == GemmTile::T128 || pl.tile == GemmTile::T64 : !fills_chip(g.m, g.n);
   const int cls = small ? PROF_GEMM_SMALL : pl.tile == GemmTile::T192 ? PROF_GEMM_ROWS192
                   : g.a_layout ? PROF_GEMM_DW : (g.b_layout ? PROF_GEMM_DX : PROF_GEMM_FWD);
   const double flops = 2.0 * (double)g.m * (double)g.n * (double)g.k;
@@ -612,6 +615,19 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 // loaded straight to LDS).
 static bool pairable(const GemmArgs& x, const GemmArgs& w) {
   return x.m > 0 && x.n > 0 && w.m > 0 && w.n > 0 && takes_tile_kernel(x) && takes_tile_kernel(w) && (((uintptr_t)x.a | (uintptr_t)x.b | (uintptr_t)w.a | (uintptr_t)w.b) & 15) == 0;
+}
+
+// The plan of both gradients of operands that may share a launch, with the tiles that run: quarters of 128x128 tiles (takes_quarters)
+// in place of a plan with both in these, and 224 rows for dX.
+// Up to 256 quarters, the same maps and tokens as there: uncut 1.20 to 1.34x (83 maps), with a product in parts 1.13 to 1.20x (20); 257 to
+// 512 0.80 to 1.37x, geomean 1.0x, and 0.80 to 1.12x with parts.
+static PairPlan pair_plan_of(const GemmArgs& x, const GemmArgs& w) {
+  PairPlan pl = plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0);
+  if (pl.x.tile == GemmTile::T256 && takes_224_rows(x)) pl.x.tile = GemmTile::T224;
+  if (pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128 && !x.swiglu_dpre &&
+      quarters(x, pl.x.splits) + quarters(w, pl.w.splits) <= QUARTERS_MOST)
+    pl.x.tile = pl.w.tile = GemmTile::T64;
+  return pl;
 }
 
 LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
@@ -646,25 +662,14 @@ static bool gradients_over_operands(const GemmArgs& x, const GemmArgs& w) {
          ranges_overlap(dx, dx_bytes, w.c, dw_bytes);
 }
 
-// Both gradients in quarters of 128x128 tiles (takes_small_form), in place of a plan with both in 128x128 tiles and dW uncut.  64 to 1728
-// tokens, 11 maps of 192 to 3584 columns, up to 256 quarters: 1.12 to 1.55x; with dX in parts 0.92 and 0.98x at 64 and 128 tokens,
-// 1.06 to 1.48x from 200 on; 257 to 350 quarters 1.0 to 1.3x, but 0.81x for 400 (576 x 1024 x 1024).
-static bool takes_small_pair(const GemmArgs& x, const GemmArgs& w, const PairPlan& pl) {
-  return pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128 && pl.w.splits == 1 && (pl.x.splits == 1 || x.m > 128) && !x.swiglu_dpre &&
-         quarters(x.m, x.n) + quarters(w.m, w.n) <= GEMM_CUS;
-}
-
 hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s) {
   const bool pair = pairable(x, w) && !gradients_over_operands(x, w);
-  PairPlan pl = pair ? plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0) : PairPlan{};
+  const PairPlan pl = pair ? pair_plan_of(x, w) : PairPlan{};
   if (!pair || !pl.pays) {
     const hipError_t e = launch_gemm(w, s);
     return e != hipSuccess ? e : launch_gemm(x, s);
   }
   if (refused(x) || refused(w)) return hipErrorInvalidValue;
-  const bool in_quarters = takes_small_pair(x, w, pl);
-  if (in_quarters) pl = {{GemmTile::T64, 1, false}, {GemmTile::T64, 1, false}, pl.x_first, true};
-  if (pl.x.tile == GemmTile::T256 && takes_224_rows(x)) pl.x.tile = GemmTile::T224;
   GemmArgs xa = x, wa = w;   // the parts of both are in the scratch at the same time
   wa.splitk_ws = (char*)x.splitk_ws + part_bytes(pl.x, x.m, x.n);
   const GemmArgs xp = pl.x.splits > 1 ? part_of(xa) : xa, wp = pl.w.splits > 1 ? part_of(wa) : wa;
@@ -678,9 +683,9 @@ hipError_t launch_linear_bwd(const GemmArgs& x, const GemmArgs& w, hipStream_t s
   p.first = pl.x_first ? x_wgs : w_wgs;
   hipError_t e;
   {
-    const bool small = in_quarters || (pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128);
+    const bool in_quarters = pl.x.tile == GemmTile::T64, small = in_quarters || (pl.x.tile == GemmTile::T128 && pl.w.tile == GemmTile::T128);
     ProfScope prof(small ? PROF_GEMM_SMALL : PROF_GEMM_DX, 4.0 * (double)x.m * (double)x.n * (double)x.k, s);
-    e = in_quarters ? launch_gemm_pair_small(p, x_wgs + w_wgs, s)
+    e = in_quarters ? launch_gemm_pair_small(p, xp.out_fp32 != 0, x_wgs + w_wgs, s)
                     : launch_gemm_pair_tiles(p, pl.x.tile, xp.out_fp32 != 0, x.swiglu_dpre ? EPI_SWIGLU_BWD : EPI_PLAIN, pl.w.tile, x_wgs + w_wgs, s);
   }
   if (e == hipSuccess && pl.x.splits > 1) e = reduce_parts(xa, pl.x.splits, s);

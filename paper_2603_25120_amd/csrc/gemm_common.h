@@ -86,7 +86,7 @@ struct GemmPairParams {
   int x_first;
 };
 hipError_t launch_gemm_pair_tiles(const GemmPairParams& p, GemmTile x_tile, bool x_f32, int x_epi, GemmTile w_tile, int workgroups, hipStream_t s);
-hipError_t launch_gemm_pair_small(const GemmPairParams& p, int workgroups, hipStream_t s);   // both in 64 x 64 tiles (gemm_small.hip)
+hipError_t launch_gemm_pair_small(const GemmPairParams& p, bool x_f32, int workgroups, hipStream_t s);   // both in 64 x 64 tiles (gemm_small.hip)
 
 // Workgroups are dealt round-robin to the 8 XCDs.  Renumber so that each XCD gets a contiguous
 // range of tile ids, then walk the tile grid in panels of group_m tile-rows.

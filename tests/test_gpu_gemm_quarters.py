@@ -1,7 +1,7 @@
-"""Products in quarters of 128x128 tiles (64 x 64, the K loop dealt to eight wavefronts) at their edges: rows and columns around 16, 32
-and 64, fewer k-tiles than wavefronts, as many and more, a ragged last k-tile of weight gradients, as many quarters as are taken and one row more, weights of 2^20 elements and just less;
+"""Products in quarters of 128x128 tiles (64 x 64, eight LDS stages of a k-tile) at their edges: rows and columns around 16, 32
+and 64, fewer k-tiles than stages, as many and more, a ragged last k-tile of weight gradients, as many quarters as are taken and one row more;
 bias, residual, accumulation; operands off 16 bytes (another kernel).  Against float64 products of the same operands: one bf16 rounding
-of the result (1e-2 of the maximum), or fp32 sums of bf16 products (2e-3)."""
+of the result (1e-2 of the maximum), or fp32 sums of bf16 products (2e-3); and to the bit against the tiles they stand for."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -58,6 +58,36 @@ def test_weight_gradient(B, m, n, k, extras):
 @pytest.mark.parametrize("a_layout,b_layout", [(0, 0), (0, 1), (1, 0)])
 def test_operands_off_16_bytes(B, a_layout, b_layout):
     product(B, 136, 192, 320, a_layout, b_layout, a_layout, True, offset=3)
+
+
+# A quarter adds up in the order of every other tile, so the form cannot be seen in a result.  Operands off 16 bytes take 128x128 tiles.
+@pytest.mark.parametrize("a_layout,b_layout", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("m,n,k", [(72, 72, 64), (104, 200, 448), (200, 264, 512), (328, 192, 576), (576, 1024, 1024), (64, 768, 3584)])
+def test_to_the_bit_the_tiles_they_stand_for(B, m, n, k, a_layout, b_layout):
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    c = [torch.empty(m, n, dtype=torch.float32, device="cuda") for _ in range(2)]
+    a, b = (torch.randn(r, s, generator=g, device="cuda").bfloat16() for r, s in ((k, m) if a_layout else (m, k), (n, k) if b_layout else (k, n)))
+    for out, offset in zip(c, (0, 3)):
+        flat = torch.zeros(a.numel() + offset, dtype=torch.bfloat16, device="cuda")
+        flat[offset:] = a.flatten()
+        B.mllm_op_gemm(flat[offset:], b, out, m, n, k, a_layout, b_layout, 1)
+    assert torch.equal(c[0], c[1])
+
+
+# tokens either side of the line of both gradients, with the same parts of dX's K loop: 4 of 256 x 2048, none of 512 x 512
+@pytest.mark.parametrize("k,n,few,many", [(256, 2048, (64, 128, 129, 288), 577), (512, 512, (64, 576, 1536), 1600)])
+def test_rows_of_both_gradients_do_not_depend_on_the_other_rows(B, k, n, few, many):
+    g = torch.Generator(device="cuda").manual_seed(k)
+    dy, x, w = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((many, n), (many, k), (k, n)))
+    dw, got = torch.empty(k, n, device="cuda"), {}
+    for t in few + (many,):
+        size = B.mllm_linear_bwd_form(t, k, n)[1]
+        ws = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        got[t] = torch.empty(t, k, dtype=torch.bfloat16, device="cuda")
+        B.mllm_op_linear_bwd(dy, x, w, got[t], dw, t, k, n, workspace=ws, scratch_bytes=size)
+        assert B.mllm_linear_bwd_form(t, k, n)[0][1][2] == B.mllm_linear_bwd_form(many, k, n)[0][1][2]
+    for t in few:
+        assert torch.equal(got[t], got[many][:t])
 
 
 # tokens, k, n: both gradients, dX uncut and (200 and 777 tokens x 256 x 2048) planned in parts; 256 quarters and one more
