@@ -224,9 +224,10 @@ mllm_status_t mllm_op_gemm(const void* a, const void* b, void* c, int64_t m, int
                            const void* bias, const void* residual, void* hip_stream);
 
 /* The form a product takes (host only, no GPU work; exported so that it can be checked which kernel a size
- * reaches): output tile tile_rows x tile_cols, or 0 x 0 for the general kernel, and into how many parts the
- * contraction is cut when scratch_bytes of fp32 scratch are at hand (mllm_op_gemm has none: 0; the stage
- * calls use their workspace). */
+ * reaches): output tile tile_rows x tile_cols (256, 224 or 192 x 256, 128 x 128, 64 x 64), or 0 x 0 for the
+ * general kernel, and into how many parts the contraction is cut when scratch_bytes of fp32 scratch are at
+ * hand (mllm_op_gemm has none: 0; the stage calls use their workspace).  For operands that start on 16
+ * bytes; others run 128 x 128 where 64 x 64 is named, and with a_layout 0, b_layout 1 in place of every tile. */
 mllm_status_t mllm_gemm_form(int64_t m, int64_t n, int64_t k, int a_layout, int b_layout,
                              size_t scratch_bytes, int32_t* tile_rows, int32_t* tile_cols,
                              int32_t* k_parts);
@@ -492,10 +493,11 @@ mllm_status_t mllm_optimize_parallelism(const mllm_module_profile_t* enc, const 
  * mllm_profile_begin(max_records) creates the events and starts recording every kernel launch of
  * the calling process' later mllm_* calls, bracketing each with HIP events on its launch stream.
  * mllm_profile_end stops recording, waits for the recorded events, and sums per class
- * (0 / 1 / 2: the 256x256-tile GEMM kernel in its Y=X.W / dX / dW layouts, 1 also every launch that forms dX and dW together unless both
- * are in 128x128 tiles (then 6): its FLOPs are those of both, its tiles may be 256x256, 192x256 and 128x128; 3 attention forward,
+ * (0 / 1 / 2: the 256x256- and 224x256-tile GEMM kernel in its Y=X.W / dX / dW layouts, 1 also every launch that forms dX and dW together
+ * unless both are in 128x128 tiles or quarters of them (then 6): its FLOPs are those of both, its tiles may be 256, 224 or 192 x 256 and
+ * 128x128; 3 attention forward,
  * 4 attention backward, 5 the norm / rotary / activation / reduction / copy kernels, 6 the
- * 128x128-tile GEMM kernel in any layout, 7 the 192x256-tile form of the large GEMM kernel in any
+ * 128x128- and 64x64-tile GEMM kernels in any layout, 7 the 192x256-tile form of the large GEMM kernel in any
  * layout): launches[8], milliseconds[8] and work[8] (algorithmic FLOPs for the GEMM and attention
  * classes, algorithmic bytes for class 5) are host arrays.
  * Not thread-safe; records beyond max_records are dropped and counted in *dropped.

@@ -522,19 +522,16 @@ bool gemm_rope_fusable(int64_t m, int64_t n, int64_t k, int32_t head_dim) {
 }
 
 namespace {
-// The plan of a product that takes the tile kernel.  With both operands k-contiguous the large tiles are loaded straight
+// The plan of a product that takes the tile kernel, with the tiles that run (224 rows in place of 256, quarters in place of
+// 128x128): the launch and gemm_form both go by it.  With both operands k-contiguous the large tiles are loaded straight
 // into LDS, 16 bytes a lane, which is only known to work from addresses that are multiples of 16; operands that start
 // elsewhere (a tensor inside a larger buffer) take 128x128 tiles, whose loads go through registers.
-GemmPlan planned(const GemmArgs& g) {
+GemmPlan plan_of(const GemmArgs& g) {
   if (!takes_tile_kernel(g)) return {GemmTile::T256, 1, false};
   if (g.a_layout == 0 && g.b_layout == 1 && (((uintptr_t)g.a | (uintptr_t)g.b) & 15)) return {GemmTile::T128, 1, false};
   const bool fused = g.swiglu_act || g.swiglu_dpre || g.rope_table;
   const bool split_ok = g.splitk_ws && g.ldc == g.n && g.n % 8 == 0;
-  return plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0, nullptr, fused);
-}
-// The same with the tiles that run in place of the planned ones.
-GemmPlan plan_of(const GemmArgs& g) {
-  GemmPlan pl = planned(g);
+  GemmPlan pl = plan_gemm(g.m, g.n, g.k, g.a_layout != 0, g.b_layout == 0, split_ok ? g.splitk_ws_bytes : 0, nullptr, fused);
   if (pl.tile == GemmTile::T256 && takes_224_rows(g)) pl = {GemmTile::T224, pl.splits, false};
   if (pl.tile == GemmTile::T128 && takes_quarters(g, pl.splits)) pl.tile = GemmTile::T64;
   return pl;
@@ -543,7 +540,7 @@ GemmPlan plan_of(const GemmArgs& g) {
 
 GemmForm gemm_form(const GemmArgs& g) {
   if (!takes_tile_kernel(g)) return {0, 0, 1};
-  const GemmPlan pl = planned(g);
+  const GemmPlan pl = plan_of(g);
   return {tile_rows(pl.tile), tile_cols(pl.tile), pl.splits};
 }
 
@@ -618,7 +615,7 @@ static bool pairable(const GemmArgs& x, const GemmArgs& w) {
 }
 
 // The plan of both gradients of operands that may share a launch, with the tiles that run: quarters of 128x128 tiles (takes_quarters)
-// in place of a plan with both in these, and 224 rows for dX.
+// in place of a plan with both in these, and 224 rows for dX.  The launch and linear_bwd_form both go by it.
 // Up to 256 quarters, the same maps and tokens as there: uncut 1.20 to 1.34x (83 maps), with a product in parts 1.13 to 1.20x (20); 257 to
 // 512 0.80 to 1.37x, geomean 1.0x, and 0.80 to 1.12x with parts.
 static PairPlan pair_plan_of(const GemmArgs& x, const GemmArgs& w) {
@@ -632,7 +629,7 @@ static PairPlan pair_plan_of(const GemmArgs& x, const GemmArgs& w) {
 
 LinearBwdForm linear_bwd_form(const GemmArgs& x, const GemmArgs& w) {
   if (!pairable(x, w)) return {false, gemm_form(x), gemm_form(w), false};
-  const PairPlan pl = plan_pair(x.m, x.n, x.k, x.swiglu_dpre != nullptr, x.splitk_ws ? x.splitk_ws_bytes : 0);
+  const PairPlan pl = pair_plan_of(x, w);
   if (!pl.pays) return {false, gemm_form(x), gemm_form(w), false};
   auto form = [](const GemmPlan& p) { return GemmForm{tile_rows(p.tile), tile_cols(p.tile), p.splits}; };
   return {true, form(pl.x), form(pl.w), pl.x_first};

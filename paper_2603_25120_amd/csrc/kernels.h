@@ -51,7 +51,8 @@ bool gemm_swiglu_fusable(int64_t m, int64_t n, int64_t k);
 // A and B are addressed through 32-bit byte offsets: each operand must stay below this size.
 constexpr int64_t GEMM_MAX_OPERAND_BYTES = 0xFFFFFFF0ll - 16;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// What launch_gemm takes for a product: output tile (0 x 0: the general kernel) and parts of the K loop.
+// What launch_gemm runs for a product: output tile (256, 224 or 192 x 256, 128 x 128, 64 x 64; 0 x 0: the general kernel) and parts
+// of the K loop.
 struct GemmForm { int tile_rows, tile_cols, k_parts; };
 GemmForm gemm_form(const GemmArgs& g);
 // Both gradients of a linear map Y [t, n] = X [t, k] . W [k, n] in one launch: x the arguments of dX = dY . W^T (or of its SwiGLU form), w

@@ -59,6 +59,14 @@ def test_no_plan_leaves_a_part_empty(B):
     assert cut > 100
 
 
+# the last product in quarters of 128x128 tiles and the first that is not; rows that fill as many tiles of 224 as of 256 and others
+@pytest.mark.parametrize("m,n,k,a_layout,b_layout,tile", [
+    (1024, 1024, 64, 0, 0, 64), (1025, 1024, 64, 0, 0, 128), (576, 1024, 1024, 0, 1, 64), (1024, 1024, 77, 1, 0, 64), (1032, 1024, 77, 1, 0, 128), (200, 520, 320, 1, 1, 128),
+    (896, 14336, 4096, 0, 0, 224), (897, 14336, 4096, 0, 0, 256), (1568, 8320, 704, 0, 1, 224), (1569, 8320, 704, 0, 1, 256), (896, 28672, 4096, 1, 0, 256)])
+def test_the_tile_that_runs_is_named(B, m, n, k, a_layout, b_layout, tile):
+    assert B.mllm_gemm_form(m, n, k, a_layout, b_layout) == (tile, 256 if tile > 128 else tile, 1)
+
+
 # rows x columns x contraction of a decoder's down projection for a few hundred tokens: fewer tiles than compute units over a long
 # contraction
 @pytest.mark.parametrize("m", [444, 600, 763, 900])

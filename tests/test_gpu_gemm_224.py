@@ -25,16 +25,12 @@ def randn(g, *shape, scale=1.0):
 
 @pytest.mark.parametrize("k", [64, 192, 704])
 @pytest.mark.parametrize("m", [193, 224, 225, 447, 448, 449, 672, 1343, 1568])
-def test_forward_with_every_epilogue(B, m, k):
+def test_fused_epilogues(B, m, k):
     g = torch.Generator(device="cuda").manual_seed(m + k)
     f = 6272 * (1 + 1024 // m)                 # 200 tiles of 256 x 256 and more
     x, w, bias = randn(g, m, k), randn(g, k, 2 * f, scale=0.125), randn(g, 2 * f)
     ref = x.double() @ w.double()
-    assert B.mllm_gemm_form(m, 2 * f, k)[0] in (256, 192, 128)
     y = torch.full((m + 1, 2 * f), 7.0, dtype=torch.bfloat16, device="cuda")
-    res = randn(g, m, 2 * f)
-    B.mllm_op_gemm(x, w, y, m, 2 * f, k, bias=bias, residual=res)
-    assert error(y[:m], ref + bias.double() + res.double()) < 1e-2 and bool((y[m:] == 7.0).all())
     pre, act = (torch.full((m + 1, c), 7.0, dtype=torch.bfloat16, device="cuda") for c in (2 * f, f))
     B.mllm_op_gemm_swiglu(x, w, pre, act, m, f, k)
     gate, up = ref.split(f, dim=1)
@@ -53,11 +49,30 @@ def test_forward_with_every_epilogue(B, m, k):
         assert error(y[:m], want) < 1e-2
 
 
+# rows and columns whose plan is tiles of 256, and one row more than the last that takes 224
+@pytest.mark.parametrize("k", [64, 192, 704])
+@pytest.mark.parametrize("b_layout", [0, 1])
+@pytest.mark.parametrize("m,n,tile", [(430, 22320, 224), (448, 21800, 224), (449, 21800, 256), (672, 17120, 224), (896, 14000, 224), (897, 14000, 256), (1343, 9840, 224),
+                                      (1568, 8280, 224), (1569, 8280, 256)])
+def test_plain_products(B, m, n, tile, b_layout, k):
+    assert B.mllm_gemm_form(m, n, k, 0, b_layout) == (tile, 256, 1)
+    g = torch.Generator(device="cuda").manual_seed(m + k)
+    x, w, bias, res = randn(g, m, k), randn(g, *((n, k) if b_layout else (k, n)), scale=0.125), randn(g, n), randn(g, m, n)
+    ref = x.double() @ (w.double().t().contiguous() if b_layout else w.double())
+    y = torch.full((m + 1, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.mllm_op_gemm(x, w, y, m, n, k, 0, b_layout, bias=bias, residual=res)
+    assert error(y[:m], ref + bias.double() + res.double()) < 1e-2 and bool((y[m:] == 7.0).all())
+    c = torch.full((m + 1, n), 3.0, device="cuda")
+    B.mllm_op_gemm(x, w, c, m, n, k, 0, b_layout, out_fp32=1, accumulate=1)
+    assert error(c[:m], ref + 3.0) < 2e-3 and bool((c[m:] == 3.0).all())
+
+
 @pytest.mark.parametrize("accumulate", [0, 1])
 @pytest.mark.parametrize("t,k,n", [(224, 3584, 18944), (430, 4096, 8192), (448, 14336, 4096), (449, 14336, 4096), (777, 4096, 6144), (777, 14336, 4096)])
 def test_both_gradients(B, t, k, n, accumulate):
     """Accumulating and not; with the scratch that is wanted and with none (then uncut)."""
-    form, want = B.mllm_linear_bwd_form(t, k, n)
+    (one, x_form, _, _), want = B.mllm_linear_bwd_form(t, k, n)
+    assert one and x_form[0] == (256 if t == 449 else 224)
     g = torch.Generator(device="cuda").manual_seed(t + k)
     dy, x, w = randn(g, t, n), randn(g, t, k), randn(g, k, n, scale=0.125)
     ref_x, ref_w = dy.double() @ w.double().t().contiguous(), x.double().t().contiguous() @ dy.double()
@@ -73,7 +88,8 @@ def test_both_gradients(B, t, k, n, accumulate):
 def test_swiglu_gradient(B, t, f, n):
     g = torch.Generator(device="cuda").manual_seed(t)
     dy, act, pre, w = randn(g, t, n), randn(g, t, f), randn(g, t, 2 * f), randn(g, f, n, scale=0.125)
-    want = B.mllm_linear_bwd_form(t, f, n, swiglu=1)[1]
+    (one, x_form, _, _), want = B.mllm_linear_bwd_form(t, f, n, swiglu=1)
+    assert one and x_form == (224, 256, 1)
     dpre, dw = torch.full((t + 1, 2 * f), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((f, n), float("nan"), device="cuda")
     ws = torch.empty(want + 256, dtype=torch.uint8, device="cuda")
     B.mllm_op_linear_bwd(dy, act, w, dpre, dw, t, f, n, swiglu_pre=pre, workspace=ws, scratch_bytes=want)

@@ -43,7 +43,7 @@ LAYOUTS = [(0, 0), (0, 1), (1, 0)]
 @pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6, 7, 8, 9])
 def test_every_remainder_of_the_four_stages(B, a_layout, b_layout, tiles):
     """128x128 tiles with a CU each: any number of k-tiles over four LDS stages, a ragged last one where k runs along the rows."""
-    m, n, k = 136, 264, 64 * tiles - (13 if a_layout else 0)
+    m, n, k = 1096, 1160, 64 * tiles - (13 if a_layout else 0)
     assert B.mllm_gemm_form(m, n, k, a_layout, b_layout)[0] == 128
     for f32 in (0, 1):
         assert product(B, m, n, k, a_layout, b_layout, f32) < (2e-3 if f32 else 1e-2)

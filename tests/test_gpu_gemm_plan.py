@@ -21,9 +21,9 @@ def B():
 
 
 @pytest.mark.parametrize("k", [1, 7, 63, 64, 65, 130, 193])
-@pytest.mark.parametrize("m,n", [(8, 8), (136, 264), (640, 120)])
+@pytest.mark.parametrize("m,n", [(8, 8), (136, 264), (640, 120), (1096, 1160)])
 def test_weight_gradient_small_tiles_any_token_count(B, m, n, k):
-    """128x128 tiles, both operands stored [K, .]: a last k-tile of any length, tile edges inside the matrix.  The
+    """128x128 tiles and quarters of them, both operands stored [K, .]: a last k-tile of any length, tile edges inside the matrix.  The
     rows behind the operands hold large values, so a row read past K would show."""
     a, b = W.draw_tensor(301, k + 64, m), W.draw_tensor(302, k + 64, n)
     a[k:], b[k:] = 1000.0, 1000.0
@@ -38,7 +38,7 @@ def test_weight_gradient_small_tiles_any_token_count(B, m, n, k):
     assert nmax_err(host_f64(c), ref) < 1e-2
 
 
-@pytest.mark.parametrize("m,n,k", [(1, 8, 64), (127, 136, 128), (129, 120, 192), (513, 264, 320)])
+@pytest.mark.parametrize("m,n,k", [(1, 8, 64), (127, 136, 128), (129, 120, 192), (513, 264, 320), (1025, 1032, 320), (1151, 1160, 192)])
 @pytest.mark.parametrize("b_layout,f32", [(0, 0), (1, 0), (0, 1), (1, 1)])
 def test_small_tiles_edges_and_epilogue_terms(B, m, n, k, b_layout, f32):
     a = W.draw_tensor(311, m, k)
@@ -63,7 +63,9 @@ def test_small_tiles_edges_and_epilogue_terms(B, m, n, k, b_layout, f32):
 # sizes that take a tile with one, two, an odd and an even number of k-tiles alike
 TILES = [(256, 2216, 5536, 0, 0), (256, 2216, 5536, 0, 1), (256, 704, 20944, 1, 0), (256, 704, 20944, 1, 1),
          (192, 5960, 1312, 0, 0), (192, 5960, 1312, 0, 1),
-         (128, 200, 520, 0, 0), (128, 200, 520, 0, 1), (128, 200, 520, 1, 0), (128, 200, 520, 1, 1)]
+         (224, 896, 14000, 0, 0), (224, 896, 14000, 0, 1), (224, 1343, 9840, 0, 0),
+         (128, 1096, 1160, 0, 0), (128, 1096, 1160, 0, 1), (128, 1096, 1160, 1, 0), (128, 200, 520, 1, 1),
+         (64, 200, 520, 0, 0), (64, 200, 520, 0, 1), (64, 200, 520, 1, 0)]
 
 
 @pytest.mark.parametrize("k", [64, 128, 192, 320])

@@ -71,6 +71,7 @@ def test_to_the_bit_the_tiles_they_stand_for(B, m, n, k, a_layout, b_layout):
         flat = torch.zeros(a.numel() + offset, dtype=torch.bfloat16, device="cuda")
         flat[offset:] = a.flatten()
         B.mllm_op_gemm(flat[offset:], b, out, m, n, k, a_layout, b_layout, 1)
+    assert B.mllm_gemm_form(m, n, k, a_layout, b_layout)[0] == 64
     assert torch.equal(c[0], c[1])
 
 
@@ -113,4 +114,6 @@ def test_whole_tiles_with_more_quarters_than_compute_units(B, a_layout, b_layout
     """128x128 tiles with a CU each that are not quartered: any number of k-tiles over their four LDS stages."""
     m, n, k = 1096, 1160, 64 * tiles - (13 if a_layout else 0)
     assert B.mllm_gemm_form(m, n, k, a_layout, b_layout)[0] == 128
-    product(B, m, n, k, a_layout, b_layout, a_layout)
+    for out_fp32 in (0, 1):
+        for extras in (False, True):
+            product(B, m, n, k, a_layout, b_layout, out_fp32, extras)

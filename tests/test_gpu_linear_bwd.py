@@ -21,7 +21,7 @@ def B():
 
 
 # tokens, k, n and the form that is meant: a tile each of dX and dW, alone and in parts, either one first
-CASES = [(1, 64, 64, 128, 1, 128, 1), (77, 192, 576, 128, 1, 128, 1), (200, 256, 2048, 128, 4, 128, 1), (130, 520, 64, 128, 1, 128, 1),
+CASES = [(1, 64, 64, 64, 1, 64, 1), (77, 192, 576, 64, 1, 64, 1), (200, 256, 2048, 64, 4, 64, 1), (130, 520, 64, 64, 1, 64, 1), (577, 256, 2048, 128, 4, 128, 1),
          (2880, 1024, 1024, 128, 1, 128, 3), (200, 4096, 8192, 128, 4, 128, 1), (5125, 640, 3200, 128, 1, 128, 2),
          (1025, 3200, 3200, 128, 1, 128, 1), (5125, 3200, 3200, 192, 1, 256, 1), (6000, 3200, 1024, 256, 1, 128, 1),
          (9216, 1024, 1024, 256, 1, 256, None)]
@@ -88,11 +88,11 @@ def test_operands_off_16_bytes_make_two_launches(B, oa, ob):
 # every kind of shared launch that the plan takes for the layers' widths: tokens, k, n; rows of dX's tiles and whether it is cut; the
 # same of dW; whether dX's workgroups come first
 FORMS = [(129, 5120, 1280, 128, 0, 256, 0, 1), (67, 1280, 5120, 128, 1, 256, 0, 1), (67, 1280, 1280, 128, 1, 128, 0, 1), (4099, 4096, 1024, 128, 0, 128, 0, 0),
-         (963, 192, 192, 128, 0, 128, 1, 1), (2435, 1280, 1280, 192, 0, 128, 0, 1), (4099, 768, 192, 192, 0, 128, 1, 1), (513, 1280, 3840, 192, 1, 128, 0, 1),
+         (963, 192, 192, 64, 0, 64, 1, 1), (996, 768, 192, 128, 0, 128, 1, 1), (2435, 1280, 1280, 192, 0, 128, 0, 1), (4099, 768, 192, 192, 0, 128, 1, 1), (513, 1280, 3840, 192, 1, 128, 0, 1),
          (1985, 5120, 1280, 192, 0, 256, 0, 0), (705, 5120, 1280, 192, 0, 256, 0, 1), (8099, 1280, 1280, 192, 0, 256, 1, 0), (4293, 1280, 1280, 192, 0, 256, 1, 1),
          (641, 2048, 2560, 192, 1, 256, 0, 1), (3397, 1280, 1280, 256, 0, 128, 0, 1), (6151, 1024, 1024, 256, 0, 128, 1, 1), (2883, 5120, 1280, 256, 0, 256, 0, 0),
          (1155, 5120, 1280, 256, 0, 256, 0, 1), (9263, 4096, 1024, 256, 0, 256, 1, 0), (7817, 1024, 1024, 256, 0, 256, 1, 1), (961, 1280, 3840, 256, 1, 128, 0, 1),
-         (193, 3200, 9600, 256, 1, 256, 0, 1)]
+         (193, 3200, 9600, 224, 1, 256, 0, 1), (225, 3200, 9600, 256, 1, 256, 0, 1)]
 
 
 @pytest.mark.parametrize("t,k,n,x_tile,x_cut,w_tile,w_cut,x_first", FORMS)

@@ -23,15 +23,23 @@ def test_no_part_is_empty_and_the_parts_fit_the_scratch(B, k, n):
             (one, x, w, first), _ = B.mllm_linear_bwd_form(t, k, n, scratch_bytes=scratch)
             used = 0
             for (rows, cols, parts), tiles, (m, c) in ((x, n // 64, (t, k)), (w, -(-t // 64), (k, n))):
-                assert (rows, cols) in ((256, 256), (192, 256), (128, 128))
+                assert (rows, cols) in ((256, 256), (224, 256), (192, 256), (128, 128), (64, 64))
                 per = -(-tiles // parts)
                 assert (parts - 1) * per < tiles and (parts == 1 or per >= 8)
                 used += parts * m * c * 4 if parts > 1 else 0
-            assert w[0] != 192
+            assert w[0] not in (192, 224) and (not one or (x[0] == 64) == (w[0] == 64))
             assert (used if one else 0) <= scratch
             paired += one
         assert B.mllm_linear_bwd_form(t, k, n, scratch_bytes=want)[0] == B.mllm_linear_bwd_form(t, k, n)[0]
     assert paired > 20
+
+
+# both gradients in quarters of 128x128 tiles up to 256 of them, in as many parts as the larger tiles
+@pytest.mark.parametrize("t,k,n,tile,parts", [(64, 256, 2048, 64, 4), (288, 256, 2048, 64, 4), (577, 256, 2048, 128, 4), (576, 512, 512, 64, 1), (600, 512, 1472, 128, 1),
+                                              (193, 3200, 9600, 224, 6), (225, 3200, 9600, 256, 6)])
+def test_the_tile_of_the_input_gradient_that_runs_is_named(B, t, k, n, tile, parts):
+    (one, x, w, _), _ = B.mllm_linear_bwd_form(t, k, n)
+    assert one and (x[0], x[2]) == (tile, parts) and w[0] == (256 if tile > 128 else tile)
 
 
 def test_what_the_tile_kernel_does_not_take_stays_apart(B):
@@ -44,7 +52,7 @@ def test_what_the_tile_kernel_does_not_take_stays_apart(B):
 def test_swiglu_form_keeps_the_tile_of_its_epilogue(B):
     for t in (777, 2999, 8192, 32768):
         (one, x, _, _), _ = B.mllm_linear_bwd_form(t, 18944, 3584, swiglu=1)
-        assert one and x == (256, 256, 1)
+        assert one and x == (224 if t == 777 else 256, 256, 1)
 
 
 @pytest.mark.parametrize("t,k,n", [(20000, 512, 520), (9000, 512, 712), (4000, 256, 72), (671050, 3200, 3200), (2880, 1024, 1024), (200, 4096, 8192)])
