@@ -471,9 +471,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_64_kernel(AttnParams p) {
   const float c2 = p.scale_log2e;
   // Reference maximum m (in units of log2: score * scale * log2(e)) and sum l of exp2(... - m).  The reference is the row's maximum
   // over the first tile and moves when a later tile exceeds it by more than 8: probabilities reach 2^8 at most, at the same relative
-  // precision in fp32 sums and in the bf16 operand.  A tile that exceeds it shows in its sum: only one above 2^8 (or past the
-  // range of fp32) has its scores formed again, its maximum taken and the accumulator rescaled (`again`); so neither the
-  // maximum of a tile's scores nor its exchange between the halves is on the path.
+  // precision in fp32 sums and in the bf16 operand.  A tile that exceeds it shows in its sum: only where one comes out above 2^8 (or past
+  // the range of fp32) is the largest probability looked for, and only where that is above 2^8 are the scores formed again, their
+  // maximum taken and the accumulator rescaled (`again`); so neither the maximum of a tile's scores nor its exchange between the
+  // halves is on the path, and a tile formed again moves the reference.  (On the sum alone 32 probabilities of 8 were enough to form
+  // every tile again: 4 x 1500 tokens, 16 heads, keys behind the first 64 scoring 2.5 to 5 nats higher 79 to 83 us and now 55 to 57; other keys 54.)
   constexpr float LIMIT = 256.f;
   float m = -INFINITY, mu = 0.f, l = 0.f, limit = -1.f;   // mu: m, or 0 where there is none yet; limit -1: no reference yet
 
@@ -530,6 +532,14 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_64_kernel(AttnParams p) {
     m = to;
     mu = to == -INFINITY ? 0.f : to;
     limit = to == -INFINITY ? -1.f : LIMIT;
+  };
+  auto largest = [&]() {   // probability of the lane's keys
+    float mx = s[0][0];
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[b][v]);
+    return mx;
   };
   auto probs = [&]() {
     rs = 0.f;
@@ -608,7 +618,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_64_kernel(AttnParams p) {
     mask(kv0);
     if (kv0 == 0) set_reference(tile_max());
     probs();
-    if (__any(rs > limit)) again(ST, kv0);
+    if (__any(rs > limit) && __any(largest() > limit - 0.01f)) again(ST, kv0);   // 0.01: more than the exponential's rounding
     l += rs;
     MLLM_SLOT_END;
 #pragma unroll

@@ -71,6 +71,35 @@ def test_edges(B, lengths, hq, hkv, causal, hd):
     run(B, lengths, hq, hkv, hd, causal)
 
 
+def forward_us(B, hd, higher):
+    """Median time of a forward pass whose keys behind the first tile of each segment score `higher` nats more."""
+    n, segments, heads = 1500, 4, 16
+    T, g = n * segments, torch.Generator(device="cuda").manual_seed(hd)
+    q, k, v = (torch.randn(T, heads, hd, generator=g, device="cuda") * s for s in (1.0, 0.2, 1.0))
+    q[:, :, 0] = hd ** 0.5
+    k[:, :, 0] = (torch.arange(T, device="cuda") % n >= 64).float()[:, None] * higher
+    q, k, v = (t.bfloat16().reshape(T, -1) for t in (q, k, v))
+    o, lse, w = torch.empty_like(q), torch.empty(heads, T, device="cuda"), heads * hd
+    pack, ws = W.make_pack([n] * segments, W.MASK_BIDIR), scratch(B.mllm_op_attn_workspace_bytes(segments, T, heads))
+    times = []
+    for _ in range(12):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(30):
+            B.mllm_op_attn_fwd(q, k, v, o, lse, pack, heads, heads, hd, w, w, w, ws)
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times[2:])[5]
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("higher", [2.5, 4.0])
+def test_keys_within_the_reference_cost_no_more(B, higher, hd):
+    """Below 2^8 of the reference no tile is formed again, whatever its sum.  1.5 times the time where the sum alone decided."""
+    assert forward_us(B, hd, higher) < 1.2 * forward_us(B, hd, 0.0)
+
+
 # times 1, 8 and 64 at unit variance: scores of about 4, 35 and 270 (390 in units of log2); falling again, the reference stays
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("causal", [0, 1])
