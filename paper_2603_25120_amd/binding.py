@@ -64,11 +64,20 @@ class ModuleProfileC(C.Structure):
 
 class PackC(C.Structure):
     _fields_ = [("total_tokens", C.c_int32), ("n_segments", C.c_int32), ("max_seqlen", C.c_int32),
-                ("cu_seqlens_host", C.c_void_p), ("mask_kind_host", C.c_void_p)]
+                ("cu_seqlens_host", C.POINTER(C.c_int32)), ("mask_kind_host", C.POINTER(C.c_uint8))]
 
 
 class BatchC(C.Structure):
-    _fields_ = [("img", PackC), ("seq", PackC), ("img_to_seq_row_host", C.c_void_p)]
+    _fields_ = [("img", PackC), ("seq", PackC), ("img_to_seq_row_host", C.POINTER(C.c_int32))]
+
+
+# The same layouts with plain addresses, for the views that a call makes (_PackKeep).
+class _PackAddresses(C.Structure):
+    _fields_ = PackC._fields_[:3] + [(name, C.c_void_p) for name, _ in PackC._fields_[3:]]
+
+
+class _BatchAddresses(C.Structure):
+    _fields_ = [("img", _PackAddresses), ("seq", _PackAddresses), ("img_to_seq_row_host", C.c_void_p)]
 
 
 _lib = None
@@ -187,7 +196,7 @@ class _PackKeep:
     """ctypes view of a packed token space; keeps the NumPy arrays alive."""
 
     def __init__(self, pack):
-        self.c = PackC()
+        self.a = _PackAddresses()
         if pack is None:
             self.cu = np.zeros(1, dtype=np.int32)
             self.mk = np.zeros(0, dtype=np.uint8)
@@ -200,20 +209,25 @@ class _PackKeep:
             longest = getattr(pack, "max_seqlen_override", None)
             if longest is None:
                 longest = _longest(self.cu) if n_seg else 0
-        self.c.total_tokens, self.c.n_segments, self.c.max_seqlen = total, n_seg, int(longest)
-        self.c.cu_seqlens_host, self.c.mask_kind_host = _address(self.cu), _address(self.mk)
+        self.a.total_tokens, self.a.n_segments, self.a.max_seqlen = total, n_seg, int(longest)
+        self.a.cu_seqlens_host, self.a.mask_kind_host = _address(self.cu), _address(self.mk)
+
+    @property
+    def c(self) -> PackC:
+        return PackC.from_buffer(self.a)
 
 
 class _BatchKeep:
     def __init__(self, batch):
         self.img = _PackKeep(getattr(batch, "img", None))
         self.seq = _PackKeep(getattr(batch, "seq", None))
-        self.c = BatchC()
-        self.c.img, self.c.seq = self.img.c, self.seq.c
+        a = _BatchAddresses()
+        a.img, a.seq = self.img.a, self.seq.a
         rows = getattr(batch, "img_to_seq_row", None)
         if rows is not None:
             self.rows = np.ascontiguousarray(rows, dtype=np.int32)
-            self.c.img_to_seq_row_host = _address(self.rows)
+            a.img_to_seq_row_host = _address(self.rows)
+        self.c = BatchC.from_buffer(a)
 
 
 def _ptr_array(tensors: Sequence):

@@ -276,3 +276,18 @@ def test_merging_connector_needs_segment_multiples(B):
         assert e.value.status == 3
     finally:
         B.mllm_stage_destroy(h)
+
+
+def test_packs_take_typed_pointers(B):
+    """A caller may fill the ABI's structures by hand, with pointers or arrays of the declared types, and read them back; the views
+    that the binding makes for its own calls hold the same."""
+    cu, mk, rows = (ctypes.c_int32 * 3)(0, 5, 9), (ctypes.c_uint8 * 2)(W.MASK_CAUSAL, W.MASK_BIDIR), (ctypes.c_int32 * 2)(0, 6)
+    pack = B.PackC(9, 2, 5, cu, ctypes.cast(mk, ctypes.POINTER(ctypes.c_uint8)))
+    batch = B.BatchC()
+    batch.img, batch.seq, batch.img_to_seq_row_host = pack, pack, rows
+    view = B._BatchKeep(W.Batch(W.make_pack([5, 4], W.MASK_CAUSAL), W.make_pack([5, 4], W.MASK_CAUSAL), np.array([0, 6], np.int32), [])).c
+    for b in (batch, view):
+        assert [b.seq.cu_seqlens_host[i] for i in range(3)] == [0, 5, 9] and b.seq.mask_kind_host[0] == W.MASK_CAUSAL
+        assert [b.img_to_seq_row_host[i] for i in range(2)] == [0, 6]
+    size = ctypes.c_size_t()
+    assert B.lib().mllm_attn_work_list(ctypes.byref(pack), 0, 2, 2, 64, None, 0, ctypes.byref(size), None) == 0 and size.value > 0
