@@ -260,8 +260,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
   const float c2 = p.scale_log2e;
   // Reference maximum m (in units of log2: score * scale * log2(e)) and sum l = sum of exp2(... - m).  The reference is the
   // row's maximum over the first tile and stays: probabilities above 1 carry the same relative precision in fp32 sums and
-  // in the bf16 operand.  Only a tile whose sum comes out above `limit` (some probability near or above 2^12, or past the range
-  // of fp32) has its scores formed again and moves the reference (`again`); so neither the maximum of a tile's scores, nor its
+  // in the bf16 operand.  Only a tile where a lane's 16 probabilities sum to more than `limit`, so that one of them is above 2^8 (or past the
+  // range of fp32), has its scores formed again and moves the reference (`again`); so neither the maximum of a tile's scores, nor its
   // exchange between lanes, nor the rescaling of the accumulator is on the path.
   constexpr float LIMIT = 4096.f;
   float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f}, limit[2] = {-1.f, -1.f};   // -1: no reference yet
@@ -439,7 +439,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(AttnParams p) {
 // ---------------------------------------------------------------------------------------------
 // forward, head_dim 64: the same walk with v_mfma_f32_32x32x16_bf16: lane l owns query l%32, and with h = l/32 the keys
 // 8i + 4h .. +3 of a block.  Here the vector ALU is the bound and the clock 2.2 GHz, so the 16x16x32 form gives little (46 x 576 tokens, 16
-// heads: 109 us at first, 95 with the maximum off the path and without the wavefronts that have no row, 92 with that form as well),
+// heads: 109 us at first, 95 with the maximum off the path and without the wavefronts that have no row (130 and 112 on another card), 92
+// with that form as well),
 // and it adds up in another order: through the roundings of a stage of 24 encoder and 8 decoder layers that moves the gradients by
 // 0.044 of their norm, as much as they are from exact ones, where this order leaves the encoder's outputs to the bit (0.020 with the
 // other kernels' orders alone).

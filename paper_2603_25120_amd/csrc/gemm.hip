@@ -375,7 +375,7 @@ double workgroups_time(const TileCost& c, bool a_t, int64_t n, int64_t k_tiles, 
 // What the parts cost besides: their trip through memory and a launch.
 double parts_cost(int64_t m, int64_t n, int64_t parts) { return parts > 1 ? 3.0 + (double)m * n * (8.0 * parts + 4.0) * 1.15e-7 : 0.0; }
 // split_bytes: scratch for the parts; the cheapest plan that fits it (and its estimate).  fused: only uncut 256x256 tiles, the ones that
-// the fused epilogues exist for.
+// the fused epilogues exist for (and 224x256, which may take their place).
 GemmPlan plan_gemm(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t, size_t split_bytes, double* estimate = nullptr, bool fused = false) {
   const int row = cost_row(a_t, b_t);
   const int64_t nk = (k + BK - 1) / BK;
@@ -503,7 +503,7 @@ size_t gemm_splitk_ws_bytes(int64_t m, int64_t n, int64_t k, bool a_t, bool b_t)
   return pl.splits > 1 ? (size_t)pl.splits * (size_t)m * (size_t)n * 4 : 0;
 }
 
-// The fused epilogues exist for 256x256 tiles; with fewer than this many of them a plan of its own for the product and a
+// The fused epilogues exist for 256x256 and 224x256 tiles; with fewer than this many of them a plan of its own for the product and a
 // pass of its own for the activation or the rotation are as good.  The line is flat: forward and backward of the three
 // decoder layers at 256 to 3072 tokens, 100 instead of 200 takes 1.002x the time on average (0.989-1.021), 300 0.997x
 // (0.978-1.014).

@@ -105,8 +105,9 @@ constexpr int ATTN_BWD_KV_TILE = 128;  // key rows per workgroup, dK/dV pass
 // every query tile of every query head of the group one after the other, so with few kv heads and few
 // tokens most CUs have no workgroup while the heaviest one sets the time (28 / 4 heads, 2999 tokens: 100
 // workgroups, 370 us).  heaviest, total: the largest and the summed number of 64-row query tiles that the
-// (key tile, kv head) items meet; rows: rows of the k matrix times kv heads.  Measured constants (microseconds):
-// a query tile 2.2 at head_dim 128, 1.1 at 64; the parts' sums go through memory at 4 TB/s and cost a launch.
+// (key tile, kv head) items meet; rows: rows of the k matrix times kv heads.  Constants (microseconds) measured on the kernels
+// before the present ones and not fitted again: a query tile 2.2 at head_dim 128 (the present kernel 1.8 with every CU busy, 13255
+// causal tokens), 1.1 at 64; the parts' sums go through memory at 4 TB/s and cost a launch.
 int attn_kv_parts(int64_t heaviest, int64_t total, int64_t rows, int head_dim);
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
@@ -150,13 +151,13 @@ hipError_t launch_rope(void* qk, const int32_t* pos, int64_t t, int64_t row_stri
 // The forward rotation of the leading n_heads heads, with the factors of launch_rope_table.
 hipError_t launch_rope_from_table(void* qk, const int32_t* pos, const float* table, int64_t t, int64_t row_stride,
                                   int32_t n_heads, int32_t head_dim, hipStream_t s);
-// table [n_pos, head_dim] fp32: cos then sin of pos * rope_base^(-2i/head_dim), i < head_dim / 2.
 // What a stage's pass begins with, in one launch: the call's metadata from pinned host memory (its device address), the tables
 // of the rotary angles, and a copy of rows that depends on nothing (all but the tables may be absent).
 struct RopeTableSpec { float* table; int32_t head_dim; float base; };
 constexpr int BEGIN_TABLES = 4;
 hipError_t launch_begin(const void* meta_src, void* meta, size_t meta_bytes, const RopeTableSpec* tables, int n_tables, int64_t n_pos,
                         const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t s);
+// table [n_pos, head_dim] fp32: cos then sin of pos * rope_base^(-2i/head_dim), i < head_dim / 2.
 hipError_t launch_rope_table(float* table, int64_t n_pos, int32_t head_dim, float rope_base, hipStream_t s);
 hipError_t launch_act_fwd(int act, const void* pre, void* a, int64_t t, int64_t f, hipStream_t s);
 hipError_t launch_act_bwd(int act, const void* da, const void* pre, void* dpre, int64_t t,
