@@ -16,7 +16,7 @@ namespace {
 // Against the 128x128 form, back to back, operands from memory (us): 148 x 768 x 256 5.1 -> 4.1, 576 x 512 x 512 6.6 -> 5.4, 576 x 1024
 // x 1024 8.9 -> 7.3, dX of 1728 x 512 x 3584 23.2 -> 16.4; both gradients of a map, 148 tokens x 192 x 768 7.7 -> 6.1, 576 x 512 x 512
 // 7.7 -> 6.2, 148 x 256 x 2048 with dX in four parts 9.4 -> 8.2.  (Eight wavefronts that deal the k-tiles out between them and add
-// their sums in LDS take as long, and add in another order than every other tile.)
+// their sums in LDS are within a tenth of that either way, and add in another order than every other tile.)
 // ---------------------------------------------------------------------------------------------
 constexpr int SMALL_TILE = 64, SMALL_WAVES = 8, SMALL_STAGES = 8;
 constexpr int SMALL_OPERAND_B = SMALL_TILE * BK * 2, SMALL_STAGE_B = 2 * SMALL_OPERAND_B, SMALL_LDS_B = SMALL_STAGES * SMALL_STAGE_B;
